@@ -129,15 +129,17 @@ void launch_wave_prep(const uint64_t *hoff, const int64_t *qoff, const uint32_t 
                       uint32_t *hrel, uint32_t *pbase, uint64_t *akey, uint32_t *tile_pos,
                       hipStream_t st);
 // Index build (Sections 2, 2.1): pack the bank 2 bits per base; code every
-// non-overlapping window (keys = code, vals = window number, counts per code);
-// after a stable sort by code, window numbers become (sequence, position) postings.
+// non-overlapping window (keys = code << 32 | window number, wseq = the window's
+// sequence); after a sort by code (the window numbers keep it stable), the list
+// lengths, and the window numbers become (sequence, position) postings.
 void launch_pack_bases(const uint8_t *ascii, int64_t total, uint32_t *dbw, int64_t nwords,
                        int32_t *err, hipStream_t st);
 void launch_window_keys(const uint32_t *dbw, const int64_t *seq_start, const uint32_t *woff,
                         int32_t n_seqs, uint32_t n_win, int32_t span, uint32_t mask,
-                        uint64_t *keys, uint32_t *vals, uint32_t *counts, hipStream_t st);
-void launch_postings(const uint32_t *vals, uint32_t n_win, const uint32_t *woff, int32_t n_seqs,
-                     int32_t span, int2 *post, hipStream_t st);
+                        uint64_t *keys, uint32_t *wseq, hipStream_t st);
+void launch_code_counts(const uint64_t *keys, uint32_t n_win, uint32_t *counts, hipStream_t st);
+void launch_postings(const uint64_t *keys, uint32_t n_win, const uint32_t *woff,
+                     const uint32_t *wseq, int32_t span, int2 *post, hipStream_t st);
 // Traceback of n reported alignments (gg_hit records, kHitInts int32 each) of one
 // query (ASCII): per-hit direction rows of 64 bytes at dirs + dir_off[h], the
 // operations right-aligned in ops[ops_off[h] .. ops_off[h] + (q span + d span)),
@@ -176,8 +178,8 @@ void launch_reverse_strand(const uint8_t *src, const int64_t *start, int32_t n_s
 // postings of kept lists placed at their kept heads.
 void launch_cut_counts(const uint32_t *off, uint32_t ncode, uint32_t max_posting, uint32_t *kept,
                        hipStream_t st);
-void launch_postings_cut(const uint32_t *vals, const uint64_t *keys, uint32_t n_win,
-                         const uint32_t *woff, int32_t n_seqs, int32_t span, const uint32_t *off,
+void launch_postings_cut(const uint64_t *keys, uint32_t n_win, const uint32_t *woff,
+                         const uint32_t *wseq, int32_t span, const uint32_t *off,
                          const uint32_t *kept_off, uint32_t max_posting, int2 *post, hipStream_t st);
 // A query searched by pieces over ranges of sequence ids: below[y] += its hits on
 // sequences < bounds[y]; per-position sub-lists of the range [s_lo, s_hi).

@@ -120,32 +120,56 @@ __device__ void lds_bitonic(const Rec *__restrict__ s_r, uint16_t *__restrict__ 
 }
 
 // ------------------------------------------------------------------ S0: index build
+// Four ASCII bases (the first in the low byte) to their codes, one per byte; *bad
+// gets a bit for a byte outside the alphabet.  Bits 2:1 of a letter of either case
+// tell A, C, T/U and G apart (0, 1, 2, 3); the letter its code stands for is then
+// compared with the byte, U differing from T in the lowest bit.
+__device__ __forceinline__ uint32_t base_codes4(uint32_t v, uint32_t *bad)
+{
+    const uint32_t x = (v >> 1) & 0x03030303u;
+    const uint32_t c = x ^ ((x >> 1) & 0x01010101u);
+    const uint32_t letter = __builtin_amdgcn_perm(0u, 0x54474341u, c);  // "ACGT"[c]
+    *bad |= ((v & 0xDFDFDFDFu) ^ letter) & ~(c & (c >> 1) & 0x01010101u);
+    return c;
+}
+
 // Formatting (Section 2): the bank's bases packed 2 bits each, 16 to a word, first
-// base most significant; a byte outside the alphabet sets *err.
+// base most significant; a byte outside the alphabet sets *err.  One 16-byte load
+// and four 4-base steps per word: 845 -> 67 us for 275 Mbp against a byte at a time.
 __global__ void k_pack_bases(const uint8_t *__restrict__ ascii, int64_t total,
                              uint32_t *__restrict__ dbw, int64_t nwords, int32_t *__restrict__ err)
 {
     for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < nwords;
          w += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t word = 0;
-        bool bad = false;
-        for (int b = 0; b < 16; ++b) {
-            const int64_t g = w * 16 + b;
-            if (g >= total) break;
-            const int32_t c = base_code(ascii[g]);
-            bad |= c < 0;
-            word |= (uint32_t)(c < 0 ? 0 : c) << (30 - 2 * b);
+        uint32_t v[4] = {0x41414141u, 0x41414141u, 0x41414141u, 0x41414141u};  // A past the end
+        if (16 * w + 16 <= total) {
+            const uint4 x = reinterpret_cast<const uint4 *>(ascii)[w];
+            v[0] = x.x;
+            v[1] = x.y;
+            v[2] = x.z;
+            v[3] = x.w;
+        } else {
+            for (int b = 0; b < 16; ++b)
+                if (16 * w + b < total)
+                    v[b >> 2] = (v[b >> 2] & ~(0xFFu << (8 * (b & 3)))) |
+                                ((uint32_t)ascii[16 * w + b] << (8 * (b & 3)));
+        }
+        uint32_t word = 0, bad = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t c = base_codes4(v[i], &bad);
+            word = (word << 8) | ((c & 3u) << 6) | ((c >> 4) & 0x30u) | ((c >> 14) & 0xCu) | (c >> 24);
         }
         dbw[w] = word;
         if (bad) atomicOr(err, 1);
     }
 }
 
-// Sequence of window w: the last s with woff[s] <= w (woff: windows before s).
-__device__ __forceinline__ int32_t window_seq(const uint32_t *__restrict__ woff, int32_t n_seqs,
-                                              uint32_t w)
+// Sequence of window w among sequences [lo, hi]: the last s with woff[s] <= w (woff:
+// windows before s).
+__device__ __forceinline__ int32_t window_seq(const uint32_t *__restrict__ woff, int32_t lo,
+                                              int32_t hi, uint32_t w)
 {
-    int32_t lo = 0, hi = n_seqs - 1;
     while (lo < hi) {
         const int32_t m = (lo + hi + 1) >> 1;
         if (woff[m] <= w) lo = m;
@@ -155,33 +179,59 @@ __device__ __forceinline__ int32_t window_seq(const uint32_t *__restrict__ woff,
 }
 
 // Index (Section 2.1): every non-overlapping window of every sequence, in (seq,
-// pos) order: its code (the sort key), its number (the value) and a count per code.
-__global__ void k_window_keys(const uint32_t *__restrict__ dbw, const int64_t *__restrict__ seq_start,
-                              const uint32_t *__restrict__ woff, int32_t n_seqs, uint32_t n_win,
-                              int32_t span, uint32_t mask, uint64_t *__restrict__ keys,
-                              uint32_t *__restrict__ vals, uint32_t *__restrict__ counts)
+// pos) order, as a sort key (code << 32) | window, and its sequence.  A block's
+// windows are consecutive, so their sequences lie between its first's and its last's.
+__global__ __launch_bounds__(kBlock) void k_window_keys(
+    const uint32_t *__restrict__ dbw, const int64_t *__restrict__ seq_start,
+    const uint32_t *__restrict__ woff, int32_t n_seqs, uint32_t n_win, int32_t span, uint32_t mask,
+    uint64_t *__restrict__ keys, uint32_t *__restrict__ wseq)
 {
-    for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < n_win;
-         w += gridDim.x * blockDim.x) {
-        const int32_t s = window_seq(woff, n_seqs, w);
+    __shared__ int32_t s_s[2];
+    for (uint64_t w0 = (uint64_t)blockIdx.x * kBlock; w0 < n_win;
+         w0 += (uint64_t)gridDim.x * kBlock) {
+        if (threadIdx.x < 2)
+            s_s[threadIdx.x] = window_seq(
+                woff, 0, n_seqs - 1,
+                (uint32_t)min(w0 + (threadIdx.x ? kBlock - 1 : 0), (uint64_t)n_win - 1));
+        __syncthreads();
+        const int32_t lo = s_s[0], hi = s_s[1];
+        __syncthreads();
+        if (w0 + threadIdx.x >= n_win) continue;
+        const uint32_t w = (uint32_t)w0 + threadIdx.x;
+        const int32_t s = window_seq(woff, lo, hi, w);
         const int64_t g = seq_start[s] + (int64_t)(w - woff[s]) * span;
-        const uint32_t code = db_code(dbw, g, span, mask);
-        keys[w] = code;
-        vals[w] = w;
-        atomicAdd(&counts[code], 1u);
+        keys[w] = ((uint64_t)db_code(dbw, g, span, mask) << 32) | w;
+        wseq[w] = (uint32_t)s;
     }
 }
 
-// Postings in list order: window number -> (sequence, position).
-__global__ void k_postings(const uint32_t *__restrict__ vals, uint32_t n_win,
-                           const uint32_t *__restrict__ woff, int32_t n_seqs, int32_t span,
-                           int2 *__restrict__ post)
+// List lengths from the windows in code order: each code's windows end where the
+// next code's begin, so two adds per code that occurs (to zeroed counts) leave its
+// length: 69 us for 25 M windows of 4^11 codes, where one add per window made the
+// window kernel take 980 us (354 now).
+__global__ void k_code_counts(const uint64_t *__restrict__ keys, uint32_t n_win,
+                              uint32_t *__restrict__ counts)
 {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_win;
-         i += gridDim.x * blockDim.x) {
-        const uint32_t w = vals[i];
-        const int32_t s = window_seq(woff, n_seqs, w);
-        post[i] = int2{s, (int32_t)((w - woff[s]) * (uint32_t)span)};
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i <= n_win;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t a = i > 0 ? (uint32_t)(keys[i - 1] >> 32) : 0u;
+        const uint32_t b = i < n_win ? (uint32_t)(keys[i] >> 32) : 0u;
+        if (i > 0 && i < n_win && a == b) continue;
+        if (i > 0) atomicAdd(&counts[a], (uint32_t)i);
+        if (i < n_win) atomicSub(&counts[b], (uint32_t)i);
+    }
+}
+
+// Postings in list order: window -> (sequence, position).
+__global__ void k_postings(const uint64_t *__restrict__ keys, uint32_t n_win,
+                           const uint32_t *__restrict__ woff, const uint32_t *__restrict__ wseq,
+                           int32_t span, int2 *__restrict__ post)
+{
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_win;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t w = (uint32_t)keys[i];
+        const uint32_t s = wseq[w];
+        post[i] = int2{(int32_t)s, (int32_t)((w - woff[s]) * (uint32_t)span)};
     }
 }
 
@@ -223,22 +273,24 @@ __global__ void k_cut_counts(const uint32_t *__restrict__ off, uint32_t ncode, u
     }
 }
 
-// Postings of the kept lists only: window i of the code-sorted order (code keys[i])
-// moves from its place in list c of the full heads (off) to the same place in
-// list c of the kept heads (kept_off); windows of dropped lists are skipped.
-__global__ void k_postings_cut(const uint32_t *__restrict__ vals, const uint64_t *__restrict__ keys,
-                               uint32_t n_win, const uint32_t *__restrict__ woff, int32_t n_seqs,
-                               int32_t span, const uint32_t *__restrict__ off,
+// Postings of the kept lists only: window i of the code order moves from its place
+// in its list of the full heads (off) to the same place in that list of the kept
+// heads (kept_off); windows of dropped lists are skipped.
+__global__ void k_postings_cut(const uint64_t *__restrict__ keys, uint32_t n_win,
+                               const uint32_t *__restrict__ woff,
+                               const uint32_t *__restrict__ wseq, int32_t span,
+                               const uint32_t *__restrict__ off,
                                const uint32_t *__restrict__ kept_off, uint32_t max_posting,
                                int2 *__restrict__ post)
 {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n_win;
-         i += gridDim.x * blockDim.x) {
-        const uint32_t c = (uint32_t)keys[i];
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_win;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const size_t c = (size_t)(keys[i] >> 32);
         if (off[c + 1] - off[c] > max_posting) continue;
-        const uint32_t w = vals[i];
-        const int32_t s = window_seq(woff, n_seqs, w);
-        post[kept_off[c] + (i - off[c])] = int2{s, (int32_t)((w - woff[s]) * (uint32_t)span)};
+        const uint32_t w = (uint32_t)keys[i];
+        const uint32_t s = wseq[w];
+        post[kept_off[c] + ((uint32_t)i - off[c])] =
+            int2{(int32_t)s, (int32_t)((w - woff[s]) * (uint32_t)span)};
     }
 }
 
@@ -257,14 +309,23 @@ void launch_cut_counts(const uint32_t *off, uint32_t ncode, uint32_t max_posting
     k_cut_counts<<<nb, kBlock, 0, st>>>(off, ncode, max_posting, kept);
 }
 
-void launch_postings_cut(const uint32_t *vals, const uint64_t *keys, uint32_t n_win,
-                         const uint32_t *woff, int32_t n_seqs, int32_t span, const uint32_t *off,
+static uint32_t window_blocks(uint64_t n)
+{
+    return (uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, kMaxGrid);
+}
+
+void launch_code_counts(const uint64_t *keys, uint32_t n_win, uint32_t *counts, hipStream_t st)
+{
+    if (n_win) k_code_counts<<<window_blocks((uint64_t)n_win + 1), kBlock, 0, st>>>(keys, n_win, counts);
+}
+
+void launch_postings_cut(const uint64_t *keys, uint32_t n_win, const uint32_t *woff,
+                         const uint32_t *wseq, int32_t span, const uint32_t *off,
                          const uint32_t *kept_off, uint32_t max_posting, int2 *post, hipStream_t st)
 {
-    if (n_win == 0) return;
-    const uint32_t nb = std::min<uint32_t>((n_win + kBlock - 1) / kBlock, kMaxGrid);
-    k_postings_cut<<<nb, kBlock, 0, st>>>(vals, keys, n_win, woff, n_seqs, span, off, kept_off,
-                                          max_posting, post);
+    if (n_win)
+        k_postings_cut<<<window_blocks(n_win), kBlock, 0, st>>>(keys, n_win, woff, wseq, span, off,
+                                                                kept_off, max_posting, post);
 }
 
 void launch_pack_bases(const uint8_t *ascii, int64_t total, uint32_t *dbw, int64_t nwords,
@@ -277,20 +338,18 @@ void launch_pack_bases(const uint8_t *ascii, int64_t total, uint32_t *dbw, int64
 
 void launch_window_keys(const uint32_t *dbw, const int64_t *seq_start, const uint32_t *woff,
                         int32_t n_seqs, uint32_t n_win, int32_t span, uint32_t mask,
-                        uint64_t *keys, uint32_t *vals, uint32_t *counts, hipStream_t st)
+                        uint64_t *keys, uint32_t *wseq, hipStream_t st)
 {
-    if (n_win == 0) return;
-    const uint32_t nb = std::min<uint32_t>((n_win + kBlock - 1) / kBlock, kMaxGrid);
-    k_window_keys<<<nb, kBlock, 0, st>>>(dbw, seq_start, woff, n_seqs, n_win, span, mask, keys,
-                                         vals, counts);
+    if (n_win)
+        k_window_keys<<<window_blocks(n_win), kBlock, 0, st>>>(dbw, seq_start, woff, n_seqs, n_win,
+                                                               span, mask, keys, wseq);
 }
 
-void launch_postings(const uint32_t *vals, uint32_t n_win, const uint32_t *woff, int32_t n_seqs,
-                     int32_t span, int2 *post, hipStream_t st)
+void launch_postings(const uint64_t *keys, uint32_t n_win, const uint32_t *woff,
+                     const uint32_t *wseq, int32_t span, int2 *post, hipStream_t st)
 {
-    if (n_win == 0) return;
-    const uint32_t nb = std::min<uint32_t>((n_win + kBlock - 1) / kBlock, kMaxGrid);
-    k_postings<<<nb, kBlock, 0, st>>>(vals, n_win, woff, n_seqs, span, post);
+    if (n_win)
+        k_postings<<<window_blocks(n_win), kBlock, 0, st>>>(keys, n_win, woff, wseq, span, post);
 }
 
 // ------------------------------------------------------------------ S1/S2: encode + count

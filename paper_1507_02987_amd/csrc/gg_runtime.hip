@@ -2112,16 +2112,14 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
         auto *d_err = static_cast<int32_t *>(tmp.get(sizeof(int32_t) * 4));
         auto *d_keys = static_cast<uint64_t *>(tmp.get(sizeof(uint64_t) * nw));
         auto *d_keys2 = static_cast<uint64_t *>(tmp.get(sizeof(uint64_t) * nw));
-        auto *d_vals = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * nw));
-        auto *d_vals2 = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * nw));
+        auto *d_wseq = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * nw));
         auto *d_hist = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * radix_hist_needed(nw)));
         const size_t parts = std::max<size_t>(scan_partials_needed(radix_hist_needed(nw)),
                                               scan_partials_needed((int64_t)ncode + 1));
         auto *d_parts = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * parts));
         auto *d_kept = cut ? static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * (ncode + 1)))
                            : nullptr;
-        if (!d_ascii || !d_woff || !d_err || !d_keys || !d_keys2 || !d_vals || !d_vals2 ||
-            !d_hist || !d_parts || (cut && !d_kept))
+        if (!d_ascii || !d_woff || !d_err || !d_keys || !d_keys2 || !d_wseq || !d_hist || !d_parts || (cut && !d_kept))
             return fail(GG_ENOMEM);
         int32_t err = 0;
         if (total_in > 0 && hipMemcpyAsync(d_ascii, seqs + base0, (size_t)total_in,
@@ -2138,13 +2136,13 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
             launch_reverse_strand(d_ascii, ix->d_seq_start, (int32_t)n_in, d_ascii + total_in, bst);
         launch_pack_bases(d_ascii, total, ix->d_dbw, nwords, d_err, bst);
         launch_window_keys(ix->d_dbw, ix->d_seq_start, d_woff, (int32_t)n_seqs, nw, span, mask,
-                           d_keys, d_vals, ix->d_list_off, bst);
+                           d_keys, d_wseq, bst);
+        if (radix_sort(d_keys, d_keys2, nullptr, nullptr, nw, 32, 32 + 2 * k, d_hist, d_parts, bst))
+            std::swap(d_keys, d_keys2);
+        launch_code_counts(d_keys, nw, ix->d_list_off, bst);
         launch_scan_u32(ix->d_list_off, ix->d_list_off, (int64_t)ncode, d_parts, bst);
-        const int cur = radix_sort(d_keys, d_keys2, d_vals, d_vals2, nw, 0, 2 * k, d_hist, d_parts,
-                                   bst);
         if (!cut) {
-            launch_postings(cur ? d_vals2 : d_vals, nw, d_woff, (int32_t)n_seqs, span, ix->d_post,
-                            bst);
+            launch_postings(d_keys, nw, d_woff, d_wseq, span, ix->d_post, bst);
         } else {  // drop the lists longer than max_posting, then place the others
             const uint32_t mp = (uint32_t)max_posting;
             uint32_t kept = 0;
@@ -2156,8 +2154,8 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
                 return fail(GG_EDEVICE);
             if ((s = alloc((void **)&ix->d_post, sizeof(int2) * kept)) != GG_OK) return fail(s);
             ix->n_post = kept;
-            launch_postings_cut(cur ? d_vals2 : d_vals, cur ? d_keys2 : d_keys, nw, d_woff,
-                                (int32_t)n_seqs, span, ix->d_list_off, d_kept, mp, ix->d_post, bst);
+            launch_postings_cut(d_keys, nw, d_woff, d_wseq, span, ix->d_list_off, d_kept, mp,
+                                ix->d_post, bst);
             if (hipMemcpyAsync(ix->d_list_off, d_kept, sizeof(uint32_t) * (ncode + 1),
                                hipMemcpyDeviceToDevice, bst) != hipSuccess)
                 return fail(GG_EDEVICE);
