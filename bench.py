@@ -178,17 +178,20 @@ def cpu_baseline(db, qs, max_hits: int, cap: int, hits_per_query: np.ndarray):
 
 
 # Algorithmic work per launch of each modelled kernel:
+#  probe   - HBM: 8 B of the following windows' codes per hit
 #  gather  - HBM: 8 B posting read + 8 B key write per hit
 #  filter  - HBM: 8 B key read per hit (the kept few are written back)
 #  sort_*  - HBM: 16 B per key per scatter pass, 8 B per histogram pass
 #  align   - integer ALU: ALIGN_OPS_PER_CELL int32 operations per in-band cell
-KERNEL = {"gather": "k_gather", "filter": "k_hit_filter", "gather_filter": "k_gather_filter",
+KERNEL = {"probe": "k_run_starts", "gather": "k_gather", "filter": "k_hit_filter",
+          "gather_filter": "k_gather_filter",
           "sort_scatter": "k_rs_scatter_seg",
           "sort_hist": "k_rs_hist_seg", "align": "k_bsw"}
 
 
 def rooflines(stages: dict, cells: int, nprof: int, workload: str):
     model = {
+        "probe": ("hbm", lambda st: 8 * st["units"]),
         "gather": ("hbm", lambda st: 16 * st["units"]),
         "filter": ("hbm", lambda st: 8 * st["units"]),
         # one posting entry read per hit; the kept keys it writes are a few per mille
@@ -218,7 +221,7 @@ def rooflines(stages: dict, cells: int, nprof: int, workload: str):
     return [one(s) for s in order]
 
 
-STAGES = ("encode", "scan", "gather_prep", "probe", "gather_count", "gather", "group",
+STAGES = ("encode", "scan", "gather_prep", "probe", "run_ends", "gather_count", "gather", "group",
           "gather_filter", "filter",
           "filter_compact", "sort_hist", "sort_scan", "sort_scatter", "chain", "chain_write",
           "extend", "merge", "merge_sweep", "select", "align", "report", "graph")

@@ -255,7 +255,10 @@ gg_status gg_index_set_hit_budget(gg_index *index, uint64_t bytes);
  * grouping   : how index hits become runs (Section 2.2 phase 2):
  *              0 probe the windows next to each hit (no hit stored),
  *              1 sort hits in LDS slices of each query's sequence range,
- *              2 radix-sort all hits of a wave (the default).
+ *              2 (the default) take run starts from the neighbour windows' codes kept
+ *              beside each posting, and sort those; radix-sort all hits of a wave where
+ *              one hit is a run long enough to keep (min_hsp_len at most the window
+ *              span) or max_gap reaches past three windows.
  * lane_steps : X-drop steps (Section 2.2 phase 3) one lane takes before a whole
  *              wave resumes the walk; 0..4096 (0: every walk by a wave), default 256.
  * ms         : gg_index_autotune only: wall time of the sample batch with this
@@ -269,7 +272,8 @@ gg_status gg_index_set_hit_budget(gg_index *index, uint64_t bytes);
  * graph_query_log2 : queries with more than 2^graph_query_log2 index hits skip the
  *              graph and take the regular path (heavy queries mostly outgrow the
  *              graph's per-query LDS sorts); 0 (default): only the wave size limits.
- * The environment variable GG_GROUPING (probe, bucket, sort) overrides grouping.
+ * The environment variable GG_GROUPING (probe, bucket, sort) overrides grouping;
+ * sort then sorts every hit.
  */
 typedef struct {
     int32_t grouping;
@@ -355,18 +359,19 @@ gg_status gg_device_read(const void *src, uint64_t bytes, uint64_t *sum);
  * Per-stage GPU timing of batched searches on this index, for roofline reports.
  * Enabling (on or off) clears the totals; when on, HIP events are recorded around
  * each stage on the stream it runs on.  Names: "encode", "scan", "gather_prep",
- * "gather" (the posting-gather kernel alone), "filter" (the kernel dropping hits
+ * "probe" (run starts, from the postings' contexts or by probing the bank), "run_ends"
+ * (the starts' runs), "gather" (the posting-gather kernel alone), "filter" (the kernel dropping hits
  * alone on their (sequence, diagonal) when M exceeds the seed span and sorting the
  * rest of each query), "filter_compact" (the kept hits' move into one array),
  * "sort_hist", "sort_scan", "sort_scatter" (one mark per radix pass of the hit
- * sort, when it runs), "chain" (run counts),
+ * or run sort, when it runs), "chain" (run counts),
  * "chain_write", "extend", "merge" (ordering for the sweep), "merge_sweep",
  * "select", "align" (the banded Smith-Waterman kernel alone), "report", and
  * "graph" (all replays of a batch's captured wave graph, whose kernels are not
  * timed one by one: units = waves).  ms is the summed GPU time between the marks,
  * launches the number of marks, units the work they covered (query bases for
- * encode and scan, positions for gather_prep, hits for gather, filter and the sort
- * marks, hits left after the filter for the chain marks, runs for
+ * encode and scan, positions for gather_prep, hits for probe, gather, filter and the
+ * sort marks (runs there when run starts are sorted), runs for run_ends, hits left after the filter for the chain marks, runs for
  * extend/merge/select, boxes for align/report).
  *
  * Batched calls without statistics, with the radix-sort grouping and 1 <= max_hits

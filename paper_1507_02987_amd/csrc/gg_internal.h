@@ -22,6 +22,7 @@ constexpr int kBswStage = 4096;          // box bases staged in LDS by the align
 constexpr int kBinCap = 1024;            // buckets one gather tile counts in LDS
 constexpr uint32_t kBucketCapMax = 512;  // most keys of one bucket (one wave sorts it in LDS)
 constexpr uint32_t kBucketBig = 16384;   // most keys of one bucket sorted by a block (128 KiB)
+constexpr int kPackSlack = 8;            // words that may be read past packed bases
 constexpr int kMaxProbe = 4;             // neighbour windows probed per side (G / k + 1)
 constexpr int kBoundCap = 2048;          // run bounds of one query paired in LDS
 constexpr int kLenBins = 1024;           // box-length bins of the selection prefilter
@@ -90,6 +91,32 @@ struct SortTile {
     uint32_t start, count, hbase, nt, tq;
 };
 
+// Context of a posting: the codes of the kCtx windows after it on its sequence
+// (next) and before it (prev), which are the only places where the next or the
+// previous hit of a run can be (bank windows sit at multiples of the span).  A
+// context is two words: lo = [count : 2 | part of window 3 | window 1], hi = [rest of
+// window 3 | window 2], count being the windows that exist.  The widths follow from
+// the code's 2k bits (CtxShape): window 2 is always whole, window 1 up to k = 15,
+// window 3 up to k = 10; a match of a field that is not whole is looked up in the bank.
+constexpr int kCtx = 3;
+struct CtxShape {
+    int32_t w1, w2, a, b;         // bits of window 1, window 2 and window 3's two parts
+    uint32_t m1, m2, m3lo, m3hi;  // the fields' bits in lo, hi, lo, hi
+    uint32_t exact;               // bit m - 1: window m's field holds the whole code
+};
+
+// The same fields for the windows after (n0, n1) and before (p0, p1) a query
+// position; vm: bit m - 1 set when the m-th window after it can be a run's next hit
+// (inside the query, its list not empty, m within the gap limit), bit 2 + m the same
+// for the m-th window before it.  qpos: the position in its query, ql that query in
+// the wave; head: its list's first posting less its first hit, so that hit j of the
+// wave is posting head + j.
+struct alignas(16) QCtx {
+    uint32_t vm, n0, n1, p0, p1;
+    int32_t qpos, ql;
+    uint32_t head;
+};
+
 // Which box field feeds a sort-key field.
 enum BoxField : int32_t {
     F_Q = 0, F_S, F_QS, F_QE, F_DS, F_DE, F_LEN_DESC
@@ -124,10 +151,21 @@ void launch_scan_u32(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *par
 size_t scan_partials_needed(int64_t n);
 void launch_query_totals(const uint64_t *hoff, const int64_t *qoff, int32_t nq, uint64_t *qtot,
                          hipStream_t st);
+// With ctx.qctx the wave finds its runs from the postings' contexts: the preparation
+// writes each position's QCtx instead of its akey, and each query's place for run
+// starts (sbase[ql] = half the hits before it, rounded up: a run has two hits at
+// least) and its zeroed count (scount[ql]).
+struct CtxPrep {
+    QCtx *qctx = nullptr;
+    const uint32_t *kcode = nullptr, *cnt = nullptr;  // per batch base
+    uint32_t *sbase = nullptr, *scount = nullptr;     // per query of the wave
+    int32_t span = 0, mmax = 0;
+    CtxShape shape{};
+};
 void launch_wave_prep(const uint64_t *hoff, const int64_t *qoff, const uint32_t *lhead,
-                      const int32_t *qid, int32_t qa, int64_t g0, int64_t g1, HitKeyLayout lay,
-                      uint32_t *hrel, uint32_t *pbase, uint64_t *akey, uint32_t *tile_pos,
-                      hipStream_t st);
+                      const int32_t *qid, int32_t qa, int32_t nqw, int64_t g0, int64_t g1,
+                      HitKeyLayout lay, uint32_t *hrel, uint32_t *pbase, uint64_t *akey,
+                      uint32_t *tile_pos, const CtxPrep &ctx, hipStream_t st);
 // Index build (Sections 2, 2.1): pack the bank 2 bits per base; code every
 // non-overlapping window (keys = code << 32 | window number, wseq = the window's
 // sequence); after a sort by code (the window numbers keep it stable), the list
@@ -189,10 +227,64 @@ void launch_range_counts(const uint32_t *kcode, const uint32_t *cnt, int64_t np,
 void launch_piece_prep(const uint32_t *kcode, const uint32_t *cnt, int64_t np,
                        const uint32_t *list_off, const int2 *post, int32_t s_lo, int32_t s_hi,
                        HitKeyLayout lay, uint32_t *pcnt, uint32_t *pbase, uint64_t *akey,
-                       hipStream_t st);
+                       const CtxPrep &ctx, hipStream_t st);
 void launch_gather(const uint32_t *hrel, const uint32_t *pbase, const uint64_t *akey,
                    int64_t npos, const int2 *post, uint32_t nhits, HitKeyLayout lay,
                    uint64_t *keys, const uint32_t *tile_pos, hipStream_t st);
+// Contexts of n postings (built once per index).
+CtxShape ctx_shape(int32_t k);
+void launch_contexts(const int2 *post, uint32_t n, const uint32_t *dbw, const int64_t *seq_start,
+                     int32_t span, uint32_t mask, CtxShape shape, uint2 *next, uint2 *prev,
+                     hipStream_t st);
+// Counts into bad[0] the postings that are not the window their list says, or not in
+// ascending order inside it, and into win[0] the windows of the bank's sequences whose
+// list is not empty; lists that pass with as many postings as windows are complete.
+void launch_check_lists(const uint32_t *list_off, const int2 *post, uint32_t n,
+                        const uint32_t *dbw, const int64_t *seq_start, int32_t n_seqs,
+                        int32_t span, uint32_t mask, unsigned long long *bad,
+                        unsigned long long *win, hipStream_t st);
+// Run starts from contexts (no hit stored): every hit with a next hit of its run
+// and no previous one, as a key [s | diag + bias | qpos], in its query's place of
+// `out` (sbase, scount), in no particular order inside it.  both: contexts of both
+// sides are read with every hit (long lists: most hits have neighbours), else the
+// side before it only for the few that have a next hit.
+struct RunStarts {
+    const uint32_t *hrel;
+    const QCtx *qctx;
+    const int2 *post;
+    const uint2 *next, *prev;
+    const uint32_t *tile_pos;
+    const int64_t *qoff;
+    const uint32_t *kcode, *kcnt;  // per batch base
+    const uint32_t *qpack, *dbw;
+    const int64_t *seq_start;
+    int64_t np, g0;
+    uint32_t nhits;
+    int32_t qa;
+    HitKeyLayout lay;
+    int32_t span;
+    uint32_t mask;
+    int32_t mmax, min_len;
+    int32_t cut;                   // a repeat cutoff dropped lists: a window's list may be empty
+    CtxShape shape;
+    uint32_t *sbase, *scount;
+    uint64_t *out;
+};
+void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const WaveCtl *ctl = nullptr,
+                       uint32_t hits_cap = 0);
+void launch_ctx_heads(const uint32_t *pbase, const uint32_t *hrel, int64_t np, QCtx *qctx,
+                      hipStream_t st);
+// Runs from their starts: each start's last hit is found along its diagonal.
+// launch_run_compact takes the starts from their queries' places (a.out) and
+// writes the runs in query order (offsets: off given, or, in a replayed wave of few
+// queries, summed here; then also off[0 .. nq_cap] and ctl->nc are written and *clear
+// zeroed); launch_run_ends takes n starts packed in query order, off[ql] their
+// offsets.
+void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *cands,
+                        hipStream_t st, WaveCtl *ctl = nullptr, int32_t nq_cap = 0,
+                        uint32_t *clear = nullptr, uint32_t *partials = nullptr);
+void launch_run_ends(const RunStarts &a, const uint64_t *keys, uint32_t n, const uint32_t *off,
+                     int32_t nqw, Cand *cands, hipStream_t st);
 // Runs found by probing the windows next to every hit (no stored hit): single-hit
 // runs and the bounds of longer runs; bounds are grouped by query, then sorted
 // and paired per query.  Runs in any order are finally grouped by query.
@@ -258,9 +350,10 @@ void launch_fill2_u32(uint32_t *a, size_t na, uint32_t *b, size_t nb, uint32_t v
 // advances the cursor.
 void launch_wave_end(uint32_t *cursor, hipStream_t st);
 void launch_wave_prep_ctl(const uint64_t *hoff, const int64_t *qoff, const uint32_t *lhead,
-                          const int32_t *qid, int64_t np_cap, uint32_t *hrel, uint32_t *pbase,
-                          uint64_t *akey, const WaveCtl *plan, const uint32_t *cursor,
-                          WaveCtl *ctl, uint32_t *tile_pos, hipStream_t st);
+                          const int32_t *qid, int64_t np_cap, int32_t nq_cap, uint32_t *hrel,
+                          uint32_t *pbase, uint64_t *akey, const WaveCtl *plan,
+                          const uint32_t *cursor, WaveCtl *ctl, uint32_t *tile_pos,
+                          const CtxPrep &ctx, hipStream_t st);
 void launch_gather_ctl(const uint32_t *hrel, const uint32_t *pbase, const uint64_t *akey,
                        const int2 *post, uint32_t hits_cap, uint64_t *keys, const WaveCtl *ctl,
                        const uint32_t *tile_pos, hipStream_t st);
@@ -330,7 +423,7 @@ void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32
                    int32_t match, int32_t mismatch, int32_t xdrop, Box *out, void *queue_mem,
                    int32_t lane_steps, hipStream_t st, const WaveCtl *ctl = nullptr,
                    uint32_t n_cap = 0, bool count_cleared = false);
-// The batch's T query codes packed 16 bases to a word ((T + 15) / 16 + 2 words).
+// The batch's T query codes packed 16 bases to a word ((T + 15) / 16 + kPackSlack words).
 void launch_pack_query(const uint8_t *qcode, int64_t T, uint32_t *qpack, hipStream_t st);
 void launch_box_keys(const Box *b, uint32_t n, KeyWord w, int32_t q_invalid, uint64_t *out,
                      const uint32_t *perm, hipStream_t st);

@@ -670,6 +670,39 @@ void launch_query_totals(const uint64_t *hoff, const int64_t *qoff, int32_t nq, 
 }
 
 // ------------------------------------------------------------------ S3: gather
+// The fields of three window codes in a context's two words (count left out).
+__device__ __forceinline__ uint2 ctx_pack(uint32_t c1, uint32_t c2, uint32_t c3, const CtxShape &s)
+{
+    uint2 r;
+    r.x = (c1 & s.m1) | ((c3 << s.w1) & s.m3lo);
+    r.y = (c2 & s.m2) | (s.b ? ((c3 >> s.a) << s.w2) & s.m3hi : 0u);
+    return r;
+}
+
+// Contexts around query position qpos of a query of L bases (kcode, cnt: of its
+// first base).
+__device__ __forceinline__ QCtx query_ctx(const CtxPrep &c, const uint32_t *__restrict__ kcode,
+                                          const uint32_t *__restrict__ cnt, int32_t qpos,
+                                          int32_t L, int32_t ql, uint32_t head)
+{
+    uint32_t nc[kCtx] = {0, 0, 0}, pc[kCtx] = {0, 0, 0}, vm = 0;
+#pragma unroll
+    for (int32_t m = 1; m <= kCtx; ++m) {
+        const int32_t qn = qpos + m * c.span, qp = qpos - m * c.span;
+        if (m <= c.mmax && qn + c.span <= L && cnt[qn] > 0u) {
+            vm |= 1u << (m - 1);
+            nc[m - 1] = kcode[qn];
+        }
+        if (m <= c.mmax && qp >= 0 && cnt[qp] > 0u) {
+            vm |= 1u << (kCtx + m - 1);
+            pc[m - 1] = kcode[qp];
+        }
+    }
+    const uint2 n = ctx_pack(nc[0], nc[1], nc[2], c.shape);
+    const uint2 p = ctx_pack(pc[0], pc[1], pc[2], c.shape);
+    return QCtx{vm, n.x, n.y, p.x, p.y, qpos, ql, head};
+}
+
 // Per position of the wave: its first hit (relative to the wave), the index of its
 // posting list's head, and the constant part of its hits' keys
 // (q << sh_q) + ((bias - qpos) << sh_d) + qpos.
@@ -678,60 +711,77 @@ void launch_query_totals(const uint64_t *hoff, const int64_t *qoff, int32_t nq, 
 // wave's end).
 __global__ void k_wave_prep(const uint64_t *__restrict__ hoff, const int64_t *__restrict__ qoff,
                             const uint32_t *__restrict__ lhead, const int32_t *__restrict__ qid,
-                            int32_t qa, int64_t g0,
+                            int32_t qa, int32_t nqw, int64_t g0,
                             int64_t np, HitKeyLayout lay, uint32_t *__restrict__ hrel,
                             uint32_t *__restrict__ pbase, uint64_t *__restrict__ akey,
                             const WaveCtl *__restrict__ plan, const uint32_t *__restrict__ cursor,
-                            WaveCtl *__restrict__ ctl, uint32_t *__restrict__ tile_pos)
+                            WaveCtl *__restrict__ ctl, uint32_t *__restrict__ tile_pos,
+                            int32_t nq_cap, CtxPrep ctx)
 {
     if (ctl) {
         const WaveCtl w = plan[*cursor];
         if (blockIdx.x == 0 && threadIdx.x == 0) *ctl = w;
         qa = w.qa;
+        nqw = w.nqw;
         g0 = w.g0;
         np = w.np;
         lay = w.lay;
     }
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > np) return;
     const uint64_t hb = hoff[g0];
+    if (ctx.qctx && p < nq_cap) {
+        if (p < nqw) ctx.sbase[p] = (uint32_t)((hoff[qoff[qa + p]] - hb + 1) >> 1);
+        ctx.scount[p] = 0;
+    }
+    if (p > np) return;
     const uint64_t r0 = hoff[g0 + p] - hb;
     hrel[p] = (uint32_t)r0;
     if (p == np) return;
-    if (tile_pos) {  // the position holding each gather tile's first hit
-        const uint64_t r1 = hoff[g0 + p + 1] - hb;
+    const uint64_t r1 = hoff[g0 + p + 1] - hb;
+    if (tile_pos)  // the position holding each gather tile's first hit
         for (uint64_t t = (r0 + kTile - 1) / kTile; t * kTile < r1; ++t) tile_pos[t] = (uint32_t)p;
-    }
     const int64_t g = g0 + p;
+    pbase[p] = lhead[g];
+    if (ctx.qctx) {
+        if (r1 > r0) {  // positions without hits are never looked at
+            const int32_t q = qid[g];
+            const int64_t qb = qoff[q];
+            ctx.qctx[p] = query_ctx(ctx, ctx.kcode + qb, ctx.cnt + qb, (int32_t)(g - qb),
+                                    (int32_t)(qoff[q + 1] - qb), q - qa,
+                                    lhead[g] - (uint32_t)r0);
+        }
+        return;
+    }
     const int32_t q = qid[g];
     const int32_t qpos = (int32_t)(g - qoff[q]);
-    pbase[p] = lhead[g];
     const int sh_d = lay.bp, sh_q = lay.bp + lay.bd + lay.bs;
     const uint64_t qpart = sh_q >= 64 ? 0ull : ((uint64_t)(uint32_t)(q - qa) << sh_q);
     akey[p] = qpart + ((uint64_t)(uint32_t)(lay.bias - qpos) << sh_d) + (uint64_t)(uint32_t)qpos;
 }
 
 void launch_wave_prep(const uint64_t *hoff, const int64_t *qoff, const uint32_t *lhead,
-                      const int32_t *qid, int32_t qa, int64_t g0, int64_t g1, HitKeyLayout lay,
-                      uint32_t *hrel, uint32_t *pbase, uint64_t *akey, uint32_t *tile_pos,
-                      hipStream_t st)
+                      const int32_t *qid, int32_t qa, int32_t nqw, int64_t g0, int64_t g1,
+                      HitKeyLayout lay, uint32_t *hrel, uint32_t *pbase, uint64_t *akey,
+                      uint32_t *tile_pos, const CtxPrep &ctx, hipStream_t st)
 {
     const int64_t np = g1 - g0;
-    const int64_t nb = (np + 1 + kBlock - 1) / kBlock;
-    k_wave_prep<<<dim3((uint32_t)nb), dim3(kBlock), 0, st>>>(hoff, qoff, lhead, qid, qa, g0, np,
-                                                             lay, hrel, pbase, akey, nullptr,
-                                                             nullptr, nullptr, tile_pos);
+    const int64_t nb = (std::max<int64_t>(np + 1, nqw) + kBlock - 1) / kBlock;
+    k_wave_prep<<<dim3((uint32_t)nb), dim3(kBlock), 0, st>>>(hoff, qoff, lhead, qid, qa, nqw, g0,
+                                                             np, lay, hrel, pbase, akey, nullptr,
+                                                             nullptr, nullptr, tile_pos, nqw, ctx);
 }
 
 void launch_wave_prep_ctl(const uint64_t *hoff, const int64_t *qoff, const uint32_t *lhead,
-                          const int32_t *qid, int64_t np_cap, uint32_t *hrel, uint32_t *pbase,
-                          uint64_t *akey, const WaveCtl *plan, const uint32_t *cursor,
-                          WaveCtl *ctl, uint32_t *tile_pos, hipStream_t st)
+                          const int32_t *qid, int64_t np_cap, int32_t nq_cap, uint32_t *hrel,
+                          uint32_t *pbase, uint64_t *akey, const WaveCtl *plan,
+                          const uint32_t *cursor, WaveCtl *ctl, uint32_t *tile_pos,
+                          const CtxPrep &ctx, hipStream_t st)
 {
-    const int64_t nb = (np_cap + 1 + kBlock - 1) / kBlock;
-    k_wave_prep<<<dim3((uint32_t)nb), dim3(kBlock), 0, st>>>(hoff, qoff, lhead, qid, 0, 0, 0,
+    const int64_t nb = (std::max<int64_t>(np_cap + 1, nq_cap) + kBlock - 1) / kBlock;
+    k_wave_prep<<<dim3((uint32_t)nb), dim3(kBlock), 0, st>>>(hoff, qoff, lhead, qid, 0, 0, 0, 0,
                                                              HitKeyLayout{}, hrel, pbase, akey,
-                                                             plan, cursor, ctl, tile_pos);
+                                                             plan, cursor, ctl, tile_pos, nq_cap,
+                                                             ctx);
 }
 
 // ------------------------------------------------------------------ S3 by sequence range
@@ -791,9 +841,10 @@ __global__ void k_piece_prep(const uint32_t *__restrict__ kcode, const uint32_t 
                              int64_t np, const uint32_t *__restrict__ list_off,
                              const int2 *__restrict__ post, int32_t s_lo, int32_t s_hi,
                              HitKeyLayout lay, uint32_t *__restrict__ pcnt,
-                             uint32_t *__restrict__ pbase, uint64_t *__restrict__ akey)
+                             uint32_t *__restrict__ pbase, uint64_t *__restrict__ akey, CtxPrep ctx)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (ctx.qctx && p == 0) ctx.sbase[0] = ctx.scount[0] = 0;
     if (p >= np) return;
     const uint32_t n = cnt[p];
     uint32_t a = 0, b = 0;
@@ -805,17 +856,21 @@ __global__ void k_piece_prep(const uint32_t *__restrict__ kcode, const uint32_t 
     pbase[p] = a;
     pcnt[p] = b - a;
     const int32_t qpos = (int32_t)p;
+    if (ctx.qctx) {  // kcode and cnt are the query's own here
+        if (b > a) ctx.qctx[p] = query_ctx(ctx, kcode, cnt, qpos, (int32_t)np, 0, 0);
+        return;
+    }
     akey[p] = ((uint64_t)(uint32_t)(lay.bias - qpos) << lay.bp) + (uint64_t)(uint32_t)qpos;
 }
 
 void launch_piece_prep(const uint32_t *kcode, const uint32_t *cnt, int64_t np,
                        const uint32_t *list_off, const int2 *post, int32_t s_lo, int32_t s_hi,
                        HitKeyLayout lay, uint32_t *pcnt, uint32_t *pbase, uint64_t *akey,
-                       hipStream_t st)
+                       const CtxPrep &ctx, hipStream_t st)
 {
     if (np <= 0) return;
     k_piece_prep<<<(uint32_t)((np + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-        kcode, cnt, np, list_off, post, s_lo, s_hi, lay, pcnt, pbase, akey);
+        kcode, cnt, np, list_off, post, s_lo, s_hi, lay, pcnt, pbase, akey, ctx);
 }
 
 // Load-balanced over hits: block b owns hits [b*kTile, (b+1)*kTile) of the wave.
@@ -2472,6 +2527,523 @@ void launch_hit_compact(const uint64_t *keys, const uint32_t *hrel, const int64_
                                          out, ctl);
 }
 
+// ------------------------------------------------------------------ S3+S4+S5 from contexts
+// Bank windows start at multiples of the span, so the next hit of a run lies on the
+// same diagonal 1, 2, ... windows on, and the previous one as many windows back,
+// no further than the gap limit allows (mmax = G / span + 1).  The codes of those
+// windows are stored with each posting, in list order (its context), so one
+// coalesced read beside the list tells for every hit whether it starts a run of at
+// least two hits (all that M > span can keep): a next hit and no previous one.
+// Nothing is stored for any other hit, nothing is sorted by diagonal or position,
+// and the runs are those of sorting all hits by (q, s, diag, qpos) and scanning them.
+// 2,000 queries of 500-5,000 bp on a 3 Gbp bank with repeats (16.7 G hits, 3.4 G
+// runs): starts 86, three passes over them 60 and their ends 72 ms, where gathering,
+// five radix passes over every hit and chaining took 618.
+CtxShape ctx_shape(int32_t k)
+{
+    auto mask = [](int32_t n) { return n >= 32 ? ~0u : (1u << n) - 1u; };
+    CtxShape s;
+    const int32_t c = 2 * k;
+    s.w1 = std::min(c, 30);
+    s.w2 = c;
+    s.a = std::min(30 - s.w1, c);
+    s.b = std::min(32 - s.w2, c - s.a);
+    s.m1 = mask(s.w1);
+    s.m2 = mask(s.w2);
+    s.m3lo = s.a ? mask(s.a) << s.w1 : 0u;
+    s.m3hi = s.b ? mask(s.b) << s.w2 : 0u;
+    s.exact = (s.w1 == c ? 1u : 0u) | 2u | (s.a + s.b == c ? 4u : 0u);
+    return s;
+}
+
+// 64 bases of a 2-bit packed array from base g (reads words g / 16 .. g / 16 + 4).
+struct Bases64 {
+    uint64_t h, l;
+};
+__device__ __forceinline__ Bases64 bases64(const uint32_t *__restrict__ w, int64_t g)
+{
+    const int64_t wi = g >> 4;
+    const uint32_t sh = 32u - ((uint32_t)(g & 15) << 1);
+    const u32x4_a4 v = *reinterpret_cast<const u32x4_a4 *>(w + wi);
+    const uint32_t e = w[wi + 4];
+    const uint32_t a = (uint32_t)((((uint64_t)v.x << 32) | v.y) >> sh);
+    const uint32_t b = (uint32_t)((((uint64_t)v.y << 32) | v.z) >> sh);
+    const uint32_t c = (uint32_t)((((uint64_t)v.z << 32) | v.w) >> sh);
+    const uint32_t d = (uint32_t)((((uint64_t)v.w << 32) | e) >> sh);
+    return Bases64{((uint64_t)a << 32) | b, ((uint64_t)c << 32) | d};
+}
+
+// A plain window's neighbours on each side lie in 64 bases, read with one wide load
+// and one word; a masked window's are coded base by base.
+__global__ void k_contexts(const int2 *__restrict__ post, uint32_t n,
+                           const uint32_t *__restrict__ dbw,
+                           const int64_t *__restrict__ seq_start, int32_t span, uint32_t mask,
+                           CtxShape shape, uint2 *__restrict__ next, uint2 *__restrict__ prev)
+{
+    static_assert(kCtx * 16 <= 64, "three plain windows fit 64 bases");
+    const bool plain = span <= 16 && mask == (1u << span) - 1u;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const int2 e = post[i];
+        const int64_t s0 = seq_start[e.x];
+        const int32_t ns = (int32_t)(seq_start[e.x + 1] - s0);
+        const int32_t from = max(0, e.y - kCtx * span);  // first base of the side before
+        unsigned __int128 xn = 0, xp = 0;
+        if (plain) {
+            const Bases64 u = bases64(dbw, s0 + e.y + span), v = bases64(dbw, s0 + from);
+            xn = ((unsigned __int128)u.h << 64) | u.l;
+            xp = ((unsigned __int128)v.h << 64) | v.l;
+        }
+        uint32_t nc[kCtx] = {0, 0, 0}, pc[kCtx] = {0, 0, 0}, nn = 0, pn = 0;
+#pragma unroll
+        for (int32_t m = 1; m <= kCtx; ++m) {
+            const int64_t dn = (int64_t)e.y + m * span;
+            const int32_t dp = e.y - m * span;
+            if (dn + span <= ns) {
+                nc[m - 1] = plain ? (uint32_t)((uint64_t)((xn << (2 * (m - 1) * span)) >> 64) >>
+                                               (64 - 2 * span))
+                                  : db_code(dbw, s0 + dn, span, mask);
+                nn = m;
+            }
+            if (dp >= 0) {
+                pc[m - 1] = plain ? (uint32_t)((uint64_t)((xp << (2 * (dp - from))) >> 64) >>
+                                               (64 - 2 * span))
+                                  : db_code(dbw, s0 + dp, span, mask);
+                pn = m;
+            }
+        }
+        uint2 c = ctx_pack(nc[0], nc[1], nc[2], shape);
+        next[i] = uint2{c.x | (nn << 30), c.y};
+        c = ctx_pack(pc[0], pc[1], pc[2], shape);
+        prev[i] = uint2{c.x | (pn << 30), c.y};
+    }
+}
+
+void launch_contexts(const int2 *post, uint32_t n, const uint32_t *dbw, const int64_t *seq_start,
+                     int32_t span, uint32_t mask, CtxShape shape, uint2 *next, uint2 *prev,
+                     hipStream_t st)
+{
+    if (n == 0) return;
+    const uint32_t nb = (uint32_t)std::min<uint64_t>(((uint64_t)n + kBlock - 1) / kBlock, kMaxGrid);
+    k_contexts<<<nb, kBlock, 0, st>>>(post, n, dbw, seq_start, span, mask, shape, next, prev);
+}
+
+__global__ void k_check_post(const uint32_t *__restrict__ list_off, const int2 *__restrict__ post,
+                             uint32_t n, const uint32_t *__restrict__ dbw,
+                             const int64_t *__restrict__ seq_start, int32_t span, uint32_t mask,
+                             unsigned long long *__restrict__ bad)
+{
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (uint64_t)gridDim.x * blockDim.x) {
+        const int2 e = post[i];
+        const uint32_t c = db_code(dbw, seq_start[e.x] + e.y, span, mask);
+        bool ok = list_off[c] <= i && i < list_off[(size_t)c + 1];
+        if (ok && i > list_off[c]) {
+            const int2 b = post[i - 1];
+            ok = b.x < e.x || (b.x == e.x && b.y < e.y);
+        }
+        if (!ok) atomicAdd(bad, 1ull);
+    }
+}
+
+__global__ void k_check_windows(const uint32_t *__restrict__ list_off,
+                                const uint32_t *__restrict__ dbw,
+                                const int64_t *__restrict__ seq_start, int32_t n_seqs,
+                                int32_t span, uint32_t mask, unsigned long long *__restrict__ win)
+{
+    unsigned long long c = 0;
+    for (int32_t s = blockIdx.x; s < n_seqs; s += gridDim.x) {
+        const int64_t s0 = seq_start[s], nw = (seq_start[s + 1] - s0) / span;
+        for (int64_t w = threadIdx.x; w < nw; w += blockDim.x) {
+            const size_t code = db_code(dbw, s0 + w * span, span, mask);
+            c += list_off[code + 1] > list_off[code];
+        }
+    }
+    if (c) atomicAdd(win, c);
+}
+
+void launch_check_lists(const uint32_t *list_off, const int2 *post, uint32_t n,
+                        const uint32_t *dbw, const int64_t *seq_start, int32_t n_seqs,
+                        int32_t span, uint32_t mask, unsigned long long *bad,
+                        unsigned long long *win, hipStream_t st)
+{
+    if (n) {
+        const uint32_t nb =
+            (uint32_t)std::min<uint64_t>(((uint64_t)n + kBlock - 1) / kBlock, kMaxGrid);
+        k_check_post<<<nb, kBlock, 0, st>>>(list_off, post, n, dbw, seq_start, span, mask, bad);
+    }
+    if (n_seqs > 0)
+        k_check_windows<<<(uint32_t)std::min(n_seqs, 16384), kBlock, 0, st>>>(
+            list_off, dbw, seq_start, n_seqs, span, mask, win);
+}
+
+// Windows of a posting's context that match a query position's, of those that exist
+// on both sides (bit m - 1: window m); a field that is not whole may match wrongly.
+__device__ __forceinline__ uint32_t ctx_match(uint2 c, uint32_t q0, uint32_t q1, uint32_t vm,
+                                              const CtxShape &s)
+{
+    const uint32_t x = c.x ^ q0, y = c.y ^ q1;
+    uint32_t r = (x & s.m1) == 0 ? 1u : 0u;
+    r |= (y & s.m2) == 0 ? 2u : 0u;
+    r |= ((x & s.m3lo) | (y & s.m3hi)) == 0 ? 4u : 0u;
+    return r & vm & ((1u << (c.x >> 30)) - 1u);
+}
+
+// Inclusive running maximum over the wave's lanes of values >= 0 (every lane active):
+// row shifts by DPP, then the last lane of each row to the next row and the last two.
+__device__ __forceinline__ int32_t wave_run_max(int32_t x)
+{
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));  // row_shr:1
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));  // row_bcast:15
+    x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
+    return x;
+}
+
+// End (query position past the last hit) of the run whose first hit is at query
+// position qs on diagonal d: 64 bases of the diagonal are compared at once, and each
+// next hit is the nearest window of the next mmax that matches.  wm: the coded
+// bases of a window, its first base in the top bits.
+__device__ __forceinline__ int32_t run_end(const RunStarts &a, uint64_t wm, int64_t q0, int32_t L,
+                                           int64_t s0, int32_t ns, int32_t d, int32_t qs)
+{
+    const int32_t k = a.span;
+    const int32_t last = min(L - qs, ns - (qs + d)) - k;  // the last window inside both
+    const int64_t gq = q0 + qs, gb = s0 + qs + d;
+    int32_t o = 0, cb = -64;
+    unsigned __int128 x = 0;
+    for (;;) {
+        bool found = false;
+        for (int32_t m = 1, w = o + k; m <= a.mmax && w <= last; ++m, w += k) {
+            if (w + k > cb + 64) {
+                cb = w;
+                const Bases64 u = bases64(a.qpack, gq + w), v = bases64(a.dbw, gb + w);
+                x = ((unsigned __int128)(u.h ^ v.h) << 64) | (u.l ^ v.l);
+            }
+            if (((uint64_t)((x << (2 * (w - cb))) >> 64) & wm) == 0 &&
+                (!a.cut || a.kcnt[gq + w] > 0u)) {
+                o = w;
+                found = true;
+                break;
+            }
+        }
+        if (!found) return qs + o + k;
+    }
+}
+
+// The coded bases of a window of `span` bases, first base in the top two bits.
+__device__ __forceinline__ uint64_t window_bits(int32_t span, uint32_t mask)
+{
+    uint64_t wm = 0;
+    for (int32_t t = 0; t < span; ++t)
+        if ((mask >> t) & 1u) wm |= 3ull << (62 - 2 * t);
+    return wm;
+}
+
+// Whether hit `idx` of position p (context q) starts a run of at least two hits that
+// is long enough, and its key; nm, pm: the windows after and before it that match by
+// context.  Fields that are not whole are looked up in the bank.
+__device__ __forceinline__ bool run_start(const RunStarts &a, const QCtx &q, uint32_t p,
+                                          uint32_t idx, uint32_t nm, uint32_t pm, uint64_t *key)
+{
+    const int2 e = a.post[idx];
+    bool ok = true;
+    if (pm != 0 || (nm & a.shape.exact) == 0) {
+        const int64_t g = a.g0 + p, s0 = a.seq_start[e.x];
+        for (; ok && pm; pm &= pm - 1) {
+            const int32_t o = -(__ffs((int)pm) * a.span);
+            ok = db_code(a.dbw, s0 + e.y + o, a.span, a.mask) != a.kcode[g + o];
+        }
+        bool succ = (nm & a.shape.exact) != 0;
+        for (; ok && !succ && nm; nm &= nm - 1) {
+            const int32_t o = __ffs((int)nm) * a.span;
+            succ = db_code(a.dbw, s0 + e.y + o, a.span, a.mask) == a.kcode[g + o];
+        }
+        ok = ok && succ;
+    }
+    if (ok && a.min_len > 2 * a.span) {  // two hits may be too short
+        const int64_t q0 = a.qoff[a.qa + q.ql], s0 = a.seq_start[e.x];
+        const int32_t qe = run_end(a, window_bits(a.span, a.mask), q0,
+                                   (int32_t)(a.qoff[a.qa + q.ql + 1] - q0), s0,
+                                   (int32_t)(a.seq_start[e.x + 1] - s0), e.y - q.qpos, q.qpos);
+        ok = qe - q.qpos >= a.min_len;
+    }
+    *key = ((uint64_t)(uint32_t)e.x << (a.lay.bd + a.lay.bp)) |
+           ((uint64_t)(uint32_t)(e.y - q.qpos + a.lay.bias) << a.lay.bp) |
+           (uint64_t)(uint32_t)q.qpos;
+    return ok;
+}
+
+// A tile of kTile consecutive hits at a time, `tiles` of them per block.  Each
+// position with hits in the tile marks its first one in LDS, and a running maximum
+// over the tile gives every hit its position (a binary search per hit took nine
+// dependent LDS reads where lists are short).  Contexts are read coalesced, four rows
+// of 64 hits in flight per wave.  The starts of tiles that lie in one query are
+// collected in LDS and written kTile or more at once, with one add to the query's
+// count: adds to one counter are done one after another, 13.5 ns each, so with one
+// per wave and row a query with long lists took 44 ps per hit.
+constexpr uint32_t kStartCap = 2 * kTile - 16;  // four blocks to a CU's LDS
+
+template <bool BOTH>
+__global__ __launch_bounds__(kBlock, 4) void k_run_starts(RunStarts a,
+                                                          const WaveCtl *__restrict__ ctl,
+                                                          int32_t tiles)
+{
+    if (ctl) {
+        a.np = ctl->np;
+        a.g0 = ctl->g0;
+        a.nhits = ctl->H;
+        a.qa = ctl->qa;
+        a.lay = ctl->lay;
+    }
+    constexpr int kWaves = kBlock / 64, kHalf = kItems / 2;
+    __shared__ int32_t s_p[kTile];    // 1 + position (from the tile's first) at its first hit
+    __shared__ uint64_t s_key[kStartCap];  // starts not yet written
+    __shared__ int32_t s_wm[kWaves];
+    __shared__ uint32_t s_lo, s_hi, s_at, s_n;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
+    int32_t lq = -1;  // the query of the s_n keys in s_key
+    if (threadIdx.x == 0) s_n = 0;
+    // nlist: s_n, read by every thread between two barriers with no add to it
+    auto flush = [&](uint32_t nlist) {
+        if (nlist == 0) return;
+        if (threadIdx.x == 0) s_at = a.sbase[lq] + atomicAdd(a.scount + lq, nlist);
+        __syncthreads();
+        const uint32_t at = s_at;
+        for (uint32_t i = threadIdx.x; i < nlist; i += kBlock) a.out[at + i] = s_key[i];
+        if (threadIdx.x == 0) s_n = 0;
+        __syncthreads();
+    };
+    for (int32_t ti = 0; ti < tiles; ++ti) {
+        const uint32_t tile = blockIdx.x * (uint32_t)tiles + (uint32_t)ti;
+        const uint32_t t0 = tile * (uint32_t)kTile;
+        if (t0 >= a.nhits) break;  // a graph's grid covers the largest wave
+        const uint32_t cnt = min((uint32_t)kTile, a.nhits - t0);
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) s_p[r * kBlock + threadIdx.x] = 0;
+        if (a.tile_pos) {
+            if (threadIdx.x == 0) {
+                s_lo = a.tile_pos[tile];
+                s_hi = t0 + cnt < a.nhits ? a.tile_pos[tile + 1] : (uint32_t)(a.np - 1);
+            }
+        } else if (threadIdx.x < 2) {  // the last position with hrel <= the tile's first or last hit
+            const uint32_t j = threadIdx.x ? t0 + cnt - 1 : t0;
+            uint32_t x = 0, y = (uint32_t)(a.np - 1);
+            while (x < y) {
+                const uint32_t m = x + ((y - x + 1) >> 1);
+                if (a.hrel[m] <= j) x = m;
+                else y = m - 1;
+            }
+            if (threadIdx.x) s_hi = x;
+            else s_lo = x;
+        }
+        __syncthreads();
+        const uint32_t lo = s_lo, hi = s_hi, held = s_n;
+        for (uint32_t p = lo + threadIdx.x; p <= hi; p += kBlock) {
+            const uint32_t r0 = a.hrel[p], r1 = a.hrel[p + 1];
+            if (r1 > r0 && r1 > t0 && r0 < t0 + cnt) s_p[max(r0, t0) - t0] = (int32_t)(p - lo) + 1;
+        }
+        __syncthreads();
+        // wave wv's hits: rows of 64 from wv * kTile / kWaves
+        const uint32_t w0 = wv * (kTile / kWaves) + lane;
+        int32_t pr[kItems], run = 0;
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            pr[r] = max(wave_run_max(s_p[w0 + r * 64]), run);
+            run = __builtin_amdgcn_readlane(pr[r], 63);
+        }
+        if (lane == 0) s_wm[wv] = run;
+        __syncthreads();
+        int32_t before = 0, last = 0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            last = max(last, s_wm[i]);
+            if (i < wv) before = last;
+        }
+        const int32_t qf = a.qctx[lo].ql, qt = a.qctx[lo + (uint32_t)last - 1u].ql;
+        const bool one = qf == qt;
+        if (lq >= 0 && (!one || qf != lq || held > kStartCap - kTile)) flush(held);
+        lq = one ? qf : -1;
+#pragma unroll
+        for (int h = 0; h < kItems; h += kHalf) {
+            QCtx q[kHalf];
+            uint32_t idx[kHalf], pos[kHalf];
+            uint2 cn[kHalf], cp[kHalf];
+#pragma unroll
+            for (int r = 0; r < kHalf; ++r) {
+                // lanes past the tile read its last hit
+                const uint32_t l = min(w0 + (h + r) * 64, cnt - 1);
+                const int32_t x = max(pr[h + r], before);
+                pos[r] = lo + (uint32_t)(w0 + (h + r) * 64 < cnt ? x : last) - 1u;
+                q[r] = a.qctx[pos[r]];
+                idx[r] = q[r].head + t0 + l;
+                cn[r] = a.next[idx[r]];
+                if (BOTH) cp[r] = a.prev[idx[r]];
+            }
+#pragma unroll
+            for (int r = 0; r < kHalf; ++r) {
+                const uint32_t nm = ctx_match(cn[r], q[r].n0, q[r].n1, q[r].vm, a.shape);
+                bool st = w0 + (h + r) * 64 < cnt && nm != 0;
+                uint32_t pm = 0;
+                uint64_t key = 0;
+                if (BOTH || st) {
+                    if (!BOTH) cp[r] = a.prev[idx[r]];
+                    pm = ctx_match(cp[r], q[r].p0, q[r].p1, q[r].vm >> kCtx, a.shape);
+                    st = st && (pm & a.shape.exact) == 0;
+                }
+                if (st) st = run_start(a, q[r], pos[r], idx[r], nm, pm, &key);
+                uint64_t left = __ballot(st);
+                if (left == 0) continue;
+                if (one) {
+                    uint32_t at = 0;
+                    if (lane == 0) at = atomicAdd(&s_n, (uint32_t)__popcll(left));
+                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
+                    if (st) s_key[at + (uint32_t)__popcll(left & below)] = key;
+                    continue;
+                }
+                const int32_t ql = st ? q[r].ql : -1;
+                while (left) {  // several queries: one counter add per row and query
+                    const int f = __ffsll((unsigned long long)left) - 1;
+                    const int32_t q1 = __shfl(ql, f, 64);
+                    const uint64_t same = __ballot(ql == q1);
+                    uint32_t at = 0;
+                    if (lane == f)
+                        at = a.sbase[q1] + atomicAdd(a.scount + q1, (uint32_t)__popcll(same));
+                    at = __shfl(at, f, 64);
+                    if (ql == q1) a.out[at + (uint32_t)__popcll(same & below)] = key;
+                    left &= ~same;
+                }
+            }
+        }
+        __syncthreads();  // keys and marks of this tile are in place and read
+    }
+    if (lq >= 0) flush(s_n);
+}
+
+void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const WaveCtl *ctl,
+                       uint32_t hits_cap)
+{
+    const uint32_t h = ctl ? hits_cap : a.nhits;
+    if (h == 0) return;
+    // eight tiles per block once every CU gets several such blocks: fewer, larger
+    // writes and counter adds
+    const uint32_t nt = (h + kTile - 1) / kTile;
+    const int32_t tiles = nt >= 8u * 256u * 8u ? 8 : 1;
+    const uint32_t nb = (nt + tiles - 1) / tiles;
+    if (both) k_run_starts<true><<<nb, kBlock, 0, st>>>(a, ctl, tiles);
+    else k_run_starts<false><<<nb, kBlock, 0, st>>>(a, ctl, tiles);
+}
+
+// QCtx::head of a piece's positions, once their hits are scanned.
+__global__ void k_ctx_heads(const uint32_t *__restrict__ pbase, const uint32_t *__restrict__ hrel,
+                            int64_t np, QCtx *__restrict__ qctx)
+{
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < np) qctx[p].head = pbase[p] - hrel[p];
+}
+
+void launch_ctx_heads(const uint32_t *pbase, const uint32_t *hrel, int64_t np, QCtx *qctx,
+                      hipStream_t st)
+{
+    if (np > 0)
+        k_ctx_heads<<<(uint32_t)((np + kBlock - 1) / kBlock), kBlock, 0, st>>>(pbase, hrel, np,
+                                                                               qctx);
+}
+
+// The run of wave query ql that starts at `key`.
+__device__ __forceinline__ Cand run_of(const RunStarts &a, uint64_t wm, const HitKeyLayout &lay,
+                                       uint64_t key, int32_t ql, int64_t q0, int32_t L)
+{
+    Cand c;
+    c.q = ql;
+    c.qs = (int32_t)(key & low_mask(lay.bp));
+    c.d = (int32_t)((key >> lay.bp) & low_mask(lay.bd)) - lay.bias;
+    c.s = (int32_t)shr64(key, lay.bp + lay.bd);
+    const int64_t s0 = a.seq_start[c.s];
+    c.qe = run_end(a, wm, q0, L, s0, (int32_t)(a.seq_start[c.s + 1] - s0), c.d, c.qs);
+    return c;
+}
+
+// Block ql: the runs of the wave's query ql, from its place in a.out to off[ql].
+__global__ __launch_bounds__(kBlock) void k_run_compact(RunStarts a, int32_t nqw,
+                                                        uint32_t *__restrict__ off,
+                                                        Cand *__restrict__ cands,
+                                                        WaveCtl *__restrict__ ctl, bool sum,
+                                                        uint32_t *__restrict__ clear)
+{
+    HitKeyLayout lay = a.lay;
+    int32_t qa = a.qa;
+    const int32_t ql = (int32_t)blockIdx.x;
+    if (ctl) {
+        qa = ctl->qa;
+        nqw = ctl->nqw;
+        lay = ctl->lay;
+    }
+    // counts past the wave's queries are zero, so offsets there are the total
+    const uint32_t at = sum ? block_sum(a.scount, (uint32_t)ql) : off[ql];
+    const uint32_t n = a.scount[ql];
+    if (ctl && threadIdx.x == 0) {
+        if (sum) off[ql] = at;
+        if (ql == (int32_t)gridDim.x - 1) {
+            if (sum) off[ql + 1] = at + n;
+            ctl->nc = at + n;
+            *clear = 0u;
+        }
+    }
+    if (ql >= nqw || n == 0) return;
+    const uint64_t *src = a.out + a.sbase[ql];
+    const int64_t q0 = a.qoff[qa + ql];
+    const int32_t L = (int32_t)(a.qoff[qa + ql + 1] - q0);
+    const uint64_t wm = window_bits(a.span, a.mask);
+    for (uint32_t i = threadIdx.x; i < n; i += kBlock)
+        cands[at + i] = run_of(a, wm, lay, src[i], ql, q0, L);
+}
+
+void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *cands,
+                        hipStream_t st, WaveCtl *ctl, int32_t nq_cap, uint32_t *clear,
+                        uint32_t *partials)
+{
+    const int32_t nb = ctl ? nq_cap : nqw;
+    if (nb <= 0) return;
+    // a replayed wave of a few thousand queries skips the scan: blocks add up the
+    // counts before them
+    const bool sum = ctl && nq_cap <= 4096;
+    if (ctl && !sum) launch_scan_u32(a.scount, off, nq_cap, partials, st);
+    k_run_compact<<<nb, kBlock, 0, st>>>(a, nqw, off, cands, ctl, sum, clear);
+}
+
+__global__ __launch_bounds__(kBlock) void k_run_ends(RunStarts a, const uint64_t *__restrict__ keys,
+                                                     uint32_t n, const uint32_t *__restrict__ off,
+                                                     int32_t nqw, Cand *__restrict__ cands)
+{
+    const uint32_t i = blockIdx.x * (uint32_t)kBlock + threadIdx.x;
+    if (i >= n) return;
+    // the query of the wave's first run; the others are seldom past its end
+    int32_t ql = 0;
+    {
+        const uint32_t i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)i);
+        int32_t hi = nqw - 1;
+        while (ql < hi) {
+            const int32_t m = (ql + hi + 1) >> 1;
+            if (off[m] <= i0) ql = m;
+            else hi = m - 1;
+        }
+    }
+    while (i >= off[ql + 1]) ++ql;
+    const int64_t q0 = a.qoff[a.qa + ql];
+    const int32_t L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
+    cands[i] = run_of(a, window_bits(a.span, a.mask), a.lay, keys[i], ql, q0, L);
+}
+
+void launch_run_ends(const RunStarts &a, const uint64_t *keys, uint32_t n, const uint32_t *off,
+                     int32_t nqw, Cand *cands, hipStream_t st)
+{
+    if (n) k_run_ends<<<(n + kBlock - 1) / kBlock, kBlock, 0, st>>>(a, keys, n, off, nqw, cands);
+}
+
 // ------------------------------------------------------------------ S5: chain + filter
 // A sorted hit ends a run when the next hit is in another (q, s, diag) group or
 // more than G past this hit's window; the run's first hit is found by walking back
@@ -2896,7 +3468,7 @@ __device__ __forceinline__ uint32_t queue_slot(bool need, uint32_t *__restrict__
 }
 
 // The batch's query codes packed 16 to a word like the data bank (first base in
-// the top bits), for the extension's word compares; two spare words at the end.
+// the top bits), for the extension's word compares; kPackSlack spare words at the end.
 __global__ void k_pack_query(const uint8_t *__restrict__ qcode, int64_t T,
                              uint32_t *__restrict__ qpack, int64_t nwords)
 {
@@ -2914,7 +3486,7 @@ __global__ void k_pack_query(const uint8_t *__restrict__ qcode, int64_t T,
 
 void launch_pack_query(const uint8_t *qcode, int64_t T, uint32_t *qpack, hipStream_t st)
 {
-    const int64_t nwords = (T + 15) / 16 + 2;
+    const int64_t nwords = (T + 15) / 16 + kPackSlack;
     k_pack_query<<<(uint32_t)((nwords + kBlock - 1) / kBlock), kBlock, 0, st>>>(qcode, T, qpack,
                                                                              nwords);
 }

@@ -115,6 +115,7 @@ struct Workspace {
     DevBuf selbox;                      // the box index of each selection (replayed waves)
     DevBuf bsw_order;                   // the aligner's class counts and box order
     DevBuf bq;                          // the query of each encode block's first base
+    DevBuf qctx, sbase, scount;         // run starts from contexts: per position, per query
     // small pinned staging: [0] a wave's counts, [1] a batch's query offsets and hit
     // totals, [2] the replayed waves' plan, overflow flags and result counts
     void *pinned[3] = {nullptr, nullptr, nullptr};
@@ -146,7 +147,7 @@ struct Workspace {
                          &gcursor, &gqflag, &stiles, &gtiles, &tb_hits, &tb_q, &tb_dir,
                          &tb_dir_off, &tb_ops_off, &tb_ops, &tb_len, &tb_status, &lhist, &lthr,
                          &lvalid, &ltile, &lbinq, &fkept, &fkoff, &fflag, &ford, &tpos, &selbox, &bq,
-                         &mbig, &mranges, &bsw_order};
+                         &mbig, &mranges, &bsw_order, &qctx, &sbase, &scount};
         for (DevBuf *b : all)
             if (b->p) (void)hipFree(b->p);
         for (hipEvent_t e : events) (void)hipEventDestroy(e);
@@ -171,6 +172,11 @@ struct gg_index {
     int2 *d_post = nullptr;
     uint32_t *d_dbw = nullptr;
     int64_t *d_seq_start = nullptr;
+    // contexts of the postings (16 bytes each beside their 8; one allocation, d_next),
+    // absent when the device has no room for them or a loaded file's lists are not
+    // the bank's
+    uint2 *d_next = nullptr, *d_prev = nullptr;
+    bool cut = false;  // some windows' lists were dropped
     uint64_t hit_budget = 0;
     uint64_t default_budget = 0;
     uint32_t bucket_cap = 0;  // keys of one bucket one wave sorts in LDS
@@ -379,12 +385,16 @@ struct BatchOut {
 
 // Radix tiles of hits sorted within query segments: the hits of the wave's query
 // ql are the next counts[ql] keys in gather order; each query gets whole tiles.
-void seg_tiles(const uint64_t *counts, int32_t nq, std::vector<SortTile> &out)
+// With starts, query ql's keys lie at starts[ql] instead of after the earlier ones'.
+template <typename N>
+void seg_tiles(const N *counts, int32_t nq, std::vector<SortTile> &out,
+               const uint32_t *starts = nullptr)
 {
     out.clear();
     uint64_t start = 0;
     for (int32_t q = 0; q < nq; ++q) {
         const uint32_t c = (uint32_t)counts[q];
+        if (starts) start = starts[q];
         const uint32_t nt = (c + kSortTile - 1) / kSortTile;
         const uint32_t hbase = (uint32_t)out.size() * kRadix;
         for (uint32_t t = 0; t < nt; ++t)
@@ -477,6 +487,65 @@ bool filter_for(const gg_index *ix, const gg_params *p, uint64_t hits, int64_t n
     return p->min_hsp_len > ix->span && hits <= (uint64_t)std::max<int64_t>(nq, 0) * kFiltMean;
 }
 
+// The sort grouping takes its runs from the postings' contexts (k_run_starts) when
+// every kept run has two hits at least (M > span) and the gap limit stays within the
+// windows a context holds; else, and when GG_GROUPING=sort pins it, every hit is
+// stored and sorted.
+bool contexts_for(const gg_index *ix, const gg_params *p)
+{
+    const char *g = getenv("GG_GROUPING");
+    if (g && !strcmp(g, "sort")) return false;
+    return ix->d_next && p->min_hsp_len > ix->span && p->max_gap / ix->span + 1 <= kCtx;
+}
+
+CtxPrep ctx_prep(const gg_index *ix, Workspace *ws, const gg_params *p)
+{
+    CtxPrep c;
+    c.qctx = as<QCtx>(ws->qctx);
+    c.kcode = as<uint32_t>(ws->kcode);
+    c.cnt = as<uint32_t>(ws->cnt);
+    c.sbase = as<uint32_t>(ws->sbase);
+    c.scount = as<uint32_t>(ws->scount);
+    c.span = ix->span;
+    c.mmax = p->max_gap / ix->span + 1;
+    c.shape = ctx_shape(ix->k);
+    return c;
+}
+
+// Arguments of the run-start kernels but for the wave's sizes.
+RunStarts run_starts(const gg_index *ix, Workspace *ws, const gg_params *p)
+{
+    RunStarts a{};
+    a.hrel = as<uint32_t>(ws->hrel);
+    a.qctx = as<QCtx>(ws->qctx);
+    a.post = ix->d_post;
+    a.next = ix->d_next;
+    a.prev = ix->d_prev;
+    a.qoff = as<int64_t>(ws->qoff);
+    a.kcode = as<uint32_t>(ws->kcode);
+    a.kcnt = as<uint32_t>(ws->cnt);
+    a.qpack = as<uint32_t>(ws->qpack);
+    a.dbw = ix->d_dbw;
+    a.seq_start = ix->d_seq_start;
+    a.span = ix->span;
+    a.mask = ix->mask;
+    a.mmax = p->max_gap / ix->span + 1;
+    a.min_len = p->min_hsp_len;
+    a.cut = ix->cut;
+    a.shape = ctx_shape(ix->k);
+    a.sbase = as<uint32_t>(ws->sbase);
+    a.scount = as<uint32_t>(ws->scount);
+    a.out = as<uint64_t>(ws->keys);
+    return a;
+}
+
+// Contexts of both sides are read together when lists average this many postings.
+// Long lists are repeats, where four hits in five have a next hit, and the side before
+// them would be a second, dependent read of nearly every line; in the short lists of
+// a bank without repeats two hits in a thousand have one, and 8 bytes per hit are
+// read instead of 16.
+constexpr uint64_t kCtxBothMean = 64;
+
 // GG_GROUPING (probe, bucket or sort) pins the strategy; otherwise the index's
 // tuned choice is used (sort until tuned).
 Grouping grouping_for(const gg_index *ix)
@@ -529,24 +598,36 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
 
     // ---- S3 gather
     const int64_t np = g1 - g0;
+    const bool lookback = sort_kind_from_env() == kOneSweep;
+    const bool ctxs = grouping == kSort && !lookback && contexts_for(ix, p);
+    CtxPrep cp;
     TRY(ensure(ws->hrel, sizeof(uint32_t) * (np + 1)));
     TRY(ensure(ws->pbase, sizeof(uint32_t) * (np + 1)));
-    TRY(ensure(ws->akey, sizeof(uint64_t) * (np + 1)));
+    if (ctxs) {
+        TRY(ensure(ws->qctx, sizeof(QCtx) * np));
+        TRY(ensure(ws->sbase, sizeof(uint32_t) * nqw));
+        TRY(ensure(ws->scount, sizeof(uint32_t) * nqw));
+        cp = ctx_prep(ix, ws, p);
+    } else {
+        TRY(ensure(ws->akey, sizeof(uint64_t) * (np + 1)));
+    }
     prof.begin("gather_prep");
     if (piece) {
         TRY(ensure(ws->pcnt, sizeof(uint32_t) * (np + 1)));
         launch_piece_prep(as<uint32_t>(ws->kcode) + g0, as<uint32_t>(ws->cnt) + g0, np,
                           ix->d_list_off, ix->d_post, piece->s_lo, piece->s_hi, lay,
                           as<uint32_t>(ws->pcnt), as<uint32_t>(ws->pbase), as<uint64_t>(ws->akey),
-                          st);
+                          cp, st);
         launch_scan_u32(as<uint32_t>(ws->pcnt), as<uint32_t>(ws->hrel), np,
                         as<uint32_t>(ws->partials), st);
+        if (ctxs)
+            launch_ctx_heads(as<uint32_t>(ws->pbase), as<uint32_t>(ws->hrel), np, cp.qctx, st);
     } else {
         TRY(ensure(ws->tpos, sizeof(uint32_t) * ((size_t)H / kTile + 2)));
         launch_wave_prep(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), as<uint32_t>(ws->lhead),
-                         as<int32_t>(ws->qid), qa, g0, g1, lay, as<uint32_t>(ws->hrel),
+                         as<int32_t>(ws->qid), qa, nqw, g0, g1, lay, as<uint32_t>(ws->hrel),
                          as<uint32_t>(ws->pbase), as<uint64_t>(ws->akey), as<uint32_t>(ws->tpos),
-                         st);
+                         cp, st);
     }
     prof.end(np);
 
@@ -565,8 +646,84 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(pin) + cells_at);
     TRY(ensure(ws->cand_q, sizeof(uint32_t) * (nqw + 1)));
     TRY(ensure(ws->cand_off, sizeof(uint32_t) * (nqw + 1)));
-    HIPCHK(hipMemsetAsync(ws->cand_q.p, 0, sizeof(uint32_t) * nqw, st));
     uint32_t nc = 0;
+
+    // ---- S3 + S4 + S5 from the postings' contexts: run starts per query, grouped by
+    // sequence by radix passes on the sequence bits when a query has more than its
+    // later LDS sorts hold, then each start's run
+    std::vector<SortTile> tiles, packed;  // copied from until the wave's next wait
+    if (ctxs) {
+        const uint64_t place = H64 / 2 + (uint64_t)nqw + 1;
+        TRY(ensure(ws->keys, sizeof(uint64_t) * place));
+        TRY(ensure(ws->partials, sizeof(uint64_t) * scan_partials_needed((int64_t)nqw + 1)));
+        RunStarts a = run_starts(ix, ws, p);
+        a.tile_pos = piece ? nullptr : as<uint32_t>(ws->tpos);
+        a.np = np;
+        a.g0 = g0;
+        a.nhits = H;
+        a.qa = qa;
+        a.lay = lay;
+        prof.begin("probe");
+        launch_run_starts(a, H64 >= kCtxBothMean * (uint64_t)np, st);
+        prof.end(H);
+        launch_scan_u32(a.scount, as<uint32_t>(ws->cand_off), nqw, as<uint32_t>(ws->partials), st);
+        HIPCHK(hipMemcpyAsync(h_cq, a.scount, sizeof(uint32_t) * nqw, hipMemcpyDeviceToHost, st));
+        SYNC(st);
+        uint32_t most = 0;
+        for (int32_t ql = 0; ql < nqw; ++ql) {
+            nc += h_cq[ql];
+            most = std::max(most, h_cq[ql]);
+        }
+        if (nc == 0) return GG_OK;
+        TRY(ensure(ws->cands, sizeof(Cand) * nc));
+        if (most <= (uint32_t)kSegCap) {
+            prof.begin("run_ends");
+            launch_run_compact(a, nqw, as<uint32_t>(ws->cand_off), as<Cand>(ws->cands), st);
+            prof.end(nc);
+        } else {
+            std::vector<uint32_t> starts((size_t)nqw);
+            uint64_t before = 0;
+            for (int32_t ql = 0; ql < nqw && !piece; ++ql) {
+                starts[(size_t)ql] = (uint32_t)((before + 1) >> 1);
+                before += qtot[qa + ql];
+            }
+            // the first pass reads the queries' places, the others packed keys
+            seg_tiles(h_cq, nqw, tiles, starts.data());
+            seg_tiles(h_cq, nqw, packed);
+            const uint32_t nst = (uint32_t)tiles.size();
+            TRY(ensure(ws->stiles, sizeof(SortTile) * 2 * nst));
+            TRY(ensure(ws->keys_alt, sizeof(uint64_t) * nc));
+            const size_t nhist = (size_t)nst * kRadix + 1;
+            TRY(ensure(ws->hist, sizeof(uint32_t) * nhist));
+            TRY(ensure(ws->rs_partials, sizeof(uint32_t) * scan_partials_needed((int64_t)nhist)));
+            SortTile *d_tiles = as<SortTile>(ws->stiles);
+            HIPCHK(hipMemcpyAsync(d_tiles, tiles.data(), sizeof(SortTile) * nst,
+                                  hipMemcpyHostToDevice, st));
+            HIPCHK(hipMemcpyAsync(d_tiles + nst, packed.data(), sizeof(SortTile) * nst,
+                                  hipMemcpyHostToDevice, st));
+            uint64_t *kin = a.out, *kout = as<uint64_t>(ws->keys_alt);
+            const int lo = lay.bp + lay.bd;
+            // one pass at least: it packs the keys
+            for (int shift = lo; shift == lo || shift < lo + lay.bs; shift += kRadixBits) {
+                const SortTile *t = shift == lo ? d_tiles : d_tiles + nst;
+                prof.begin("sort_hist");
+                launch_rs_hist_seg(kin, nst, shift, t, as<uint32_t>(ws->hist), st);
+                prof.end(nc);
+                prof.begin("sort_scan");
+                launch_rs_scan_seg(as<uint32_t>(ws->hist), nst, as<uint32_t>(ws->rs_partials), st);
+                prof.end(nc);
+                prof.begin("sort_scatter");
+                launch_rs_scatter_seg(kin, kout, nst, shift, t, as<uint32_t>(ws->hist), st);
+                prof.end(nc);
+                std::swap(kin, kout);
+            }
+            prof.begin("run_ends");
+            launch_run_ends(a, kin, nc, as<uint32_t>(ws->cand_off), nqw, as<Cand>(ws->cands), st);
+            prof.end(nc);
+        }
+    } else {
+        HIPCHK(hipMemsetAsync(ws->cand_q.p, 0, sizeof(uint32_t) * nqw, st));
+    }
 
     // ---- S3 + S4 + S5, bucketed: a query's hits are cut into slices of its
     // sequence-id range of about bucket_cap / 4 hits; each slice is sorted and
@@ -574,7 +731,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     const uint32_t target = std::max<uint32_t>(ix->bucket_cap / 4, 1);
     std::vector<uint32_t> plan(2 * (size_t)nqw);  // bucket base | bucket count per query
     uint64_t nbk64 = 0;
-    for (int32_t ql = 0; ql < nqw; ++ql) {
+    for (int32_t ql = 0; ql < nqw && !ctxs; ++ql) {
         const uint64_t nb = std::max<uint64_t>(1, (qtot[qa + ql] + target - 1) / target);
         plan[ql] = (uint32_t)nbk64;
         plan[nqw + ql] = (uint32_t)nb;
@@ -667,7 +824,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         if (grouping != kProbe && lay.bp + lay.bd + lay.bs + lay.bq > 64) return GG_EINVAL;
     }
     bool bucketed = grouping == kBucket && nbk64 < (1ull << 30);
-    if (grouping != kProbe) TRY(ensure(ws->keys, sizeof(uint64_t) * H));
+    if (grouping != kProbe && !ctxs) TRY(ensure(ws->keys, sizeof(uint64_t) * H));
     if (bucketed) {
         const uint32_t nbk = (uint32_t)nbk64;
         TRY(ensure(ws->bplan, sizeof(uint32_t) * 2 * nqw));
@@ -747,7 +904,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
             }
         }
     }
-    if (grouping != kProbe && !bucketed) {
+    if (grouping != kProbe && !bucketed && !ctxs) {
         // ---- global path: gather in place, lone-diagonal filter with per-query LDS
         // sorts, or a stable LSD radix sort within query segments; chain
         TRY(ensure(ws->keys_alt, sizeof(uint64_t) * H));
@@ -759,7 +916,6 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         TRY(ensure(ws->ccount, sizeof(uint32_t) * (ntile + 1)));
         TRY(ensure(ws->partials,
                    sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(ntile, nqw) + 1)));
-        const bool lookback = sort_kind_from_env() == kOneSweep;
         const bool filt = !lookback && !piece && filter_for(ix, p, H, nqw);
         const bool fused = fused_filter_enabled();
         if (lookback) TRY(ensure(ws->os_scratch, onesweep_scratch_bytes(H)));
@@ -779,7 +935,6 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         auto radix_passes = [&](uint64_t *kin, uint64_t *kout, const std::vector<uint64_t> &counts,
                                 uint32_t n) -> gg_status {
             // tiles within query segments: the passes skip the query bits of the keys
-            std::vector<SortTile> tiles;
             seg_tiles(counts.data(), nqw, tiles);
             const uint32_t nst = (uint32_t)tiles.size();
             TRY(ensure(ws->stiles, sizeof(SortTile) * std::max<uint32_t>(nst, 1)));
@@ -909,7 +1064,9 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         }
     }
     if (nc == 0) return GG_OK;
-    HIPCHK(hipMemcpyAsync(h_cq, ws->cand_q.p, sizeof(uint32_t) * nqw, hipMemcpyDeviceToHost, st));
+    if (!ctxs)
+        HIPCHK(hipMemcpyAsync(h_cq, ws->cand_q.p, sizeof(uint32_t) * nqw, hipMemcpyDeviceToHost,
+                              st));
 
     // ---- S6 extend (one lane per run, long walks resumed by a wave)
     TRY(ensure(ws->boxes, sizeof(Box) * nc));
@@ -922,7 +1079,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
                   ix->d_dbw, ix->d_seq_start, p->match, p->mismatch, p->xdrop, as<Box>(ws->boxes),
                   ws->xqueue.p, ix->tune_lane_steps.load(), st);
     prof.end(nc);
-    SYNC(st);  // h_cq ready
+    if (!ctxs) SYNC(st);  // h_cq ready
     uint32_t max_seg = 0;
     for (int32_t ql = 0; ql < nqw; ++ql) max_seg = std::max(max_seg, h_cq[ql]);
     const bool seg_path = max_seg <= (uint32_t)kSegCap;
@@ -1511,16 +1668,18 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     if ((uint64_t)maxL * (uint64_t)p->match >= (1ull << 30)) return GG_EINVAL;
     uint64_t hsum = 0;
     for (const WaveCtl &w : plan) hsum += w.H;
-    const bool filt = filter_for(ix, p, hsum, nq);
+    const bool ctxs = contexts_for(ix, p);
+    const bool filt = !ctxs && filter_for(ix, p, hsum, nq);
     const bool fused = fused_filter_enabled();
     // radix tiles within query segments, all waves in one table (none when the
-    // lone-diagonal filter and the per-query LDS sorts replace the radix passes)
+    // contexts, or the lone-diagonal filter and the per-query LDS sorts, replace the
+    // radix passes)
     std::vector<SortTile> tiles, wt;
     std::vector<uint64_t> qc;
     uint32_t ntile_max = 1;
     for (WaveCtl &w : plan) {
         w.lay = lay;
-        if (filt) {
+        if (filt || ctxs) {
             w.tile0 = w.ntile = 0;
             continue;
         }
@@ -1544,9 +1703,17 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     // while its key matches)
     TRY(ensure(ws->hrel, sizeof(uint32_t) * (np_cap + 1)));
     TRY(ensure(ws->pbase, sizeof(uint32_t) * (np_cap + 1)));
-    TRY(ensure(ws->akey, sizeof(uint64_t) * (np_cap + 1)));
-    TRY(ensure(ws->keys, sizeof(uint64_t) * hits_cap));
-    TRY(ensure(ws->keys_alt, sizeof(uint64_t) * hits_cap));
+    // from contexts only run starts are stored, one for every two hits at most
+    const uint32_t runs_cap = ctxs ? hits_cap / 2 + (uint32_t)nq_cap + 1 : hits_cap;
+    TRY(ensure(ws->keys, sizeof(uint64_t) * runs_cap));
+    if (ctxs) {
+        TRY(ensure(ws->qctx, sizeof(QCtx) * np_cap));
+        TRY(ensure(ws->sbase, sizeof(uint32_t) * nq_cap));
+        TRY(ensure(ws->scount, sizeof(uint32_t) * nq_cap));
+    } else {
+        TRY(ensure(ws->akey, sizeof(uint64_t) * (np_cap + 1)));
+        TRY(ensure(ws->keys_alt, sizeof(uint64_t) * hits_cap));
+    }
     TRY(ensure(ws->hist, sizeof(uint32_t) * ((size_t)ntile_cap * kRadix + 1)));
     TRY(ensure(ws->rs_partials,
                sizeof(uint32_t) * scan_partials_needed((int64_t)ntile_cap * kRadix + 1)));
@@ -1555,11 +1722,11 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     TRY(ensure(ws->ccount, sizeof(uint32_t) * (ntile + 1)));
     TRY(ensure(ws->partials,
                sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(ntile, nq_cap) + 1)));
-    TRY(ensure(ws->cands, sizeof(Cand) * hits_cap));
-    TRY(ensure(ws->boxes, sizeof(Box) * hits_cap));
-    TRY(ensure(ws->boxes2, sizeof(Box) * hits_cap));
-    TRY(ensure(ws->boxes3, sizeof(Box) * hits_cap));
-    TRY(ensure(ws->xqueue, extend_queue_bytes(hits_cap)));
+    TRY(ensure(ws->cands, sizeof(Cand) * runs_cap));
+    TRY(ensure(ws->boxes, sizeof(Box) * runs_cap));
+    TRY(ensure(ws->boxes2, sizeof(Box) * runs_cap));
+    TRY(ensure(ws->boxes3, sizeof(Box) * runs_cap));
+    TRY(ensure(ws->xqueue, extend_queue_bytes(runs_cap)));
     for (DevBuf *b : {&ws->qstart, &ws->qend, &ws->cand_q, &ws->cand_off, &ws->nsel, &ws->sel_off,
                       &ws->rstart, &ws->rend})
         TRY(ensure(*b, sizeof(uint32_t) * (nq_cap + 1)));
@@ -1584,6 +1751,9 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     const uint64_t *sorted = (filt || (passes & 1)) ? as<uint64_t>(ws->keys_alt)
                                                     : as<uint64_t>(ws->keys);
     const int32_t steps = ix->tune_lane_steps.load();
+    int64_t npsum = 0;
+    for (const WaveCtl &w : plan) npsum += w.np;
+    const bool both = hsum >= kCtxBothMean * (uint64_t)npsum;
     std::vector<uint64_t> key = {hits_cap, (uint64_t)np_cap, (uint64_t)nq_cap, (uint64_t)passes,
                                  (uint64_t)ntile_cap,
                                  (uint64_t)lay.bp, (uint64_t)lay.bd, (uint64_t)lay.bs,
@@ -1591,7 +1761,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                                  (uint64_t)(uint32_t)steps, (uint64_t)ix->span,
                                  (uint64_t)ix->mask,
                                  (uint64_t)(uintptr_t)ix->d_post, (uint64_t)filt,
-                                 (uint64_t)fused};
+                                 (uint64_t)fused, (uint64_t)ctxs, (uint64_t)both};
     for (int32_t v : {p->match, p->mismatch, p->gap_open, p->gap_extend, p->band, p->xdrop,
                       p->max_gap, p->min_hsp_len, p->max_hits})
         key.push_back((uint64_t)(uint32_t)v);
@@ -1609,7 +1779,8 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                             &ws->cand_q, &ws->cand_off, &ws->nsel, &ws->sel_off, &ws->rstart,
                             &ws->rend, &ws->aligns, &ws->aligns2, &ws->gout, &ws->gn, &ws->gctl,
                             &ws->gplan, &ws->gcursor, &ws->gqflag, &ws->gtiles, &ws->fkept,
-                            &ws->fkoff, &ws->ford, &ws->tpos, &ws->selbox, &ws->bsw_order})
+                            &ws->fkoff, &ws->ford, &ws->tpos, &ws->selbox, &ws->bsw_order,
+                            &ws->cnt, &ws->lhead, &ws->qctx, &ws->sbase, &ws->scount})
         key.push_back((uint64_t)(uintptr_t)b->p);
 
     if (!ws->gexec || ws->gkey != key) {
@@ -1619,11 +1790,20 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
         }
         hipGraph_t g = nullptr;
         HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+        const CtxPrep cp = ctxs ? ctx_prep(ix, ws, p) : CtxPrep{};
         launch_wave_prep_ctl(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), as<uint32_t>(ws->lhead),
-                             as<int32_t>(ws->qid), np_cap, as<uint32_t>(ws->hrel),
+                             as<int32_t>(ws->qid), np_cap, nq_cap, as<uint32_t>(ws->hrel),
                              as<uint32_t>(ws->pbase), as<uint64_t>(ws->akey),
-                             as<WaveCtl>(ws->gplan), cursor, ctl, as<uint32_t>(ws->tpos), st);
-        if (!(filt && fused))
+                             as<WaveCtl>(ws->gplan), cursor, ctl, as<uint32_t>(ws->tpos), cp, st);
+        if (ctxs) {
+            RunStarts a = run_starts(ix, ws, p);
+            a.tile_pos = as<uint32_t>(ws->tpos);
+            launch_run_starts(a, both, st, ctl, hits_cap);
+            launch_run_compact(a, 0, as<uint32_t>(ws->cand_off), as<Cand>(ws->cands), st, ctl,
+                               nq_cap, static_cast<uint32_t *>(ws->xqueue.p),
+                               as<uint32_t>(ws->partials));
+        }
+        if (!ctxs && !(filt && fused))
             launch_gather_ctl(as<uint32_t>(ws->hrel), as<uint32_t>(ws->pbase),
                               as<uint64_t>(ws->akey), ix->d_post, hits_cap,
                               as<uint64_t>(ws->keys), ctl, as<uint32_t>(ws->tpos), st);
@@ -1643,24 +1823,26 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                                as<uint32_t>(ws->fkoff), as<uint32_t>(ws->partials),
                                as<uint64_t>(ws->keys_alt), st, ctl, nq_cap);
         }
-        for (int pass = 0; pass < passes && !filt; ++pass) {
+        for (int pass = 0; pass < passes && !filt && !ctxs; ++pass) {
             const bool odd = pass & 1;
             launch_rs_pass_ctl(odd ? as<uint64_t>(ws->keys_alt) : as<uint64_t>(ws->keys),
                                odd ? as<uint64_t>(ws->keys) : as<uint64_t>(ws->keys_alt), ntile_cap,
                                pass, as<SortTile>(ws->gtiles), as<uint32_t>(ws->hist),
                                as<uint32_t>(ws->rs_partials), ctl, st);
         }
-        launch_chain_ctl(sorted, hits_cap, ix->span, p->max_gap, p->min_hsp_len,
-                         as<uint32_t>(ws->ccount), as<uint32_t>(ws->partials), as<Cand>(ws->cands),
-                         ctl, st, filt);
-        launch_cand_ranges_ctl(as<Cand>(ws->cands), nq_cap, as<uint32_t>(ws->qstart),
-                               as<uint32_t>(ws->qend), as<uint32_t>(ws->cand_q),
-                               as<uint32_t>(ws->cand_off), static_cast<uint32_t *>(ws->xqueue.p),
-                               ctl, st);
+        if (!ctxs) {
+            launch_chain_ctl(sorted, hits_cap, ix->span, p->max_gap, p->min_hsp_len,
+                             as<uint32_t>(ws->ccount), as<uint32_t>(ws->partials), as<Cand>(ws->cands),
+                             ctl, st, filt);
+            launch_cand_ranges_ctl(as<Cand>(ws->cands), nq_cap, as<uint32_t>(ws->qstart),
+                                   as<uint32_t>(ws->qend), as<uint32_t>(ws->cand_q),
+                                   as<uint32_t>(ws->cand_off), static_cast<uint32_t *>(ws->xqueue.p),
+                                   ctl, st);
+        }
         launch_extend(as<Cand>(ws->cands), 0, as<uint8_t>(ws->qcode), as<uint32_t>(ws->qpack),
                       as<int64_t>(ws->qoff), 0,
                       ix->d_dbw, ix->d_seq_start, p->match, p->mismatch, p->xdrop,
-                      as<Box>(ws->boxes), ws->xqueue.p, steps, st, ctl, hits_cap,
+                      as<Box>(ws->boxes), ws->xqueue.p, steps, st, ctl, runs_cap,
                       /*count_cleared=*/true);
         launch_merge_select_seg(as<Box>(ws->boxes), as<Box>(ws->boxes2),
                                 as<uint32_t>(ws->cand_off), nq_cap, ctl, st);
@@ -1719,7 +1901,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
         }
         HIPCHK(hipMemcpyAsync(ws->ford.p, h_ord, sizeof(int32_t) * nq, hipMemcpyHostToDevice, st));
     }
-    if (!tiles.empty() && !filt)
+    if (!tiles.empty())
         HIPCHK(hipMemcpyAsync(ws->gtiles.p, tiles.data(), sizeof(SortTile) * tiles.size(),
                               hipMemcpyHostToDevice, st));
     launch_fill2_u32(cursor, 1, reinterpret_cast<uint32_t *>(gn), (size_t)nq, 0u, st);
@@ -1819,7 +2001,7 @@ gg_status run_batch(const gg_index *ix, Workspace *ws, const char *qbuf, const i
     launch_query_totals(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), (int32_t)nq,
                         as<uint64_t>(ws->qtot), st);
     prof.end(T);
-    TRY(ensure(ws->qpack, sizeof(uint32_t) * ((size_t)(T + 15) / 16 + 2)));
+    TRY(ensure(ws->qpack, sizeof(uint32_t) * ((size_t)(T + 15) / 16 + kPackSlack)));
     launch_pack_query(as<uint8_t>(ws->qcode), T, as<uint32_t>(ws->qpack), st);
     HIPCHK(hipMemcpyAsync(h_qtot, ws->qtot.p, sizeof(uint64_t) * nq, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(h_err, ws->err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -1977,6 +2159,7 @@ void gg_index_free(gg_index *ix)
     if (ix->d_post) (void)hipFree(ix->d_post);
     if (ix->d_dbw) (void)hipFree(ix->d_dbw);
     if (ix->d_seq_start) (void)hipFree(ix->d_seq_start);
+    if (ix->d_next) (void)hipFree(ix->d_next);
     delete ix;
 }
 
@@ -2002,6 +2185,41 @@ gg_status index_finish(gg_index *ix)
                          ? kBucketBig
                          : kBucketCapMax;
     (void)hipGetLastError();
+    return GG_OK;
+}
+
+// The postings' contexts, on the given stream (waited for by the caller's next
+// synchronisation; the null stream is waited for here).  Without room for them the
+// index goes on without.
+gg_status index_contexts(gg_index *ix, hipStream_t st)
+{
+    if (hipMalloc((void **)&ix->d_next, 2 * sizeof(uint2) * std::max<uint64_t>(ix->n_post, 1)) !=
+        hipSuccess) {
+        (void)hipGetLastError();
+        ix->d_next = nullptr;
+        return GG_OK;
+    }
+    ix->d_prev = ix->d_next + ix->n_post;
+    launch_contexts(ix->d_post, (uint32_t)ix->n_post, ix->d_dbw, ix->d_seq_start, ix->span,
+                    ix->mask, ctx_shape(ix->k), ix->d_next, ix->d_prev, st);
+    if (!st) SYNC(st);
+    return GG_OK;
+}
+
+// Whether every list of a loaded index holds exactly the bank's windows of its code,
+// in order, or none of them (a repeat cutoff).
+gg_status lists_complete(const gg_index *ix, bool *complete)
+{
+    unsigned long long *d = nullptr, h[2] = {0, 0};
+    HIPCHK(hipMalloc((void **)&d, sizeof(h)));
+    hipError_t e = hipMemcpy(d, h, sizeof(h), hipMemcpyHostToDevice);
+    launch_check_lists(ix->d_list_off, ix->d_post, (uint32_t)ix->n_post, ix->d_dbw,
+                       ix->d_seq_start, (int32_t)ix->n_seqs, ix->span, ix->mask, d, d + 1, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(h, d, sizeof(h), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipGetLastError();
+    (void)hipFree(d);
+    HIPCHK(e);
+    *complete = h[0] == 0 && h[1] == ix->n_post;
     return GG_OK;
 }
 
@@ -2075,7 +2293,7 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     const bool cut = max_posting > 0 && (uint64_t)max_posting < n_post;
     if ((s = alloc((void **)&ix->d_list_off, sizeof(uint32_t) * (ncode + 1))) != GG_OK ||
         (!cut && (s = alloc((void **)&ix->d_post, sizeof(int2) * n_post)) != GG_OK) ||
-        (s = alloc((void **)&ix->d_dbw, sizeof(uint32_t) * nwords)) != GG_OK ||
+        (s = alloc((void **)&ix->d_dbw, sizeof(uint32_t) * (nwords + kPackSlack))) != GG_OK ||
         (s = alloc((void **)&ix->d_seq_start, sizeof(int64_t) * (n_seqs + 1))) != GG_OK)
         return fail(s);
 
@@ -2083,21 +2301,20 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     // windows stably by code (they start in (seq, pos) order, so every list stays
     // in that order), list heads = exclusive scan of the per-code counts.
     {
+        // the build's temporaries in one allocation (a large one costs its 0.1 - 0.6 ms
+        // of mapping and unmapping once)
         struct Tmp {
-            std::vector<void *> p;
+            size_t bytes = 0;
+            char *p = nullptr;
             ~Tmp()
             {
-                for (void *x : p) (void)hipFree(x);
+                if (p) (void)hipFree(p);
             }
-            void *get(size_t bytes)
+            size_t take(size_t n)
             {
-                void *x = nullptr;
-                if (hipMalloc(&x, std::max<size_t>(bytes, 16)) != hipSuccess) {
-                    (void)hipGetLastError();
-                    return nullptr;
-                }
-                p.push_back(x);
-                return x;
+                const size_t at = bytes;
+                bytes += (n + 255) & ~(size_t)255;
+                return at;
             }
         } tmp;
         hipStream_t bst = nullptr;
@@ -2107,20 +2324,30 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
             ~StreamGuard() { (void)hipStreamDestroy(s); }
         } sg{bst};
         const uint32_t nw = (uint32_t)n_post;
-        auto *d_ascii = static_cast<uint8_t *>(tmp.get((size_t)total));
-        auto *d_woff = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * (n_seqs + 1)));
-        auto *d_err = static_cast<int32_t *>(tmp.get(sizeof(int32_t) * 4));
-        auto *d_keys = static_cast<uint64_t *>(tmp.get(sizeof(uint64_t) * nw));
-        auto *d_keys2 = static_cast<uint64_t *>(tmp.get(sizeof(uint64_t) * nw));
-        auto *d_wseq = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * nw));
-        auto *d_hist = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * radix_hist_needed(nw)));
         const size_t parts = std::max<size_t>(scan_partials_needed(radix_hist_needed(nw)),
                                               scan_partials_needed((int64_t)ncode + 1));
-        auto *d_parts = static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * parts));
-        auto *d_kept = cut ? static_cast<uint32_t *>(tmp.get(sizeof(uint32_t) * (ncode + 1)))
-                           : nullptr;
-        if (!d_ascii || !d_woff || !d_err || !d_keys || !d_keys2 || !d_wseq || !d_hist || !d_parts || (cut && !d_kept))
+        const size_t o_ascii = tmp.take((size_t)total);
+        const size_t o_woff = tmp.take(sizeof(uint32_t) * (n_seqs + 1));
+        const size_t o_err = tmp.take(sizeof(int32_t) * 4);
+        const size_t o_keys = tmp.take(sizeof(uint64_t) * nw), o_keys2 = tmp.take(sizeof(uint64_t) * nw);
+        const size_t o_wseq = tmp.take(sizeof(uint32_t) * nw);
+        const size_t o_hist = tmp.take(sizeof(uint32_t) * radix_hist_needed(nw));
+        const size_t o_parts = tmp.take(sizeof(uint32_t) * parts);
+        const size_t o_kept = tmp.take(cut ? sizeof(uint32_t) * (ncode + 1) : 0);
+        if (hipMalloc((void **)&tmp.p, tmp.bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            tmp.p = nullptr;
             return fail(GG_ENOMEM);
+        }
+        auto *d_ascii = reinterpret_cast<uint8_t *>(tmp.p + o_ascii);
+        auto *d_woff = reinterpret_cast<uint32_t *>(tmp.p + o_woff);
+        auto *d_err = reinterpret_cast<int32_t *>(tmp.p + o_err);
+        auto *d_keys = reinterpret_cast<uint64_t *>(tmp.p + o_keys);
+        auto *d_keys2 = reinterpret_cast<uint64_t *>(tmp.p + o_keys2);
+        auto *d_wseq = reinterpret_cast<uint32_t *>(tmp.p + o_wseq);
+        auto *d_hist = reinterpret_cast<uint32_t *>(tmp.p + o_hist);
+        auto *d_parts = reinterpret_cast<uint32_t *>(tmp.p + o_parts);
+        auto *d_kept = reinterpret_cast<uint32_t *>(tmp.p + o_kept);
         int32_t err = 0;
         if (total_in > 0 && hipMemcpyAsync(d_ascii, seqs + base0, (size_t)total_in,
                                            hipMemcpyHostToDevice, bst) != hipSuccess)
@@ -2159,7 +2386,9 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
             if (hipMemcpyAsync(ix->d_list_off, d_kept, sizeof(uint32_t) * (ncode + 1),
                                hipMemcpyDeviceToDevice, bst) != hipSuccess)
                 return fail(GG_EDEVICE);
+            ix->cut = kept != nw;
         }
+        if ((s = index_contexts(ix, bst)) != GG_OK) return fail(s);
         if (hipMemcpyAsync(&err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, bst) != hipSuccess ||
             hipStreamSynchronize(bst) != hipSuccess || hipGetLastError() != hipSuccess)
             return fail(GG_EDEVICE);
@@ -2445,8 +2674,8 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
         return st;
     };
     if (hipSetDevice(device) != hipSuccess) return fail(GG_EDEVICE);
-    auto up = [](void **dst, const void *src, size_t bytes) -> gg_status {
-        if (hipMalloc(dst, std::max<size_t>(bytes, 16)) != hipSuccess) {
+    auto up = [](void **dst, const void *src, size_t bytes, size_t slack = 0) -> gg_status {
+        if (hipMalloc(dst, std::max<size_t>(bytes + slack, 16)) != hipSuccess) {
             (void)hipGetLastError();
             *dst = nullptr;
             return GG_ENOMEM;
@@ -2460,8 +2689,17 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
             GG_OK ||
         (st = up((void **)&ix->d_list_off, heads.data(), sizeof(uint32_t) * heads.size())) != GG_OK ||
         (st = up((void **)&ix->d_post, post.data(), sizeof(int2) * post.size())) != GG_OK ||
-        (st = up((void **)&ix->d_dbw, bank.data(), sizeof(uint32_t) * bank.size())) != GG_OK)
+        (st = up((void **)&ix->d_dbw, bank.data(), sizeof(uint32_t) * bank.size(),
+                 sizeof(uint32_t) * kPackSlack)) != GG_OK)
         return fail(st);
+    // contexts stand for the lists only where each list holds every window of its code
+    uint64_t nwin = 0;
+    for (int64_t s = 0; s < hd.n_seqs; ++s)
+        nwin += (uint64_t)((seq_start[(size_t)s + 1] - seq_start[(size_t)s]) / hd.span);
+    bool complete = false;
+    if ((st = lists_complete(ix, &complete)) != GG_OK) return fail(st);
+    ix->cut = nwin != ix->n_post;
+    if (complete && (st = index_contexts(ix, nullptr)) != GG_OK) return fail(st);
     if ((st = index_finish(ix)) != GG_OK) return fail(st);
     *out = ix;
     return GG_OK;
