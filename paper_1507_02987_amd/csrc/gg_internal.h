@@ -23,6 +23,7 @@ constexpr int kBinCap = 1024;            // buckets one gather tile counts in LD
 constexpr uint32_t kBucketCapMax = 512;  // most keys of one bucket (one wave sorts it in LDS)
 constexpr uint32_t kBucketBig = 16384;   // most keys of one bucket sorted by a block (128 KiB)
 constexpr int kPackSlack = 8;            // words that may be read past packed bases
+constexpr int kPackFront = 64;           // and before them (a left walk reads 32 bases back)
 constexpr int kMaxProbe = 4;             // neighbour windows probed per side (G / k + 1)
 constexpr int kBoundCap = 2048;          // run bounds of one query paired in LDS
 constexpr int kLenBins = 1024;           // box-length bins of the selection prefilter

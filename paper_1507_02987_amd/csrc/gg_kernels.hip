@@ -449,6 +449,7 @@ constexpr int64_t kScanFuse = 2048;
 // only aligned to the value size (global accesses need dword alignment only).
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint64_t u64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
 // v[0 .. kItems) = p[i0 .. i0 + kItems), zeros past n; 16-byte loads when the
 // thread's kItems values are all in range.
@@ -2537,7 +2538,7 @@ void launch_hit_compact(const uint64_t *keys, const uint32_t *hrel, const int64_
 // Nothing is stored for any other hit, nothing is sorted by diagonal or position,
 // and the runs are those of sorting all hits by (q, s, diag, qpos) and scanning them.
 // 2,000 queries of 500-5,000 bp on a 3 Gbp bank with repeats (16.7 G hits, 3.4 G
-// runs): starts 86, three passes over them 60 and their ends 72 ms, where gathering,
+// runs): starts 87, three passes over them 64 and their ends 56 ms, where gathering,
 // five radix passes over every hit and chaining took 618.
 CtxShape ctx_shape(int32_t k)
 {
@@ -2702,37 +2703,6 @@ __device__ __forceinline__ int32_t wave_run_max(int32_t x)
     return x;
 }
 
-// End (query position past the last hit) of the run whose first hit is at query
-// position qs on diagonal d: 64 bases of the diagonal are compared at once, and each
-// next hit is the nearest window of the next mmax that matches.  wm: the coded
-// bases of a window, its first base in the top bits.
-__device__ __forceinline__ int32_t run_end(const RunStarts &a, uint64_t wm, int64_t q0, int32_t L,
-                                           int64_t s0, int32_t ns, int32_t d, int32_t qs)
-{
-    const int32_t k = a.span;
-    const int32_t last = min(L - qs, ns - (qs + d)) - k;  // the last window inside both
-    const int64_t gq = q0 + qs, gb = s0 + qs + d;
-    int32_t o = 0, cb = -64;
-    unsigned __int128 x = 0;
-    for (;;) {
-        bool found = false;
-        for (int32_t m = 1, w = o + k; m <= a.mmax && w <= last; ++m, w += k) {
-            if (w + k > cb + 64) {
-                cb = w;
-                const Bases64 u = bases64(a.qpack, gq + w), v = bases64(a.dbw, gb + w);
-                x = ((unsigned __int128)(u.h ^ v.h) << 64) | (u.l ^ v.l);
-            }
-            if (((uint64_t)((x << (2 * (w - cb))) >> 64) & wm) == 0 &&
-                (!a.cut || a.kcnt[gq + w] > 0u)) {
-                o = w;
-                found = true;
-                break;
-            }
-        }
-        if (!found) return qs + o + k;
-    }
-}
-
 // The coded bases of a window of `span` bases, first base in the top two bits.
 __device__ __forceinline__ uint64_t window_bits(int32_t span, uint32_t mask)
 {
@@ -2741,6 +2711,89 @@ __device__ __forceinline__ uint64_t window_bits(int32_t span, uint32_t mask)
         if ((mask >> t) & 1u) wm |= 3ull << (62 - 2 * t);
     return wm;
 }
+
+// A run's last hit, found along its diagonal in chunks of 64 bases: the windows at
+// multiples of the span from the run's first hit (query base gq, bank base gb; the
+// last window inside query and sequence at offset `last`) that lie in a chunk, each
+// a hit when its coded bases match.  `miss` windows in a row without a hit end the run
+// at mmax; hit: the last one's offset; o: the chunk's.
+struct RunWalk {
+    int64_t gq, gb;
+    int32_t last, o, miss, hit;
+};
+
+__device__ __forceinline__ RunWalk run_walk(int64_t q0, int32_t L, int64_t s0, int32_t ns,
+                                            int32_t d, int32_t qs, int32_t span)
+{
+    return RunWalk{q0 + qs, s0 + qs + d, min(L - qs, ns - (qs + d)) - span, 0, 0, 0};
+}
+
+// The chunk's windows, in order (nw of them); each(j, offset, hit).
+template <typename F>
+__device__ __forceinline__ void chunk_windows(const RunStarts &a, uint64_t wm, int32_t nw,
+                                              const RunWalk &w, int32_t o, F each)
+{
+    const Bases64 u = bases64(a.qpack, w.gq + o), v = bases64(a.dbw, w.gb + o);
+    const uint64_t h = u.h ^ v.h, l = u.l ^ v.l;
+    for (int32_t j = 0, b = 0; j < nw; ++j, b += a.span) {
+        const int sh = 2 * b;  // the window's bases in the chunk's 128 bits
+        const uint64_t mh = sh < 64 ? wm >> sh : 0ull;
+        const uint64_t ml = sh == 0 ? 0ull : sh < 64 ? wm << (64 - sh) : wm >> (sh - 64);
+        bool hit = ((h & mh) | (l & ml)) == 0 && o + b <= w.last;
+        if (a.cut && hit) hit = a.kcnt[w.gq + o + b] > 0u;
+        each(j, o + b, hit);
+    }
+}
+
+// Takes the walk's next chunk (w.o <= w.last); true when the run ends in it.
+__device__ __forceinline__ bool run_chunk(const RunStarts &a, uint64_t wm, int32_t nw, RunWalk &w)
+{
+    bool end = false;
+    chunk_windows(a, wm, nw, w, w.o, [&](int32_t, int32_t at, bool hit) {
+        w.hit = hit && !end ? at : w.hit;
+        w.miss = hit ? 0 : w.miss + 1;
+        end = end || w.miss >= a.mmax;
+    });
+    w.o += nw * a.span;
+    return end || w.o > w.last;
+}
+
+// The rest of one walk by the whole wave, a chunk per lane and step (w is the same in
+// every lane); returns the last hit's offset.
+__device__ int32_t run_rest(const RunStarts &a, uint64_t wm, int32_t nw, RunWalk w, int lane)
+{
+    for (;; w.o += 64 * nw * a.span) {
+        const int32_t o = w.o + lane * nw * a.span;
+        uint32_t bits = 0;
+        if (o <= w.last)
+            chunk_windows(a, wm, nw, w, o,
+                          [&](int32_t j, int32_t, bool hit) { bits |= (hit ? 1u : 0u) << j; });
+        // windows without a hit just before the lane's: mmax - 1 <= 2 matter, and a
+        // chunk holds two at least
+        const uint32_t pb = __shfl_up(bits, 1, 64);
+        int32_t miss = (pb >> (nw - 1)) & 1u ? 0 : (pb >> (nw - 2)) & 1u ? 1 : 2;
+        if (lane == 0) miss = w.miss;
+        int32_t hit = -1;
+        bool end = false;
+        for (int32_t j = 0; j < nw && !end; ++j) {
+            if ((bits >> j) & 1u) {
+                hit = o + j * a.span;
+                miss = 0;
+            } else {
+                end = ++miss >= a.mmax;
+            }
+        }
+        const uint64_t em = __ballot(end);
+        const uint64_t upto = em ? em ^ (em - 1) : ~0ull;  // lanes up to the first that ends
+        const uint64_t hm = __ballot(hit >= 0) & upto;
+        if (hm) w.hit = __shfl(hit, 63 - __clzll((long long)hm), 64);
+        if (em) return w.hit;
+        w.miss = __shfl(miss, 63, 64);
+    }
+}
+
+// Windows a chunk holds.
+__device__ __forceinline__ int32_t chunk_count(int32_t span) { return 64 / span; }
 
 // Whether hit `idx` of position p (context q) starts a run of at least two hits that
 // is long enough, and its key; nm, pm: the windows after and before it that match by
@@ -2765,10 +2818,11 @@ __device__ __forceinline__ bool run_start(const RunStarts &a, const QCtx &q, uin
     }
     if (ok && a.min_len > 2 * a.span) {  // two hits may be too short
         const int64_t q0 = a.qoff[a.qa + q.ql], s0 = a.seq_start[e.x];
-        const int32_t qe = run_end(a, window_bits(a.span, a.mask), q0,
-                                   (int32_t)(a.qoff[a.qa + q.ql + 1] - q0), s0,
-                                   (int32_t)(a.seq_start[e.x + 1] - s0), e.y - q.qpos, q.qpos);
-        ok = qe - q.qpos >= a.min_len;
+        RunWalk w = run_walk(q0, (int32_t)(a.qoff[a.qa + q.ql + 1] - q0), s0,
+                             (int32_t)(a.seq_start[e.x + 1] - s0), e.y - q.qpos, q.qpos, a.span);
+        const uint64_t wm = window_bits(a.span, a.mask);
+        while (w.hit + a.span < a.min_len && !run_chunk(a, wm, chunk_count(a.span), w)) {}
+        ok = w.hit + a.span >= a.min_len;
     }
     *key = ((uint64_t)(uint32_t)e.x << (a.lay.bd + a.lay.bp)) |
            ((uint64_t)(uint32_t)(e.y - q.qpos + a.lay.bias) << a.lay.bp) |
@@ -2953,21 +3007,22 @@ void launch_ctx_heads(const uint32_t *pbase, const uint32_t *hrel, int64_t np, Q
                                                                                qctx);
 }
 
-// The run of wave query ql that starts at `key`.
-__device__ __forceinline__ Cand run_of(const RunStarts &a, uint64_t wm, const HitKeyLayout &lay,
-                                       uint64_t key, int32_t ql, int64_t q0, int32_t L)
+// The run that starts at `key`, its end not yet known, and its walk.
+__device__ __forceinline__ RunWalk run_open(const RunStarts &a, const HitKeyLayout &lay,
+                                            uint64_t key, int64_t q0, int32_t L, Cand *c)
 {
-    Cand c;
-    c.q = ql;
-    c.qs = (int32_t)(key & low_mask(lay.bp));
-    c.d = (int32_t)((key >> lay.bp) & low_mask(lay.bd)) - lay.bias;
-    c.s = (int32_t)shr64(key, lay.bp + lay.bd);
-    const int64_t s0 = a.seq_start[c.s];
-    c.qe = run_end(a, wm, q0, L, s0, (int32_t)(a.seq_start[c.s + 1] - s0), c.d, c.qs);
-    return c;
+    c->qs = (int32_t)(key & low_mask(lay.bp));
+    c->d = (int32_t)((key >> lay.bp) & low_mask(lay.bd)) - lay.bias;
+    c->s = (int32_t)shr64(key, lay.bp + lay.bd);
+    const int64_t s0 = a.seq_start[c->s];
+    return run_walk(q0, L, s0, (int32_t)(a.seq_start[c->s + 1] - s0), c->d, c->qs, a.span);
 }
 
-// Block ql: the runs of the wave's query ql, from its place in a.out to off[ql].
+// Block ql: the runs of the wave's query ql, from its place in a.out to off[ql].  A
+// lane takes a run for kRunLane chunks; what is left of a long one is finished by its
+// whole wave (a 10 kb copy alone took 30 us a lane at a time).
+constexpr int kRunLane = 4;
+
 __global__ __launch_bounds__(kBlock) void k_run_compact(RunStarts a, int32_t nqw,
                                                         uint32_t *__restrict__ off,
                                                         Cand *__restrict__ cands,
@@ -2998,8 +3053,33 @@ __global__ __launch_bounds__(kBlock) void k_run_compact(RunStarts a, int32_t nqw
     const int64_t q0 = a.qoff[qa + ql];
     const int32_t L = (int32_t)(a.qoff[qa + ql + 1] - q0);
     const uint64_t wm = window_bits(a.span, a.mask);
-    for (uint32_t i = threadIdx.x; i < n; i += kBlock)
-        cands[at + i] = run_of(a, wm, lay, src[i], ql, q0, L);
+    const int32_t nw = chunk_count(a.span);
+    const int lane = threadIdx.x & 63;
+    for (uint32_t i = threadIdx.x; i - lane < n; i += kBlock) {  // whole waves
+        Cand c{ql, 0, 0, 0, 0};
+        RunWalk w{};
+        bool going = i < n;
+        if (going) {
+            w = run_open(a, lay, src[i], q0, L, &c);
+            for (int r = 0; r < kRunLane && going; ++r) going = !run_chunk(a, wm, nw, w);
+        }
+        for (uint64_t left = __ballot(going); left; left &= left - 1) {
+            const int f = __ffsll((unsigned long long)left) - 1;
+            RunWalk x;
+            x.gq = __shfl(w.gq, f, 64);
+            x.gb = __shfl(w.gb, f, 64);
+            x.last = __shfl(w.last, f, 64);
+            x.o = __shfl(w.o, f, 64);
+            x.miss = __shfl(w.miss, f, 64);
+            x.hit = __shfl(w.hit, f, 64);
+            const int32_t hit = run_rest(a, wm, nw, x, lane);
+            if (lane == f) w.hit = hit;
+        }
+        if (i < n) {
+            c.qe = c.qs + w.hit + a.span;
+            cands[at + i] = c;
+        }
+    }
 }
 
 void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *cands,
@@ -3015,33 +3095,69 @@ void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *ca
     k_run_compact<<<nb, kBlock, 0, st>>>(a, nqw, off, cands, ctl, sum, clear);
 }
 
+// Whole waves take contiguous ranges of runs, and a lane whose run ends takes the
+// next one of its wave's range, a chunk of every lane's run per round: a run has five
+// hits on average, but one in a wave of 64 often has the 27 of a 300 bp repeat (72 ms
+// for 3.4 G runs when a wave waited for its longest run, window by window; 56 now).
 __global__ __launch_bounds__(kBlock) void k_run_ends(RunStarts a, const uint64_t *__restrict__ keys,
                                                      uint32_t n, const uint32_t *__restrict__ off,
                                                      int32_t nqw, Cand *__restrict__ cands)
 {
-    const uint32_t i = blockIdx.x * (uint32_t)kBlock + threadIdx.x;
-    if (i >= n) return;
-    // the query of the wave's first run; the others are seldom past its end
-    int32_t ql = 0;
-    {
-        const uint32_t i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)i);
-        int32_t hi = nqw - 1;
-        while (ql < hi) {
-            const int32_t m = (ql + hi + 1) >> 1;
-            if (off[m] <= i0) ql = m;
-            else hi = m - 1;
+    const uint64_t nwave = (uint64_t)gridDim.x * (kBlock / 64);
+    const uint64_t wave = (uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    const uint64_t per = ((uint64_t)n + nwave - 1) / nwave;
+    uint64_t next = wave * per;
+    const uint64_t stop = min((uint64_t)n, next + per);
+    if (next >= stop) return;
+    const int lane = threadIdx.x & 63;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const uint64_t wm = window_bits(a.span, a.mask);
+    const int32_t nw = chunk_count(a.span);
+    int32_t ql = 0;  // the query of the lane's run: of the wave's first one at the start
+    for (int32_t hi = nqw - 1; ql < hi;) {
+        const int32_t m = (ql + hi + 1) >> 1;
+        if (off[m] <= next) ql = m;
+        else hi = m - 1;
+    }
+    uint32_t qend = off[ql + 1], i = 0;
+    int64_t q0 = a.qoff[a.qa + ql];
+    int32_t L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
+    bool have = false;
+    Cand c{0, 0, 0, 0, 0};
+    RunWalk w{};
+    for (;;) {
+        const uint64_t need = __ballot(!have);
+        if (need && next < stop) {
+            if (!have) {
+                const uint64_t x = next + (uint64_t)__popcll(need & below);
+                if (x < stop) {
+                    have = true;
+                    i = (uint32_t)x;
+                    if (i >= qend) {
+                        while (i >= off[ql + 1]) ++ql;
+                        qend = off[ql + 1];
+                        q0 = a.qoff[a.qa + ql];
+                        L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
+                    }
+                    w = run_open(a, a.lay, keys[i], q0, L, &c);
+                }
+            }
+            next += (uint64_t)__popcll(need);
+        }
+        if (__ballot(have) == 0) break;
+        if (have && run_chunk(a, wm, nw, w)) {
+            cands[i] = Cand{ql, c.s, c.d, c.qs, c.qs + w.hit + a.span};
+            have = false;
         }
     }
-    while (i >= off[ql + 1]) ++ql;
-    const int64_t q0 = a.qoff[a.qa + ql];
-    const int32_t L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
-    cands[i] = run_of(a, window_bits(a.span, a.mask), a.lay, keys[i], ql, q0, L);
 }
 
 void launch_run_ends(const RunStarts &a, const uint64_t *keys, uint32_t n, const uint32_t *off,
                      int32_t nqw, Cand *cands, hipStream_t st)
 {
-    if (n) k_run_ends<<<(n + kBlock - 1) / kBlock, kBlock, 0, st>>>(a, keys, n, off, nqw, cands);
+    if (n == 0) return;
+    const uint32_t nb = (uint32_t)std::min<uint64_t>(((uint64_t)n + kBlock - 1) / kBlock, 8192);
+    k_run_ends<<<nb, kBlock, 0, st>>>(a, keys, n, off, nqw, cands);
 }
 
 // ------------------------------------------------------------------ S5: chain + filter
@@ -3394,56 +3510,6 @@ __device__ __forceinline__ int32_t xdrop_side(const uint8_t *__restrict__ q,
     return bl;
 }
 
-// The same walk one step at a time in one lane, for at most `cap` steps (bases
-// read four steps ahead; the data-bank word is kept while the walk stays in it).
-// Returns true when the walk ended (drop over X, or the sequence or query end);
-// otherwise (t, run, best, bl) hold the state after `cap` steps.
-template <bool RIGHT>
-__device__ __forceinline__ bool xdrop_lane(const uint8_t *__restrict__ q,
-                                           const uint32_t *__restrict__ dbw, int64_t s0,
-                                           int32_t from, int32_t d, int32_t T, int32_t match,
-                                           int32_t mismatch, int32_t X, int32_t cap, int32_t &t,
-                                           int32_t &run, int32_t &best, int32_t &bl)
-{
-    t = 0;
-    run = 0;
-    best = 0;
-    bl = 0;
-    const int32_t end = min(T, cap);
-    int64_t wi = -1;
-    uint32_t word = 0;
-    while (t < end) {
-        int32_t qb[4], db[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            qb[u] = -1;
-            db[u] = -2;
-            if (t + u < end) {
-                const int32_t qi = RIGHT ? from + t + u : from - 1 - (t + u);
-                const int64_t g = s0 + qi + d;
-                if ((g >> 4) != wi) {
-                    wi = g >> 4;
-                    word = dbw[wi];
-                }
-                qb[u] = q[qi];
-                db[u] = (int32_t)((word >> (30u - ((uint32_t)(g & 15) << 1))) & 3u);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (t >= end) break;
-            run += qb[u] == db[u] ? match : -mismatch;
-            ++t;
-            if (run > best) {
-                best = run;
-                bl = t;
-            }
-            if (best - run > X) return true;
-        }
-    }
-    return t >= T;
-}
-
 // Extension in two kernels.  k_extend walks both sides of every run in one lane
 // for up to lane_steps steps (0: none), which ends most walks in random sequence;
 // the state of a walk still going is queued, and k_extend_long resumes each
@@ -3491,53 +3557,38 @@ void launch_pack_query(const uint8_t *qcode, int64_t T, uint32_t *qpack, hipStre
                                                                              nwords);
 }
 
-// 16 bases of a 2-bit packed array (first base in the top bits) starting at g,
-// first base in bits 31:30.  Reads words g / 16 and g / 16 + 1.
-__device__ __forceinline__ uint32_t bases16_from(const uint32_t *__restrict__ w, int64_t g)
+// X-drop walk of one lane, 32 steps per round.  The query and data-bank bases of the
+// round's steps are read as packed words and compared at once (a 2-bit XOR): step i
+// in bits 2i+1:2i of x[0], or of x[1] for steps 16 to 31.  A left walk's bases are read
+// 32 positions lower, its first step (the base nearest the run) in the low bits; a
+// right walk's words are bit-reversed into the same order.  Both sides of a wave's
+// walks then take one code path.  w: the word of the walk's first base in each array,
+// r: the base's place in it (the arrays have kPackFront words before their first).
+// Between mismatches the running sum only rises, so its maximum over a stretch of
+// matches is at the stretch's end (the first step at that value), and it can only
+// fall more than X below the best at a mismatch: the step-by-step rule exactly.
+struct WalkAt {
+    const uint32_t *w;
+    int32_t r;
+};
+__device__ __forceinline__ uint64_t walk_bases(const WalkAt &a, int32_t t, bool left)
 {
-    const int64_t wi = g >> 4;
-    const uint64_t v = ((uint64_t)w[wi] << 32) | (uint64_t)w[wi + 1];
-    return (uint32_t)(v >> (32u - ((uint32_t)(g & 15) << 1)));
+    const int32_t p = left ? a.r - t - 32 : a.r + t;
+    const uint32_t *w = a.w + (p >> 4);
+    const uint32_t v0 = w[0], v1 = w[1], v2 = w[2];
+    const uint32_t sh = 32u - ((uint32_t)(p & 15) << 1);
+    const uint32_t hi = (uint32_t)((((uint64_t)v0 << 32) | v1) >> sh);
+    const uint32_t lo = (uint32_t)((((uint64_t)v1 << 32) | v2) >> sh);
+    return ((uint64_t)hi << 32) | lo;
 }
 
-// The 16 bases before position p (p - 16 .. p - 1), base p - 1 in bits 1:0.  Below
-// p = 16 the missing bases read as zero; a walk never consumes them.
-__device__ __forceinline__ uint32_t bases16_before(const uint32_t *__restrict__ w, int64_t p)
+__device__ __forceinline__ void xdrop_xw(const WalkAt &q, const WalkAt &b, int32_t t, bool left,
+                                         uint32_t (&x)[2])
 {
-    if (p >= 16) return bases16_from(w, p - 16);
-    return p <= 0 ? 0u : (bases16_from(w, 0) >> (2u * (uint32_t)(16 - p)));
-}
-
-// X-drop walk of one lane, 16 steps per chunk.  The query and data-bank bases of
-// the chunk's 16 steps are read as packed words, compared at once (a 2-bit XOR),
-// and the running sum moves from one mismatch to the next: between mismatches it
-// only rises, so its maximum over a stretch of matches is at the stretch's end
-// (the first step at that value), and it can only fall more than X below the best
-// at a mismatch.  This is the step-by-step rule exactly.  xdrop_x reads a chunk's
-// XOR word (t < T: the walk's own bases).
-template <bool RIGHT>
-__device__ __forceinline__ uint32_t xdrop_x(const uint32_t *__restrict__ qpack, int64_t gq,
-                                            const uint32_t *__restrict__ dbw, int64_t gb,
-                                            int32_t t)
-{
-    // RIGHT: step i (0-based) is the base in bits 31-2i:30-2i; otherwise in bits 2i+1:2i
-    return RIGHT ? bases16_from(qpack, gq + t) ^ bases16_from(dbw, gb + t)
-                 : bases16_before(qpack, gq - t) ^ bases16_before(dbw, gb - t);
-}
-
-// The chunk's XOR word for a walk of either side, step i in bits 2i+1:2i.  A left
-// walk's word is read 16 positions lower, its first step (the base nearest the
-// run) in the low bits; a right walk's word is bit-reversed into the same order.
-// Both sides of a wave's walks then take one code path.
-__device__ __forceinline__ uint32_t xdrop_xw(const uint32_t *__restrict__ qpack, int64_t gq,
-                                             const uint32_t *__restrict__ dbw, int64_t gb,
-                                             int32_t t, bool left)
-{
-    const int64_t pq = left ? gq - t - 16 : gq + t, pb = left ? gb - t - 16 : gb + t;
-    uint32_t x;
-    if (pq >= 0 && pb >= 0) x = bases16_from(qpack, pq) ^ bases16_from(dbw, pb);
-    else x = xdrop_x<false>(qpack, gq, dbw, gb, t);  // a left walk near the arrays' starts
-    return left ? x : __brev(x);
+    const uint64_t v = walk_bases(q, t, left) ^ walk_bases(b, t, left);
+    const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
+    x[0] = left ? lo : __brev(hi);
+    x[1] = left ? hi : __brev(lo);
 }
 
 // One chunk of a walk (t < T): the up to 16 steps from t, whose query and bank
@@ -3545,13 +3596,12 @@ __device__ __forceinline__ uint32_t xdrop_xw(const uint32_t *__restrict__ qpack,
 // turn of the loop takes the stretch of matches up to the next mismatch (the
 // running sum's maximum over it is at its end) and then that mismatch, whose drop
 // is tested; past the chunk's last mismatch the stretch runs to the chunk's end.
+// dd is the best sum less the running sum: nothing else of the two is needed.
 // Returns true when the walk ended (drop over X, or T steps); otherwise t has
-// moved 16 steps on.  SMALL: match < 2^24, so a stretch's gain (at most 16
-// matches) takes a 24-bit multiply.
-template <bool SMALL>
+// moved 16 steps on.  (Scores too large for the step tables below.)
 __device__ __forceinline__ bool xdrop_chunk(uint32_t x, int32_t T, int32_t match,
-                                            int32_t mismatch, int32_t X, int32_t &t, int32_t &run,
-                                            int32_t &best, int32_t &bl)
+                                            int32_t mismatch, int32_t X, int32_t &t, int32_t &dd,
+                                            int32_t &bl)
 {
     const int32_t nstep = min(16, T - t);
     uint32_t mm = (x | (x >> 1)) & 0x55555555u;  // one flag bit per step
@@ -3560,17 +3610,16 @@ __device__ __forceinline__ bool xdrop_chunk(uint32_t x, int32_t T, int32_t match
     bool drop;
     do {
         nx = mm ? (int32_t)(__builtin_ctz(mm) >> 1) : nstep;  // the next mismatch
-        run += SMALL ? (int32_t)__umul24((uint32_t)(nx - pos), (uint32_t)match) : (nx - pos) * match;
-        blx = run > best ? nx : blx;  // first step at a new best
-        best = max(best, run);
-        run -= mismatch;  // undone below when the chunk had no mismatch left
-        drop = best - run > X;
+        dd -= (nx - pos) * match;
+        blx = dd < 0 ? nx : blx;  // first step at a new best
+        dd = max(dd, 0) + mismatch;  // undone below when the chunk had no mismatch left
+        drop = dd > X;
         mm &= mm - 1u;
         pos = nx + 1;
     } while (nx < nstep && !drop);
     if (blx >= 0) bl = t + blx;
     if (nx >= nstep) {
-        run += mismatch;
+        dd -= mismatch;
         t += nstep;
         return t >= T;
     }
@@ -3578,14 +3627,93 @@ __device__ __forceinline__ bool xdrop_chunk(uint32_t x, int32_t T, int32_t match
     return true;
 }
 
-// Extension of every run on both sides (Section 2.2 phase 3).  Each side of each
-// run is one walk; whole waves take contiguous ranges of walks, and a lane whose
-// walk ends takes the next one of its wave's range at once, so lanes do not idle
-// behind the longest walk of a group.  A walk still going after `lane_steps`
-// steps is queued (its state saved) and k_extend_long resumes it with a whole
-// wave; a full queue makes the lane finish the walk itself.  The right walk of a
-// run writes its box's run fields and right end, the left walk its left end; a
-// queued side is rewritten by k_extend_long.
+// Eight steps of a walk by table: entry f (bit i set: step i is a mismatch) holds the
+// steps' sum, the highest sum after any of them (0 when none is above the start) and
+// the first step there, the lowest sum, and the largest fall from a sum (the start's
+// included) to a later one.  A walk dd below its best drops within the eight steps
+// exactly when the fall or dd less the lowest sum exceeds X.
+//   bits 31:24 sum (signed), 23:18 highest, 17:14 its step, 13:7 -lowest, 6:0 fall
+// Scores up to 7 and 15 fit the fields.
+constexpr int32_t kStepMatch = 7, kStepMismatch = 15;
+
+__device__ __forceinline__ uint32_t step_entry(uint32_t f, int32_t match, int32_t mismatch)
+{
+    int32_t r = 0, hi = 0, at = 0, lo = 0, fall = 0;
+    for (int32_t i = 0; i < 8; ++i) {
+        r += (f >> i) & 1u ? -mismatch : match;
+        if (r > hi) {
+            hi = r;
+            at = i + 1;
+        }
+        lo = min(lo, r);
+        fall = max(fall, hi - r);
+    }
+    return ((uint32_t)r << 24) | ((uint32_t)hi << 18) | ((uint32_t)at << 14) |
+           ((uint32_t)-lo << 7) | (uint32_t)fall;
+}
+
+// Steps t .. t + 7 with mismatch flags f.  Returns true when the walk dropped.
+__device__ __forceinline__ bool xdrop_steps(uint32_t e, uint32_t f, int32_t match,
+                                            int32_t mismatch, int32_t X, int32_t t, int32_t &dd,
+                                            int32_t &bl)
+{
+    const int32_t hi = (int32_t)((e >> 18) & 63u);
+    const bool drop = max(dd + (int32_t)((e >> 7) & 127u), (int32_t)(e & 127u)) > X;
+    if (drop && hi > dd) {  // a new best and a drop in the same eight steps: step by step
+        int32_t r = 0, best = dd;
+        for (int32_t i = 0; i < 8; ++i) {
+            r += (f >> i) & 1u ? -mismatch : match;
+            if (r > best) {
+                best = r;
+                bl = t + i + 1;
+            }
+            if (best - r > X) break;
+        }
+        return true;
+    }
+    bl = hi > dd ? t + (int32_t)((e >> 14) & 15u) : bl;
+    dd = max(dd, hi) - ((int32_t)e >> 24);
+    return drop;
+}
+
+// 16 steps of a walk from t by two table entries; x: their XOR word.  Steps past the
+// walk's end T count as mismatches, which move no best.  True when the walk dropped.
+__device__ __forceinline__ bool xdrop_table(const uint32_t *__restrict__ tab, uint32_t x, int32_t T,
+                                            int32_t match, int32_t mismatch, int32_t X, int32_t t,
+                                            int32_t &dd, int32_t &bl)
+{
+    uint32_t f = x | (x >> 1);  // one flag per step, gathered to bits 7:0 and 23:16
+    if (T - t < 16) f |= ~0u << (2 * max(T - t, 0));
+    f &= 0x55555555u;
+    f = (f | (f >> 1)) & 0x33333333u;
+    f = (f | (f >> 2)) & 0x0F0F0F0Fu;
+    f |= f >> 4;
+    const uint32_t f0 = f & 255u, f1 = (f >> 16) & 255u;
+    const uint32_t e0 = tab[f0], e1 = tab[f1];
+    return xdrop_steps(e0, f0, match, mismatch, X, t, dd, bl) ||
+           xdrop_steps(e1, f1, match, mismatch, X, t + 8, dd, bl);
+}
+
+// Extension of every run on both sides (Section 2.2 phase 3), a walk per side.  Whole
+// waves take contiguous ranges of runs (SPLIT: of sides); every lane moves its walk a
+// round on, and once kServe lanes' walks have ended (or all), those lanes write their
+// boxes, turn to the other side or take the next run of the wave's range, so lanes
+// do not idle long behind the longest walk, and that work, as long as a round, is
+// not done for a few lanes in every round.  A walk still going after `lane_steps`
+// steps is queued (its state saved) and k_extend_long resumes it with a whole wave; a
+// full queue makes the lane finish the walk itself.  A queued side's end is rewritten
+// by k_extend_long.
+// SPLIT: the two sides of a run are two lanes' walks, for fewer runs than lanes on
+// the chip; each writes its own part of the box.  Else a lane walks right, then left,
+// and writes the box whole (a lane per side wrote 56 bytes per 32-byte box).
+// Bound by VALU instructions (walks among repeats take some 50 steps): 3.4 G runs in
+// 88 ms, at 80% of the issue rate, against 182 with 16 steps a round, a refill in every
+// round and a loop over the mismatches.
+// TAB: steps go by table entries, eight at a time; a loop over the mismatches ran as
+// long as its lane with the most.
+constexpr int kServe = 16;
+
+template <bool TAB, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_extend(const Cand *__restrict__ cands, uint32_t n,
                                                    const uint32_t *__restrict__ qpack,
                                                    const int64_t *__restrict__ qoff, int32_t qa,
@@ -3600,92 +3728,110 @@ __global__ __launch_bounds__(kBlock) void k_extend(const Cand *__restrict__ cand
         n = ctl->nc;
         qa = ctl->qa;
     }
-    const int lane = threadIdx.x & 63;
     const uint64_t nwave = (uint64_t)gridDim.x * (kBlock / 64);
-    const uint64_t wave = (uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    const uint64_t items = 2ull * n;  // walk w: run w / 2, left side when w is odd
+    const uint64_t items = SPLIT ? 2ull * n : n;  // SPLIT: run w / 2, left side when w is odd
     const uint64_t per = (items + nwave - 1) / nwave;
-    uint64_t next = wave * per;
+    if ((uint64_t)blockIdx.x * (kBlock / 64) * per >= items) return;  // nothing for this block
+    __shared__ uint32_t s_tab[TAB ? 256 : 1];
+    if (TAB) {
+        s_tab[threadIdx.x] = step_entry(threadIdx.x, match, mismatch);
+        __syncthreads();
+    }
+    const int lane = threadIdx.x & 63;
+    const uint64_t wave = (uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    uint64_t next = min(items, wave * per);
     const uint64_t stop = min(items, next + per);
     const uint64_t below = (1ull << lane) - 1ull;
-    bool have = false, left = false;
+    enum : int32_t { kIdle, kWalk, kEnd };  // no run; walking; the side's walk has ended
+    int32_t state = kIdle;
+    bool left = false, park = false;  // park: ended for this lane, goes on in the queue
     uint32_t ri = 0;
     Cand c{0, 0, 0, 0, 0};
-    int64_t gq = 0, gb = 0;
-    int32_t T = 0, t = 0, run = 0, best = 0, bl = 0, cap = 0;
-    uint32_t xn = 0;   // the bases' XOR of a going walk's next chunk, when xok
-    bool xok = false;
+    WalkAt qw{qpack, 0}, bw{dbw, 0};
+    int64_t q0 = 0, s0 = 0;
+    int32_t TR = 0, T = 0, t = 0, dd = 0, bl = 0, cap = 0;
     for (;;) {
-        // lanes without a walk take the next walks of the wave's range
-        const uint64_t need = __ballot(!have);
-        if (need && next < stop) {
-            if (!have) {
-                const uint64_t w = next + (uint64_t)__popcll(need & below);
-                if (w < stop) {
-                    have = true;
-                    ri = (uint32_t)(w >> 1);
-                    left = (w & 1) != 0;
-                    c = cands[ri];
-                    const int64_t q0 = qoff[qa + c.q];
-                    const int32_t L = (int32_t)(qoff[qa + c.q + 1] - q0);
-                    const int64_t s0 = seq_start[c.s];
-                    const int32_t ns = (int32_t)(seq_start[c.s + 1] - s0);
+        const uint64_t serve = __ballot(state == kEnd || (state == kIdle && next < stop));
+        const uint64_t walking = __ballot(state == kWalk);
+        if (__popcll(serve) >= kServe || walking == 0) {
+            if (serve == 0) break;
+            if (__ballot(park)) {
+                const uint32_t slot = queue_slot(park, qcount, lane);
+                if (park && slot < qcap) {
+                    queue[slot] = XWalk{ri | (left ? 0x80000000u : 0u), t, -dd, 0, bl};
+                } else if (park) {  // queue full: this lane finishes the walk
+                    cap = INT32_MAX;
+                    state = kWalk;
+                }
+                park = false;
+            }
+            bool open = false;
+            if (state == kEnd) {
+                Box *b = out + ri;
+                if (SPLIT) {
                     if (left) {
-                        T = min(c.qs, c.qs + c.d);
-                        gq = q0 + c.qs;
-                        gb = s0 + c.qs + c.d;
+                        b->qs = c.qs - bl;
+                        b->ds = c.qs - bl + c.d;
                     } else {
-                        T = min(L - c.qe, ns - (c.qe + c.d));
-                        gq = q0 + c.qe;
-                        gb = s0 + c.qe + c.d;
+                        b->q = c.q;
+                        b->s = c.s;
+                        b->qe = c.qe + bl;
+                        b->de = c.qe + bl + c.d;
+                        b->dmin = c.d;
+                        b->dmax = c.d;
                     }
-                    t = run = best = bl = 0;
-                    cap = lane_steps;
+                    state = kIdle;
+                } else if (!left) {  // the right end waits in c.qe: the left walk needs qs alone
+                    c.qe += bl;
+                    left = open = true;
+                } else {
+                    const int32_t qs = c.qs - bl;
+                    *b = Box{c.q, c.s, qs, c.qe, qs + c.d, c.qe + c.d, c.d, c.d};
+                    state = kIdle;
                 }
             }
-            next += (uint64_t)__popcll(need);
-        }
-        if (__ballot(have) == 0) break;
-        // one 16-step chunk of every walk per round, so that a lane whose walk ends
-        // takes its next walk without waiting for the longest walk of the wave; a
-        // walk that goes on has its next chunk's bases read at the end of the round,
-        // so the reads overlap the other lanes' refills
-        bool done = false, park = false;
-        if (have) {
-            if (t >= T) {
-                done = true;
-            } else if (t >= cap) {
-                park = true;  // past the lane's cap: to the queue for a whole wave
-            } else {
-                const uint32_t x = xok ? xn : xdrop_xw(qpack, gq, dbw, gb, t, left);
-                done = match < (1 << 24)
-                           ? xdrop_chunk<true>(x, T, match, mismatch, X, t, run, best, bl)
-                           : xdrop_chunk<false>(x, T, match, mismatch, X, t, run, best, bl);
+            const uint64_t need = __ballot(state == kIdle);
+            if (state == kIdle) {
+                const uint64_t w = next + (uint64_t)__popcll(need & below);
+                if (w < stop) {
+                    open = true;
+                    ri = (uint32_t)(SPLIT ? w >> 1 : w);
+                    left = SPLIT && (w & 1) != 0;
+                    c = cands[ri];
+                    q0 = qoff[qa + c.q];
+                    s0 = seq_start[c.s];
+                    TR = min((int32_t)(qoff[qa + c.q + 1] - q0) - c.qe,
+                             (int32_t)(seq_start[c.s + 1] - s0) - (c.qe + c.d));
+                }
+            }
+            next = min(stop, next + (uint64_t)__popcll(need));
+            if (open) {
+                const int32_t at = left ? c.qs : c.qe;
+                const int64_t gq = q0 + at, gb = s0 + at + c.d;
+                T = left ? min(c.qs, c.qs + c.d) : TR;
+                qw = WalkAt{qpack + (gq >> 4), (int32_t)(gq & 15)};
+                bw = WalkAt{dbw + (gb >> 4), (int32_t)(gb & 15)};
+                t = dd = bl = 0;
+                cap = lane_steps;
+                park = T > 0 && cap <= 0;
+                state = T > 0 && cap > 0 ? kWalk : kEnd;
             }
         }
-        xok = false;
-        const uint32_t slot = queue_slot(park, qcount, lane);
-        const bool queued = park && slot < qcap;
-        if (queued) queue[slot] = XWalk{ri | (left ? 0x80000000u : 0u), t, run, best, bl};
-        if (park && !queued) cap = INT32_MAX;  // queue full: this lane finishes the walk
-        if (have && !done && !queued && t < cap) {
-            xn = xdrop_xw(qpack, gq, dbw, gb, t, left);
-            xok = true;
-        }
-        if (done || queued) {
-            Box *b = out + ri;
-            if (left) {
-                b->qs = c.qs - bl;
-                b->ds = c.qs - bl + c.d;
+        if (state == kWalk) {
+            uint32_t x[2];
+            xdrop_xw(qw, bw, t, left, x);
+            bool done;
+            if (TAB) {
+                done = xdrop_table(s_tab, x[0], T, match, mismatch, X, t, dd, bl) ||
+                       xdrop_table(s_tab, x[1], T, match, mismatch, X, t + 16, dd, bl);
+                t += 32;
             } else {
-                b->q = c.q;
-                b->s = c.s;
-                b->qe = c.qe + bl;
-                b->de = c.qe + bl + c.d;
-                b->dmin = c.d;
-                b->dmax = c.d;
+                done = xdrop_chunk(x[0], T, match, mismatch, X, t, dd, bl) || t >= T ||
+                       xdrop_chunk(x[1], T, match, mismatch, X, t, dd, bl);
             }
-            have = false;
+            done = done || t >= T;
+            park = !done && t >= cap;  // past the lane's cap: to the queue for a whole wave
+            if (done || park) state = kEnd;
         }
     }
 }
@@ -3759,10 +3905,17 @@ void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32
     if (!count_cleared) launch_fill_u32(qcount, 1, 0u, st);
     // one wave per 64 walks up to 8 waves per SIMD on every CU; beyond that each
     // wave's range grows
+    // a lane per side until the runs alone give every lane of the chip one
+    const bool split = ctl || n < (1u << 19);
+    const uint64_t items = split ? 2ull * n : n;
     const uint32_t nb = ctl ? kStrideGrid
-                            : (uint32_t)std::min<uint64_t>((2ull * n + kBlock - 1) / kBlock, 8192);
-    k_extend<<<nb, kBlock, 0, st>>>(c, n, qpack, qoff, qa, dbw, seq_start, match, mismatch, xdrop,
-                                    out, queue, qcap, qcount, std::max(lane_steps, 0), ctl);
+                            : (uint32_t)std::min<uint64_t>((items + kBlock - 1) / kBlock, 8192);
+    const int32_t steps = std::max(lane_steps, 0);
+    const bool tab = match <= kStepMatch && mismatch <= kStepMismatch;
+    auto k = tab ? (split ? k_extend<true, true> : k_extend<true, false>)
+                 : (split ? k_extend<false, true> : k_extend<false, false>);
+    k<<<nb, kBlock, 0, st>>>(c, n, qpack, qoff, qa, dbw, seq_start, match, mismatch, xdrop, out,
+                             queue, qcap, qcount, steps, ctl);
     const uint64_t most = std::min<uint64_t>(2ull * nmax, qcap);  // queued walks at most
     const uint32_t lb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((most + 3) / 4, 1u << 16));
     k_extend_long<<<lb, kBlock, 0, st>>>(c, qcode, qoff, qa, dbw, seq_start, match, mismatch,

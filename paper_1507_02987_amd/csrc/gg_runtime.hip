@@ -157,6 +157,9 @@ struct Workspace {
     }
 };
 
+// The packed queries' first word, after the words that may be read before it.
+uint32_t *qpack_of(Workspace *ws) { return as<uint32_t>(ws->qpack) + kPackFront; }
+
 }  // namespace
 
 struct gg_index {
@@ -524,7 +527,7 @@ RunStarts run_starts(const gg_index *ix, Workspace *ws, const gg_params *p)
     a.qoff = as<int64_t>(ws->qoff);
     a.kcode = as<uint32_t>(ws->kcode);
     a.kcnt = as<uint32_t>(ws->cnt);
-    a.qpack = as<uint32_t>(ws->qpack);
+    a.qpack = qpack_of(ws);
     a.dbw = ix->d_dbw;
     a.seq_start = ix->d_seq_start;
     a.span = ix->span;
@@ -1074,7 +1077,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     TRY(ensure(ws->boxes3, sizeof(Box) * nc));
     TRY(ensure(ws->xqueue, extend_queue_bytes(nc)));
     prof.begin("extend");
-    launch_extend(as<Cand>(ws->cands), nc, as<uint8_t>(ws->qcode), as<uint32_t>(ws->qpack),
+    launch_extend(as<Cand>(ws->cands), nc, as<uint8_t>(ws->qcode), qpack_of(ws),
                   as<int64_t>(ws->qoff), qa,
                   ix->d_dbw, ix->d_seq_start, p->match, p->mismatch, p->xdrop, as<Box>(ws->boxes),
                   ws->xqueue.p, ix->tune_lane_steps.load(), st);
@@ -1839,7 +1842,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                                    as<uint32_t>(ws->cand_off), static_cast<uint32_t *>(ws->xqueue.p),
                                    ctl, st);
         }
-        launch_extend(as<Cand>(ws->cands), 0, as<uint8_t>(ws->qcode), as<uint32_t>(ws->qpack),
+        launch_extend(as<Cand>(ws->cands), 0, as<uint8_t>(ws->qcode), qpack_of(ws),
                       as<int64_t>(ws->qoff), 0,
                       ix->d_dbw, ix->d_seq_start, p->match, p->mismatch, p->xdrop,
                       as<Box>(ws->boxes), ws->xqueue.p, steps, st, ctl, runs_cap,
@@ -2001,8 +2004,8 @@ gg_status run_batch(const gg_index *ix, Workspace *ws, const char *qbuf, const i
     launch_query_totals(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), (int32_t)nq,
                         as<uint64_t>(ws->qtot), st);
     prof.end(T);
-    TRY(ensure(ws->qpack, sizeof(uint32_t) * ((size_t)(T + 15) / 16 + kPackSlack)));
-    launch_pack_query(as<uint8_t>(ws->qcode), T, as<uint32_t>(ws->qpack), st);
+    TRY(ensure(ws->qpack, sizeof(uint32_t) * (kPackFront + (size_t)(T + 15) / 16 + kPackSlack)));
+    launch_pack_query(as<uint8_t>(ws->qcode), T, qpack_of(ws), st);
     HIPCHK(hipMemcpyAsync(h_qtot, ws->qtot.p, sizeof(uint64_t) * nq, hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(h_err, ws->err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     SYNC(st);
@@ -2157,7 +2160,7 @@ void gg_index_free(gg_index *ix)
     ix->ws_free.clear();
     if (ix->d_list_off) (void)hipFree(ix->d_list_off);
     if (ix->d_post) (void)hipFree(ix->d_post);
-    if (ix->d_dbw) (void)hipFree(ix->d_dbw);
+    if (ix->d_dbw) (void)hipFree(ix->d_dbw - kPackFront);
     if (ix->d_seq_start) (void)hipFree(ix->d_seq_start);
     if (ix->d_next) (void)hipFree(ix->d_next);
     delete ix;
@@ -2203,6 +2206,19 @@ gg_status index_contexts(gg_index *ix, hipStream_t st)
     launch_contexts(ix->d_post, (uint32_t)ix->n_post, ix->d_dbw, ix->d_seq_start, ix->span,
                     ix->mask, ctx_shape(ix->k), ix->d_next, ix->d_prev, st);
     if (!st) SYNC(st);
+    return GG_OK;
+}
+
+// The packed bank's words, with those that may be read before and past them.
+gg_status alloc_bank(gg_index *ix, int64_t nwords)
+{
+    uint32_t *p = nullptr;
+    if (hipMalloc((void **)&p, sizeof(uint32_t) * (size_t)(kPackFront + nwords + kPackSlack)) !=
+        hipSuccess) {
+        (void)hipGetLastError();
+        return GG_ENOMEM;
+    }
+    ix->d_dbw = p + kPackFront;
     return GG_OK;
 }
 
@@ -2293,7 +2309,7 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     const bool cut = max_posting > 0 && (uint64_t)max_posting < n_post;
     if ((s = alloc((void **)&ix->d_list_off, sizeof(uint32_t) * (ncode + 1))) != GG_OK ||
         (!cut && (s = alloc((void **)&ix->d_post, sizeof(int2) * n_post)) != GG_OK) ||
-        (s = alloc((void **)&ix->d_dbw, sizeof(uint32_t) * (nwords + kPackSlack))) != GG_OK ||
+        (s = alloc_bank(ix, nwords)) != GG_OK ||
         (s = alloc((void **)&ix->d_seq_start, sizeof(int64_t) * (n_seqs + 1))) != GG_OK)
         return fail(s);
 
@@ -2674,8 +2690,8 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
         return st;
     };
     if (hipSetDevice(device) != hipSuccess) return fail(GG_EDEVICE);
-    auto up = [](void **dst, const void *src, size_t bytes, size_t slack = 0) -> gg_status {
-        if (hipMalloc(dst, std::max<size_t>(bytes + slack, 16)) != hipSuccess) {
+    auto up = [](void **dst, const void *src, size_t bytes) -> gg_status {
+        if (hipMalloc(dst, std::max<size_t>(bytes, 16)) != hipSuccess) {
             (void)hipGetLastError();
             *dst = nullptr;
             return GG_ENOMEM;
@@ -2689,9 +2705,11 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
             GG_OK ||
         (st = up((void **)&ix->d_list_off, heads.data(), sizeof(uint32_t) * heads.size())) != GG_OK ||
         (st = up((void **)&ix->d_post, post.data(), sizeof(int2) * post.size())) != GG_OK ||
-        (st = up((void **)&ix->d_dbw, bank.data(), sizeof(uint32_t) * bank.size(),
-                 sizeof(uint32_t) * kPackSlack)) != GG_OK)
+        (st = alloc_bank(ix, (int64_t)bank.size())) != GG_OK)
         return fail(st);
+    if (hipMemcpy(ix->d_dbw, bank.data(), sizeof(uint32_t) * bank.size(), hipMemcpyHostToDevice) !=
+        hipSuccess)
+        return fail(GG_EDEVICE);
     // contexts stand for the lists only where each list holds every window of its code
     uint64_t nwin = 0;
     for (int64_t s = 0; s < hd.n_seqs; ++s)
