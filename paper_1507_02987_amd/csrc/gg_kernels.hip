@@ -2538,7 +2538,7 @@ void launch_hit_compact(const uint64_t *keys, const uint32_t *hrel, const int64_
 // Nothing is stored for any other hit, nothing is sorted by diagonal or position,
 // and the runs are those of sorting all hits by (q, s, diag, qpos) and scanning them.
 // 2,000 queries of 500-5,000 bp on a 3 Gbp bank with repeats (16.7 G hits, 3.4 G
-// runs): starts 87, three passes over them 64 and their ends 56 ms, where gathering,
+// runs): starts 63, three passes over them 64 and their ends 54 ms, where gathering,
 // five radix passes over every hit and chaining took 618.
 CtxShape ctx_shape(int32_t k)
 {
@@ -2557,20 +2557,23 @@ CtxShape ctx_shape(int32_t k)
     return s;
 }
 
-// 64 bases of a 2-bit packed array from base g (reads words g / 16 .. g / 16 + 4).
+// 64 bases of a 2-bit packed array from base g (reads words (g - 1) / 16 .. + 4).
 struct Bases64 {
     uint64_t h, l;
 };
 __device__ __forceinline__ Bases64 bases64(const uint32_t *__restrict__ w, int64_t g)
 {
-    const int64_t wi = g >> 4;
-    const uint32_t sh = 32u - ((uint32_t)(g & 15) << 1);
-    const u32x4_a4 v = *reinterpret_cast<const u32x4_a4 *>(w + wi);
-    const uint32_t e = w[wi + 4];
-    const uint32_t a = (uint32_t)((((uint64_t)v.x << 32) | v.y) >> sh);
-    const uint32_t b = (uint32_t)((((uint64_t)v.y << 32) | v.z) >> sh);
-    const uint32_t c = (uint32_t)((((uint64_t)v.z << 32) | v.w) >> sh);
-    const uint32_t d = (uint32_t)((((uint64_t)v.w << 32) | e) >> sh);
+    // the word of the base before, so that a base's two bits are shifted by 2 to 32
+    // (a funnel shift of 32 is the next word whole)
+    const int64_t p = g - 1;
+    const uint32_t sh = ~(uint32_t)p << 1;  // 30 - 2 (p % 16) in its low five bits
+    const uint32_t *v = w + (p >> 4);
+    const u32x4_a4 x = *reinterpret_cast<const u32x4_a4 *>(v);
+    const uint32_t e = v[4];
+    const uint32_t a = __builtin_amdgcn_alignbit(x.x, x.y, sh);
+    const uint32_t b = __builtin_amdgcn_alignbit(x.y, x.z, sh);
+    const uint32_t c = __builtin_amdgcn_alignbit(x.z, x.w, sh);
+    const uint32_t d = __builtin_amdgcn_alignbit(x.w, e, sh);
     return Bases64{((uint64_t)a << 32) | b, ((uint64_t)c << 32) | d};
 }
 
@@ -2690,6 +2693,42 @@ __device__ __forceinline__ uint32_t ctx_match(uint2 c, uint32_t q0, uint32_t q1,
     return r & vm & ((1u << (c.x >> 30)) - 1u);
 }
 
+// The same for one position's context in every lane, as conditions: some whole field
+// matches; some field that is not whole does.  The lanes' tests are then two compares
+// a field and scalar mask operations.  over[m - 1]: a context's first word is above it
+// when window m exists on both sides.
+struct CtxTest {
+    bool exact, part;
+};
+struct CtxSide {
+    uint32_t q0, q1, over[kCtx];
+};
+__device__ __forceinline__ CtxSide ctx_side(uint32_t q0, uint32_t q1, uint32_t vm)
+{
+    CtxSide r{q0, q1, {}};
+#pragma unroll
+    for (int m = 1; m <= kCtx; ++m)
+        r.over[m - 1] = (vm >> (m - 1)) & 1u ? ((uint32_t)m << 30) - 1u : ~0u;
+    return r;
+}
+__device__ __forceinline__ CtxTest ctx_test(uint2 c, const CtxSide &q, const CtxShape &s)
+{
+    const uint32_t x = c.x ^ q.q0, y = c.y ^ q.q1;
+    const bool b1 = (x & s.m1) == 0 && c.x > q.over[0];
+    const bool b2 = (y & s.m2) == 0 && c.x > q.over[1];
+    const bool b3 = ((x & s.m3lo) | (y & s.m3hi)) == 0 && c.x > q.over[2];
+    const bool e1 = s.exact & 1u, e3 = s.exact & 4u;
+    return CtxTest{(e1 && b1) || b2 || (e3 && b3), (!e1 && b1) || (!e3 && b3)};
+}
+
+// A context that every lane of the wave holds alike, in scalar registers.
+__device__ __forceinline__ QCtx uniform_ctx(const QCtx &q)
+{
+    auto u = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)v); };
+    return QCtx{u(q.vm), u(q.n0), u(q.n1), u(q.p0), u(q.p1), (int32_t)u((uint32_t)q.qpos),
+                (int32_t)u((uint32_t)q.ql), u(q.head)};
+}
+
 // Inclusive running maximum over the wave's lanes of values >= 0 (every lane active):
 // row shifts by DPP, then the last lane of each row to the next row and the last two.
 __device__ __forceinline__ int32_t wave_run_max(int32_t x)
@@ -2702,6 +2741,11 @@ __device__ __forceinline__ int32_t wave_run_max(int32_t x)
     x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));  // row_bcast:31
     return x;
 }
+
+// Blocks of the diagonal walks, 16 times what the chip holds at once: the waves'
+// ranges differ in work, and with 8,192 blocks the last ones left 5% of the time idle
+// (with 2,048, a fifth).
+constexpr uint32_t kWalkGrid = 32768;
 
 // The coded bases of a window of `span` bases, first base in the top two bits.
 __device__ __forceinline__ uint64_t window_bits(int32_t span, uint32_t mask)
@@ -2795,53 +2839,62 @@ __device__ int32_t run_rest(const RunStarts &a, uint64_t wm, int32_t nw, RunWalk
 // Windows a chunk holds.
 __device__ __forceinline__ int32_t chunk_count(int32_t span) { return 64 / span; }
 
-// Whether hit `idx` of position p (context q) starts a run of at least two hits that
-// is long enough, and its key; nm, pm: the windows after and before it that match by
-// context.  Fields that are not whole are looked up in the bank.
-__device__ __forceinline__ bool run_start(const RunStarts &a, const QCtx &q, uint32_t p,
-                                          uint32_t idx, uint32_t nm, uint32_t pm, uint64_t *key)
+// Whether hit `idx` of position p (context q), whose whole fields say that it starts a
+// run of at least two hits, does so and the run is long enough.  Fields that are not
+// whole are looked up in the bank.
+__device__ bool start_kept(const RunStarts &a, const QCtx &q, uint32_t p, uint32_t idx)
 {
+    uint32_t nm = ctx_match(a.next[idx], q.n0, q.n1, q.vm, a.shape);
+    uint32_t pm = ctx_match(a.prev[idx], q.p0, q.p1, q.vm >> kCtx, a.shape);
     const int2 e = a.post[idx];
-    bool ok = true;
-    if (pm != 0 || (nm & a.shape.exact) == 0) {
-        const int64_t g = a.g0 + p, s0 = a.seq_start[e.x];
-        for (; ok && pm; pm &= pm - 1) {
-            const int32_t o = -(__ffs((int)pm) * a.span);
-            ok = db_code(a.dbw, s0 + e.y + o, a.span, a.mask) != a.kcode[g + o];
-        }
-        bool succ = (nm & a.shape.exact) != 0;
-        for (; ok && !succ && nm; nm &= nm - 1) {
-            const int32_t o = __ffs((int)nm) * a.span;
-            succ = db_code(a.dbw, s0 + e.y + o, a.span, a.mask) == a.kcode[g + o];
-        }
-        ok = ok && succ;
+    const int64_t g = a.g0 + p, s0 = a.seq_start[e.x];
+    for (; pm; pm &= pm - 1) {
+        const int32_t o = -(__ffs((int)pm) * a.span);
+        if (db_code(a.dbw, s0 + e.y + o, a.span, a.mask) == a.kcode[g + o]) return false;
     }
-    if (ok && a.min_len > 2 * a.span) {  // two hits may be too short
-        const int64_t q0 = a.qoff[a.qa + q.ql], s0 = a.seq_start[e.x];
-        RunWalk w = run_walk(q0, (int32_t)(a.qoff[a.qa + q.ql + 1] - q0), s0,
-                             (int32_t)(a.seq_start[e.x + 1] - s0), e.y - q.qpos, q.qpos, a.span);
-        const uint64_t wm = window_bits(a.span, a.mask);
-        while (w.hit + a.span < a.min_len && !run_chunk(a, wm, chunk_count(a.span), w)) {}
-        ok = w.hit + a.span >= a.min_len;
+    bool succ = (nm & a.shape.exact) != 0;
+    for (; !succ && nm; nm &= nm - 1) {
+        const int32_t o = __ffs((int)nm) * a.span;
+        succ = db_code(a.dbw, s0 + e.y + o, a.span, a.mask) == a.kcode[g + o];
     }
-    *key = ((uint64_t)(uint32_t)e.x << (a.lay.bd + a.lay.bp)) |
-           ((uint64_t)(uint32_t)(e.y - q.qpos + a.lay.bias) << a.lay.bp) |
-           (uint64_t)(uint32_t)q.qpos;
-    return ok;
+    if (!succ) return false;
+    if (a.min_len <= 2 * a.span) return true;  // two hits are long enough
+    const int64_t q0 = a.qoff[a.qa + q.ql];
+    RunWalk w = run_walk(q0, (int32_t)(a.qoff[a.qa + q.ql + 1] - q0), s0,
+                         (int32_t)(a.seq_start[e.x + 1] - s0), e.y - q.qpos, q.qpos, a.span);
+    const uint64_t wm = window_bits(a.span, a.mask);
+    while (w.hit + a.span < a.min_len && !run_chunk(a, wm, chunk_count(a.span), w)) {}
+    return w.hit + a.span >= a.min_len;
 }
 
-// A tile of kTile consecutive hits at a time, `tiles` of them per block.  Each
-// position with hits in the tile marks its first one in LDS, and a running maximum
-// over the tile gives every hit its position (a binary search per hit took nine
-// dependent LDS reads where lists are short).  Contexts are read coalesced, four rows
-// of 64 hits in flight per wave.  The starts of tiles that lie in one query are
-// collected in LDS and written kTile or more at once, with one add to the query's
-// count: adds to one counter are done one after another, 13.5 ns each, so with one
-// per wave and row a query with long lists took 44 ps per hit.
-constexpr uint32_t kStartCap = 2 * kTile - 16;  // four blocks to a CU's LDS
+// The key of the run that starts at posting e and query position qpos.
+__device__ __forceinline__ uint64_t start_key(const HitKeyLayout &lay, int2 e, int32_t qpos)
+{
+    return ((uint64_t)(uint32_t)e.x << (lay.bd + lay.bp)) |
+           ((uint64_t)(uint32_t)(e.y - qpos + lay.bias) << lay.bp) | (uint64_t)(uint32_t)qpos;
+}
+
+// A tile of kTile consecutive hits at a time, `tiles` of them per block.  In a tile of
+// several lists each position with hits marks its first one in LDS, and a running
+// maximum over the tile gives every hit its position (a binary search per hit took
+// nine dependent LDS reads where lists are short); in a tile of one list there is one
+// position, its context in scalar registers.  Contexts are read coalesced, four rows
+// of 64 hits in flight per wave: 16 bytes a hit, 16.7 G hits in 63 ms (4.2 TB/s; 87 with
+// every row its own positions, keys and look-ups).  The starts are noted in LDS, hit and position in a
+// word, and their keys built and written together, with one add to a query's count
+// for all starts of a block that lie in one query: adds to one counter are done one
+// after another, 13.5 ns each, so with one per wave and row a query with long lists
+// took 44 ps per hit; and a start in five hits would make every row build keys for a
+// few lanes.  Starts that are not sure from their contexts are noted as such and
+// settled before the keys are built, whole waves of them at a time.
+constexpr uint32_t kStartCap = 2 * kTile;
+constexpr int kStartTiles = 8;                 // tiles per block at most
+constexpr int kStartHit = 14, kStartPos = 17;  // bits of a hit in its block, a position in its tile
+constexpr uint32_t kStartUnsure = 1u << 31, kStartNone = ~0u;
+static_assert(kStartTiles * kTile <= 1 << kStartHit, "a block's hits fit a note");
 
 template <bool BOTH>
-__global__ __launch_bounds__(kBlock, 4) void k_run_starts(RunStarts a,
+__global__ __launch_bounds__(kBlock, 5) void k_run_starts(RunStarts a,
                                                           const WaveCtl *__restrict__ ctl,
                                                           int32_t tiles)
 {
@@ -2853,29 +2906,119 @@ __global__ __launch_bounds__(kBlock, 4) void k_run_starts(RunStarts a,
         a.lay = ctl->lay;
     }
     constexpr int kWaves = kBlock / 64, kHalf = kItems / 2;
-    __shared__ int32_t s_p[kTile];    // 1 + position (from the tile's first) at its first hit
-    __shared__ uint64_t s_key[kStartCap];  // starts not yet written
+    __shared__ int32_t s_p[kTile];  // 1 + position (from the tile's first) at its first hit
+    __shared__ uint32_t s_note[kStartCap];  // starts not yet written: hit | position | unsure
+    __shared__ uint32_t s_tlo[kStartTiles];  // each tile's first position
     __shared__ int32_t s_wm[kWaves];
-    __shared__ uint32_t s_lo, s_hi, s_at, s_n;
+    __shared__ uint32_t s_lo, s_hi, s_at, s_n, s_u, s_cnt[3];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
-    int32_t lq = -1;  // the query of the s_n keys in s_key
-    if (threadIdx.x == 0) s_n = 0;
-    // nlist: s_n, read by every thread between two barriers with no add to it
-    auto flush = [&](uint32_t nlist) {
-        if (nlist == 0) return;
-        if (threadIdx.x == 0) s_at = a.sbase[lq] + atomicAdd(a.scount + lq, nlist);
+    const uint32_t b0 = blockIdx.x * (uint32_t)(tiles * kTile);  // the block's first hit
+    const bool lengths = a.min_len > 2 * a.span;                 // two hits may be too short
+    int32_t lq = -1;  // the query of the noted starts
+    if (threadIdx.x == 0) s_n = s_u = 0;
+    __syncthreads();
+    // Settles the unsure ones of the n notes and closes the gaps of those dropped (the
+    // last notes move there); returns how many are left.  Uses s_p.
+    auto settle = [&](uint32_t n) {
+        uint16_t *list = reinterpret_cast<uint16_t *>(s_p);
+        static_assert(sizeof(s_p) >= sizeof(uint16_t) * kStartCap, "a note's number each");
+        if (threadIdx.x < 3) s_cnt[threadIdx.x] = 0;
         __syncthreads();
+        for (uint32_t i = threadIdx.x; i < n; i += kBlock)
+            if (s_note[i] & kStartUnsure) list[atomicAdd(&s_cnt[0], 1u)] = (uint16_t)i;
+        __syncthreads();
+        const uint32_t nu = s_cnt[0];
+        for (uint32_t i = threadIdx.x; i < nu; i += kBlock) {
+            const uint32_t x = list[i], v = s_note[x] & ~kStartUnsure;
+            const uint32_t l = v & ((1u << kStartHit) - 1u);
+            const uint32_t p = s_tlo[l / kTile] + (v >> kStartHit);
+            const QCtx q = a.qctx[p];
+            const bool keep = start_kept(a, q, p, q.head + b0 + l);
+            s_note[x] = keep ? v : kStartNone;
+            if (!keep) atomicAdd(&s_cnt[1], 1u);
+        }
+        __syncthreads();
+        const uint32_t left = n - s_cnt[1];
+        if (left == n) return n;
+        for (uint32_t i = threadIdx.x; i < left; i += kBlock)
+            if (s_note[i] == kStartNone) list[atomicAdd(&s_cnt[2], 1u)] = (uint16_t)i;
+        __syncthreads();
+        for (uint32_t i = left + threadIdx.x; i < n; i += kBlock)
+            if (s_note[i] != kStartNone) s_note[list[atomicSub(&s_cnt[2], 1u) - 1u]] = s_note[i];
+        __syncthreads();
+        return left;
+    };
+    // n, u: s_n and s_u, read by every thread between two barriers with no add to them
+    auto flush = [&](uint32_t n, uint32_t u, bool one) {
+        if (u) n = settle(n);
+        if (one && n) {
+            if (threadIdx.x == 0) s_at = a.sbase[lq] + atomicAdd(a.scount + lq, n);
+            __syncthreads();
+        }
         const uint32_t at = s_at;
-        for (uint32_t i = threadIdx.x; i < nlist; i += kBlock) a.out[at + i] = s_key[i];
-        if (threadIdx.x == 0) s_n = 0;
+        for (uint32_t i = threadIdx.x; i - lane < n; i += kBlock) {  // whole waves
+            int32_t ql = -1;
+            uint64_t key = 0;
+            if (i < n) {
+                const uint32_t v = s_note[i], l = v & ((1u << kStartHit) - 1u);
+                const QCtx q = a.qctx[s_tlo[l / kTile] + (v >> kStartHit)];
+                key = start_key(a.lay, a.post[q.head + b0 + l], q.qpos);
+                ql = q.ql;
+                if (one) a.out[at + i] = key;
+            }
+            if (one) continue;
+            for (uint64_t left = __ballot(ql >= 0); left;) {  // an add per wave and query
+                const int f = __ffsll((unsigned long long)left) - 1;
+                const int32_t q1 = __shfl(ql, f, 64);
+                const uint64_t same = __ballot(ql == q1);
+                uint32_t o = 0;
+                if (lane == f)
+                    o = a.sbase[q1] + atomicAdd(a.scount + q1, (uint32_t)__popcll(same));
+                o = __shfl(o, f, 64);
+                if (ql == q1) a.out[o + (uint32_t)__popcll(same & below)] = key;
+                left &= ~same;
+            }
+        }
         __syncthreads();
+        if (threadIdx.x == 0) s_n = s_u = 0;
+        __syncthreads();
+    };
+    // the starts among four rows' lanes (st; un: not sure), l + 64 r the lane's hit in
+    // the block, off its position in the tile
+    auto note = [&](const bool (&st)[kHalf], const bool (&un)[kHalf], uint32_t l,
+                    const uint32_t (&off)[kHalf]) {
+        uint64_t m[kHalf], um = 0;
+        uint32_t n = 0;
+#pragma unroll
+        for (int r = 0; r < kHalf; ++r) {
+            m[r] = __ballot(st[r]);
+            um |= __ballot(st[r] && un[r]);
+            n += (uint32_t)__popcll(m[r]);
+        }
+        if (n == 0) return;
+        uint32_t at = 0;
+        if (lane == 0) {
+            at = atomicAdd(&s_n, n);
+            if (um) s_u = 1;
+        }
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
+#pragma unroll
+        for (int r = 0; r < kHalf; ++r) {
+            if (st[r])
+                s_note[at + (uint32_t)__popcll(m[r] & below)] =
+                    (l + 64 * r) | (off[r] << kStartHit) | (un[r] ? kStartUnsure : 0u);
+            at += (uint32_t)__popcll(m[r]);
+        }
     };
     for (int32_t ti = 0; ti < tiles; ++ti) {
         const uint32_t tile = blockIdx.x * (uint32_t)tiles + (uint32_t)ti;
         const uint32_t t0 = tile * (uint32_t)kTile;
         if (t0 >= a.nhits) break;  // a graph's grid covers the largest wave
         const uint32_t cnt = min((uint32_t)kTile, a.nhits - t0);
+        const uint32_t held = s_n, unsure = s_u;  // no add to them before the barrier below
+        // wave wv's hits: rows of 64 from wv * kTile / kWaves
+        const uint32_t w0 = wv * (kTile / kWaves) + lane;
 #pragma unroll
         for (int r = 0; r < kItems; ++r) s_p[r * kBlock + threadIdx.x] = 0;
         if (a.tile_pos) {
@@ -2895,14 +3038,44 @@ __global__ __launch_bounds__(kBlock, 4) void k_run_starts(RunStarts a,
             else s_lo = x;
         }
         __syncthreads();
-        const uint32_t lo = s_lo, hi = s_hi, held = s_n;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)s_lo);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)s_hi);
+        if (BOTH && lo == hi) {
+            const QCtx q = uniform_ctx(a.qctx[lo]);
+            if (lq >= 0 && (q.ql != lq || held > kStartCap - kTile)) flush(held, unsure, true);
+            lq = q.ql;
+            if (threadIdx.x == 0) s_tlo[ti] = lo;
+            const uint32_t base = q.head + t0;
+            const uint2 *next = a.next + base, *prev = a.prev + base;
+            const CtxSide qn = ctx_side(q.n0, q.n1, q.vm), qp = ctx_side(q.p0, q.p1, q.vm >> kCtx);
+#pragma unroll
+            for (int h = 0; h < kItems; h += kHalf) {
+                uint2 cn[kHalf], cp[kHalf];
+                bool st[kHalf], un[kHalf];
+                const uint32_t off[kHalf] = {0, 0, 0, 0};
+#pragma unroll
+                for (int r = 0; r < kHalf; ++r) {
+                    const uint32_t l = min(w0 + (h + r) * 64, cnt - 1);
+                    cn[r] = next[l];
+                    cp[r] = prev[l];
+                }
+#pragma unroll
+                for (int r = 0; r < kHalf; ++r) {
+                    const CtxTest n = ctx_test(cn[r], qn, a.shape);
+                    const CtxTest p = ctx_test(cp[r], qp, a.shape);
+                    st[r] = w0 + (h + r) * 64 < cnt && (n.exact || n.part) && !p.exact;
+                    un[r] = lengths || !n.exact || p.part;
+                }
+                note(st, un, ti * kTile + w0 + h * 64, off);
+            }
+            __syncthreads();
+            continue;
+        }
         for (uint32_t p = lo + threadIdx.x; p <= hi; p += kBlock) {
             const uint32_t r0 = a.hrel[p], r1 = a.hrel[p + 1];
             if (r1 > r0 && r1 > t0 && r0 < t0 + cnt) s_p[max(r0, t0) - t0] = (int32_t)(p - lo) + 1;
         }
         __syncthreads();
-        // wave wv's hits: rows of 64 from wv * kTile / kWaves
-        const uint32_t w0 = wv * (kTile / kWaves) + lane;
         int32_t pr[kItems], run = 0;
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
@@ -2919,62 +3092,53 @@ __global__ __launch_bounds__(kBlock, 4) void k_run_starts(RunStarts a,
         }
         const int32_t qf = a.qctx[lo].ql, qt = a.qctx[lo + (uint32_t)last - 1u].ql;
         const bool one = qf == qt;
-        if (lq >= 0 && (!one || qf != lq || held > kStartCap - kTile)) flush(held);
+        if (lq >= 0 && (!one || qf != lq || held > kStartCap - kTile)) flush(held, unsure, true);
         lq = one ? qf : -1;
+        // a tile's first position in its notes, moved on where the tile's positions
+        // (those without hits included) outrun a note: such tiles are noted in parts
+        uint32_t from = 0;
+        do {
+            const uint32_t upto = from + (1u << kStartPos) - 1u;
+            if (threadIdx.x == 0) s_tlo[ti] = lo + from;
 #pragma unroll
-        for (int h = 0; h < kItems; h += kHalf) {
-            QCtx q[kHalf];
-            uint32_t idx[kHalf], pos[kHalf];
-            uint2 cn[kHalf], cp[kHalf];
+            for (int h = 0; h < kItems; h += kHalf) {
+                QCtx q[kHalf];
+                uint32_t idx[kHalf], off[kHalf];
+                uint2 cn[kHalf], cp[kHalf];
+                bool st[kHalf], un[kHalf];
 #pragma unroll
-            for (int r = 0; r < kHalf; ++r) {
-                // lanes past the tile read its last hit
-                const uint32_t l = min(w0 + (h + r) * 64, cnt - 1);
-                const int32_t x = max(pr[h + r], before);
-                pos[r] = lo + (uint32_t)(w0 + (h + r) * 64 < cnt ? x : last) - 1u;
-                q[r] = a.qctx[pos[r]];
-                idx[r] = q[r].head + t0 + l;
-                cn[r] = a.next[idx[r]];
-                if (BOTH) cp[r] = a.prev[idx[r]];
+                for (int r = 0; r < kHalf; ++r) {
+                    // lanes past the tile read its last hit
+                    const uint32_t l = min(w0 + (h + r) * 64, cnt - 1);
+                    const int32_t x = max(pr[h + r], before);
+                    off[r] = (uint32_t)(w0 + (h + r) * 64 < cnt ? x : last) - 1u;
+                    q[r] = a.qctx[lo + off[r]];
+                    idx[r] = q[r].head + t0 + l;
+                    cn[r] = a.next[idx[r]];
+                    if (BOTH) cp[r] = a.prev[idx[r]];
+                }
+#pragma unroll
+                for (int r = 0; r < kHalf; ++r) {
+                    const uint32_t nm = ctx_match(cn[r], q[r].n0, q[r].n1, q[r].vm, a.shape);
+                    st[r] = w0 + (h + r) * 64 < cnt && nm != 0 && off[r] >= from && off[r] < upto;
+                    un[r] = false;
+                    if (BOTH || st[r]) {
+                        if (!BOTH) cp[r] = a.prev[idx[r]];
+                        const uint32_t pm =
+                            ctx_match(cp[r], q[r].p0, q[r].p1, q[r].vm >> kCtx, a.shape);
+                        st[r] = st[r] && (pm & a.shape.exact) == 0;
+                        un[r] = lengths || (nm & a.shape.exact) == 0 || pm != 0;
+                    }
+                    off[r] -= from;
+                }
+                note(st, un, ti * kTile + w0 + h * 64, off);
             }
-#pragma unroll
-            for (int r = 0; r < kHalf; ++r) {
-                const uint32_t nm = ctx_match(cn[r], q[r].n0, q[r].n1, q[r].vm, a.shape);
-                bool st = w0 + (h + r) * 64 < cnt && nm != 0;
-                uint32_t pm = 0;
-                uint64_t key = 0;
-                if (BOTH || st) {
-                    if (!BOTH) cp[r] = a.prev[idx[r]];
-                    pm = ctx_match(cp[r], q[r].p0, q[r].p1, q[r].vm >> kCtx, a.shape);
-                    st = st && (pm & a.shape.exact) == 0;
-                }
-                if (st) st = run_start(a, q[r], pos[r], idx[r], nm, pm, &key);
-                uint64_t left = __ballot(st);
-                if (left == 0) continue;
-                if (one) {
-                    uint32_t at = 0;
-                    if (lane == 0) at = atomicAdd(&s_n, (uint32_t)__popcll(left));
-                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
-                    if (st) s_key[at + (uint32_t)__popcll(left & below)] = key;
-                    continue;
-                }
-                const int32_t ql = st ? q[r].ql : -1;
-                while (left) {  // several queries: one counter add per row and query
-                    const int f = __ffsll((unsigned long long)left) - 1;
-                    const int32_t q1 = __shfl(ql, f, 64);
-                    const uint64_t same = __ballot(ql == q1);
-                    uint32_t at = 0;
-                    if (lane == f)
-                        at = a.sbase[q1] + atomicAdd(a.scount + q1, (uint32_t)__popcll(same));
-                    at = __shfl(at, f, 64);
-                    if (ql == q1) a.out[at + (uint32_t)__popcll(same & below)] = key;
-                    left &= ~same;
-                }
-            }
-        }
-        __syncthreads();  // keys and marks of this tile are in place and read
+            __syncthreads();  // notes and marks of this tile are in place and read
+            from = upto;
+            if (!one || from <= hi - lo) flush(s_n, s_u, one);
+        } while (from <= hi - lo);
     }
-    if (lq >= 0) flush(s_n);
+    if (lq >= 0) flush(s_n, s_u, true);
 }
 
 void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const WaveCtl *ctl,
@@ -2985,7 +3149,7 @@ void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const Wave
     // eight tiles per block once every CU gets several such blocks: fewer, larger
     // writes and counter adds
     const uint32_t nt = (h + kTile - 1) / kTile;
-    const int32_t tiles = nt >= 8u * 256u * 8u ? 8 : 1;
+    const int32_t tiles = nt >= kStartTiles * 256u * 8u ? kStartTiles : 1;
     const uint32_t nb = (nt + tiles - 1) / tiles;
     if (both) k_run_starts<true><<<nb, kBlock, 0, st>>>(a, ctl, tiles);
     else k_run_starts<false><<<nb, kBlock, 0, st>>>(a, ctl, tiles);
@@ -3098,7 +3262,7 @@ void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *ca
 // Whole waves take contiguous ranges of runs, and a lane whose run ends takes the
 // next one of its wave's range, a chunk of every lane's run per round: a run has five
 // hits on average, but one in a wave of 64 often has the 27 of a 300 bp repeat (72 ms
-// for 3.4 G runs when a wave waited for its longest run, window by window; 56 now).
+// for 3.4 G runs when a wave waited for its longest run, window by window; 54 now).
 __global__ __launch_bounds__(kBlock) void k_run_ends(RunStarts a, const uint64_t *__restrict__ keys,
                                                      uint32_t n, const uint32_t *__restrict__ off,
                                                      int32_t nqw, Cand *__restrict__ cands)
@@ -3156,7 +3320,7 @@ void launch_run_ends(const RunStarts &a, const uint64_t *keys, uint32_t n, const
                      int32_t nqw, Cand *cands, hipStream_t st)
 {
     if (n == 0) return;
-    const uint32_t nb = (uint32_t)std::min<uint64_t>(((uint64_t)n + kBlock - 1) / kBlock, 8192);
+    const uint32_t nb = (uint32_t)std::min<uint64_t>(((uint64_t)n + kBlock - 1) / kBlock, kWalkGrid);
     k_run_ends<<<nb, kBlock, 0, st>>>(a, keys, n, off, nqw, cands);
 }
 
@@ -3571,22 +3735,17 @@ struct WalkAt {
     const uint32_t *w;
     int32_t r;
 };
-__device__ __forceinline__ uint64_t walk_bases(const WalkAt &a, int32_t t, bool left)
-{
-    const int32_t p = left ? a.r - t - 32 : a.r + t;
-    const uint32_t *w = a.w + (p >> 4);
-    const uint32_t v0 = w[0], v1 = w[1], v2 = w[2];
-    const uint32_t sh = 32u - ((uint32_t)(p & 15) << 1);
-    const uint32_t hi = (uint32_t)((((uint64_t)v0 << 32) | v1) >> sh);
-    const uint32_t lo = (uint32_t)((((uint64_t)v1 << 32) | v2) >> sh);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ void xdrop_xw(const WalkAt &q, const WalkAt &b, int32_t t, bool left,
                                          uint32_t (&x)[2])
 {
-    const uint64_t v = walk_bases(q, t, left) ^ walk_bases(b, t, left);
-    const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
+    // from the word of the base before, as bases64 reads
+    const int32_t o = left ? -t - 33 : t - 1;
+    const int32_t pq = q.r + o, pb = b.r + o;
+    const uint32_t *u = q.w + (pq >> 4), *v = b.w + (pb >> 4);
+    const uint32_t u0 = u[0], u1 = u[1], u2 = u[2], v0 = v[0], v1 = v[1], v2 = v[2];
+    const uint32_t su = ~(uint32_t)pq << 1, sv = ~(uint32_t)pb << 1;
+    const uint32_t hi = __builtin_amdgcn_alignbit(u0, u1, su) ^ __builtin_amdgcn_alignbit(v0, v1, sv);
+    const uint32_t lo = __builtin_amdgcn_alignbit(u1, u2, su) ^ __builtin_amdgcn_alignbit(v1, v2, sv);
     x[0] = left ? lo : __brev(hi);
     x[1] = left ? hi : __brev(lo);
 }
@@ -3629,14 +3788,16 @@ __device__ __forceinline__ bool xdrop_chunk(uint32_t x, int32_t T, int32_t match
 
 // Eight steps of a walk by table: entry f (bit i set: step i is a mismatch) holds the
 // steps' sum, the highest sum after any of them (0 when none is above the start) and
-// the first step there, the lowest sum, and the largest fall from a sum (the start's
-// included) to a later one.  A walk dd below its best drops within the eight steps
-// exactly when the fall or dd less the lowest sum exceeds X.
-//   bits 31:24 sum (signed), 23:18 highest, 17:14 its step, 13:7 -lowest, 6:0 fall
-// Scores up to 7 and 15 fit the fields.
-constexpr int32_t kStepMatch = 7, kStepMismatch = 15;
+// the first step there, and how far the lowest sum is below the start; or, when the
+// steps fall more than X from a sum (the start's included) to a later one, kStepFall,
+// more than any such X.  A walk dd below its best drops within the eight steps
+// exactly when dd and that value together exceed X.
+//   bits 31:24 sum (signed), 23:18 highest, 17:14 its step, 13:0 lowest
+// Scores up to 7 and 15 fit the fields (a fall is 120 at most).
+constexpr int32_t kStepMatch = 7, kStepMismatch = 15, kStepFall = 121;
 
-__device__ __forceinline__ uint32_t step_entry(uint32_t f, int32_t match, int32_t mismatch)
+__device__ __forceinline__ uint32_t step_entry(uint32_t f, int32_t match, int32_t mismatch,
+                                               int32_t X)
 {
     int32_t r = 0, hi = 0, at = 0, lo = 0, fall = 0;
     for (int32_t i = 0; i < 8; ++i) {
@@ -3649,7 +3810,7 @@ __device__ __forceinline__ uint32_t step_entry(uint32_t f, int32_t match, int32_
         fall = max(fall, hi - r);
     }
     return ((uint32_t)r << 24) | ((uint32_t)hi << 18) | ((uint32_t)at << 14) |
-           ((uint32_t)-lo << 7) | (uint32_t)fall;
+           (uint32_t)(fall > X ? kStepFall : -lo);
 }
 
 // Steps t .. t + 7 with mismatch flags f.  Returns true when the walk dropped.
@@ -3658,7 +3819,7 @@ __device__ __forceinline__ bool xdrop_steps(uint32_t e, uint32_t f, int32_t matc
                                             int32_t &bl)
 {
     const int32_t hi = (int32_t)((e >> 18) & 63u);
-    const bool drop = max(dd + (int32_t)((e >> 7) & 127u), (int32_t)(e & 127u)) > X;
+    const bool drop = dd + (int32_t)(e & 0x3FFFu) > X;
     if (drop && hi > dd) {  // a new best and a drop in the same eight steps: step by step
         int32_t r = 0, best = dd;
         for (int32_t i = 0; i < 8; ++i) {
@@ -3676,15 +3837,13 @@ __device__ __forceinline__ bool xdrop_steps(uint32_t e, uint32_t f, int32_t matc
     return drop;
 }
 
-// 16 steps of a walk from t by two table entries; x: their XOR word.  Steps past the
-// walk's end T count as mismatches, which move no best.  True when the walk dropped.
-__device__ __forceinline__ bool xdrop_table(const uint32_t *__restrict__ tab, uint32_t x, int32_t T,
+// 16 steps of a walk from t by two table entries; x: their XOR word.  True when the
+// walk dropped.
+__device__ __forceinline__ bool xdrop_table(const uint32_t *__restrict__ tab, uint32_t x,
                                             int32_t match, int32_t mismatch, int32_t X, int32_t t,
                                             int32_t &dd, int32_t &bl)
 {
-    uint32_t f = x | (x >> 1);  // one flag per step, gathered to bits 7:0 and 23:16
-    if (T - t < 16) f |= ~0u << (2 * max(T - t, 0));
-    f &= 0x55555555u;
+    uint32_t f = (x | (x >> 1)) & 0x55555555u;  // one flag per step, gathered to bits 7:0, 23:16
     f = (f | (f >> 1)) & 0x33333333u;
     f = (f | (f >> 2)) & 0x0F0F0F0Fu;
     f |= f >> 4;
@@ -3707,7 +3866,7 @@ __device__ __forceinline__ bool xdrop_table(const uint32_t *__restrict__ tab, ui
 // the chip; each writes its own part of the box.  Else a lane walks right, then left,
 // and writes the box whole (a lane per side wrote 56 bytes per 32-byte box).
 // Bound by VALU instructions (walks among repeats take some 50 steps): 3.4 G runs in
-// 88 ms, at 80% of the issue rate, against 182 with 16 steps a round, a refill in every
+// 83 ms, at 80% of the issue rate, against 182 with 16 steps a round, a refill in every
 // round and a loop over the mismatches.
 // TAB: steps go by table entries, eight at a time; a loop over the mismatches ran as
 // long as its lane with the most.
@@ -3734,7 +3893,7 @@ __global__ __launch_bounds__(kBlock) void k_extend(const Cand *__restrict__ cand
     if ((uint64_t)blockIdx.x * (kBlock / 64) * per >= items) return;  // nothing for this block
     __shared__ uint32_t s_tab[TAB ? 256 : 1];
     if (TAB) {
-        s_tab[threadIdx.x] = step_entry(threadIdx.x, match, mismatch);
+        s_tab[threadIdx.x] = step_entry(threadIdx.x, match, mismatch, X);
         __syncthreads();
     }
     const int lane = threadIdx.x & 63;
@@ -3822,8 +3981,14 @@ __global__ __launch_bounds__(kBlock) void k_extend(const Cand *__restrict__ cand
             xdrop_xw(qw, bw, t, left, x);
             bool done;
             if (TAB) {
-                done = xdrop_table(s_tab, x[0], T, match, mismatch, X, t, dd, bl) ||
-                       xdrop_table(s_tab, x[1], T, match, mismatch, X, t + 16, dd, bl);
+                if (T - t < 32) {
+                    // steps past the walk's end count as mismatches, which move no best
+                    const int32_t v = T - t;
+                    if (v < 16) x[0] |= ~0u << (2 * v);
+                    x[1] |= v <= 16 ? ~0u : ~0u << (2 * (v - 16));
+                }
+                done = xdrop_table(s_tab, x[0], match, mismatch, X, t, dd, bl) ||
+                       xdrop_table(s_tab, x[1], match, mismatch, X, t + 16, dd, bl);
                 t += 32;
             } else {
                 done = xdrop_chunk(x[0], T, match, mismatch, X, t, dd, bl) || t >= T ||
@@ -3903,13 +4068,11 @@ void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32
     XWalk *queue = reinterpret_cast<XWalk *>(static_cast<char *>(queue_mem) + 256);
     const uint32_t qcap = (uint32_t)((extend_queue_bytes(nmax) - 256) / sizeof(XWalk));
     if (!count_cleared) launch_fill_u32(qcount, 1, 0u, st);
-    // one wave per 64 walks up to 8 waves per SIMD on every CU; beyond that each
-    // wave's range grows
     // a lane per side until the runs alone give every lane of the chip one
     const bool split = ctl || n < (1u << 19);
     const uint64_t items = split ? 2ull * n : n;
     const uint32_t nb = ctl ? kStrideGrid
-                            : (uint32_t)std::min<uint64_t>((items + kBlock - 1) / kBlock, 8192);
+                            : (uint32_t)std::min<uint64_t>((items + kBlock - 1) / kBlock, kWalkGrid);
     const int32_t steps = std::max(lane_steps, 0);
     const bool tab = match <= kStepMatch && mismatch <= kStepMismatch;
     auto k = tab ? (split ? k_extend<true, true> : k_extend<true, false>)
