@@ -4468,14 +4468,21 @@ __global__ void k_merge_sweep(const Box *__restrict__ s, uint32_t n, Box *__rest
 // are sorted in LDS (radix passes) and the owned groups are then swept from their
 // keys with the result of k_merge_sweep's one-thread sweep, in parallel over the
 // window (merge_sweep_parallel) or, when that has not settled, one thread per
-// group: merged boxes from the group's first position, the rest marked empty.  A group that may not fit (the last one the
-// block owns, when no other group starts before the block's reach) is recorded
+// group: merged boxes from the group's first position, the rest marked empty (by
+// their length records alone where there are any).  A group that may not fit (the last
+// one the block owns, when no other group starts before the block's reach) is recorded
 // in big[1 ..] as (first, end) and left to the global sort; big[0] counts them.
-constexpr uint32_t kMergeWin = 1024;
-constexpr uint32_t kMergeSpan = 2 * kMergeWin;
+// Bound by VALU instructions: 3.4 G runs in 107 ms, 39 of them in the sort (132 with
+// 512 keys to a wave, two waves of the four idle, and a 4-byte mark in every slot).
+// W is short of 1,024, so that a window's boxes (W more or less a group) seldom take
+// a fifth round of the block's threads.
+constexpr uint32_t kMergeWin = 960;
+constexpr uint32_t kMergeSpan = 2048;
+static_assert(kMergeWin % 64 == 0 && kMergeSpan >= 2 * kMergeWin, "whole waves of positions");
 
 // Stable LSD radix sort of the m <= kMergeSpan keys in s_key (LDS), 8 bits per
-// pass, by a 256-thread block.  Wave w holds keys [512 w, 512 w + 512) in
+// pass, by a 256-thread block.  The keys are dealt to the four waves evenly (a window
+// holds about half of what it may; with 512 keys to a wave two waves had none), in
 // registers, 64 per round; a key's rank among equal digits of its wave comes from
 // eight ballots (as the global passes rank a tile), the block scans the per-wave
 // digit counts, and the keys are written to their places in s_key and read back
@@ -4489,10 +4496,13 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
     __shared__ uint16_t s_wc[kBlock / 64][kRadix];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
+    const int rounds = (int)((m + kBlock - 1) / kBlock);
+    const uint32_t first = (uint32_t)(w * rounds * 64 + lane);  // the lane's first key
     uint64_t k[kRounds];
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
-        const uint32_t idx = w * kPerWave + r * 64 + lane;
+        if (r >= rounds) break;
+        const uint32_t idx = first + r * 64;
         k[r] = idx < m ? s_key[idx] : 0ull;
     }
     for (int shift = lo; shift < 64; shift += kRadixBits) {
@@ -4503,7 +4513,8 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
         uint32_t rank[kRounds];
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t idx = w * kPerWave + r * 64 + lane;
+            if (r >= rounds) break;
+            const uint32_t idx = first + r * 64;
             const bool ok = idx < m;
             const uint32_t d = (uint32_t)(k[r] >> shift) & (kRadix - 1);
             uint64_t peers = __ballot(ok);
@@ -4537,7 +4548,8 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t idx = w * kPerWave + r * 64 + lane;
+            if (r >= rounds) break;
+            const uint32_t idx = first + r * 64;
             if (idx < m) {
                 const uint32_t d = (uint32_t)(k[r] >> shift) & (kRadix - 1);
                 s_key[s_wc[w][d] + rank[r]] = k[r];
@@ -4546,7 +4558,8 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t idx = w * kPerWave + r * 64 + lane;
+            if (r >= rounds) break;
+            const uint32_t idx = first + r * 64;
             if (idx < m) k[r] = s_key[idx];
         }
     }
@@ -4619,45 +4632,87 @@ __device__ __forceinline__ bool magg_takes(const MAgg &cur, int32_t qs, int32_t 
     return qs < cur.qe && ds < cur.de && cur.ds < de;
 }
 
-__device__ __forceinline__ MAgg magg_shfl_up(const MAgg &a, int o)
+// The part of a union that the sweep's test looks at (all that the rounds need).
+struct MTest {
+    int32_t qe, ds, de;
+};
+__device__ __forceinline__ MTest mtest(const MAgg &a) { return MTest{a.qe, a.ds, a.de}; }
+__device__ __forceinline__ MTest magg_join(const MTest &a, const MTest &b)
 {
-    return MAgg{__shfl_up(a.qs, o, 64), __shfl_up(a.qe, o, 64), __shfl_up(a.ds, o, 64),
-                __shfl_up(a.de, o, 64), __shfl_up(a.dmin, o, 64), __shfl_up(a.dmax, o, 64)};
+    return MTest{max(a.qe, b.qe), min(a.ds, b.ds), max(a.de, b.de)};
+}
+__device__ __forceinline__ bool magg_takes(const MTest &cur, int32_t qs, int32_t ds, int32_t de)
+{
+    return qs < cur.qe && ds < cur.de && cur.ds < de;
+}
+template <typename T>
+__device__ __forceinline__ T magg_empty();
+template <>
+__device__ __forceinline__ MAgg magg_empty<MAgg>()
+{
+    return magg_none();
+}
+template <>
+__device__ __forceinline__ MTest magg_empty<MTest>()
+{
+    return MTest{INT32_MIN, INT32_MAX, INT32_MIN};
+}
+
+// Lanes' values moved up by a DPP pattern, the empty union where none arrives.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t dpp_up(int32_t none, int32_t x)
+{
+    return __builtin_amdgcn_update_dpp(none, x, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ MAgg dpp_up(const MAgg &a)
+{
+    const MAgg n = magg_none();
+    return MAgg{dpp_up<CTRL, ROWS>(n.qs, a.qs),     dpp_up<CTRL, ROWS>(n.qe, a.qe),
+                dpp_up<CTRL, ROWS>(n.ds, a.ds),     dpp_up<CTRL, ROWS>(n.de, a.de),
+                dpp_up<CTRL, ROWS>(n.dmin, a.dmin), dpp_up<CTRL, ROWS>(n.dmax, a.dmax)};
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ MTest dpp_up(const MTest &a)
+{
+    const MTest n = magg_empty<MTest>();
+    return MTest{dpp_up<CTRL, ROWS>(n.qe, a.qe), dpp_up<CTRL, ROWS>(n.ds, a.ds),
+                 dpp_up<CTRL, ROWS>(n.de, a.de)};
 }
 
 // Exclusive segmented scan over the block's threads: thread t holds (f, a) = (a
 // segment starts in its items, union of its items from its last start on); it
 // receives the union over the items before its own back to the last start (the
 // union of the segment its first item continues).  Pairs combine as (f1, a1) then
-// (f2, a2) -> (f1 | f2, f2 ? a2 : a1 + a2).
-__device__ MAgg seg_excl_union(bool f, const MAgg &a, bool *start_before = nullptr)
+// (f2, a2) -> (f1 | f2, f2 ? a2 : a1 + a2); within a wave by DPP (row shifts, then
+// the last lane of a row to the next one and of the first half to the second), so
+// no step goes through LDS.  Every thread of the block calls it.
+template <typename T>
+__device__ T seg_excl_union(bool f, const T &a, bool *start_before = nullptr)
 {
     __shared__ int32_t s_wf[kBlock / 64];
-    __shared__ MAgg s_wa[kBlock / 64];
+    __shared__ T s_wa[kBlock / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int32_t fi = f ? 1 : 0;
-    MAgg x = a;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int32_t yf = __shfl_up(fi, o, 64);
-        const MAgg y = magg_shfl_up(x, o);
-        if (lane >= o) {
-            if (!fi) x = magg_join(y, x);
-            fi |= yf;
-        }
-    }
+    T x = a;
+    auto step = [&](int32_t yf, const T &y) {
+        if (!fi) x = magg_join(y, x);
+        fi |= yf;
+    };
+    step(dpp_up<0x111, 0xf>(0, fi), dpp_up<0x111, 0xf>(x));  // row_shr:1
+    step(dpp_up<0x112, 0xf>(0, fi), dpp_up<0x112, 0xf>(x));
+    step(dpp_up<0x114, 0xf>(0, fi), dpp_up<0x114, 0xf>(x));
+    step(dpp_up<0x118, 0xf>(0, fi), dpp_up<0x118, 0xf>(x));
+    step(dpp_up<0x142, 0xa>(0, fi), dpp_up<0x142, 0xa>(x));  // row_bcast:15
+    step(dpp_up<0x143, 0xc>(0, fi), dpp_up<0x143, 0xc>(x));  // row_bcast:31
     if (lane == 63) {
         s_wf[w] = fi;
         s_wa[w] = x;
     }
-    int32_t ef = __shfl_up(fi, 1, 64);
-    MAgg ex = magg_shfl_up(x, 1);
-    if (lane == 0) {
-        ef = 0;
-        ex = magg_none();
-    }
+    const int32_t ef = dpp_up<0x138, 0xf>(0, fi);  // wave_shr:1
+    const T ex = dpp_up<0x138, 0xf>(x);
     __syncthreads();
-    MAgg pre = magg_none();
+    T pre = magg_empty<T>();
     int32_t pf = 0;
     for (int i = 0; i < w; ++i) {
         pre = s_wf[i] ? s_wa[i] : magg_join(pre, s_wa[i]);
@@ -4669,8 +4724,8 @@ __device__ MAgg seg_excl_union(bool f, const MAgg &a, bool *start_before = nullp
 }
 
 // Parallel form of the sweep of a window's owned groups (keys [0, m) sorted in
-// s_key, group g's keys [s_start[g] - o, s_start[g + 1] - o)).  Thread t takes keys
-// [8 t, 8 t + 8).  A key starts a merged box when it starts its group or the sweep
+// s_key, group g's keys [s_start[g] - o, s_start[g + 1] - o)).  Each thread takes the
+// same number of consecutive keys, eight at most.  A key starts a merged box when it starts its group or the sweep
 // does not join it to the union before it.  Tentative starts: group starts and
 // the keys that do not join the one box before them (a box that joins its
 // predecessor joins any union holding it).  Each round scans the unions of the
@@ -4687,10 +4742,11 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
                                      const Box *__restrict__ in, Box *__restrict__ out,
                                      uint32_t at, int rounds, LenSel ls)
 {
-    constexpr int kPer = kMergeSpan / kBlock;  // 8 keys per thread
+    constexpr int kPer = kMergeSpan / kBlock;
+    const int per = (int)((m + kBlock - 1) / kBlock);
     const uint64_t mbl = (1ull << bl) - 1ull, mbd = (1ull << bd) - 1ull;
     const int gsh = 2 * bl + bd;
-    const uint32_t j0 = threadIdx.x * kPer;
+    const uint32_t j0 = threadIdx.x * (uint32_t)per;
     // key j's box (read from LDS on each pass rather than held in registers)
     auto box_of = [&](uint64_t key) {
         const int32_t qe = (int32_t)(key & mbl);
@@ -4704,7 +4760,7 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
             const uint32_t j = j0 + r;
-            if (j >= m) break;
+            if (r >= per || j >= m) break;
             const uint64_t key = s_key[j];
             const bool gs = j == 0 || (prev >> gsh) != (key >> gsh);
             bool st = gs;
@@ -4718,15 +4774,15 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
             prev = key;
         }
     }
-    MAgg carry;
     for (int round = 0;; ++round) {
         if (round == rounds) return false;
         bool sf = false;
-        MAgg sa = magg_none();
+        MTest sa = magg_empty<MTest>();
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
+            if (r >= per) break;
             if (!((V >> r) & 1u)) continue;
-            const MAgg b = box_of(s_key[j0 + r]);
+            const MTest b = mtest(box_of(s_key[j0 + r]));
             if ((F >> r) & 1u) {
                 sf = true;
                 sa = b;
@@ -4734,11 +4790,11 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
                 sa = magg_join(sa, b);
             }
         }
-        carry = seg_excl_union(sf, sa);
-        MAgg run = carry;
+        MTest run = seg_excl_union(sf, sa);
         bool changed = false;
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
+            if (r >= per) break;
             if (!((V >> r) & 1u)) continue;
             const uint32_t bit = 1u << r;
             const MAgg b = box_of(s_key[j0 + r]);
@@ -4746,9 +4802,24 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
                 F &= ~bit;
                 changed = true;
             }
-            run = (F & bit) ? b : magg_join(run, b);
+            run = (F & bit) ? mtest(b) : magg_join(run, mtest(b));
         }
         if (!__syncthreads_or(changed)) break;
+    }
+    // the settled segments' whole unions
+    MAgg carry = magg_none();
+    {
+        bool sf = false;
+#pragma unroll
+        for (int r = 0; r < kPer; ++r) {
+            if (r >= per) break;
+            if (!((V >> r) & 1u)) continue;
+            const MAgg b = box_of(s_key[j0 + r]);
+            const bool st = (F >> r) & 1u;
+            carry = st ? b : magg_join(carry, b);
+            sf = sf || st;
+        }
+        carry = seg_excl_union(sf, carry);
     }
     // merged box k of group g goes to the group's k-th position: k is its rank
     // among the group's starts, P(j) - P(first key of g) with P(j) the starts in
@@ -4764,6 +4835,7 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
     MAgg run = carry;
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
+        if (r >= per) break;
         if (!((V >> r) & 1u)) continue;
         const uint32_t j = j0 + r;
         const uint64_t key = s_key[j];
@@ -4774,10 +4846,11 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
         const uint32_t p0 = s_pg[g];
         const uint32_t nseg = (g + 1 < nw ? (uint32_t)s_pg[g + 1] - 1u : tot) - p0 + 1u;
         if (j - first >= nseg) {
-            out[at + j].q = -1;
+            // with length records only the records tell the slot empty
             if (ls.binq) ls.binq[at + j] = kNoBin;
+            else out[at + j].q = -1;
         }
-        const bool last = j + 1 >= m || (r + 1 < kPer ? ((F >> (r + 1)) & 1u) != 0
+        const bool last = j + 1 >= m || (r + 1 < per ? ((F >> (r + 1)) & 1u) != 0
                                                         : (s_f8[threadIdx.x + 1] & 1u) != 0);
         if (!last) continue;
         const uint32_t rank = before + __popc(F & ((2u << r) - 1u)) - p0;
@@ -4799,7 +4872,6 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
     __shared__ uint16_t s_start[kMergeSpan + 1];
     __shared__ uint16_t s_rank[kMergeSpan];
     __shared__ uint32_t s_wc[kBlock / 64];
-    __shared__ uint32_t s_nw;
     __shared__ uint64_t s_vary[2];
     const uint32_t base = blockIdx.x * kMergeWin;
     if (base >= n) return;
@@ -4829,6 +4901,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
         for (int w = 0; w < kBlock / 64; ++w) {
             if (w < wv) before += s_wc[w];
             round += s_wc[w];
+            if (u * kBlock + w * 64 < kMergeWin) nwin += s_wc[w];  // starts below kMergeWin
         }
         const uint32_t at = before + (uint32_t)__popcll(m & below);
         if (f) s_start[at] = (uint16_t)r;
@@ -4836,18 +4909,12 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
         // start belong to an earlier block's group and are never used)
         if (r < R) s_rank[r] = (uint16_t)(at + (f ? 1u : 0u) - 1u);
         ns += round;
-        if (u < kMergeWin / kBlock) nwin = ns;  // starts below kMergeWin
         __syncthreads();
-        if (u + 1 >= kMergeWin / kBlock && ns > nwin) break;
+        if ((u + 1) * kBlock >= kMergeWin && ns > nwin) break;
     }
-    if (threadIdx.x == 0) {
-        s_start[ns] = (uint16_t)R;
-        uint32_t nw = 0;  // owned groups: starts below kMergeWin
-        while (nw < ns && s_start[nw] < kMergeWin) ++nw;
-        s_nw = nw;
-    }
+    if (threadIdx.x == 0) s_start[ns] = (uint16_t)R;
     __syncthreads();
-    uint32_t nw = s_nw;
+    uint32_t nw = nwin;  // owned groups: starts below kMergeWin
     if (nw == 0) return;
     if (nw == ns && lim < n) {
         // the last owned group reaches past the range: find its end, leave it to
@@ -4956,8 +5023,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
         }
         emit(w++, cur);
         for (; w < j1; ++w) {
-            out[base + o + w].q = -1;
             if (ls.binq) ls.binq[base + o + w] = kNoBin;
+            else out[base + o + w].q = -1;
         }
     }
 }
