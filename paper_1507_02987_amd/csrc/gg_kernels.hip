@@ -6147,20 +6147,171 @@ void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_o
 }
 
 // ------------------------------------------------------------------ traceback
-// The path of each reported alignment (one wave per hit, grid-stride): the banded
-// DP recomputed over the hit's rectangle [q_start, q_end) x [d_start, d_end) in the
-// band |j - i - cc| <= W around the hit's band centre, row by row.  Row i's band
-// slot t is column j = i + cc - W + t; a lane holds slots lane and lane + 64.  The
-// horizontal gap of a row is a prefix maximum over its slots: E(t) = max over
-// t' < t of H'(t') - o1 - ext (t - 1 - t'), with H' = max(0, G, F) (a gap opened
-// after a gap never beats extending it when gap_open >= 0), then H = max(H', E).
-// Each cell stores 4 bits: how H was reached (0 diagonal, 1 horizontal gap, 2
-// vertical gap, 3 diagonal from a non-positive predecessor or H <= 0) and whether
-// each gap was opened here (ties open).  Lane 0 then walks back from the end cell
-// with the same priorities, rescoring as it goes, and writes the operations
-// right-aligned in the hit's slot.  status[h] = 0 when the walk ends on the
-// rectangle's first cell with the hit's score, 1 otherwise (not an alignment of
-// this query, bank and scoring).
+// One cell of the recurrence (sw_cell) and its four direction bits: how H was reached
+// (0 diagonal, 1 gap in the query, 2 gap in the bank, 3 diagonal from a predecessor <= 0:
+// the path's first pair) and whether each gap was opened here (ties open).  The bits
+// of a cell with H <= 0 are never read: a path's cells in state 0 have H > 0, and a gap
+// with a value > 0 opens from such a cell.
+struct DirCell {
+    int32_t H, E, F;
+    uint32_t dir;
+};
+
+__device__ __forceinline__ DirCell dir_cell(int32_t hl, int32_t el, int32_t hu, int32_t fu,
+                                            int32_t hd, int32_t sub, int32_t o1, int32_t ext)
+{
+    DirCell c;
+    const int32_t eo = hl - o1, ee = el - ext, fo = hu - o1, fe = fu - ext;
+    c.E = max(eo, ee);
+    c.F = max(fo, fe);
+    const int32_t g = hd + sub;
+    c.H = max(max(g, 0), max(c.E, c.F));
+    c.dir = (g == c.H ? (hd > 0 ? 0u : 3u) : c.E == c.H ? 1u : 2u) | (eo >= ee ? 4u : 0u) |
+            (fo >= fe ? 8u : 0u);
+    return c;
+}
+
+// Where the directions of row i, lane u (its slots 2u and 2u + 1) lie in a hit's 64 R
+// bytes: the lanes of one step hold rows i, i - 1, ..., so rows skewed by the lane put
+// a step's bytes side by side.
+__device__ __forceinline__ size_t dir_at(int32_t i, int32_t u, int32_t R)
+{
+    return (size_t)((uint32_t)(i + u) % (uint32_t)R) * 64 + (uint32_t)u;
+}
+
+// The directions of every band cell of an R x C rectangle, swept over anti-diagonals in
+// pairs exactly as bsw_sweep does (slots, borders and minus infinities are its rule);
+// qbase(i), dbase(j): the codes of a row and a column of the rectangle.  Returns H of the
+// rectangle's last cell (0 in lanes that do not hold it).
+template <typename Q, typename D>
+__device__ int32_t dir_sweep(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0, int32_t W,
+                             int32_t match, int32_t mismatch, int32_t o1, int32_t ext,
+                             int32_t lane, uint8_t *__restrict__ dirs)
+{
+    const int32_t clo = max(c0 - W, -(R - 1)), chi = min(c0 + W, C - 1);
+    const int32_t cs = min(max(C - R, clo), chi);
+    const int64_t a_lo = clo <= 0 && chi >= 0 ? 0 : clo > 0 ? clo : -chi;
+    const int64_t a_hi = cs <= C - R ? 2 * (int64_t)(R - 1) + cs : 2 * (int64_t)(C - 1) - cs;
+    const int64_t a0 = a_lo - ((a_lo - c0 + W) & 1);
+    const uint32_t pairs = (uint32_t)((a_hi - a0) / 2) + 1u;
+    const int32_t tX = 2 * lane;
+    const bool laneX = tX <= 2 * W, laneY = tX < 2 * W;
+    const int32_t dX = min(tX, 2 * W) - W + c0;  // the lane's X diagonal j - i
+    int32_t i = (int32_t)((a0 - dX) >> 1), j = i + dX;
+    uint32_t row = (uint32_t)((a0 + W - c0) >> 1) % (uint32_t)R;  // (i + lane) % R of band lanes
+    int32_t HX = i < 1 || j < 1 ? 0 : kNegInf, EX = kNegInf, FX = kNegInf;
+    int32_t HY = i < 1 || j < 0 ? 0 : kNegInf, EY = kNegInf, FY = kNegInf;
+    int32_t end = 0;
+    auto row_base = [&](int32_t x) { return qbase(min(max(x, 0), R - 1)); };
+    auto col_base = [&](int32_t x) { return dbase(min(max(x, 0), C - 1)); };
+    int32_t nq = row_base(i), nx = col_base(j), ny = col_base(j + 1);  // read one pair ahead
+    int32_t edge = laneX ? max(0, max(-i, -j)) : 0;  // pairs with cells before the rectangle
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) edge = max(edge, __shfl_xor(edge, off, 64));
+    auto pair = [&](auto edge_tag) {
+        constexpr bool EDGE = decltype(edge_tag)::value;
+        const int32_t qb = nq, bx = nx, by = ny;
+        nq = row_base(i + 1);
+        nx = by;  // the next pair's X column is this pair's Y column
+        ny = col_base(j + 2);
+        const bool rowin = (uint32_t)i < (uint32_t)R;
+        int32_t hl = from_lower_lane(HY), el = from_lower_lane(EY);
+        if (lane == 0) {
+            hl = j == 0 ? 0 : kNegInf;
+            el = kNegInf;
+        }
+        const DirCell x =
+            dir_cell(hl, el, HY, FY, HX, qb == bx ? match : -mismatch, o1, ext);
+        const bool bdx = EDGE && (i < 0 || j < 0);
+        HX = bdx ? 0 : x.H;
+        EX = bdx ? kNegInf : x.E;
+        FX = bdx ? kNegInf : x.F;
+        const DirCell y = dir_cell(HX, EX, from_upper_lane(HX), from_upper_lane(FX), HY,
+                                   qb == by ? match : -mismatch, o1, ext);
+        const bool bdy = EDGE && (i < 0 || j + 1 < 0);
+        HY = bdy ? 0 : laneY ? y.H : kNegInf;
+        EY = bdy ? kNegInf : y.E;
+        FY = bdy || !laneY ? kNegInf : y.F;
+        if (laneX && rowin) dirs[(size_t)row * 64 + (uint32_t)lane] = (uint8_t)(x.dir | y.dir << 4);
+        if (i == R - 1) {
+            if (laneX && j == C - 1) end = x.H;
+            if (laneY && j + 1 == C - 1) end = y.H;
+        }
+        row = row + 1u == (uint32_t)R ? 0u : row + 1u;
+        ++i;
+        ++j;
+    };
+    uint32_t p = 0;
+    for (const uint32_t pe = min(pairs, (uint32_t)edge + 1u); p < pe; ++p) pair(std::true_type{});
+    for (; p < pairs; ++p) pair(std::false_type{});
+    return end;
+}
+
+// The walk back from the rectangle's last cell, by the whole wave: the lanes look at
+// the next 64 cells of the state the walk is in (along the diagonal, the row or the
+// column) and the operations up to the first cell that changes it are written at once,
+// right-aligned in [0, R + C) of ops.  Returns their number, or -1 when the walk does not
+// end on the rectangle's first cell with the hit's score.
+template <typename Q, typename D>
+__device__ int32_t dir_walk(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0, int32_t W,
+                            int32_t match, int32_t mismatch, int32_t o1, int32_t ext,
+                            int32_t score, int32_t lane, const uint8_t *dirs, char *ops)
+{
+    char *const last = ops + (int64_t)R + C - 1;
+    int32_t i = R - 1, j = C - 1, state = 0, sum = 0;
+    int64_t k = 0;
+    for (;;) {
+        const int32_t t = j - (i + c0 - W);
+        if (i < 0 || j < 0 || t < 0 || t > 2 * W) return -1;
+        const int32_t ci = state == 1 ? i : i - lane, cj = state == 2 ? j : j - lane;
+        const int32_t ct = state == 0 ? t : state == 1 ? t - lane : t + lane;
+        const bool ok = ci >= 0 && cj >= 0 && ct >= 0 && ct <= 2 * W;
+        uint32_t dir = 0;
+        if (ok) dir = dirs[dir_at(ci, ct >> 1, R)] >> (4 * (ct & 1)) & 15u;
+        // lanes that end the stretch: by leaving the band, by the path's first pair or a
+        // gap's end (state 0), or by a gap's opening
+        const bool stop = !ok || (state == 0 ? (dir & 3u) != 0u
+                                             : (dir & (state == 1 ? 4u : 8u)) != 0u);
+        const uint64_t sm = __ballot(stop);
+        const int32_t f = sm ? __ffsll((unsigned long long)sm) - 1 : 64;
+        const bool lost = f < 64 && !((__ballot(ok) >> (f & 63)) & 1ull);
+        const uint32_t fd = (uint32_t)__builtin_amdgcn_readlane((int32_t)dir, f & 63);
+        if (lost) return -1;
+        if (state == 0) {
+            // lane f's own pair belongs to the path only where the path starts with it
+            const int32_t n = f + (f < 64 && (fd & 3u) == 3u ? 1 : 0);
+            const bool in = lane < n;
+            const bool eq = in && qbase(max(ci, 0)) == dbase(max(cj, 0));
+            if (in) last[-(k + lane)] = eq ? '=' : 'X';
+            const int32_t same = (int32_t)__popcll(__ballot(eq));
+            sum += same * match - (n - same) * mismatch;
+            k += n;
+            if (n > f) return i == f && j == f && sum == score ? (int32_t)k : -1;
+            i -= f;
+            j -= f;
+            if (f < 64) state = (int32_t)(fd & 3u);
+        } else {
+            const int32_t n = min(f + 1, 64);
+            if (lane < n) last[-(k + lane)] = state == 1 ? 'D' : 'I';
+            sum -= f < 64 ? f * ext + o1 : 64 * ext;
+            k += n;
+            if (state == 1) j -= n;
+            else i -= n;
+            if (f < 64) state = 0;
+        }
+    }
+}
+
+// The path of each reported alignment (one wave per hit, grid-stride): the banded DP
+// recomputed over the hit's rectangle [q_start, q_end) x [d_start, d_end) in the band
+// |j - i - cc| <= W around the hit's band centre, four direction bits a cell, then walked
+// back with the search's priorities and rescored on the way.  status[h] = 0 when the walk
+// ends on the rectangle's first cell with the hit's score, 1 otherwise (not an alignment
+// of this query, bank and scoring).  Both parts are one serial chain per hit.  The sweep
+// takes a pair of anti-diagonals a step, its lanes' values handed over by DPP, where a row
+// a step needed a 6-step prefix maximum through LDS; and the walk takes a stretch of up to
+// 64 cells a step, where a cell a step waited for its own load.  The hits of a query of
+// 3,000 bases: 64 us, 389 a row and a cell a step.
 __global__ __launch_bounds__(64) void k_traceback(
     const int32_t *__restrict__ hits, int32_t n, const uint8_t *__restrict__ qascii, int64_t qlen,
     const uint32_t *__restrict__ dbw, const int64_t *__restrict__ seq_start, int32_t n_seqs,
@@ -6169,189 +6320,57 @@ __global__ __launch_bounds__(64) void k_traceback(
     const int64_t *__restrict__ ops_off, char *__restrict__ ops, int32_t *__restrict__ ops_len,
     int32_t *__restrict__ status)
 {
-    constexpr int32_t NEG = kNegInf;
-    constexpr int32_t LOW = -(1 << 30) - (1 << 28);  // below every score a scan can see
+    __shared__ uint8_t s_q[kBswStage], s_d[kBswStage];
     const int32_t lane = threadIdx.x;
-    __shared__ int32_t s_hend, s_bad;
     for (int32_t h = blockIdx.x; h < n; h += gridDim.x) {
         const int32_t *hr = hits + (size_t)h * kHitInts;
         const int32_t s = hr[0], score = hr[1], qs = hr[2], qe = hr[3], ds = hr[4], de = hr[5];
         const int32_t d0 = hr[11];
         const int32_t R = qe - qs, C = de - ds, cc = d0 - (ds - qs);
-        if (lane == 0) {
-            s_hend = NEG;
-            s_bad = 0;
-        }
-        __syncthreads();
         // the host checked the query span and the sequence id; the bank span is
         // checked here, before any base is read
         const bool shape_ok = s >= 0 && s < n_seqs && qs >= 0 && R > 0 && (int64_t)qe <= qlen &&
                               ds >= 0 && C > 0 &&
                               (int64_t)de <= seq_start[s + 1] - seq_start[s] && score > 0 &&
                               (C - 1) - (R - 1) - cc <= W && (C - 1) - (R - 1) - cc >= -W;
-        if (!shape_ok) {
-            if (lane == 0) {
-                ops_len[h] = 0;
-                status[h] = 1;
+        int32_t len = -1;
+        if (shape_ok) {
+            const uint8_t *qp = qascii + qs;
+            const int64_t db0 = seq_start[s] + ds;
+            uint8_t *dh = dirs + dir_off[h];
+            const bool staged = R <= kBswStage && C <= kBswStage;
+            bool bad = false;
+            for (int32_t x = lane; x < R; x += 64) {
+                const int32_t c = base_code(qp[x]);
+                bad |= c < 0;
+                if (staged) s_q[x] = (uint8_t)c;
             }
+            if (staged)
+                for (int32_t x = lane; x < C; x += 64) s_d[x] = (uint8_t)db_base(dbw, db0 + x);
             __syncthreads();
-            continue;
+            auto trace = [&](auto qbase, auto dbase) {
+                const int32_t end = dir_sweep(qbase, dbase, R, C, cc, W, match, mismatch, o1, ext,
+                                              lane, dh);
+                __threadfence_block();
+                __syncthreads();
+                if (__ballot(end == score) == 0ull) return -1;
+                return dir_walk(qbase, dbase, R, C, cc, W, match, mismatch, o1, ext, score, lane,
+                                dh, ops + ops_off[h]);
+            };
+            if (__ballot(bad) == 0ull) {
+                if (staged)
+                    len = trace([&](int32_t x) { return (int32_t)s_q[x]; },
+                                [&](int32_t x) { return (int32_t)s_d[x]; });
+                else
+                    len = trace([&](int32_t x) { return base_code(qp[x]); },
+                                [&](int32_t x) { return (int32_t)db_base(dbw, db0 + x); });
+            }
         }
-        const uint8_t *qp = qascii + qs;
-        const int64_t dbase = seq_start[s] + ds;
-        uint8_t *drow = dirs + dir_off[h];
-        int32_t hp1 = NEG, hp2 = NEG, fp1 = NEG, fp2 = NEG;  // previous row, slots lane, lane + 64
-        int32_t bad = 0;
-        for (int32_t i = 0; i < R; ++i) {
-            const int32_t jb = i + cc - W;  // column of slot 0
-            const int32_t qb = base_code(qp[i]);
-            bad |= qb < 0;
-            // up neighbours: slot t + 1 of the previous row
-            const int32_t up1h = __shfl_down(hp1, 1, 64), up1f = __shfl_down(fp1, 1, 64);
-            const int32_t up2h = __shfl_down(hp2, 1, 64), up2f = __shfl_down(fp2, 1, 64);
-            const int32_t wrap_h = __shfl(hp2, 0, 64), wrap_f = __shfl(fp2, 0, 64);
-            int32_t hv[2], ev[2], fv[2], gv[2], dg[2], fo[2], tt[2], jj[2];
-            bool ok[2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int32_t t = lane + 64 * x;
-                const int32_t j = jb + t;
-                tt[x] = t;
-                jj[x] = j;
-                ok[x] = t <= 2 * W && j >= 0 && j < C;
-                const int32_t hprev = x ? hp2 : hp1;
-                int32_t uh = x ? (lane == 63 ? NEG : up2h) : (lane == 63 ? wrap_h : up1h);
-                int32_t uf = x ? (lane == 63 ? NEG : up2f) : (lane == 63 ? wrap_f : up1f);
-                if (i == 0) {
-                    uh = 0;
-                    uf = NEG;
-                }
-                const int32_t dh = (i == 0 || j == 0) ? 0 : hprev;
-                int32_t g = NEG, f = NEG, hpr = NEG;
-                fo[x] = 0;
-                if (ok[x]) {
-                    const int32_t db = db_base(dbw, dbase + j);
-                    g = dh + (qb == db ? match : -mismatch);
-                    f = max(uh - o1, uf - ext);
-                    fo[x] = (uh - o1 >= uf - ext) ? 1 : 0;
-                    hpr = max(max(0, g), f);
-                }
-                gv[x] = g;
-                dg[x] = dh;
-                fv[x] = f;
-                hv[x] = hpr;
-            }
-            // horizontal gaps: exclusive prefix maximum of H'(t) + ext t over the slots
-            int32_t a1 = ok[0] ? hv[0] + ext * tt[0] : LOW;
-            int32_t a2 = ok[1] ? hv[1] + ext * tt[1] : LOW;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int32_t b1 = __shfl_up(a1, off, 64), b2 = __shfl_up(a2, off, 64);
-                if (lane >= off) {
-                    a1 = max(a1, b1);
-                    a2 = max(a2, b2);
-                }
-            }
-            const int32_t tot1 = __shfl(a1, 63, 64);
-            int32_t pm1 = __shfl_up(a1, 1, 64), pm2 = __shfl_up(a2, 1, 64);
-            if (lane == 0) {
-                pm1 = LOW;
-                pm2 = LOW;
-            }
-            pm2 = max(pm2, tot1);
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                const int32_t pm = x ? pm2 : pm1;
-                ev[x] = (ok[x] && pm > LOW) ? max(pm - o1 - ext * (tt[x] - 1), NEG - ext) : NEG;
-                if (ok[x]) hv[x] = max(hv[x], ev[x]);
-            }
-            // left neighbours: slot t - 1 of this row
-            int32_t l1h = __shfl_up(hv[0], 1, 64), l1e = __shfl_up(ev[0], 1, 64);
-            int32_t l2h = __shfl_up(hv[1], 1, 64), l2e = __shfl_up(ev[1], 1, 64);
-            const int32_t w2h = __shfl(hv[0], 63, 64), w2e = __shfl(ev[0], 63, 64);
-            if (lane == 0) {
-                l1h = NEG;
-                l1e = NEG;
-                l2h = w2h;
-                l2e = w2e;
-            }
-            uint8_t byte = 0;
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                int32_t lh = x ? l2h : l1h, le = x ? l2e : l1e;
-                if (jj[x] == 0) {
-                    lh = 0;
-                    le = NEG;
-                }
-                const int32_t eo = (lh - o1 >= le - ext) ? 1 : 0;
-                int32_t src = 3;
-                if (ok[x] && hv[x] > 0) {
-                    if (gv[x] == hv[x]) src = dg[x] > 0 ? 0 : 3;
-                    else if (ev[x] == hv[x]) src = 1;
-                    else src = 2;
-                }
-                const uint8_t nib = (uint8_t)(src | (eo << 2) | (fo[x] << 3));
-                byte |= (uint8_t)(nib << (4 * x));
-                if (ok[x] && i == R - 1 && jj[x] == C - 1) s_hend = hv[x];
-            }
-            drow[(size_t)i * 64 + lane] = byte;
-            hp1 = ok[0] ? hv[0] : NEG;
-            hp2 = ok[1] ? hv[1] : NEG;
-            fp1 = ok[0] ? fv[0] : NEG;
-            fp2 = ok[1] ? fv[1] : NEG;
-        }
-        if (bad) s_bad = 1;
-        __threadfence_block();
-        __syncthreads();
         if (lane == 0) {
-            bool good = s_hend == score && !s_bad;
-            const volatile uint8_t *vd = drow;
-            char *o = ops + ops_off[h];
-            const int64_t cap = (int64_t)R + C;
-            int32_t i = R - 1, j = C - 1, state = 0;
-            int64_t k = 0;
-            int64_t sum = 0;
-            while (good) {
-                const int32_t t = j - (i + cc - W);
-                if (i < 0 || j < 0 || k >= cap || t < 0 || t > 2 * W) {
-                    good = false;
-                    break;
-                }
-                const uint8_t nib = (uint8_t)(vd[(size_t)i * 64 + (t & 63)] >> (4 * (t >> 6))) & 15u;
-                if (state == 0) {
-                    const int32_t src = nib & 3;
-                    if (src == 0 || src == 3) {
-                        const bool eq = base_code(qp[i]) == db_base(dbw, dbase + j);
-                        o[cap - 1 - k++] = eq ? '=' : 'X';
-                        sum += eq ? match : -mismatch;
-                        if (src == 3) {
-                            good = i == 0 && j == 0;
-                            break;
-                        }
-                        --i;
-                        --j;
-                    } else {
-                        state = src;
-                    }
-                } else if (state == 1) {
-                    o[cap - 1 - k++] = 'D';
-                    const bool opened = (nib >> 2) & 1u;
-                    sum -= opened ? o1 : ext;
-                    state = opened ? 0 : 1;
-                    --j;
-                } else {
-                    o[cap - 1 - k++] = 'I';
-                    const bool opened = (nib >> 3) & 1u;
-                    sum -= opened ? o1 : ext;
-                    state = opened ? 0 : 2;
-                    --i;
-                }
-            }
-            good = good && sum == score;
-            ops_len[h] = good ? (int32_t)k : 0;
-            status[h] = good ? 0 : 1;
+            ops_len[h] = max(len, 0);
+            status[h] = len < 0 ? 1 : 0;
         }
-        __syncthreads();
+        __syncthreads();  // the next hit restages the bases
     }
 }
 

@@ -107,7 +107,7 @@ struct Workspace {
     DevBuf bplan, bcount, boff, bcands, btmp, bcoff, ctmp, cursor, qcur, bound_q, bound_off,
         btmp_b, bounds, blist, pcnt, cells_box, rbounds, rbelow, os_scratch, xqueue, gout, gn,
         gctl, gplan, gcursor, gqflag, stiles, gtiles;
-    DevBuf tb_hits, tb_q, tb_dir, tb_dir_off, tb_ops_off, tb_ops, tb_len, tb_status;  // traceback
+    DevBuf tb_in, tb_dir, tb_out;       // traceback: uploads, directions, results
     DevBuf lhist, lthr, lvalid, ltile, lbinq;  // selection prefilter
     DevBuf fkept, fkoff, fflag, ford;   // lone-diagonal filter (ford: largest query first)
     DevBuf tpos;                        // the position where each gather tile starts
@@ -144,8 +144,7 @@ struct Workspace {
                          &cells_q, &bplan, &bcount, &boff, &bcands, &btmp, &bcoff, &ctmp, &cursor, &qcur,
                          &bound_q, &bound_off, &btmp_b, &bounds, &blist, &pcnt, &cells_box,
                          &rbounds, &rbelow, &os_scratch, &xqueue, &gout, &gn, &gctl, &gplan,
-                         &gcursor, &gqflag, &stiles, &gtiles, &tb_hits, &tb_q, &tb_dir,
-                         &tb_dir_off, &tb_ops_off, &tb_ops, &tb_len, &tb_status, &lhist, &lthr,
+                         &gcursor, &gqflag, &stiles, &gtiles, &tb_in, &tb_dir, &tb_out, &lhist, &lthr,
                          &lvalid, &ltile, &lbinq, &fkept, &fkoff, &fflag, &ford, &tpos, &selbox, &bq,
                          &mbig, &mranges, &bsw_order, &qctx, &sbase, &scount};
         for (DevBuf *b : all)
@@ -2949,6 +2948,9 @@ gg_status gg_search(const gg_index *ix, const char *query, int64_t qlen, const g
     return gg_search_batch(ix, query, off, 1, params, out, cap, n_out, nullptr);
 }
 
+// The most a traceback stages in pinned memory (which its workspace then keeps).
+static constexpr size_t kTracePinned = 4u << 20;
+
 gg_status gg_traceback(const gg_index *ix, const char *query, int64_t qlen, const gg_params *params,
                        const gg_hit *hits, int32_t n, char *ops, int64_t ops_cap, int64_t *ops_off,
                        int32_t *ops_len)
@@ -2974,38 +2976,44 @@ gg_status gg_traceback(const gg_index *ix, const char *query, int64_t qlen, cons
     if (hipSetDevice(ix->device) != hipSuccess) return GG_EDEVICE;
     Workspace *ws = nullptr;
     TRY(get_ws(ix, &ws));
-    std::vector<char> slots((size_t)ops_off[n]);
-    std::vector<int32_t> len((size_t)n), status((size_t)n);
+    // one upload (hits | direction offsets | operation offsets | query) and one download
+    // (lengths | statuses | operations), staged in pinned memory unless they are large
+    const size_t nh = (size_t)n, offs = sizeof(int64_t) * (nh + 1);
+    const size_t o_doff = sizeof(gg_hit) * nh, o_ooff = o_doff + offs, o_q = o_ooff + offs;
+    const size_t in_bytes = o_q + (size_t)qlen;
+    const size_t o_st = sizeof(int32_t) * nh, o_ops = 2 * o_st;
+    const size_t out_bytes = o_ops + (size_t)ops_off[n];
+    std::vector<uint8_t> large;
+    uint8_t *io = nullptr;
     auto run = [&]() -> gg_status {
         hipStream_t st = ws->st;
-        TRY(ensure(ws->tb_hits, sizeof(gg_hit) * (size_t)n));
-        TRY(ensure(ws->tb_q, (size_t)qlen));
-        TRY(ensure(ws->tb_dir, (size_t)dir_off[(size_t)n]));
-        TRY(ensure(ws->tb_dir_off, sizeof(int64_t) * (size_t)(n + 1)));
-        TRY(ensure(ws->tb_ops_off, sizeof(int64_t) * (size_t)(n + 1)));
-        TRY(ensure(ws->tb_ops, (size_t)ops_off[n]));
-        TRY(ensure(ws->tb_len, sizeof(int32_t) * (size_t)n));
-        TRY(ensure(ws->tb_status, sizeof(int32_t) * (size_t)n));
-        HIPCHK(hipMemcpyAsync(ws->tb_hits.p, hits, sizeof(gg_hit) * (size_t)n,
-                              hipMemcpyHostToDevice, st));
-        if (qlen > 0)
-            HIPCHK(hipMemcpyAsync(ws->tb_q.p, query, (size_t)qlen, hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(ws->tb_dir_off.p, dir_off.data(), sizeof(int64_t) * (size_t)(n + 1),
-                              hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(ws->tb_ops_off.p, ops_off, sizeof(int64_t) * (size_t)(n + 1),
-                              hipMemcpyHostToDevice, st));
-        launch_traceback(as<int32_t>(ws->tb_hits), n, as<uint8_t>(ws->tb_q), qlen, ix->d_dbw,
+        const size_t io_bytes = std::max(in_bytes, out_bytes);
+        if (io_bytes <= kTracePinned) {
+            void *pin = nullptr;
+            TRY(pinned(ws, io_bytes, &pin));
+            io = static_cast<uint8_t *>(pin);
+        } else {
+            large.resize(io_bytes);
+            io = large.data();
+        }
+        TRY(ensure(ws->tb_in, in_bytes));
+        TRY(ensure(ws->tb_dir, (size_t)dir_off[nh]));
+        TRY(ensure(ws->tb_out, out_bytes));
+        memcpy(io, hits, o_doff);
+        memcpy(io + o_doff, dir_off.data(), offs);
+        memcpy(io + o_ooff, ops_off, offs);
+        if (qlen > 0) memcpy(io + o_q, query, (size_t)qlen);
+        uint8_t *in = as<uint8_t>(ws->tb_in), *out = as<uint8_t>(ws->tb_out);
+        HIPCHK(hipMemcpyAsync(in, io, in_bytes, hipMemcpyHostToDevice, st));
+        launch_traceback(reinterpret_cast<const int32_t *>(in), n, in + o_q, qlen, ix->d_dbw,
                          ix->d_seq_start, (int32_t)ix->n_seqs, params->match, params->mismatch,
                          params->gap_open, params->gap_extend, params->band,
-                         as<int64_t>(ws->tb_dir_off), as<uint8_t>(ws->tb_dir),
-                         as<int64_t>(ws->tb_ops_off), as<char>(ws->tb_ops), as<int32_t>(ws->tb_len),
-                         as<int32_t>(ws->tb_status), st);
+                         reinterpret_cast<const int64_t *>(in + o_doff), as<uint8_t>(ws->tb_dir),
+                         reinterpret_cast<const int64_t *>(in + o_ooff),
+                         reinterpret_cast<char *>(out + o_ops), reinterpret_cast<int32_t *>(out),
+                         reinterpret_cast<int32_t *>(out + o_st), st);
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(slots.data(), ws->tb_ops.p, slots.size(), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipMemcpyAsync(len.data(), ws->tb_len.p, sizeof(int32_t) * (size_t)n,
-                              hipMemcpyDeviceToHost, st));
-        HIPCHK(hipMemcpyAsync(status.data(), ws->tb_status.p, sizeof(int32_t) * (size_t)n,
-                              hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(io, out, out_bytes, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         return GG_OK;
     };
@@ -3013,17 +3021,18 @@ gg_status gg_traceback(const gg_index *ix, const char *query, int64_t qlen, cons
     if (s != GG_OK) {
         (void)hipStreamSynchronize(ws->st);
         (void)hipGetLastError();
+        put_ws(ix, ws);
+        return s;
     }
-    put_ws(ix, ws);
-    if (s != GG_OK) return s;
     // the kernel wrote each path right-aligned in its slot; hand it over left-aligned
+    const int32_t *len = reinterpret_cast<const int32_t *>(io), *status = len + n;
     bool all_ok = true;
     for (int32_t h = 0; h < n; ++h) {
-        const int64_t slot = ops_off[h + 1] - ops_off[h];
-        ops_len[h] = status[(size_t)h] == 0 ? len[(size_t)h] : 0;
-        all_ok = all_ok && status[(size_t)h] == 0;
-        memcpy(ops + ops_off[h], slots.data() + ops_off[h] + slot - ops_len[h], (size_t)ops_len[h]);
+        ops_len[h] = status[h] == 0 ? len[h] : 0;
+        all_ok = all_ok && status[h] == 0;
+        memcpy(ops + ops_off[h], io + o_ops + ops_off[h + 1] - ops_len[h], (size_t)ops_len[h]);
     }
+    put_ws(ix, ws);
     return all_ok ? GG_OK : GG_EINVAL;
 }
 
