@@ -349,7 +349,6 @@ void launch_fill2_u32(uint32_t *a, size_t na, uint32_t *b, size_t nb, uint32_t v
 // grids are sized for the largest wave of the batch (hits_cap, np_cap, nq_cap).
 // The first node takes the wave's plan entry plan[*cursor] into ctl; the last
 // advances the cursor.
-void launch_wave_end(uint32_t *cursor, hipStream_t st);
 void launch_wave_prep_ctl(const uint64_t *hoff, const int64_t *qoff, const uint32_t *lhead,
                           const int32_t *qid, int64_t np_cap, int32_t nq_cap, uint32_t *hrel,
                           uint32_t *pbase, uint64_t *akey, const WaveCtl *plan,
@@ -410,13 +409,12 @@ void launch_chain_write(const uint64_t *keys, uint32_t n, HitKeyLayout lay, int3
 // Each query's range of runs [qstart[q], qend[q]) in n runs in query order, q < nq.
 void launch_cand_segments(const Cand *c, uint32_t n, int32_t nq, uint32_t *qstart, uint32_t *qend,
                           hipStream_t st);
-// Per-query LDS sorts (segments of at most kSegCap records; longer ones are skipped).
-// mode 0: merge order, mode 1: selection order.
-void launch_seg_sort_box(int mode, const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
-                         hipStream_t st);
+// Per-query report order in LDS (segments of at most kSegCap records; longer ones are
+// skipped).
 void launch_report_seg(const Align *in, Align *out, const uint32_t *sel_off, int32_t nq,
-                       uint32_t *rstart, uint32_t *rend, int32_t qa, int32_t cap, int32_t *dev_out,
-                       int32_t *dev_n, hipStream_t st, WaveCtl *ctl = nullptr);
+                       HitKeyLayout lay, int32_t match, uint32_t *rstart, uint32_t *rend,
+                       int32_t qa, int32_t cap, int32_t *dev_out, int32_t *dev_n, hipStream_t st,
+                       WaveCtl *ctl = nullptr);
 // queue_mem: extend_queue_bytes(n) bytes of device scratch.
 size_t extend_queue_bytes(uint32_t n);
 void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32_t *qpack,
@@ -435,11 +433,15 @@ void launch_gather_boxes(const Box *in, const uint32_t *perm, uint32_t n, Box *o
                          hipStream_t st);
 void launch_gather_aligns(const Align *in, const uint32_t *perm, uint32_t n, Align *out,
                           hipStream_t st);
-// A replayed wave's merge (sort, sweep) and selection sort of each query's boxes
-// in one launch (in -> out, per-query segments seg_off; a query over the LDS sort
-// sets its ctl->qflag entry and is skipped).
-void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq_cap,
-                             WaveCtl *ctl, hipStream_t st);
+// The merge (sort, sweep) and selection sort of each query's boxes in one launch (in ->
+// out, per-query segments seg_off of at most kSegCap boxes), and the kept boxes' ranges
+// and the counts of the selected (the first N, all for N = 0).  A replayed wave: a query
+// over the LDS sort sets its ctl->qflag entry and selects none; the launch also moves
+// *cursor on and clears classes[0..64).
+void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
+                             HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
+                             uint32_t *nsel, hipStream_t st, WaveCtl *ctl = nullptr,
+                             uint32_t *cursor = nullptr, uint32_t *classes = nullptr);
 void launch_merge_sweep(const Box *sorted, uint32_t n, Box *out, hipStream_t st);
 // The same sweep of ngroup whole groups, boxes [offs[g], offs[g + 1]) of sorted,
 // one block per group sweeping in parallel for at most `rounds` rounds per chunk
@@ -477,12 +479,8 @@ void launch_segments_align(const Align *sorted, uint32_t n, int32_t nq, uint32_t
 void launch_cand_ranges_ctl(const Cand *c, int32_t nq_cap, uint32_t *qstart, uint32_t *qend,
                             uint32_t *counts, uint32_t *off, uint32_t *clear, const WaveCtl *ctl,
                             hipStream_t st);
-void launch_box_ranges_ctl(const Box *s, const uint32_t *seg_off, int32_t nq_cap, int32_t N,
-                           uint32_t *qstart, uint32_t *qend, uint32_t *counts, const WaveCtl *ctl,
-                           hipStream_t st);
-void launch_box_ranges_scan_ctl(const Box *s, const uint32_t *seg_off, int32_t nq_cap, int32_t N,
-                                uint32_t *qstart, uint32_t *qend, uint32_t *sel_off,
-                                uint32_t *sel_box, const WaveCtl *ctl, hipStream_t st);
+void launch_select_scan(const uint32_t *qstart, const uint32_t *nsel, int32_t nq_cap,
+                        uint32_t *sel_off, uint32_t *sel_box, hipStream_t st);
 void launch_select_counts(const uint32_t *qstart, const uint32_t *qend, int32_t nq,
                           int32_t max_hits, uint32_t *nsel, hipStream_t st);
 void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_off, int32_t nq,

@@ -85,6 +85,32 @@ __device__ __forceinline__ T block_excl_scan(T v, T *total)
     return before + x - v;
 }
 
+// Exclusive running maximum over the threads of a block (0 before the first); *all
+// receives the block's.  s_max: one word per wave.
+__device__ __forceinline__ uint64_t block_excl_max(uint64_t v, uint64_t *s_max, uint64_t *all)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    unsigned long long x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(x, o, 64);
+        if (lane >= o && y > x) x = y;
+    }
+    __syncthreads();
+    if (lane == 63) s_max[w] = x;
+    x = __shfl_up(x, 1, 64);
+    if (lane == 0) x = 0;
+    __syncthreads();
+    uint64_t before = x, most = 0;
+#pragma unroll
+    for (int i = 0; i < kBlock / 64; ++i) {
+        if (i < w) before = max(before, s_max[i]);
+        most = max(most, s_max[i]);
+    }
+    *all = most;
+    return before;
+}
+
 // Bitonic sort of n <= 65536 records in LDS, through an index array.
 template <typename Rec, typename Less>
 __device__ void lds_bitonic(const Rec *__restrict__ s_r, uint16_t *__restrict__ s_ix, uint32_t n,
@@ -708,8 +734,7 @@ __device__ __forceinline__ QCtx query_ctx(const CtxPrep &c, const uint32_t *__re
 // posting list's head, and the constant part of its hits' keys
 // (q << sh_q) + ((bias - qpos) << sh_d) + qpos.
 // A replayed wave (ctl given) takes its plan entry plan[*cursor] here, and block 0
-// publishes it in ctl for the wave's later kernels (the cursor moves on at the
-// wave's end).
+// publishes it in ctl for the wave's later kernels (one of which moves the cursor on).
 __global__ void k_wave_prep(const uint64_t *__restrict__ hoff, const int64_t *__restrict__ qoff,
                             const uint32_t *__restrict__ lhead, const int32_t *__restrict__ qid,
                             int32_t qa, int32_t nqw, int64_t g0,
@@ -1810,10 +1835,6 @@ __global__ __launch_bounds__(kBlock) void k_os_scan(uint32_t *__restrict__ hist,
 
 // Last node of a replayed wave graph: move the cursor to the next planned wave
 // (the first node, the wave preparation, takes the plan entry at the cursor).
-__global__ void k_wave_end(uint32_t *__restrict__ cursor) { *cursor += 1; }
-
-void launch_wave_end(uint32_t *cursor, hipStream_t st) { k_wave_end<<<1, 1, 0, st>>>(cursor); }
-
 __global__ void k_fill_u32(uint32_t *__restrict__ p, size_t n, uint32_t v)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -4192,17 +4213,220 @@ void launch_gather_aligns(const Align *in, const uint32_t *perm, uint32_t n, Ali
 
 // ------------------------------------------------------------------ per-query LDS sorts
 // The runs of one query are contiguous, so the record sorts of merging, selection
-// and reporting are segmented sorts: one block per query sorts its records in LDS
-// with a bitonic network on indices.  Ties between equal records fall back to the
-// input position, which makes the order total and the result deterministic.
-// Segments longer than kSegCap go through the global radix sort instead.
-// MODE 0: merge order (s, qs, ds, qe, de); MODE 1: selection order (kept boxes
-// first, then length descending, s, qs, ds, qe, de).  Length = min of the spans.
-template <int MODE>
+// and reporting are segmented sorts: one block per query orders its records, up to
+// kSegCap of them.  A record's fields, most significant first, are packed
+// into a 64-bit key and the upper 22 bits of a second word, as many as fit; the word's
+// low 10 bits are the record's input position, so the order is total and the result
+// deterministic.  Where the fields do not all fit and two records agree in those that
+// do, the whole segment is ordered again by comparing records.  Segments longer than
+// kSegCap go through the global radix sort instead.
+// Up to kBlock records, a thread holds one and counts those before it: for the usual
+// tens of records a loop of some hundred instructions, where a network takes 28 steps,
+// each a lane exchange or a barrier (merging and selecting queries of up to 80 boxes: 25
+// us, 30 by the network alone).  More records take the network, as the count grows with
+// their square.
+struct SegKey {
+    uint64_t k = 0;
+    uint32_t x = 0;
+    int bits = 0;  // bits of k and x used so far, of 63 + 22 (a live key's top bit is 0)
+
+    // appends v < 2^w (w >= 1, the same in every lane), cut to what is left
+    __device__ __forceinline__ void add(uint32_t v, int w)
+    {
+        const int left = 63 - bits;
+        if (left >= w) {
+            k |= (uint64_t)v << (left - w);
+        } else {
+            if (left > 0) k |= (uint64_t)v >> (w - left);
+            const int in_x = max(left, 0), lx = min(22 + left, 22);  // v's bits placed, x's left
+            const uint32_t rest = in_x ? v & ((1u << (w - in_x)) - 1u) : v;
+            const int wr = w - in_x;
+            if (lx >= wr) x |= rest << (lx - wr);
+            else if (lx > 0) x |= rest >> (wr - lx);
+        }
+        bits += w;
+    }
+    __device__ __forceinline__ bool whole() const { return bits <= 63 + 22; }
+};
+constexpr int kSegIx = 10;
+static_assert(kSegCap <= 1 << kSegIx && kSegCap == 4 * kBlock, "four records per thread");
+
+// Bitonic sort of n2 (a power of two, 4 to kSegCap) pairs (key, word) by a block, four
+// consecutive ones per thread.  Partners in other lanes come by lane exchange, those
+// in other waves (more than 256 pairs) through LDS.
+__device__ void seg_bitonic(uint64_t (&key)[4], uint32_t (&w)[4], uint32_t n2,
+                            uint64_t *__restrict__ s_key, uint32_t *__restrict__ s_w)
+{
+    const uint32_t i0 = threadIdx.x * 4;
+    for (uint32_t k = 2; k <= n2; k <<= 1) {
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            if (j >= 4) {
+                uint64_t pk[4];
+                uint32_t pw[4];
+                if (j >= 256) {
+                    __syncthreads();
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        s_key[e * kBlock + threadIdx.x] = key[e];
+                        s_w[e * kBlock + threadIdx.x] = w[e];
+                    }
+                    __syncthreads();
+                    const uint32_t o = threadIdx.x ^ (j >> 2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        pk[e] = s_key[e * kBlock + o];
+                        pw[e] = s_w[e * kBlock + o];
+                    }
+                } else {
+                    const int m = (int)(j >> 2);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        pk[e] = __shfl_xor((unsigned long long)key[e], m, 64);
+                        pw[e] = (uint32_t)__shfl_xor((int32_t)w[e], m, 64);
+                    }
+                }
+                const bool least = ((i0 & j) == 0) == ((i0 & k) == 0);  // keep the smaller
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool lt = pk[e] < key[e] || (pk[e] == key[e] && pw[e] < w[e]);
+                    const bool take = lt == least;
+                    key[e] = take ? pk[e] : key[e];
+                    w[e] = take ? pw[e] : w[e];
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int a2 = h, b2 = h + 2, a1 = 2 * h, b1 = 2 * h + 1;
+                    const bool two = j == 2;
+                    const uint64_t ka = two ? key[a2] : key[a1], kb = two ? key[b2] : key[b1];
+                    const uint32_t wa = two ? w[a2] : w[a1], wb = two ? w[b2] : w[b1];
+                    const bool up = ((i0 + (two ? a2 : a1)) & k) == 0;
+                    const bool gt = kb < ka || (kb == ka && wb < wa);
+                    const bool swap = gt == up;
+                    const uint64_t kl = swap ? kb : ka, kh = swap ? ka : kb;
+                    const uint32_t wl = swap ? wb : wa, wh = swap ? wa : wb;
+                    if (two) {
+                        key[a2] = kl;
+                        key[b2] = kh;
+                        w[a2] = wl;
+                        w[b2] = wh;
+                    } else {
+                        key[a1] = kl;
+                        key[b1] = kh;
+                        w[a1] = wl;
+                        w[b1] = wh;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// The place of this thread's record `r` (input position threadIdx.x < n; live: it has a
+// key, the others come last in input order) among the n <= kBlock of the block.
+// pack(r): its SegKey; less: the whole comparison.  Uses s_r; starts and ends with a
+// barrier.
+template <typename Rec, typename Pack, typename Less>
+__device__ uint32_t seg_rank(const Rec &r, bool live, uint32_t n, Pack pack, Less less,
+                             Rec *__restrict__ s_r, uint64_t *__restrict__ s_key,
+                             uint32_t *__restrict__ s_w)
+{
+    __shared__ uint32_t s_tie;
+    const uint32_t i = threadIdx.x, n4 = (n + 3) & ~3u;
+    const SegKey p = pack(r);
+    const uint64_t key = live ? p.k : ~0ull;  // a live key's top bit is 0
+    const uint32_t w = live ? p.x << kSegIx | i : i;
+    __syncthreads();
+    if (i == 0) s_tie = 0;
+    if (i < n4) {
+        s_key[i] = i < n ? key : ~0ull;
+        s_w[i] = i < n ? w : i;
+    }
+    __syncthreads();
+    uint32_t rank = 0, same = 0;
+    if ((i & ~63u) < n) {
+        for (uint32_t j = 0; j < n4; j += 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint64_t k = s_key[j + e];
+                const uint32_t x = s_w[j + e];
+                const bool eq = k == key;
+                rank += k < key || (eq && x < w) ? 1u : 0u;
+                same += eq && (x ^ w) >> kSegIx == 0u ? 1u : 0u;
+            }
+        }
+    }
+    if (i < n && live && same > 1 && !p.whole()) s_tie = 1;
+    __syncthreads();
+    if (s_tie) {
+        if (i < n) s_r[i] = r;
+        __syncthreads();
+        rank = 0;
+        for (uint32_t j = 0; j < n; ++j)
+            rank += less(s_r[j], r) || (j < i && !less(r, s_r[j])) ? 1u : 0u;
+        __syncthreads();
+    }
+    return rank;
+}
+
+// The order of n records of LDS (kBlock < n <= kSegCap) in s_ix, their input positions;
+// live, pack and less as above.  Starts and ends with a barrier.
+template <typename Rec, typename Live, typename Pack, typename Less>
+__device__ void seg_order(const Rec *__restrict__ s_r, uint32_t n, Live live, Pack pack, Less less,
+                          uint64_t *__restrict__ s_key, uint32_t *__restrict__ s_w)
+{
+    __shared__ uint32_t s_tie;
+    uint16_t *s_ix = reinterpret_cast<uint16_t *>(s_key);
+    uint32_t n2 = 2 * kBlock;
+    while (n2 < n) n2 <<= 1;
+    __syncthreads();
+    if (threadIdx.x == 0) s_tie = 0;
+    uint64_t key[4];
+    uint32_t w[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t i = threadIdx.x * 4 + e;
+        key[e] = ~0ull;
+        w[e] = i;  // beyond every live record: a live key's top bit is 0
+        if (i < n && live(s_r[i])) {
+            const SegKey p = pack(s_r[i]);
+            key[e] = p.k;
+            w[e] = p.x << kSegIx | i;
+        }
+    }
+    seg_bitonic(key, w, n2, s_key, s_w);
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        s_key[threadIdx.x * 4 + e] = key[e];
+        s_w[threadIdx.x * 4 + e] = w[e];
+    }
+    __syncthreads();
+    bool tie = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t i = threadIdx.x * 4 + e + 1;
+        tie |= i < n && key[e] == s_key[i] && key[e] != ~0ull && (w[e] ^ s_w[i]) >> kSegIx == 0u;
+    }
+    if (tie && !pack(s_r[0]).whole()) s_tie = 1;  // whole by the widths alone
+    __syncthreads();
+    if (s_tie) {
+        lds_bitonic(s_r, s_ix, n, less);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            s_ix[threadIdx.x * 4 + e] = (uint16_t)(w[e] & ((1u << kSegIx) - 1u));
+        __syncthreads();
+    }
+}
+
+// Merge order (s, qs, ds, qe, de) and selection order (kept boxes first, then length
+// descending, s, qs, ds, qe, de).  Length = min of the spans.
+template <bool SELECT>
 struct BoxLess {
     __device__ bool operator()(const Box &x, const Box &y) const
     {
-        if (MODE == 1) {
+        if (SELECT) {
             const bool vx = x.q >= 0, vy = y.q >= 0;
             if (vx != vy) return vx;
             if (!vx) return false;
@@ -4217,98 +4441,154 @@ struct BoxLess {
     }
 };
 
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_seg_sort_box(const Box *__restrict__ in,
-                                                         Box *__restrict__ out,
-                                                         const uint32_t *__restrict__ seg_off)
+// The merge and selection order for one query in one block: its boxes put in merge
+// order in LDS, each sequence's boxes swept in place with the joins of k_merge_sweep
+// (merged boxes from a stretch's start, the rest marked empty), then written out in selection
+// order, with the range of the kept ones (qstart, qend) and how many of them are
+// selected (nsel; the first N, all for N = 0).  A replayed wave (ctl given) flags a
+// query of more boxes, and its block 0 moves the wave cursor on and clears the
+// aligner's class counts.  A serial chain: 1,000 queries of up to 80 boxes took 46 us by
+// a network of record comparisons in LDS and one thread's sweep of each sequence's
+// boxes; 25 by counted places, 16 with the sweep in stretches.
+__global__ __launch_bounds__(kBlock) void k_merge_select_seg(
+    const Box *__restrict__ in, Box *__restrict__ out, const uint32_t *__restrict__ seg_off,
+    HitKeyLayout lay, int32_t N, uint32_t *__restrict__ qstart, uint32_t *__restrict__ qend,
+    uint32_t *__restrict__ nsel, WaveCtl *__restrict__ ctl, uint32_t *__restrict__ cursor,
+    uint32_t *__restrict__ classes)
 {
     __shared__ Box s_r[kSegCap];
-    __shared__ uint16_t s_ix[kSegCap];
-    const uint32_t a0 = seg_off[blockIdx.x], n = seg_off[blockIdx.x + 1] - a0;
-    if (n == 0 || n > (uint32_t)kSegCap) return;  // longer segments take the global sort
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) s_r[i] = in[a0 + i];
-    lds_bitonic(s_r, s_ix, n, BoxLess<MODE>());
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[a0 + i] = s_r[s_ix[i]];
-}
-
-void launch_seg_sort_box(int mode, const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
-                         hipStream_t st)
-{
-    if (nq <= 0) return;
-    if (mode == 0) k_seg_sort_box<0><<<nq, kBlock, 0, st>>>(in, out, seg_off);
-    else k_seg_sort_box<1><<<nq, kBlock, 0, st>>>(in, out, seg_off);
-}
-
-// A replayed wave's merge and selection order for one query in one block: its
-// boxes sorted by merge order (s, qs, ds, qe, de) in LDS and put in that order,
-// each sequence's group swept in place as k_merge_sweep does (merged boxes from
-// the group's start, the rest marked empty), then sorted by selection order and
-// written out.  The same three steps as k_seg_sort_box<0>, k_merge_sweep and
-// k_seg_sort_box<1>, with the boxes kept in LDS between them.
-__global__ __launch_bounds__(kBlock) void k_merge_select_seg(const Box *__restrict__ in,
-                                                             Box *__restrict__ out,
-                                                             const uint32_t *__restrict__ seg_off,
-                                                             WaveCtl *__restrict__ ctl)
-{
-    __shared__ Box s_r[kSegCap];
-    __shared__ uint16_t s_ix[kSegCap];
-    if ((int32_t)blockIdx.x >= ctl->nqw) return;
-    const uint32_t a0 = seg_off[blockIdx.x], n = seg_off[blockIdx.x + 1] - a0;
-    if (n > (uint32_t)kSegCap) {
-        if (threadIdx.x == 0) ctl->qflag[ctl->qa + (int32_t)blockIdx.x] = 1u;
+    __shared__ uint64_t s_key[kSegCap];
+    __shared__ uint32_t s_w[kSegCap];
+    __shared__ uint64_t s_max[kBlock / 64];
+    __shared__ uint32_t s_live;
+    const uint16_t *s_ix = reinterpret_cast<const uint16_t *>(s_key);  // seg_order's result
+    const int32_t ql = blockIdx.x;
+    if (ctl) {
+        if (ql == 0) {
+            if (threadIdx.x == 0) *cursor += 1;
+            if (threadIdx.x < 64) classes[threadIdx.x] = 0;
+        }
+        lay = ctl->lay;
+    }
+    uint32_t a0 = 0, n = 0;
+    if (!ctl || ql < ctl->nqw) {
+        a0 = seg_off[ql];
+        n = seg_off[ql + 1] - a0;
+        if (ctl && n > (uint32_t)kSegCap && threadIdx.x == 0) ctl->qflag[ctl->qa + ql] = 1u;
+        if (ctl && (n > (uint32_t)kSegCap || ctl->qflag[ctl->qa + ql])) n = 0;
+    }
+    if (n == 0) {
+        if (threadIdx.x == 0) {
+            qstart[ql] = qend[ql] = a0;
+            nsel[ql] = 0;
+        }
         return;
     }
-    if (n == 0) return;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) s_r[i] = in[a0 + i];
-    lds_bitonic(s_r, s_ix, n, BoxLess<0>());  // starts and ends with a barrier
-    constexpr int kPer = kSegCap / kBlock;
-    Box tmp[kPer];
+    const int bl = lay.bp + 1;  // positions and lengths up to the longest query
+    const bool small = n <= (uint32_t)kBlock;
+    if (threadIdx.x == 0) s_live = 0;
+    // the boxes leave the extension unmerged, each on one diagonal: ds = qs + d, de = qe + d
+    auto merge_key = [&](const Box &b) {
+        SegKey k;
+        k.add((uint32_t)b.s, lay.bs);
+        k.add((uint32_t)b.qs, bl);
+        k.add((uint32_t)(b.ds - b.qs + lay.bias), lay.bd);
+        k.add((uint32_t)b.qe, bl);
+        return k;
+    };
+    if (small) {
+        Box b{};
+        if (threadIdx.x < n) b = in[a0 + threadIdx.x];
+        const uint32_t at = seg_rank(b, true, n, merge_key, BoxLess<false>(), s_r, s_key, s_w);
+        if (threadIdx.x < n) s_r[at] = b;
+    } else {
+        for (uint32_t i = threadIdx.x; i < n; i += kBlock) s_r[i] = in[a0 + i];
+        seg_order(
+            s_r, n, [](const Box &) { return true; }, merge_key, BoxLess<false>(), s_key, s_w);
+        Box tmp[4];
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const uint32_t i = threadIdx.x + k * kBlock;
-        if (i < n) tmp[k] = s_r[s_ix[i]];
+        for (int e = 0; e < 4; ++e)
+            if (threadIdx.x + e * kBlock < n) tmp[e] = s_r[s_ix[threadIdx.x + e * kBlock]];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (threadIdx.x + e * kBlock < n) s_r[threadIdx.x + e * kBlock] = tmp[e];
     }
     __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-        const uint32_t i = threadIdx.x + k * kBlock;
-        if (i < n) s_r[i] = tmp[k];
+    // A box that starts, in the query, at or past every end before it in its sequence joins
+    // none of those, and no later box joins across it: the sweep starts anew there.
+    // s rises along the order, so the largest (s, qe) before a box tells.
+    uint64_t most = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += kBlock) {
+        const uint32_t i = i0 + threadIdx.x;
+        const Box b = s_r[min(i, n - 1)];
+        uint64_t all;
+        const uint64_t before =
+            max(most, block_excl_max((uint64_t)(uint32_t)b.s << 32 | (uint32_t)b.qe, s_max, &all));
+        if (i < n) s_w[i] = (uint32_t)(before >> 32) != (uint32_t)b.s || (int32_t)before <= b.qs;
+        most = max(most, all);
     }
     __syncthreads();
-    // the thread at each group's first box sweeps it; a group's first slot always
-    // keeps a box of that sequence, so a neighbour's end test reads a valid s
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        if (i > 0 && s_r[i - 1].s == s_r[i].s) continue;
+    // each stretch swept by the thread at its first box
+    uint32_t kept = 0;
+    for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+        if (i > 0 && !s_w[i]) continue;
         Box cur = s_r[i];
-        const int32_t sq = cur.s;
         uint32_t w = i, j = i + 1;
-        for (; j < n; ++j) {
+        bool more = j < n && !s_w[min(j, n - 1)];
+        while (more) {
             const Box h = s_r[j];
-            if (h.s != sq) break;
-            if (h.qs < cur.qe && h.ds < cur.de && cur.ds < h.de) {
-                cur.qs = min(cur.qs, h.qs);
-                cur.qe = max(cur.qe, h.qe);
-                cur.ds = min(cur.ds, h.ds);
-                cur.de = max(cur.de, h.de);
-                cur.dmin = min(cur.dmin, h.dmin);
-                cur.dmax = max(cur.dmax, h.dmax);
-            } else {
-                s_r[w++] = cur;
-                cur = h;
-            }
+            more = ++j < n && !s_w[min(j, n - 1)];
+            // by arithmetic, not by branches: one wait for the box, none for its tests
+            const bool join = (h.qs < cur.qe) & (h.ds < cur.de) & (cur.ds < h.de);
+            if (!join) s_r[w++] = cur;
+            cur.qs = join ? min(cur.qs, h.qs) : h.qs;
+            cur.qe = join ? max(cur.qe, h.qe) : h.qe;
+            cur.ds = join ? min(cur.ds, h.ds) : h.ds;
+            cur.de = join ? max(cur.de, h.de) : h.de;
+            cur.dmin = join ? min(cur.dmin, h.dmin) : h.dmin;
+            cur.dmax = join ? max(cur.dmax, h.dmax) : h.dmax;
         }
         s_r[w++] = cur;
+        kept += w - i;
         for (; w < j; ++w) s_r[w].q = -1;
     }
+    if (kept) atomicAdd(&s_live, kept);
+    auto select_key = [&](const Box &b) {
+        SegKey k;
+        k.add((1u << bl) - 1u - (uint32_t)min(b.qe - b.qs, b.de - b.ds), bl);
+        k.add((uint32_t)b.s, lay.bs);
+        k.add((uint32_t)b.qs, bl);
+        k.add((uint32_t)b.ds, lay.bd);
+        k.add((uint32_t)b.qe, bl);
+        k.add((uint32_t)b.de, lay.bd);
+        return k;
+    };
     __syncthreads();
-    lds_bitonic(s_r, s_ix, n, BoxLess<1>());
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[a0 + i] = s_r[s_ix[i]];
+    if (small) {
+        const Box b = s_r[min(threadIdx.x, n - 1)];
+        const uint32_t at = seg_rank(b, b.q >= 0, n, select_key, BoxLess<true>(), s_r, s_key, s_w);
+        if (threadIdx.x < n) out[a0 + at] = b;
+    } else {
+        seg_order(
+            s_r, n, [](const Box &b) { return b.q >= 0; }, select_key, BoxLess<true>(), s_key, s_w);
+        for (uint32_t i = threadIdx.x; i < n; i += kBlock) out[a0 + i] = s_r[s_ix[i]];
+    }
+    if (threadIdx.x == 0) {
+        qstart[ql] = a0;
+        qend[ql] = a0 + s_live;
+        nsel[ql] = N > 0 ? min(s_live, (uint32_t)N) : s_live;
+    }
 }
 
-void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq_cap,
-                             WaveCtl *ctl, hipStream_t st)
+void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
+                             HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
+                             uint32_t *nsel, hipStream_t st, WaveCtl *ctl, uint32_t *cursor,
+                             uint32_t *classes)
 {
-    if (nq_cap > 0) k_merge_select_seg<<<nq_cap, kBlock, 0, st>>>(in, out, seg_off, ctl);
+    if (nq > 0)
+        k_merge_select_seg<<<nq, kBlock, 0, st>>>(in, out, seg_off, lay, N, qstart, qend, nsel, ctl,
+                                                  cursor, classes);
 }
 
 // Report order: alignments with score > 0 first, score descending, then seq,
@@ -4338,6 +4618,7 @@ struct AlignLess {
 __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__ in,
                                                        Align *__restrict__ out,
                                                        const uint32_t *__restrict__ sel_off,
+                                                       HitKeyLayout lay, int32_t match,
                                                        uint32_t *__restrict__ rstart,
                                                        uint32_t *__restrict__ rend, int32_t qa,
                                                        int32_t cap, int32_t *__restrict__ dev_out,
@@ -4345,49 +4626,78 @@ __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__
                                                        WaveCtl *__restrict__ ctl)
 {
     __shared__ Align s_r[kSegCap];
-    __shared__ uint16_t s_ix[kSegCap];
+    __shared__ uint64_t s_key[kSegCap];
+    __shared__ uint32_t s_w[kSegCap];
     __shared__ uint32_t s_valid;
     const int32_t ql = blockIdx.x;
     if (ctl) {
         if (ql >= ctl->nqw) return;
         qa = ctl->qa;
+        lay = ctl->lay;
     }
     const uint32_t a0 = sel_off[ql], n = sel_off[ql + 1] - a0;
     if (ctl && n > (uint32_t)kSegCap && threadIdx.x == 0) ctl->qflag[qa + ql] = 1u;
     if (n > (uint32_t)kSegCap) return;  // longer segments take the global sort
     if (threadIdx.x == 0) s_valid = 0;
     __syncthreads();
-    uint32_t v = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        s_r[i] = in[a0 + i];
-        v += s_r[i].score > 0 ? 1u : 0u;
+    if (n > 0) {
+        const int bl = lay.bp + 1;
+        const uint32_t top = (uint32_t)lay.bias * (uint32_t)match;  // no score is above it
+        const int bsc = 32 - __clz((int32_t)(top | 1u));
+        auto key = [&](const Align &a) {
+            SegKey k;
+            k.add(top - (uint32_t)a.score, bsc);
+            k.add((uint32_t)a.seq_id, lay.bs);
+            k.add((uint32_t)a.q_start, bl);
+            k.add((uint32_t)a.d_start, lay.bd);
+            k.add((uint32_t)a.q_end, bl);
+            k.bits = 99;  // the box is left to the whole comparison
+            return k;
+        };
+        auto put = [&](const Align &a, uint32_t at) {
+            out[a0 + at] = a;
+            if (!dev_out || at >= (uint32_t)cap || a.score <= 0) return;
+            int32_t *dst = dev_out + ((size_t)(qa + ql) * (size_t)cap + at) * kHitInts;
+            const int32_t *src = reinterpret_cast<const int32_t *>(&a);
+#pragma unroll
+            for (int f = 0; f < kHitInts; ++f) dst[f] = src[1 + f];
+        };
+        if (n <= (uint32_t)kBlock) {
+            Align a{};
+            if (threadIdx.x < n) a = in[a0 + threadIdx.x];
+            const bool valid = a.score > 0;
+            if (valid) atomicAdd(&s_valid, 1u);
+            const uint32_t at = seg_rank(a, valid, n, key, AlignLess(), s_r, s_key, s_w);
+            if (threadIdx.x < n) put(a, at);
+        } else {
+            uint32_t v = 0;
+            for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+                s_r[i] = in[a0 + i];
+                v += s_r[i].score > 0 ? 1u : 0u;
+            }
+            if (v) atomicAdd(&s_valid, v);
+            seg_order(
+                s_r, n, [](const Align &a) { return a.score > 0; }, key, AlignLess(), s_key, s_w);
+            const uint16_t *s_ix = reinterpret_cast<const uint16_t *>(s_key);
+            for (uint32_t i = threadIdx.x; i < n; i += kBlock) put(s_r[s_ix[i]], i);
+        }
     }
-    if (v) atomicAdd(&s_valid, v);
-    lds_bitonic(s_r, s_ix, n, AlignLess());  // starts and ends with a barrier
     const uint32_t nv = s_valid;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[a0 + i] = s_r[s_ix[i]];
     if (threadIdx.x == 0) {
         rstart[ql] = a0;
         rend[ql] = a0 + nv;
         if (dev_n) dev_n[qa + ql] = (int32_t)nv;
     }
-    if (dev_out) {
-        const uint32_t m = min(nv, (uint32_t)cap);
-        int32_t *dst = dev_out + ((size_t)(qa + ql) * (size_t)cap) * kHitInts;
-        for (uint32_t e = threadIdx.x; e < m * kHitInts; e += blockDim.x) {
-            const int32_t *src = reinterpret_cast<const int32_t *>(&s_r[s_ix[e / kHitInts]]);
-            dst[e] = src[1 + e % kHitInts];
-        }
-    }
 }
 
 void launch_report_seg(const Align *in, Align *out, const uint32_t *sel_off, int32_t nq,
-                       uint32_t *rstart, uint32_t *rend, int32_t qa, int32_t cap, int32_t *dev_out,
-                       int32_t *dev_n, hipStream_t st, WaveCtl *ctl)
+                       HitKeyLayout lay, int32_t match, uint32_t *rstart, uint32_t *rend,
+                       int32_t qa, int32_t cap, int32_t *dev_out, int32_t *dev_n, hipStream_t st,
+                       WaveCtl *ctl)
 {
     if (nq > 0)
-        k_report_seg<<<nq, kBlock, 0, st>>>(in, out, sel_off, rstart, rend, qa, cap, dev_out, dev_n,
-                                            ctl);
+        k_report_seg<<<nq, kBlock, 0, st>>>(in, out, sel_off, lay, match, rstart, rend, qa, cap,
+                                            dev_out, dev_n, ctl);
 }
 
 // ------------------------------------------------------------------ S7: merge overlaps
@@ -5509,30 +5819,6 @@ __global__ void k_cand_ranges(const Cand *__restrict__ c, int32_t nq_cap,
     off[q] = a;  // runs are in query order: a query's first run is its offset
 }
 
-__global__ void k_box_ranges(const Box *__restrict__ s, const uint32_t *__restrict__ seg_off,
-                             int32_t nq_cap, int32_t N, uint32_t *__restrict__ qstart,
-                             uint32_t *__restrict__ qend, uint32_t *__restrict__ counts,
-                             const WaveCtl *__restrict__ ctl)
-{
-    const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nq_cap) return;
-    uint32_t a = 0, b = 0;
-    if (q < ctl->nqw && !ctl->qflag[ctl->qa + q]) {
-        a = seg_off[q];
-        uint32_t lo = a, hi = seg_off[q + 1];  // first empty slot of the segment
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (s[mid].q >= 0) lo = mid + 1;
-            else hi = mid;
-        }
-        b = lo;
-    }
-    qstart[q] = a;
-    qend[q] = b;
-    const uint32_t cnt = b - a;
-    counts[q] = (N > 0 && cnt > (uint32_t)N) ? (uint32_t)N : cnt;
-}
-
 void launch_cand_ranges_ctl(const Cand *c, int32_t nq_cap, uint32_t *qstart, uint32_t *qend,
                             uint32_t *counts, uint32_t *off, uint32_t *clear, const WaveCtl *ctl,
                             hipStream_t st)
@@ -5541,33 +5827,21 @@ void launch_cand_ranges_ctl(const Cand *c, int32_t nq_cap, uint32_t *qstart, uin
                                                                    off, clear, ctl);
 }
 
-// The same ranges, with the exclusive scan of the capped counts (sel_off[0..nq_cap],
-// total last) in the same launch: one block of kRangeBlock threads, a query per
-// thread (looping when there are more), so the segments' searches run side by side.
+// A replayed wave's selections: the exclusive scan of their counts (sel_off[0..nq_cap],
+// total last) and the box of each, in one launch of one block of kRangeBlock threads, a
+// query per thread (looping when there are more).
 constexpr int kRangeBlock = 1024;
 
-__global__ __launch_bounds__(kRangeBlock) void k_box_ranges_scan(
-    const Box *__restrict__ s, const uint32_t *__restrict__ seg_off, int32_t nq_cap, int32_t N,
-    uint32_t *__restrict__ qstart, uint32_t *__restrict__ qend, uint32_t *__restrict__ sel_off,
-    uint32_t *__restrict__ sel_box, const WaveCtl *__restrict__ ctl)
+__global__ __launch_bounds__(kRangeBlock) void k_select_scan(
+    const uint32_t *__restrict__ qstart, const uint32_t *__restrict__ nsel, int32_t nq_cap,
+    uint32_t *__restrict__ sel_off, uint32_t *__restrict__ sel_box)
 {
     __shared__ uint32_t s_w[kRangeBlock / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t carry = 0;
     for (int32_t q0 = 0; q0 < nq_cap; q0 += kRangeBlock) {
         const int32_t q = q0 + (int32_t)threadIdx.x;
-        uint32_t a = 0, b = 0;
-        if (q < nq_cap && q < ctl->nqw && !ctl->qflag[ctl->qa + q]) {
-            a = seg_off[q];
-            uint32_t lo = a, hi = seg_off[q + 1];  // first empty slot of the segment
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (s[mid].q >= 0) lo = mid + 1;
-                else hi = mid;
-            }
-            b = lo;
-        }
-        const uint32_t cnt = (N > 0 && b - a > (uint32_t)N) ? (uint32_t)N : b - a;
+        const uint32_t cnt = q < nq_cap ? nsel[q] : 0u, a = q < nq_cap ? qstart[q] : 0u;
         uint32_t x = cnt;  // block-wide exclusive scan of cnt
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -5586,8 +5860,6 @@ __global__ __launch_bounds__(kRangeBlock) void k_box_ranges_scan(
         __syncthreads();
         const uint32_t ex = carry + before + x - cnt;
         if (q < nq_cap) {
-            qstart[q] = a;
-            qend[q] = b;
             sel_off[q] = ex;
             // the aligner's boxes, in selection order: the r-th is box a + r
             for (uint32_t r = 0; r < cnt; ++r) sel_box[ex + r] = a + r;
@@ -5597,20 +5869,10 @@ __global__ __launch_bounds__(kRangeBlock) void k_box_ranges_scan(
     if (threadIdx.x == 0) sel_off[nq_cap] = carry;
 }
 
-void launch_box_ranges_ctl(const Box *s, const uint32_t *seg_off, int32_t nq_cap, int32_t N,
-                           uint32_t *qstart, uint32_t *qend, uint32_t *counts, const WaveCtl *ctl,
-                           hipStream_t st)
+void launch_select_scan(const uint32_t *qstart, const uint32_t *nsel, int32_t nq_cap,
+                        uint32_t *sel_off, uint32_t *sel_box, hipStream_t st)
 {
-    k_box_ranges<<<(nq_cap + kBlock - 1) / kBlock, kBlock, 0, st>>>(s, seg_off, nq_cap, N, qstart,
-                                                                      qend, counts, ctl);
-}
-
-void launch_box_ranges_scan_ctl(const Box *s, const uint32_t *seg_off, int32_t nq_cap, int32_t N,
-                                uint32_t *qstart, uint32_t *qend, uint32_t *sel_off,
-                                uint32_t *sel_box, const WaveCtl *ctl, hipStream_t st)
-{
-    k_box_ranges_scan<<<1, kRangeBlock, 0, st>>>(s, seg_off, nq_cap, N, qstart, qend, sel_off,
-                                                 sel_box, ctl);
+    k_select_scan<<<1, kRangeBlock, 0, st>>>(qstart, nsel, nq_cap, sel_off, sel_box);
 }
 
 void launch_select_counts(const uint32_t *qstart, const uint32_t *qend, int32_t nq,
@@ -6135,7 +6397,7 @@ void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_o
     if (order_buf) {
         uint32_t *cnt = order_buf;
         order = order_buf + 64;
-        launch_fill_u32(cnt, 64, 0u, st);
+        if (!ctl) launch_fill_u32(cnt, 64, 0u, st);  // a replayed wave's are cleared before
         k_bsw_classes<<<kOrderBlocks, kBlock, 0, st>>>(sorted, qstart, sel_off, nq, nsel_total,
                                                        sel_box, cnt, ctl);
         k_bsw_order<<<kOrderBlocks, kBlock, 0, st>>>(sorted, qstart, sel_off, nq, nsel_total,

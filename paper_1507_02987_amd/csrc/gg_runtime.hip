@@ -1127,11 +1127,14 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         TRY(ensure(ws->lbinq, sizeof(uint32_t) * (size_t)nc));
         ls = LenSel{as<uint32_t>(ws->lbinq), std::max(0, bits_for((uint64_t)maxL + 1) - 10)};
     }
-    if (seg_path) {
-        launch_seg_sort_box(0, boxes, as<Box>(ws->boxes2), as<uint32_t>(ws->cand_off), nqw, st);
-        prof.end(nc);
-        prof.begin("merge_sweep");
-        launch_merge_sweep(as<Box>(ws->boxes2), nc, as<Box>(ws->boxes3), st);
+    TRY(ensure(ws->qstart, sizeof(uint32_t) * (nqw + 1)));
+    TRY(ensure(ws->qend, sizeof(uint32_t) * (nqw + 1)));
+    TRY(ensure(ws->nsel, sizeof(uint32_t) * (nqw + 1)));
+    TRY(ensure(ws->sel_off, sizeof(uint32_t) * (nqw + 1)));
+    if (seg_path) {  // merged and put in selection order, with each query's ranges
+        launch_merge_select_seg(boxes, as<Box>(ws->boxes2), as<uint32_t>(ws->cand_off), nqw, lay,
+                                p->max_hits, as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
+                                as<uint32_t>(ws->nsel), st);
         prof.end(nc);
     } else if (windows) {
         // groups in LDS windows; the few that may outgrow a window by the global sort
@@ -1190,9 +1193,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     Box *merged = as<Box>(ws->boxes3);
     uint32_t nbox = nc;                // boxes in the selection order
     std::vector<uint32_t> nvalid_h;    // merged boxes per query, when prefiltered
-    if (seg_path) {
-        launch_seg_sort_box(1, merged, as<Box>(ws->boxes2), as<uint32_t>(ws->cand_off), nqw, st);
-    } else {
+    if (!seg_path) {
         if (ls.binq) {
             // only boxes at least as long as a query's N-th longest can be selected
             const uint32_t tiles = (nc + kTile - 1) / kTile;
@@ -1225,16 +1226,14 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
                          &perm));
         launch_gather_boxes(merged, perm, nbox, as<Box>(ws->boxes2), st);
     }
-    TRY(ensure(ws->qstart, sizeof(uint32_t) * (nqw + 1)));
-    TRY(ensure(ws->qend, sizeof(uint32_t) * (nqw + 1)));
-    TRY(ensure(ws->nsel, sizeof(uint32_t) * (nqw + 1)));
-    TRY(ensure(ws->sel_off, sizeof(uint32_t) * (nqw + 1)));
-    HIPCHK(hipMemsetAsync(ws->qstart.p, 0, sizeof(uint32_t) * nqw, st));
-    HIPCHK(hipMemsetAsync(ws->qend.p, 0, sizeof(uint32_t) * nqw, st));
-    launch_segments_box(as<Box>(ws->boxes2), nbox, nqw, as<uint32_t>(ws->qstart),
-                        as<uint32_t>(ws->qend), st);
-    launch_select_counts(as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend), nqw, p->max_hits,
-                         as<uint32_t>(ws->nsel), st);
+    if (!seg_path) {
+        HIPCHK(hipMemsetAsync(ws->qstart.p, 0, sizeof(uint32_t) * nqw, st));
+        HIPCHK(hipMemsetAsync(ws->qend.p, 0, sizeof(uint32_t) * nqw, st));
+        launch_segments_box(as<Box>(ws->boxes2), nbox, nqw, as<uint32_t>(ws->qstart),
+                            as<uint32_t>(ws->qend), st);
+        launch_select_counts(as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend), nqw, p->max_hits,
+                             as<uint32_t>(ws->nsel), st);
+    }
     launch_scan_u32(as<uint32_t>(ws->nsel), as<uint32_t>(ws->sel_off), nqw,
                     as<uint32_t>(ws->partials), st);
     prof.end(nc);
@@ -1294,8 +1293,8 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     Align *al = as<Align>(ws->aligns);
     bool written = false;
     if (max_sel <= (uint32_t)kSegCap) {
-        launch_report_seg(al, as<Align>(ws->aligns2), as<uint32_t>(ws->sel_off), nqw,
-                          as<uint32_t>(ws->rstart), as<uint32_t>(ws->rend), qa, bo.cap,
+        launch_report_seg(al, as<Align>(ws->aligns2), as<uint32_t>(ws->sel_off), nqw, lay,
+                          p->match, as<uint32_t>(ws->rstart), as<uint32_t>(ws->rend), qa, bo.cap,
                           bo.device ? reinterpret_cast<int32_t *>(bo.out) : nullptr,
                           bo.device ? bo.n_out : nullptr, st);
         written = bo.device;
@@ -1847,19 +1846,16 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                       as<Box>(ws->boxes), ws->xqueue.p, steps, st, ctl, runs_cap,
                       /*count_cleared=*/true);
         launch_merge_select_seg(as<Box>(ws->boxes), as<Box>(ws->boxes2),
-                                as<uint32_t>(ws->cand_off), nq_cap, ctl, st);
-        if (nq_cap <= 4096) {  // ranges and their scan in one launch
-            launch_box_ranges_scan_ctl(as<Box>(ws->boxes2), as<uint32_t>(ws->cand_off), nq_cap, N,
-                                       as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
-                                       as<uint32_t>(ws->sel_off), as<uint32_t>(ws->selbox), ctl,
-                                       st);
-        } else {
-            launch_box_ranges_ctl(as<Box>(ws->boxes2), as<uint32_t>(ws->cand_off), nq_cap, N,
-                                  as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
-                                  as<uint32_t>(ws->nsel), ctl, st);
+                                as<uint32_t>(ws->cand_off), nq_cap, HitKeyLayout{}, N,
+                                as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
+                                as<uint32_t>(ws->nsel), st, ctl, cursor,
+                                as<uint32_t>(ws->bsw_order));
+        if (nq_cap <= 4096)  // scanned by one block, which lists the boxes too
+            launch_select_scan(as<uint32_t>(ws->qstart), as<uint32_t>(ws->nsel), nq_cap,
+                               as<uint32_t>(ws->sel_off), as<uint32_t>(ws->selbox), st);
+        else
             launch_scan_u32(as<uint32_t>(ws->nsel), as<uint32_t>(ws->sel_off), nq_cap,
                             as<uint32_t>(ws->partials), st);
-        }
         launch_bsw(as<Box>(ws->boxes2), as<uint32_t>(ws->qstart), as<uint32_t>(ws->sel_off), 0, 0,
                    as<uint8_t>(ws->qcode), as<int64_t>(ws->qoff), 0, ix->d_dbw, ix->d_seq_start,
                    p->match, p->mismatch, p->gap_open, p->gap_extend, p->band,
@@ -1867,9 +1863,8 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                    nq_cap <= 4096 ? as<uint32_t>(ws->selbox) : nullptr,
                    as<uint32_t>(ws->bsw_order));
         launch_report_seg(as<Align>(ws->aligns), as<Align>(ws->aligns2), as<uint32_t>(ws->sel_off),
-                          nq_cap, as<uint32_t>(ws->rstart), as<uint32_t>(ws->rend), 0, cap,
-                          gout, gn, st, ctl);
-        launch_wave_end(cursor, st);
+                          nq_cap, HitKeyLayout{}, p->match, as<uint32_t>(ws->rstart),
+                          as<uint32_t>(ws->rend), 0, cap, gout, gn, st, ctl);
         const hipError_t ec = hipStreamEndCapture(st, &g);
         if (ec != hipSuccess) {
             (void)hipGetLastError();
