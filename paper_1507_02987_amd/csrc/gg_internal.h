@@ -139,10 +139,15 @@ struct KeyWord {
 // ---------------------------------------------------------------- launchers
 // Every launcher only enqueues work on `st`; sizes are checked by the caller.
 
+// bq[b]: the query of base b * kBlock; *err (host memory) is set at a byte outside the
+// alphabet; qpack, when given: the codes packed 16 bases to a word like the data bank,
+// (T + 15) / 16 + kPackSlack words.
 void launch_encode_kmers(const uint8_t *ascii, const int64_t *qoff, int32_t nq, int64_t T,
                          int32_t span, uint32_t mask, const uint32_t *list_off, uint8_t *qcode,
                          uint32_t *kcode, uint32_t *cnt, uint32_t *lhead, int32_t *qid,
-                         int32_t *err, int32_t *bq, hipStream_t st);
+                         int32_t *err, const int32_t *bq, uint32_t *qpack, hipStream_t st);
+// bytes (rounded up to 16) from pinned memory to the device; both 16-byte aligned.
+void launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st);
 // out[i] = sum of in[0..i) for i in [0, n]; in is u32, out u64.
 void launch_scan_u32_to_u64(const uint32_t *in, uint64_t *out, int64_t n, uint64_t *partials,
                             hipStream_t st);
@@ -343,7 +348,10 @@ void launch_fill_u32(uint32_t *p, size_t n, uint32_t v, hipStream_t st);
 // Read `bytes` (a multiple of 16) once and add their 32-bit words into *sum
 // (memory-counter calibration).
 void launch_stream_read(const void *src, size_t bytes, unsigned long long *sum, hipStream_t st);
-void launch_fill2_u32(uint32_t *a, size_t na, uint32_t *b, size_t nb, uint32_t v, hipStream_t st);
+// Before a batch's replays: plan[0..n) from pinned memory, *cursor, flags[0..nq) and (when
+// given) counts[0..nq) cleared.
+void launch_waves_begin(WaveCtl *plan, const WaveCtl *from, size_t n, uint32_t *cursor,
+                        uint32_t *flags, int32_t *counts, size_t nq, hipStream_t st);
 
 // ---- graph-replayed waves: the kernels below read the wave's sizes from ctl;
 // grids are sized for the largest wave of the batch (hits_cap, np_cap, nq_cap).
@@ -410,11 +418,12 @@ void launch_chain_write(const uint64_t *keys, uint32_t n, HitKeyLayout lay, int3
 void launch_cand_segments(const Cand *c, uint32_t n, int32_t nq, uint32_t *qstart, uint32_t *qend,
                           hipStream_t st);
 // Per-query report order in LDS (segments of at most kSegCap records; longer ones are
-// skipped).
+// skipped), to out, or as gg_hit rows to dev_out when given.  host_n: each query's count
+// once more, -1 for one that was skipped or flagged.
 void launch_report_seg(const Align *in, Align *out, const uint32_t *sel_off, int32_t nq,
                        HitKeyLayout lay, int32_t match, uint32_t *rstart, uint32_t *rend,
                        int32_t qa, int32_t cap, int32_t *dev_out, int32_t *dev_n, hipStream_t st,
-                       WaveCtl *ctl = nullptr);
+                       WaveCtl *ctl = nullptr, int32_t *host_n = nullptr);
 // queue_mem: extend_queue_bytes(n) bytes of device scratch.
 size_t extend_queue_bytes(uint32_t n);
 void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32_t *qpack,
@@ -422,8 +431,6 @@ void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32
                    int32_t match, int32_t mismatch, int32_t xdrop, Box *out, void *queue_mem,
                    int32_t lane_steps, hipStream_t st, const WaveCtl *ctl = nullptr,
                    uint32_t n_cap = 0, bool count_cleared = false);
-// The batch's T query codes packed 16 bases to a word ((T + 15) / 16 + kPackSlack words).
-void launch_pack_query(const uint8_t *qcode, int64_t T, uint32_t *qpack, hipStream_t st);
 void launch_box_keys(const Box *b, uint32_t n, KeyWord w, int32_t q_invalid, uint64_t *out,
                      const uint32_t *perm, hipStream_t st);
 void launch_align_keys(const Align *a, uint32_t n, KeyWord w, int32_t q_invalid, uint64_t *out,

@@ -386,39 +386,37 @@ __global__ __launch_bounds__(kBlock) void k_encode_kmers(
     const uint8_t *__restrict__ ascii, const int64_t *__restrict__ qoff, int32_t nq, int64_t T,
     int32_t span, uint32_t mask, const uint32_t *__restrict__ list_off, uint8_t *__restrict__ qcode,
     uint32_t *__restrict__ kcode, uint32_t *__restrict__ cnt, uint32_t *__restrict__ lhead,
-    int32_t *__restrict__ qid, int32_t *__restrict__ err, const int32_t *__restrict__ bq)
+    int32_t *__restrict__ qid, int32_t *err, const int32_t *__restrict__ bq,
+    uint32_t *__restrict__ qpack)
 {
-    // the block's bases and the span after them, coded once in LDS; the block's
-    // first and last queries found once (bq: the query of each block's first base,
-    // so the next block's bounds this one's last)
+    // the block's bases and the span after them, coded once in LDS; the block's first
+    // and last queries are bq's (the query of each block's first base, so the next
+    // block's bounds this one's last)
     __shared__ uint8_t s_c[kBlock + 32];
     __shared__ int32_t s_q[2];
     const int64_t g0 = (int64_t)blockIdx.x * kBlock;
-    if (bq) {
-        if (threadIdx.x < 2) {
-            const bool last = g0 + kBlock >= T;
-            s_q[threadIdx.x] = threadIdx.x == 0 ? bq[blockIdx.x] : (last ? nq - 1 : bq[blockIdx.x + 1]);
-        }
-    } else if (threadIdx.x < 2) {
-        const int64_t x = min(g0 + (int64_t)(threadIdx.x ? kBlock - 1 : 0), T - 1);
-        int32_t lo = 0, hi = nq - 1;  // last query whose first base is <= x
-        while (lo < hi) {
-            const int32_t mid = (lo + hi + 1) >> 1;
-            if (qoff[mid] <= x) lo = mid;
-            else hi = mid - 1;
-        }
-        s_q[threadIdx.x] = lo;
-    }
+    const bool last = g0 + kBlock >= T;
+    if (threadIdx.x < 2)
+        s_q[threadIdx.x] = threadIdx.x == 0 ? bq[blockIdx.x] : (last ? nq - 1 : bq[blockIdx.x + 1]);
     for (int32_t x = threadIdx.x; x < kBlock + 32; x += kBlock) {
         const int64_t gx = g0 + x;
         int32_t c = gx < T ? base_code(ascii[gx]) : 0;
         if (c < 0) {
-            if (x < kBlock) atomicOr(err, 1);  // flagged by the base's own block
+            if (x < kBlock) *err = 1;  // flagged by the base's own block
             c = 0;
         }
         s_c[x] = (uint8_t)c;
     }
     __syncthreads();
+    constexpr int kWords = kBlock / 16;
+    if (qpack && threadIdx.x < kWords + kPackSlack) {  // packed, zeros after the last
+        const int64_t w = (int64_t)blockIdx.x * kWords + threadIdx.x;
+        uint32_t v = 0;
+        if (threadIdx.x < kWords)
+#pragma unroll
+            for (int t = 0; t < 16; ++t) v |= (uint32_t)s_c[16 * threadIdx.x + t] << (30 - 2 * t);
+        if (threadIdx.x < kWords || (last && w < (T + 15) / 16 + kPackSlack)) qpack[w] = v;
+    }
     const int64_t g = g0 + threadIdx.x;
     if (g >= T) return;
     qcode[g] = s_c[threadIdx.x];
@@ -441,28 +439,32 @@ __global__ __launch_bounds__(kBlock) void k_encode_kmers(
     lhead[g] = head;
 }
 
-// bq[b] = the query holding base b * kBlock, for every encode block b: each
-// non-empty query writes the blocks that start inside it.
-__global__ void k_block_query(const int64_t *__restrict__ qoff, int32_t nq,
-                              int32_t *__restrict__ bq)
-{
-    const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nq) return;
-    for (int64_t b = (qoff[q] + kBlock - 1) / kBlock; b * kBlock < qoff[q + 1]; ++b)
-        bq[b] = q;
-}
-
 void launch_encode_kmers(const uint8_t *ascii, const int64_t *qoff, int32_t nq, int64_t T,
                          int32_t span, uint32_t mask, const uint32_t *list_off, uint8_t *qcode,
                          uint32_t *kcode, uint32_t *cnt, uint32_t *lhead, int32_t *qid,
-                         int32_t *err, int32_t *bq, hipStream_t st)
+                         int32_t *err, const int32_t *bq, uint32_t *qpack, hipStream_t st)
 {
     if (T <= 0) return;
     const int64_t nb = (T + kBlock - 1) / kBlock;
-    if (bq) k_block_query<<<(nq + kBlock - 1) / kBlock, kBlock, 0, st>>>(qoff, nq, bq);
     k_encode_kmers<<<dim3((uint32_t)nb), dim3(kBlock), 0, st>>>(ascii, qoff, nq, T, span, mask,
                                                                 list_off, qcode, kcode, cnt, lhead,
-                                                                qid, err, bq);
+                                                                qid, err, bq, qpack);
+}
+
+// A batch's small uploads from pinned memory by a kernel, 16 bytes a thread: the call
+// costs a launch (8 us of the host), an asynchronous copy 15 to 30.
+__global__ void k_upload(uint4 *__restrict__ dst, const uint4 *__restrict__ src, size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
+void launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st)
+{
+    const size_t n = (bytes + 15) / 16;
+    if (n)
+        k_upload<<<(uint32_t)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+            static_cast<uint4 *>(dst), static_cast<const uint4 *>(src), n);
 }
 
 // ------------------------------------------------------------------ scans
@@ -1881,22 +1883,32 @@ void launch_stream_read(const void *src, size_t bytes, unsigned long long *sum, 
     k_stream_read<<<(uint32_t)nb, kBlock, 0, st>>>(static_cast<const uint4 *>(src), n16, sum);
 }
 
-// Two arrays set to v in one launch (a graph node less than two fills).
-__global__ void k_fill2_u32(uint32_t *__restrict__ a, size_t na, uint32_t *__restrict__ b,
-                            size_t nb, uint32_t v)
+// Before a batch's replays: its plan (nplan words, from pinned memory), the wave cursor and
+// the queries' flags and counts.
+__global__ void k_waves_begin(uint32_t *__restrict__ plan, const uint32_t *__restrict__ from,
+                              size_t nplan, uint32_t *__restrict__ cursor,
+                              uint32_t *__restrict__ flags, uint32_t *__restrict__ counts,
+                              size_t nq)
 {
     const size_t step = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += step) {
-        if (i < na) a[i] = v;
-        else b[i - na] = v;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0) *cursor = 0;
+    for (size_t i = i0; i < nplan; i += step) plan[i] = from[i];
+    for (size_t i = i0; i < nq; i += step) {
+        flags[i] = 0;
+        if (counts) counts[i] = 0;
     }
 }
 
-void launch_fill2_u32(uint32_t *a, size_t na, uint32_t *b, size_t nb, uint32_t v, hipStream_t st)
+void launch_waves_begin(WaveCtl *plan, const WaveCtl *from, size_t n, uint32_t *cursor,
+                        uint32_t *flags, int32_t *counts, size_t nq, hipStream_t st)
 {
-    if (na + nb == 0) return;
-    const size_t blocks = std::min<size_t>((na + nb + kBlock - 1) / kBlock, 4096);
-    k_fill2_u32<<<(uint32_t)blocks, kBlock, 0, st>>>(a, na, b, nb, v);
+    static_assert(sizeof(WaveCtl) % sizeof(uint32_t) == 0, "copied by words");
+    const size_t words = n * (sizeof(WaveCtl) / sizeof(uint32_t));
+    const size_t nb = std::min<size_t>((std::max(words, nq) + kBlock - 1) / kBlock, 4096);
+    k_waves_begin<<<(uint32_t)std::max<size_t>(nb, 1), kBlock, 0, st>>>(
+        reinterpret_cast<uint32_t *>(plan), reinterpret_cast<const uint32_t *>(from), words, cursor,
+        flags, reinterpret_cast<uint32_t *>(counts), nq);
 }
 
 // Scratch of a one-sweep sort of n keys: digit counts (8 passes x 256), tile
@@ -3718,30 +3730,6 @@ __device__ __forceinline__ uint32_t queue_slot(bool need, uint32_t *__restrict__
     return base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
 }
 
-// The batch's query codes packed 16 to a word like the data bank (first base in
-// the top bits), for the extension's word compares; kPackSlack spare words at the end.
-__global__ void k_pack_query(const uint8_t *__restrict__ qcode, int64_t T,
-                             uint32_t *__restrict__ qpack, int64_t nwords)
-{
-    const int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= nwords) return;
-    uint32_t v = 0;
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const int64_t g = 16 * w + t;
-        const uint32_t c = g < T ? (uint32_t)(qcode[g] & 3u) : 0u;
-        v |= c << (30 - 2 * t);
-    }
-    qpack[w] = v;
-}
-
-void launch_pack_query(const uint8_t *qcode, int64_t T, uint32_t *qpack, hipStream_t st)
-{
-    const int64_t nwords = (T + 15) / 16 + kPackSlack;
-    k_pack_query<<<(uint32_t)((nwords + kBlock - 1) / kBlock), kBlock, 0, st>>>(qcode, T, qpack,
-                                                                             nwords);
-}
-
 // X-drop walk of one lane, 32 steps per round.  The query and data-bank bases of the
 // round's steps are read as packed words and compared at once (a 2-bit XOR): step i
 // in bits 2i+1:2i of x[0], or of x[1] for steps 16 to 31.  A left walk's bases are read
@@ -4623,7 +4611,8 @@ __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__
                                                        uint32_t *__restrict__ rend, int32_t qa,
                                                        int32_t cap, int32_t *__restrict__ dev_out,
                                                        int32_t *__restrict__ dev_n,
-                                                       WaveCtl *__restrict__ ctl)
+                                                       WaveCtl *__restrict__ ctl,
+                                                       int32_t *__restrict__ host_n)
 {
     __shared__ Align s_r[kSegCap];
     __shared__ uint64_t s_key[kSegCap];
@@ -4636,8 +4625,9 @@ __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__
         lay = ctl->lay;
     }
     const uint32_t a0 = sel_off[ql], n = sel_off[ql + 1] - a0;
-    if (ctl && n > (uint32_t)kSegCap && threadIdx.x == 0) ctl->qflag[qa + ql] = 1u;
-    if (n > (uint32_t)kSegCap) return;  // longer segments take the global sort
+    const bool over = n > (uint32_t)kSegCap || (ctl && ctl->qflag[qa + ql]);
+    if (over && host_n && threadIdx.x == 0) host_n[qa + ql] = -1;
+    if (over) return;  // longer segments take the global sort
     if (threadIdx.x == 0) s_valid = 0;
     __syncthreads();
     if (n > 0) {
@@ -4654,21 +4644,15 @@ __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__
             k.bits = 99;  // the box is left to the whole comparison
             return k;
         };
-        auto put = [&](const Align &a, uint32_t at) {
-            out[a0 + at] = a;
-            if (!dev_out || at >= (uint32_t)cap || a.score <= 0) return;
-            int32_t *dst = dev_out + ((size_t)(qa + ql) * (size_t)cap + at) * kHitInts;
-            const int32_t *src = reinterpret_cast<const int32_t *>(&a);
-#pragma unroll
-            for (int f = 0; f < kHitInts; ++f) dst[f] = src[1 + f];
-        };
         if (n <= (uint32_t)kBlock) {
             Align a{};
             if (threadIdx.x < n) a = in[a0 + threadIdx.x];
             const bool valid = a.score > 0;
             if (valid) atomicAdd(&s_valid, 1u);
             const uint32_t at = seg_rank(a, valid, n, key, AlignLess(), s_r, s_key, s_w);
-            if (threadIdx.x < n) put(a, at);
+            if (threadIdx.x < n) s_r[at] = a;
+            __syncthreads();
+            if (!dev_out && threadIdx.x < n) out[a0 + at] = a;
         } else {
             uint32_t v = 0;
             for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
@@ -4679,7 +4663,19 @@ __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__
             seg_order(
                 s_r, n, [](const Align &a) { return a.score > 0; }, key, AlignLess(), s_key, s_w);
             const uint16_t *s_ix = reinterpret_cast<const uint16_t *>(s_key);
-            for (uint32_t i = threadIdx.x; i < n; i += kBlock) put(s_r[s_ix[i]], i);
+            if (!dev_out)
+                for (uint32_t i = threadIdx.x; i < n; i += kBlock) out[a0 + i] = s_r[s_ix[i]];
+        }
+        if (dev_out) {  // whole rows, so that a write to host memory is one of 64 bytes
+            const uint16_t *s_ix = reinterpret_cast<const uint16_t *>(s_key);
+            const uint32_t m = min(s_valid, (uint32_t)cap);
+            int32_t *dst = dev_out + ((size_t)(qa + ql) * (size_t)cap) * kHitInts;
+            for (uint32_t e = threadIdx.x; e < m * kHitInts; e += kBlock) {
+                const uint32_t i = e / kHitInts;
+                const int32_t *src = reinterpret_cast<const int32_t *>(
+                    &s_r[n <= (uint32_t)kBlock ? i : s_ix[i]]);
+                dst[e] = src[1 + e % kHitInts];
+            }
         }
     }
     const uint32_t nv = s_valid;
@@ -4687,17 +4683,18 @@ __global__ __launch_bounds__(kBlock) void k_report_seg(const Align *__restrict__
         rstart[ql] = a0;
         rend[ql] = a0 + nv;
         if (dev_n) dev_n[qa + ql] = (int32_t)nv;
+        if (host_n) host_n[qa + ql] = (int32_t)nv;
     }
 }
 
 void launch_report_seg(const Align *in, Align *out, const uint32_t *sel_off, int32_t nq,
                        HitKeyLayout lay, int32_t match, uint32_t *rstart, uint32_t *rend,
                        int32_t qa, int32_t cap, int32_t *dev_out, int32_t *dev_n, hipStream_t st,
-                       WaveCtl *ctl)
+                       WaveCtl *ctl, int32_t *host_n)
 {
     if (nq > 0)
         k_report_seg<<<nq, kBlock, 0, st>>>(in, out, sel_off, lay, match, rstart, rend, qa, cap,
-                                            dev_out, dev_n, ctl);
+                                            dev_out, dev_n, ctl, host_n);
 }
 
 // ------------------------------------------------------------------ S7: merge overlaps

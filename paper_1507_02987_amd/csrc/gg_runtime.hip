@@ -100,12 +100,12 @@ struct StageTime {
 struct Workspace {
     int device = 0;
     hipStream_t st = nullptr;
-    DevBuf ascii, qoff, qcode, qpack, kcode, cnt, lhead, qid, hoff, partials, qtot, err;
+    DevBuf ascii, qoff, qcode, qpack, kcode, cnt, lhead, qid, hoff, partials;
     DevBuf hrel, pbase, akey, keys, keys_alt, hist, rs_partials;
     DevBuf cands, ccount, cand_q, cand_off, boxes, boxes2, boxes3, wkeys, wkeys_alt, perm, perm_alt;
     DevBuf qstart, qend, nsel, sel_off, rstart, rend, aligns, aligns2, cells_q;
     DevBuf bplan, bcount, boff, bcands, btmp, bcoff, ctmp, cursor, qcur, bound_q, bound_off,
-        btmp_b, bounds, blist, pcnt, cells_box, rbounds, rbelow, os_scratch, xqueue, gout, gn,
+        btmp_b, bounds, blist, pcnt, cells_box, rbounds, rbelow, os_scratch, xqueue, gout,
         gctl, gplan, gcursor, gqflag, stiles, gtiles;
     DevBuf tb_in, tb_dir, tb_out;       // traceback: uploads, directions, results
     DevBuf lhist, lthr, lvalid, ltile, lbinq;  // selection prefilter
@@ -114,12 +114,12 @@ struct Workspace {
     DevBuf mbig, mranges;               // merge groups that may outgrow an LDS window
     DevBuf selbox;                      // the box index of each selection (replayed waves)
     DevBuf bsw_order;                   // the aligner's class counts and box order
-    DevBuf bq;                          // the query of each encode block's first base
     DevBuf qctx, sbase, scount;         // run starts from contexts: per position, per query
-    // small pinned staging: [0] a wave's counts, [1] a batch's query offsets and hit
-    // totals, [2] the replayed waves' plan, overflow flags and result counts
-    void *pinned[3] = {nullptr, nullptr, nullptr};
-    size_t pinned_cap[3] = {0, 0, 0};
+    // small pinned staging: [0] a wave's counts, [1] a batch's hit totals, query offsets
+    // and small texts, [2] the replayed waves' plan, [3] their result counts and [4] their
+    // results (where a captured graph writes: nothing else lies in those two)
+    void *pinned[5] = {};
+    size_t pinned_cap[5] = {};
     // the captured wave graph and what it was captured for (every argument baked
     // into its nodes: capacities, parameters, buffer addresses)
     hipGraphExec_t gexec = nullptr;
@@ -137,15 +137,15 @@ struct Workspace {
     {
         if (st) (void)hipSetDevice(device);
         if (gexec) (void)hipGraphExecDestroy(gexec);
-        DevBuf *all[] = {&ascii, &qoff, &qcode, &qpack, &kcode, &cnt, &lhead, &qid, &hoff, &partials, &qtot, &err,
+        DevBuf *all[] = {&ascii, &qoff, &qcode, &qpack, &kcode, &cnt, &lhead, &qid, &hoff, &partials,
                          &hrel, &pbase, &akey, &keys, &keys_alt, &hist, &rs_partials, &cands,
                          &ccount, &cand_q, &cand_off, &boxes, &boxes2, &boxes3, &wkeys, &wkeys_alt, &perm,
                          &perm_alt, &qstart, &qend, &nsel, &sel_off, &rstart, &rend, &aligns, &aligns2,
                          &cells_q, &bplan, &bcount, &boff, &bcands, &btmp, &bcoff, &ctmp, &cursor, &qcur,
                          &bound_q, &bound_off, &btmp_b, &bounds, &blist, &pcnt, &cells_box,
-                         &rbounds, &rbelow, &os_scratch, &xqueue, &gout, &gn, &gctl, &gplan,
+                         &rbounds, &rbelow, &os_scratch, &xqueue, &gout, &gctl, &gplan,
                          &gcursor, &gqflag, &stiles, &gtiles, &tb_in, &tb_dir, &tb_out, &lhist, &lthr,
-                         &lvalid, &ltile, &lbinq, &fkept, &fkoff, &fflag, &ford, &tpos, &selbox, &bq,
+                         &lvalid, &ltile, &lbinq, &fkept, &fkoff, &fflag, &ford, &tpos, &selbox,
                          &mbig, &mranges, &bsw_order, &qctx, &sbase, &scount};
         for (DevBuf *b : all)
             if (b->p) (void)hipFree(b->p);
@@ -232,7 +232,8 @@ gg_status pinned(Workspace *ws, size_t bytes, void **p, int slot = 0)
         ws->pinned[slot] = nullptr;
         ws->pinned_cap[slot] = 0;
         size_t want = std::max<size_t>(bytes, 1 << 16);
-        HIPCHK(hipHostMalloc(&ws->pinned[slot], want, hipHostMallocDefault));
+        // coherent: kernels read and write it in place
+        HIPCHK(hipHostMalloc(&ws->pinned[slot], want, hipHostMallocMapped | hipHostMallocCoherent));
         ws->pinned_cap[slot] = want;
     }
     *p = ws->pinned[slot];
@@ -1597,6 +1598,10 @@ gg_status run_packed(const gg_index *ix, Workspace *ws, const gg_params *p, cons
     return GG_OK;
 }
 
+// Replayed waves' result rows that are written to pinned memory (which the workspace
+// then keeps).
+constexpr size_t kPinnedOut = 8u << 20;
+
 gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const gg_params *p,
                           const char *qbuf, const std::vector<int64_t> &qoff_h,
                           const std::vector<uint64_t> &qtot, int64_t nq, BatchOut &bo,
@@ -1735,8 +1740,6 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     TRY(ensure(ws->aligns2, sizeof(Align) * std::max<uint32_t>(sel_cap, 1)));
     TRY(ensure(ws->selbox, sizeof(uint32_t) * std::max<uint32_t>(sel_cap, 1)));
     TRY(ensure(ws->bsw_order, sizeof(uint32_t) * ((size_t)sel_cap + 64)));
-    TRY(ensure(ws->gout, sizeof(gg_hit) * nq_out * std::max(cap, 1)));
-    TRY(ensure(ws->gn, sizeof(int32_t) * nq_out));
     TRY(ensure(ws->gctl, sizeof(WaveCtl)));
     TRY(ensure(ws->gplan, sizeof(WaveCtl) * nwave_cap));
     TRY(ensure(ws->gcursor, sizeof(uint32_t) * 4));
@@ -1766,19 +1769,30 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     for (int32_t v : {p->match, p->mismatch, p->gap_open, p->gap_extend, p->band, p->xdrop,
                       p->max_gap, p->min_hsp_len, p->max_hits})
         key.push_back((uint64_t)(uint32_t)v);
-    // device-form results go straight to the caller's buffers
+    // device-form results go straight to the caller's buffers, host-form results of up to
+    // kPinnedOut bytes of rows to pinned memory (only rows with a hit cross the link),
+    // larger ones to the device and from there in one copy; counts to pinned memory
+    const size_t out_bytes = sizeof(gg_hit) * nq_out * std::max(cap, 1);
     const bool direct = bo.device && cap > 0;
-    int32_t *gout = direct ? reinterpret_cast<int32_t *>(bo.out) : as<int32_t>(ws->gout);
-    int32_t *gn = bo.device ? bo.n_out : as<int32_t>(ws->gn);
+    const bool rows_here = !bo.device && out_bytes <= kPinnedOut;
+    void *pin_n, *pin_out = nullptr;
+    TRY(pinned(ws, sizeof(int32_t) * nq_out, &pin_n, 3));
+    if (rows_here) TRY(pinned(ws, out_bytes, &pin_out, 4));
+    else if (!direct) TRY(ensure(ws->gout, out_bytes));
+    int32_t *nout = static_cast<int32_t *>(pin_n);
+    int32_t *gout = direct ? reinterpret_cast<int32_t *>(bo.out)
+                           : rows_here ? static_cast<int32_t *>(pin_out) : as<int32_t>(ws->gout);
+    int32_t *gn = bo.device ? bo.n_out : nullptr;
     key.push_back((uint64_t)(uintptr_t)gout);
     key.push_back((uint64_t)(uintptr_t)gn);
+    key.push_back((uint64_t)(uintptr_t)nout);
     for (const DevBuf *b : {&ws->hoff, &ws->qoff, &ws->kcode, &ws->qid, &ws->qcode, &ws->qpack,
                             &ws->hrel,
                             &ws->pbase, &ws->akey, &ws->keys, &ws->keys_alt, &ws->hist,
                             &ws->rs_partials, &ws->ccount, &ws->partials, &ws->cands, &ws->boxes,
                             &ws->boxes2, &ws->boxes3, &ws->xqueue, &ws->qstart, &ws->qend,
                             &ws->cand_q, &ws->cand_off, &ws->nsel, &ws->sel_off, &ws->rstart,
-                            &ws->rend, &ws->aligns, &ws->aligns2, &ws->gout, &ws->gn, &ws->gctl,
+                            &ws->rend, &ws->aligns, &ws->aligns2, &ws->gctl,
                             &ws->gplan, &ws->gcursor, &ws->gqflag, &ws->gtiles, &ws->fkept,
                             &ws->fkoff, &ws->ford, &ws->tpos, &ws->selbox, &ws->bsw_order,
                             &ws->cnt, &ws->lhead, &ws->qctx, &ws->sbase, &ws->scount})
@@ -1864,7 +1878,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                    as<uint32_t>(ws->bsw_order));
         launch_report_seg(as<Align>(ws->aligns), as<Align>(ws->aligns2), as<uint32_t>(ws->sel_off),
                           nq_cap, HitKeyLayout{}, p->match, as<uint32_t>(ws->rstart),
-                          as<uint32_t>(ws->rend), 0, cap, gout, gn, st, ctl);
+                          as<uint32_t>(ws->rend), 0, cap, gout, gn, st, ctl, nout);
         const hipError_t ec = hipStreamEndCapture(st, &g);
         if (ec != hipSuccess) {
             (void)hipGetLastError();
@@ -1882,17 +1896,15 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
 
     // replay it once per wave
     const size_t W = plan.size();
-    // staging: plan [W] | query flags [nq] | result counts [nq] | filter order [nq]
+    // staging: plan [W] | filter order [nq]
     void *pin;
-    TRY(pinned(ws, sizeof(WaveCtl) * W + 3 * sizeof(int32_t) * nq + 64, &pin, 2));
+    TRY(pinned(ws, sizeof(WaveCtl) * W + sizeof(int32_t) * nq + 64, &pin, 2));
     WaveCtl *h_plan = static_cast<WaveCtl *>(pin);
-    uint32_t *qflags = reinterpret_cast<uint32_t *>(h_plan + W);
-    int32_t *nout = reinterpret_cast<int32_t *>(qflags + nq);
     for (WaveCtl &w : plan) w.qflag = as<uint32_t>(ws->gqflag);
     std::copy(plan.begin(), plan.end(), h_plan);
-    HIPCHK(hipMemcpyAsync(ws->gplan.p, h_plan, sizeof(WaveCtl) * W, hipMemcpyHostToDevice, st));
+    std::fill(nout, nout + nq, 0);
     if (filt) {  // each wave's queries, largest first, at the wave's own positions
-        int32_t *h_ord = nout + nq;
+        int32_t *h_ord = reinterpret_cast<int32_t *>(h_plan + W);
         for (const WaveCtl &w : plan) {
             filter_order(qtot.data() + w.qa, w.nqw, h_ord + w.qa);
         }
@@ -1901,29 +1913,30 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     if (!tiles.empty())
         HIPCHK(hipMemcpyAsync(ws->gtiles.p, tiles.data(), sizeof(SortTile) * tiles.size(),
                               hipMemcpyHostToDevice, st));
-    launch_fill2_u32(cursor, 1, reinterpret_cast<uint32_t *>(gn), (size_t)nq, 0u, st);
-    launch_fill_u32(as<uint32_t>(ws->gqflag), (size_t)nq, 0u, st);
+    launch_waves_begin(as<WaveCtl>(ws->gplan), h_plan, W, cursor, as<uint32_t>(ws->gqflag), gn,
+                       (size_t)nq, st);
     prof.begin("graph");
     for (size_t w = 0; w < W; ++w) HIPCHK(hipGraphLaunch(ws->gexec, st));
     prof.end((int64_t)W);
-    HIPCHK(hipMemcpyAsync(qflags, ws->gqflag.p, sizeof(uint32_t) * nq, hipMemcpyDeviceToHost,
-                          st));
-    HIPCHK(hipMemcpyAsync(nout, gn, sizeof(int32_t) * nq, hipMemcpyDeviceToHost, st));
-    if (cap > 0 && !direct)
+    if (cap > 0 && !direct && !rows_here)
         HIPCHK(hipMemcpyAsync(bo.out, ws->gout.p, sizeof(gg_hit) * (size_t)nq * cap,
                               hipMemcpyDeviceToHost, st));
     SYNC(st);
     prof.collect();
     *used = true;
-    if (!bo.device) std::copy(nout, nout + nq, bo.n_out);
-    for (int64_t q = 0; q < nq; ++q)
-        if (nout[(size_t)q] > cap) bo.truncated = true;
+    for (int64_t q = 0; q < nq; ++q) {
+        if (!bo.device) bo.n_out[q] = std::max(nout[q], 0);
+        if (nout[q] > cap) bo.truncated = true;
+        if (rows_here && nout[q] > 0 && cap > 0)
+            memcpy(bo.out + (size_t)q * cap, static_cast<gg_hit *>(pin_out) + (size_t)q * cap,
+                   sizeof(gg_hit) * (size_t)std::min(nout[q], cap));
+    }
     // the regular path for the queries over a wave and those whose kept hits, runs
     // or selections outgrew a per-query LDS sort
     std::vector<std::pair<int32_t, int32_t>> rest;
     std::vector<int32_t> idx;
     for (int32_t q = 0; q < (int32_t)nq; ++q) {
-        if (qtot[q] <= graph_q && !qflags[q]) continue;
+        if (qtot[q] <= graph_q && nout[q] >= 0) continue;  // -1: flagged
         idx.push_back(q);
         if (!rest.empty() && rest.back().second == q) rest.back().second = q + 1;
         else rest.emplace_back(q, q + 1);
@@ -1938,11 +1951,83 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     return run_packed(ix, ws, p, qbuf, qoff_h, idx, bo, budget_bytes, false);
 }
 
+// Query text up to this long is staged in pinned memory and goes up with the offsets;
+// longer text by a copy from the caller's memory.
+constexpr int64_t kStageText = 256 << 10;
+
+// S1 and S2 of a batch: its nq queries, T bases of text (on the host, or the device) at
+// offsets qoff, encoded, counted and scanned.  Returns with the stream idle and
+// *qtot[q] the hits of query q (pinned memory, until the next batch).  One upload, four
+// kernels and one wait; the kernels write totals and the error flag to pinned memory.
+gg_status encode_batch(const gg_index *ix, Workspace *ws, Prof *prof, const char *text, bool device,
+                       const int64_t *qoff, int64_t nq, int64_t T, bool pack,
+                       const uint64_t **qtot)
+{
+    hipStream_t st = ws->st;
+    const int64_t nb = (T + kBlock - 1) / kBlock;
+    const bool staged = !device && T <= kStageText;
+    // staging: hit totals [nq] | error flag | to 16 bytes | uploaded: query offsets [nq + 1]
+    // | query of each encode block's first base [nb + 1] | to 16 bytes | text, when staged
+    const auto up16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+    const size_t o_up = up16(sizeof(uint64_t) * ((size_t)nq + 1));
+    const size_t o_bq = sizeof(int64_t) * ((size_t)nq + 1);
+    const size_t o_text = up16(o_bq + sizeof(int32_t) * ((size_t)nb + 1));
+    const size_t up = o_text + (staged ? up16((size_t)T) : 0);
+    TRY(ensure(ws->qoff, up));
+    if (!device && !staged) TRY(ensure(ws->ascii, T));
+    TRY(ensure(ws->qcode, T));
+    TRY(ensure(ws->kcode, sizeof(uint32_t) * T));
+    TRY(ensure(ws->cnt, sizeof(uint32_t) * T));
+    TRY(ensure(ws->lhead, sizeof(uint32_t) * T));
+    TRY(ensure(ws->qid, sizeof(int32_t) * T));
+    TRY(ensure(ws->hoff, sizeof(uint64_t) * (T + 1)));
+    TRY(ensure(ws->partials, sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(T, nq + 1))));
+    if (pack)
+        TRY(ensure(ws->qpack, sizeof(uint32_t) * (kPackFront + (size_t)(T + 15) / 16 + kPackSlack)));
+    void *pin;
+    TRY(pinned(ws, o_up + up, &pin, 1));
+    uint64_t *h_qtot = static_cast<uint64_t *>(pin);
+    int32_t *h_err = reinterpret_cast<int32_t *>(h_qtot + nq);
+    char *h_up = static_cast<char *>(pin) + o_up;
+    int64_t *h_qoff = reinterpret_cast<int64_t *>(h_up);
+    int32_t *h_bq = reinterpret_cast<int32_t *>(h_up + o_bq);
+    *h_err = 0;
+    for (int64_t q = 0; q <= nq; ++q) h_qoff[q] = qoff[q] - qoff[0];
+    for (int64_t q = 0, b = 0; q < nq; ++q)
+        for (; b * kBlock < h_qoff[q + 1]; ++b) h_bq[b] = (int32_t)q;
+    const uint8_t *ascii;
+    if (device) {
+        ascii = reinterpret_cast<const uint8_t *>(text);
+    } else if (staged) {
+        memcpy(h_up + o_text, text, (size_t)T);
+        ascii = as<uint8_t>(ws->qoff) + o_text;
+    } else {
+        HIPCHK(hipMemcpyAsync(ws->ascii.p, text, T, hipMemcpyHostToDevice, st));
+        ascii = as<uint8_t>(ws->ascii);
+    }
+    launch_upload(ws->qoff.p, h_up, up, st);
+    if (prof) prof->begin("encode");
+    launch_encode_kmers(ascii, as<int64_t>(ws->qoff), (int32_t)nq, T, ix->span, ix->mask,
+                        ix->d_list_off, as<uint8_t>(ws->qcode), as<uint32_t>(ws->kcode),
+                        as<uint32_t>(ws->cnt), as<uint32_t>(ws->lhead), as<int32_t>(ws->qid), h_err,
+                        reinterpret_cast<int32_t *>(as<uint8_t>(ws->qoff) + o_bq),
+                        pack ? qpack_of(ws) : nullptr, st);
+    if (prof) prof->end(T);
+    if (prof) prof->begin("scan");
+    launch_scan_u32_to_u64(as<uint32_t>(ws->cnt), as<uint64_t>(ws->hoff), T,
+                           as<uint64_t>(ws->partials), st);
+    launch_query_totals(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), (int32_t)nq, h_qtot, st);
+    if (prof) prof->end(T);
+    SYNC(st);
+    if (*h_err) return GG_EINVAL;
+    *qtot = h_qtot;
+    return GG_OK;
+}
+
 gg_status run_batch(const gg_index *ix, Workspace *ws, const char *qbuf, const int64_t *qoff,
                     int64_t nq, const gg_params *p, BatchOut &bo, uint64_t budget_bytes,
                     bool allow_graph)
 {
-    hipStream_t st = ws->st;
     if (nq == 0) return GG_OK;
     std::vector<int64_t> qoff_h(nq + 1);
     for (int64_t q = 0; q <= nq; ++q) qoff_h[q] = qoff[q] - qoff[0];
@@ -1953,57 +2038,9 @@ gg_status run_batch(const gg_index *ix, Workspace *ws, const char *qbuf, const i
     if (T > (int64_t)INT32_MAX) return GG_EINVAL;
     if (T > 0 && !qbuf) return GG_EINVAL;
     Prof prof(ix, ws);
-
-    const uint8_t *ascii = nullptr;
-    if (bo.device) {
-        ascii = reinterpret_cast<const uint8_t *>(qbuf) + qoff[0];
-    } else {
-        TRY(ensure(ws->ascii, T));
-        ascii = as<uint8_t>(ws->ascii);
-    }
-    TRY(ensure(ws->qoff, sizeof(int64_t) * (nq + 1)));
-    TRY(ensure(ws->qcode, T));
-    TRY(ensure(ws->kcode, sizeof(uint32_t) * T));
-    TRY(ensure(ws->cnt, sizeof(uint32_t) * T));
-    TRY(ensure(ws->lhead, sizeof(uint32_t) * T));
-    TRY(ensure(ws->qid, sizeof(int32_t) * T));
-    TRY(ensure(ws->hoff, sizeof(uint64_t) * (T + 1)));
-    TRY(ensure(ws->partials, sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(T, nq + 1))));
-    TRY(ensure(ws->qtot, sizeof(uint64_t) * nq));
-    TRY(ensure(ws->err, sizeof(int32_t) * 4));
-    TRY(ensure(ws->bq, sizeof(int32_t) * ((size_t)(T + kBlock - 1) / kBlock + 1)));
-    if (T > 0 && !bo.device)
-        HIPCHK(hipMemcpyAsync(ws->ascii.p, qbuf + qoff[0], T, hipMemcpyHostToDevice, st));
-    // staging: query offsets [nq + 1] | hit totals [nq] | error flag
-    void *pin;
-    TRY(pinned(ws, sizeof(int64_t) * (2 * (size_t)nq + 2), &pin, 1));
-    int64_t *h_qoff = static_cast<int64_t *>(pin);
-    uint64_t *h_qtot = reinterpret_cast<uint64_t *>(h_qoff + nq + 1);
-    int32_t *h_err = reinterpret_cast<int32_t *>(h_qtot + nq);
-    std::copy(qoff_h.begin(), qoff_h.end(), h_qoff);
-    HIPCHK(hipMemcpyAsync(ws->qoff.p, h_qoff, sizeof(int64_t) * (nq + 1), hipMemcpyHostToDevice,
-                          st));
-    HIPCHK(hipMemsetAsync(ws->err.p, 0, sizeof(int32_t), st));
-
-    // ---- S1 encode + S2 count and scan
-    prof.begin("encode");
-    launch_encode_kmers(ascii, as<int64_t>(ws->qoff), (int32_t)nq, T, ix->span, ix->mask,
-                        ix->d_list_off, as<uint8_t>(ws->qcode), as<uint32_t>(ws->kcode),
-                        as<uint32_t>(ws->cnt), as<uint32_t>(ws->lhead), as<int32_t>(ws->qid),
-                        as<int32_t>(ws->err), as<int32_t>(ws->bq), st);
-    prof.end(T);
-    prof.begin("scan");
-    launch_scan_u32_to_u64(as<uint32_t>(ws->cnt), as<uint64_t>(ws->hoff), T,
-                           as<uint64_t>(ws->partials), st);
-    launch_query_totals(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), (int32_t)nq,
-                        as<uint64_t>(ws->qtot), st);
-    prof.end(T);
-    TRY(ensure(ws->qpack, sizeof(uint32_t) * (kPackFront + (size_t)(T + 15) / 16 + kPackSlack)));
-    launch_pack_query(as<uint8_t>(ws->qcode), T, qpack_of(ws), st);
-    HIPCHK(hipMemcpyAsync(h_qtot, ws->qtot.p, sizeof(uint64_t) * nq, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(h_err, ws->err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    SYNC(st);
-    if (*h_err) return GG_EINVAL;
+    const uint64_t *h_qtot = nullptr;
+    TRY(encode_batch(ix, ws, &prof, T > 0 ? qbuf + qoff[0] : nullptr, bo.device, qoff_h.data(), nq,
+                     T, true, &h_qtot));
     const std::vector<uint64_t> qtot(h_qtot, h_qtot + nq);
 
     // ---- waves: consecutive queries whose stored hit keys fit the budget and the key
@@ -2048,45 +2085,9 @@ gg_status count_hits(const gg_index *ix, const char *qbuf, const int64_t *qoff, 
     Workspace *ws = nullptr;
     TRY(get_ws(ix, &ws));
     auto run = [&]() -> gg_status {
-        hipStream_t st = ws->st;
-        TRY(ensure(ws->ascii, T));
-        TRY(ensure(ws->qoff, sizeof(int64_t) * (n_q + 1)));
-        TRY(ensure(ws->qcode, T));
-        TRY(ensure(ws->kcode, sizeof(uint32_t) * T));
-        TRY(ensure(ws->cnt, sizeof(uint32_t) * T));
-        TRY(ensure(ws->lhead, sizeof(uint32_t) * T));
-        TRY(ensure(ws->qid, sizeof(int32_t) * T));
-        TRY(ensure(ws->hoff, sizeof(uint64_t) * (T + 1)));
-        TRY(ensure(ws->partials,
-                   sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(T, n_q + 1))));
-        TRY(ensure(ws->qtot, sizeof(uint64_t) * n_q));
-        TRY(ensure(ws->err, sizeof(int32_t) * 4));
-        TRY(ensure(ws->bq, sizeof(int32_t) * ((size_t)(T + kBlock - 1) / kBlock + 1)));
-        void *pin;
-        TRY(pinned(ws, sizeof(int64_t) * (2 * (size_t)n_q + 2), &pin, 1));
-        int64_t *h_qoff = static_cast<int64_t *>(pin);
-        uint64_t *h_qtot = reinterpret_cast<uint64_t *>(h_qoff + n_q + 1);
-        int32_t *h_err = reinterpret_cast<int32_t *>(h_qtot + n_q);
-        for (int64_t q = 0; q <= n_q; ++q) h_qoff[q] = qoff[q] - qoff[0];
-        if (T > 0)
-            HIPCHK(hipMemcpyAsync(ws->ascii.p, qbuf + qoff[0], T, hipMemcpyHostToDevice, st));
-        HIPCHK(hipMemcpyAsync(ws->qoff.p, h_qoff, sizeof(int64_t) * (n_q + 1),
-                              hipMemcpyHostToDevice, st));
-        launch_fill_u32(as<uint32_t>(ws->err), 1, 0u, st);
-        launch_encode_kmers(as<uint8_t>(ws->ascii), as<int64_t>(ws->qoff), (int32_t)n_q, T,
-                            ix->span, ix->mask, ix->d_list_off, as<uint8_t>(ws->qcode),
-                            as<uint32_t>(ws->kcode), as<uint32_t>(ws->cnt),
-                            as<uint32_t>(ws->lhead), as<int32_t>(ws->qid), as<int32_t>(ws->err),
-                            as<int32_t>(ws->bq), st);
-        launch_scan_u32_to_u64(as<uint32_t>(ws->cnt), as<uint64_t>(ws->hoff), T,
-                               as<uint64_t>(ws->partials), st);
-        launch_query_totals(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), (int32_t)n_q,
-                            as<uint64_t>(ws->qtot), st);
-        HIPCHK(hipMemcpyAsync(h_qtot, ws->qtot.p, sizeof(uint64_t) * n_q, hipMemcpyDeviceToHost,
-                              st));
-        HIPCHK(hipMemcpyAsync(h_err, ws->err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SYNC(st);
-        if (*h_err) return GG_EINVAL;
+        const uint64_t *h_qtot = nullptr;
+        TRY(encode_batch(ix, ws, nullptr, T > 0 ? qbuf + qoff[0] : nullptr, false, qoff, n_q, T,
+                         false, &h_qtot));
         std::copy(h_qtot, h_qtot + n_q, hits);
         return GG_OK;
     };

@@ -169,6 +169,15 @@ def _u8(x) -> np.ndarray:
     return np.frombuffer(bytes(x), dtype=np.uint8)
 
 
+def _rows(raw: memoryview, first: int, n: int) -> np.ndarray:
+    """A copy of n hit records from record `first` of raw's bytes.  By bytes: numpy copies
+    structured arrays field by field (80 queries' hits in 580 us, 76 by bytes)."""
+    if n == 0:
+        return np.zeros(0, HIT_DTYPE)
+    size = HIT_DTYPE.itemsize
+    return np.frombuffer(bytearray(raw[first * size:(first + n) * size]), HIT_DTYPE)
+
+
 class Index:
     """gg_index_build / gg_index_free: device-resident data bank and inverted index."""
 
@@ -319,7 +328,7 @@ class Index:
                              cap, C.byref(n))
         if rc not in (GG_OK, GG_ETRUNC):
             return rc, np.zeros(0, HIT_DTYPE), 0
-        return rc, out[: min(n.value, cap)].copy(), n.value
+        return rc, _rows(memoryview(out.view(np.uint8)), 0, min(n.value, cap)), n.value
 
     def search_batch(self, qbuf, qoff, prm: Params, cap: int = 1024, stats: bool = False):
         """gg_search_batch: returns (status, list of hit arrays, counts, stats or None)."""
@@ -334,7 +343,8 @@ class Index:
                                    _ptr(st) if stats else None)
         if rc not in (GG_OK, GG_ETRUNC):
             return rc, [], nout[:nq], None
-        res = [out[i * cap: i * cap + min(int(nout[i]), cap)].copy() for i in range(nq)]
+        raw = memoryview(out.view(np.uint8))
+        res = [_rows(raw, i * cap, min(m, cap)) for i, m in enumerate(nout[:nq].tolist())]
         return rc, res, nout[:nq].copy(), (st[:nq] if stats else None)
 
     def search_batch_into(self, qbuf: np.ndarray, qoff: np.ndarray, prm: Params, out: np.ndarray,
@@ -446,7 +456,7 @@ class Server:
         n = C.c_int32()
         rc = lib().gg_serve_poll(self._h, ticket, _ptr(out), cap, C.byref(n), timeout_us)
         if rc in (GG_OK, GG_ETRUNC):
-            return rc, out[: min(n.value, cap)].copy(), n.value
+            return rc, _rows(memoryview(out.view(np.uint8)), 0, min(n.value, cap)), n.value
         return rc, np.zeros(0, HIT_DTYPE), 0
 
     def info(self) -> dict:
