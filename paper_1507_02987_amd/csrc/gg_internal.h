@@ -11,6 +11,7 @@ constexpr int32_t kNegInf = -(1 << 30);  // minus infinity of the alignment DP
 constexpr int kBlock = 256;              // threads per block for the stream kernels
 constexpr int kItems = 8;                // hits per thread in the gather and chain passes
 constexpr int kTile = kBlock * kItems;   // hits per gather / chain tile
+constexpr int kSubTile = 64 * kItems;    // and per wave
 constexpr int kSortItems = 8;            // keys per thread in the radix passes
 constexpr int kSortTile = kBlock * kSortItems;  // keys per radix tile
 constexpr int kRadixBits = 8;
@@ -113,9 +114,9 @@ struct CtxShape {
 // the wave; head: its list's first posting less its first hit, so that hit j of the
 // wave is posting head + j.
 struct alignas(16) QCtx {
-    uint32_t vm, n0, n1, p0, p1;
+    uint32_t vm, n0, n1, head;  // what a hit's windows after it need, in one load
+    uint32_t p0, p1;
     int32_t qpos, ql;
-    uint32_t head;
 };
 
 // Which box field feeds a sort-key field.
@@ -166,6 +167,7 @@ struct CtxPrep {
     const uint32_t *kcode = nullptr, *cnt = nullptr;  // per batch base
     uint32_t *sbase = nullptr, *scount = nullptr;     // per query of the wave
     int32_t span = 0, mmax = 0;
+    int32_t tile = kTile;  // hits between two entries of tile_pos
     CtxShape shape{};
 };
 void launch_wave_prep(const uint64_t *hoff, const int64_t *qoff, const uint32_t *lhead,

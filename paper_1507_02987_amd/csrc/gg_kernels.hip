@@ -729,7 +729,7 @@ __device__ __forceinline__ QCtx query_ctx(const CtxPrep &c, const uint32_t *__re
     }
     const uint2 n = ctx_pack(nc[0], nc[1], nc[2], c.shape);
     const uint2 p = ctx_pack(pc[0], pc[1], pc[2], c.shape);
-    return QCtx{vm, n.x, n.y, p.x, p.y, qpos, ql, head};
+    return QCtx{vm, n.x, n.y, head, p.x, p.y, qpos, ql};
 }
 
 // Per position of the wave: its first hit (relative to the wave), the index of its
@@ -766,10 +766,25 @@ __global__ void k_wave_prep(const uint64_t *__restrict__ hoff, const int64_t *__
     hrel[p] = (uint32_t)r0;
     if (p == np) return;
     const uint64_t r1 = hoff[g0 + p + 1] - hb;
-    if (tile_pos)  // the position holding each gather tile's first hit
-        for (uint64_t t = (r0 + kTile - 1) / kTile; t * kTile < r1; ++t) tile_pos[t] = (uint32_t)p;
+    if (tile_pos) {  // the position holding the first hit of each gather tile, or wave's part
+        const uint32_t per = ctx.qctx ? (uint32_t)ctx.tile : kTile;
+        const uint32_t t0 = (uint32_t)((r0 + per - 1) / per), t1 = (uint32_t)((r1 + per - 1) / per);
+        // long lists' tiles by the whole wave (one thread alone took 140 us over a list
+        // of a million hits)
+        const bool many = t1 - t0 > 4;
+        if (!many)
+            for (uint32_t t = t0; t < t1; ++t) tile_pos[t] = (uint32_t)p;
+        const uint64_t here = __ballot(true);
+        const uint32_t step = (uint32_t)__popcll(here);
+        const uint32_t rank =
+            (uint32_t)__popcll(here & ((1ull << (threadIdx.x & 63)) - 1ull));
+        for (uint64_t m = __ballot(many); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            const uint32_t pl = __shfl((uint32_t)p, l, 64), end = __shfl(t1, l, 64);
+            for (uint32_t t = __shfl(t0, l, 64) + rank; t < end; t += step) tile_pos[t] = pl;
+        }
+    }
     const int64_t g = g0 + p;
-    pbase[p] = lhead[g];
     if (ctx.qctx) {
         if (r1 > r0) {  // positions without hits are never looked at
             const int32_t q = qid[g];
@@ -780,6 +795,7 @@ __global__ void k_wave_prep(const uint64_t *__restrict__ hoff, const int64_t *__
         }
         return;
     }
+    pbase[p] = lhead[g];
     const int32_t q = qid[g];
     const int32_t qpos = (int32_t)(g - qoff[q]);
     const int sh_d = lay.bp, sh_q = lay.bp + lay.bd + lay.bs;
@@ -2758,8 +2774,8 @@ __device__ __forceinline__ CtxTest ctx_test(uint2 c, const CtxSide &q, const Ctx
 __device__ __forceinline__ QCtx uniform_ctx(const QCtx &q)
 {
     auto u = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)v); };
-    return QCtx{u(q.vm), u(q.n0), u(q.n1), u(q.p0), u(q.p1), (int32_t)u((uint32_t)q.qpos),
-                (int32_t)u((uint32_t)q.ql), u(q.head)};
+    return QCtx{u(q.vm), u(q.n0), u(q.n1), u(q.head), u(q.p0), u(q.p1),
+                (int32_t)u((uint32_t)q.qpos), (int32_t)u((uint32_t)q.ql)};
 }
 
 // Inclusive running maximum over the wave's lanes of values >= 0 (every lane active):
@@ -2926,7 +2942,6 @@ constexpr int kStartHit = 14, kStartPos = 17;  // bits of a hit in its block, a 
 constexpr uint32_t kStartUnsure = 1u << 31, kStartNone = ~0u;
 static_assert(kStartTiles * kTile <= 1 << kStartHit, "a block's hits fit a note");
 
-template <bool BOTH>
 __global__ __launch_bounds__(kBlock, 5) void k_run_starts(RunStarts a,
                                                           const WaveCtl *__restrict__ ctl,
                                                           int32_t tiles)
@@ -3073,7 +3088,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_run_starts(RunStarts a,
         __syncthreads();
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)s_lo);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)s_hi);
-        if (BOTH && lo == hi) {
+        if (lo == hi) {
             const QCtx q = uniform_ctx(a.qctx[lo]);
             if (lq >= 0 && (q.ql != lq || held > kStartCap - kTile)) flush(held, unsure, true);
             lq = q.ql;
@@ -3148,20 +3163,15 @@ __global__ __launch_bounds__(kBlock, 5) void k_run_starts(RunStarts a,
                     q[r] = a.qctx[lo + off[r]];
                     idx[r] = q[r].head + t0 + l;
                     cn[r] = a.next[idx[r]];
-                    if (BOTH) cp[r] = a.prev[idx[r]];
+                    cp[r] = a.prev[idx[r]];
                 }
 #pragma unroll
                 for (int r = 0; r < kHalf; ++r) {
                     const uint32_t nm = ctx_match(cn[r], q[r].n0, q[r].n1, q[r].vm, a.shape);
-                    st[r] = w0 + (h + r) * 64 < cnt && nm != 0 && off[r] >= from && off[r] < upto;
-                    un[r] = false;
-                    if (BOTH || st[r]) {
-                        if (!BOTH) cp[r] = a.prev[idx[r]];
-                        const uint32_t pm =
-                            ctx_match(cp[r], q[r].p0, q[r].p1, q[r].vm >> kCtx, a.shape);
-                        st[r] = st[r] && (pm & a.shape.exact) == 0;
-                        un[r] = lengths || (nm & a.shape.exact) == 0 || pm != 0;
-                    }
+                    const uint32_t pm = ctx_match(cp[r], q[r].p0, q[r].p1, q[r].vm >> kCtx, a.shape);
+                    st[r] = w0 + (h + r) * 64 < cnt && nm != 0 && off[r] >= from && off[r] < upto &&
+                            (pm & a.shape.exact) == 0;
+                    un[r] = lengths || (nm & a.shape.exact) == 0 || pm != 0;
                     off[r] -= from;
                 }
                 note(st, un, ti * kTile + w0 + h * 64, off);
@@ -3174,6 +3184,188 @@ __global__ __launch_bounds__(kBlock, 5) void k_run_starts(RunStarts a,
     if (lq >= 0) flush(s_n, s_u, true);
 }
 
+// The same for short lists (a mean below kCtxBothMean hits per position): starts are
+// few, so the contexts before a hit are read only where those after it match, and the
+// waves work apart, each on its kSubTile hits: positions marked, spread and looked up
+// without a barrier, where a block's waves waited three times a tile for each other's
+// loads.  A start's hit and position take a word each, and the block writes its tile's
+// starts at the tile's end, if there are any.  12.0 M hits of 2.0 M positions in 62 us
+// (75 by blocks): what is left is the lists themselves, a 128-byte line or two of the
+// postings for six hits; more rows under way or more waves change nothing.
+__global__ __launch_bounds__(kBlock, 6) void k_run_starts_short(RunStarts a,
+                                                                const WaveCtl *__restrict__ ctl,
+                                                                int32_t tiles)
+{
+    if (ctl) {
+        a.np = ctl->np;
+        a.g0 = ctl->g0;
+        a.nhits = ctl->H;
+        a.qa = ctl->qa;
+        a.lay = ctl->lay;
+    }
+    constexpr int kWaves = kBlock / 64, kRows = 4;  // rows with loads under way
+    __shared__ int32_t s_p[kTile];   // 1 + position (from the wave's first) at its first hit
+    __shared__ uint32_t s_hit[kTile], s_pos[kTile];  // the starts: hit | unsure, position
+    __shared__ uint32_t s_n[2], s_at, s_m;  // starts of the tile (even and odd ones in turn)
+    __shared__ int32_t s_q[2];              // first and last query of those kept
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const bool lengths = a.min_len > 2 * a.span;  // two hits may be too short
+    int32_t *mark = s_p + wv * kSubTile;
+    const uint32_t b0 = blockIdx.x * (uint32_t)(tiles * kTile);  // the block's first hit
+    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+    __syncthreads();
+    // Settles the unsure ones of the tile's n starts, then writes the keys of those kept:
+    // with one add to the query's count where they all are of one query.
+    auto flush = [&](uint32_t n) {
+        uint32_t *kept = reinterpret_cast<uint32_t *>(s_p);
+        if (threadIdx.x == 0) {
+            s_m = 0;
+            s_q[0] = INT32_MAX;
+            s_q[1] = -1;
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i - lane < n; i += kBlock) {  // whole waves
+            bool keep = false;
+            int32_t ql = 0;
+            if (i < n) {
+                const uint32_t v = s_hit[i], p = s_pos[i];
+                const QCtx q = a.qctx[p];
+                ql = q.ql;
+                keep = !(v & kStartUnsure) || start_kept(a, q, p, q.head + b0 + (v & ~kStartUnsure));
+            }
+            const uint64_t m = __ballot(keep);
+            if (m == 0) continue;
+            uint32_t at = 0;
+            if (lane == 0) at = atomicAdd(&s_m, (uint32_t)__popcll(m));
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
+            const int32_t q1 = __shfl(ql, __ffsll((unsigned long long)m) - 1, 64);
+            if (__ballot(keep && ql != q1) != 0ull) {
+                if (keep) {
+                    atomicMin(&s_q[0], ql);
+                    atomicMax(&s_q[1], ql);
+                }
+            } else if (lane == 0) {
+                atomicMin(&s_q[0], q1);
+                atomicMax(&s_q[1], q1);
+            }
+            if (keep) kept[at + (uint32_t)__popcll(m & below)] = i;
+        }
+        __syncthreads();
+        const uint32_t left = s_m;
+        const bool one = left && s_q[0] == s_q[1];
+        if (one && threadIdx.x == 0) s_at = a.sbase[s_q[0]] + atomicAdd(a.scount + s_q[0], left);
+        __syncthreads();
+        const uint32_t at = s_at;
+        for (uint32_t j = threadIdx.x; j - lane < left; j += kBlock) {
+            int32_t ql = -1;
+            uint64_t key = 0;
+            if (j < left) {
+                const uint32_t i = kept[j];
+                const QCtx q = a.qctx[s_pos[i]];
+                key = start_key(a.lay, a.post[q.head + b0 + (s_hit[i] & ~kStartUnsure)], q.qpos);
+                ql = q.ql;
+                if (one) a.out[at + j] = key;
+            }
+            if (one) continue;
+            for (uint64_t rest = __ballot(ql >= 0); rest;) {  // an add per wave and query
+                const int f = __ffsll((unsigned long long)rest) - 1;
+                const int32_t q1 = __shfl(ql, f, 64);
+                const uint64_t same = __ballot(ql == q1);
+                uint32_t o = 0;
+                if (lane == f)
+                    o = a.sbase[q1] + atomicAdd(a.scount + q1, (uint32_t)__popcll(same));
+                o = __shfl(o, f, 64);
+                if (ql == q1) a.out[o + (uint32_t)__popcll(same & below)] = key;
+                rest &= ~same;
+            }
+        }
+        __syncthreads();
+    };
+    for (int32_t ti = 0; ti < tiles; ++ti) {
+        const uint32_t tile = blockIdx.x * (uint32_t)tiles + (uint32_t)ti;
+        if (tile * (uint32_t)kTile >= a.nhits) break;  // a graph's grid covers the largest wave
+        uint32_t *count = &s_n[ti & 1];
+        const uint32_t sub = tile * kWaves + (uint32_t)wv, h0 = sub * kSubTile;
+        if (h0 < a.nhits) {
+            const uint32_t cnt = min((uint32_t)kSubTile, a.nhits - h0);
+            uint32_t lo, hi;  // positions of the wave's first hit and of the first after it
+            if (a.tile_pos) {
+                lo = a.tile_pos[sub];
+                hi = h0 + cnt < a.nhits ? a.tile_pos[sub + 1] : (uint32_t)(a.np - 1);
+            } else {  // the last position with hrel <= the first or last hit
+                const uint32_t j = lane & 1 ? h0 + cnt - 1 : h0;
+                uint32_t x = 0, y = (uint32_t)(a.np - 1);
+                while (x < y) {
+                    const uint32_t m = x + ((y - x + 1) >> 1);
+                    if (a.hrel[m] <= j) x = m;
+                    else y = m - 1;
+                }
+                lo = __shfl(x, 0, 64);
+                hi = __shfl(x, 1, 64);
+            }
+            lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)lo);
+            hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)hi);
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) mark[r * 64 + lane] = 0;
+            __builtin_amdgcn_wave_barrier();
+            for (uint32_t p = lo + lane; p <= hi; p += 64) {
+                const uint32_t r0 = a.hrel[p], r1 = a.hrel[p + 1];
+                if (r1 > r0 && r1 > h0 && r0 < h0 + cnt)
+                    mark[max(r0, h0) - h0] = (int32_t)(p - lo) + 1;
+            }
+            __builtin_amdgcn_wave_barrier();
+            int32_t run = 0;
+#pragma unroll
+            for (int h = 0; h < kItems; h += kRows) {
+                uint32_t pos[kRows];
+                uint4 q[kRows];  // vm, n0, n1, head
+                uint2 cn[kRows];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    const int32_t pr = max(wave_run_max(mark[(h + r) * 64 + lane]), run);
+                    run = __builtin_amdgcn_readlane(pr, 63);
+                    pos[r] = lo + (uint32_t)pr - 1u;  // lanes past the last hit: its position
+                    q[r] = *reinterpret_cast<const uint4 *>(a.qctx + pos[r]);
+                }
+#pragma unroll
+                for (int r = 0; r < kRows; ++r)
+                    cn[r] = a.next[q[r].w + h0 + min((uint32_t)((h + r) * 64 + lane), cnt - 1)];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    const uint32_t l = (uint32_t)((h + r) * 64 + lane);
+                    const uint32_t nm = ctx_match(cn[r], q[r].y, q[r].z, q[r].x, a.shape);
+                    bool st = l < cnt && nm != 0, un = false;
+                    if (__ballot(st) == 0ull) continue;
+                    if (st) {
+                        const QCtx &c = a.qctx[pos[r]];
+                        const uint32_t pm = ctx_match(a.prev[q[r].w + h0 + l], c.p0, c.p1,
+                                                      q[r].x >> kCtx, a.shape);
+                        st = (pm & a.shape.exact) == 0;
+                        un = lengths || (nm & a.shape.exact) == 0 || pm != 0;
+                    }
+                    const uint64_t m = __ballot(st);
+                    if (m == 0) continue;
+                    uint32_t at = 0;
+                    if (lane == 0) at = atomicAdd(count, (uint32_t)__popcll(m));
+                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
+                    if (st) {
+                        at += (uint32_t)__popcll(m & below);
+                        s_hit[at] = (h0 - b0 + l) | (un ? kStartUnsure : 0u);
+                        s_pos[at] = pos[r];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        const uint32_t n = *count;  // the next tile adds to the other one
+        if (n) {
+            flush(n);
+            if (threadIdx.x == 0) *count = 0;  // added to again after the next barrier
+        }
+    }
+}
+
 void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const WaveCtl *ctl,
                        uint32_t hits_cap)
 {
@@ -3184,8 +3376,8 @@ void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const Wave
     const uint32_t nt = (h + kTile - 1) / kTile;
     const int32_t tiles = nt >= kStartTiles * 256u * 8u ? kStartTiles : 1;
     const uint32_t nb = (nt + tiles - 1) / tiles;
-    if (both) k_run_starts<true><<<nb, kBlock, 0, st>>>(a, ctl, tiles);
-    else k_run_starts<false><<<nb, kBlock, 0, st>>>(a, ctl, tiles);
+    if (both) k_run_starts<<<nb, kBlock, 0, st>>>(a, ctl, tiles);
+    else k_run_starts_short<<<nb, kBlock, 0, st>>>(a, ctl, tiles);
 }
 
 // QCtx::head of a piece's positions, once their hits are scanned.

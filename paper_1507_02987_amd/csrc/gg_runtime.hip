@@ -603,6 +603,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     const int64_t np = g1 - g0;
     const bool lookback = sort_kind_from_env() == kOneSweep;
     const bool ctxs = grouping == kSort && !lookback && contexts_for(ix, p);
+    const bool both = H64 >= kCtxBothMean * (uint64_t)np;  // long lists
     CtxPrep cp;
     TRY(ensure(ws->hrel, sizeof(uint32_t) * (np + 1)));
     TRY(ensure(ws->pbase, sizeof(uint32_t) * (np + 1)));
@@ -611,6 +612,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         TRY(ensure(ws->sbase, sizeof(uint32_t) * nqw));
         TRY(ensure(ws->scount, sizeof(uint32_t) * nqw));
         cp = ctx_prep(ix, ws, p);
+        if (!both) cp.tile = kSubTile;
     } else {
         TRY(ensure(ws->akey, sizeof(uint64_t) * (np + 1)));
     }
@@ -626,7 +628,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         if (ctxs)
             launch_ctx_heads(as<uint32_t>(ws->pbase), as<uint32_t>(ws->hrel), np, cp.qctx, st);
     } else {
-        TRY(ensure(ws->tpos, sizeof(uint32_t) * ((size_t)H / kTile + 2)));
+        TRY(ensure(ws->tpos, sizeof(uint32_t) * ((size_t)H / cp.tile + 2)));
         launch_wave_prep(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), as<uint32_t>(ws->lhead),
                          as<int32_t>(ws->qid), qa, nqw, g0, g1, lay, as<uint32_t>(ws->hrel),
                          as<uint32_t>(ws->pbase), as<uint64_t>(ws->akey), as<uint32_t>(ws->tpos),
@@ -667,7 +669,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
         a.qa = qa;
         a.lay = lay;
         prof.begin("probe");
-        launch_run_starts(a, H64 >= kCtxBothMean * (uint64_t)np, st);
+        launch_run_starts(a, both, st);
         prof.end(H);
         launch_scan_u32(a.scount, as<uint32_t>(ws->cand_off), nqw, as<uint32_t>(ws->partials), st);
         HIPCHK(hipMemcpyAsync(h_cq, a.scount, sizeof(uint32_t) * nqw, hipMemcpyDeviceToHost, st));
@@ -1724,7 +1726,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     TRY(ensure(ws->rs_partials,
                sizeof(uint32_t) * scan_partials_needed((int64_t)ntile_cap * kRadix + 1)));
     TRY(ensure(ws->gtiles, sizeof(SortTile) * tiles_cap));
-    TRY(ensure(ws->tpos, sizeof(uint32_t) * ((size_t)hits_cap / kTile + 2)));
+    TRY(ensure(ws->tpos, sizeof(uint32_t) * ((size_t)hits_cap / kSubTile + 2)));
     TRY(ensure(ws->ccount, sizeof(uint32_t) * (ntile + 1)));
     TRY(ensure(ws->partials,
                sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(ntile, nq_cap) + 1)));
@@ -1805,7 +1807,8 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
         }
         hipGraph_t g = nullptr;
         HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        const CtxPrep cp = ctxs ? ctx_prep(ix, ws, p) : CtxPrep{};
+        CtxPrep cp = ctxs ? ctx_prep(ix, ws, p) : CtxPrep{};
+        if (!both) cp.tile = kSubTile;
         launch_wave_prep_ctl(as<uint64_t>(ws->hoff), as<int64_t>(ws->qoff), as<uint32_t>(ws->lhead),
                              as<int32_t>(ws->qid), np_cap, nq_cap, as<uint32_t>(ws->hrel),
                              as<uint32_t>(ws->pbase), as<uint64_t>(ws->akey),

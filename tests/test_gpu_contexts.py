@@ -166,3 +166,28 @@ def test_loaded_index(ggo, tmp_path):
     assert rc == 0 and (st == wst).all()
     for a, b in zip(got, want):
         assert as_rows(a) == as_rows(b)
+
+
+@pytest.mark.parametrize("copies", [1, 511, 512, 513, 2049, 40_000])
+def test_one_long_list_among_short_ones(ggo, copies):
+    """A window that the bank holds `copies` times, alone each time, in a query of random
+    bases: one position's hits span many waves' parts while the lists stay short on
+    average, and starts lie on both sides of them."""
+    G = gpu()
+    rng = np.random.Generator(np.random.PCG64([21, copies]))
+    rand = lambda n: rng.choice(list(b"ACGT"), n).astype(np.uint8)
+    word = np.frombuffer(b"ACCGTTGACAG", np.uint8)
+    plain = rand(30_000)
+    body = rand(22 * copies).reshape(copies, 22)
+    body[:, :11] = word  # at a multiple of the span, so indexed; the window after is random
+    seqs = np.concatenate([plain, body.reshape(-1)])
+    db = synth.Database(seqs, np.array([0, len(plain), len(seqs)], np.int64), "one long list")
+    parts, off = [], [0]
+    for _ in range(3):
+        a = int(rng.integers(0, 25_000))
+        parts += [plain[a:a + 300], word, rand(900), plain[a + 400:a + 700]]
+        off.append(sum(len(p) for p in parts))
+    qs = synth.QuerySet(np.concatenate(parts), np.array(off, np.int64), *[np.zeros(3)] * 4)
+    gix, oix = G.Index(db.seqs, db.off, 11), ggo.Index(db.seqs, db.off, 11)
+    probed, wst = both_forms(G, ggo, gix, oix, qs, 20)
+    assert probed >= 3 * copies and all(s["n_cands"] >= 2 for s in wst)
