@@ -199,9 +199,9 @@ void launch_traceback(const int32_t *hits, int32_t n, const uint8_t *qascii, int
 // record binq[i] = (q << 10) | length bin (kNoBin: empty slot), written where the
 // boxes are merged (LenSel) or by launch_len_records[_ranges] over the slots.
 // From the records alone the prefilter takes the per-query length histograms
-// (hist: nq * kLenBins, cleared here), the threshold bin thr[q] and box count
-// nvalid[q], and per-tile kept counts scanned in place (kept total at
-// tile_counts[tiles]); launch_len_compact then writes the kept boxes, in order, to
+// (hist: nq * kLenBins, cleared here), the threshold bin thr[q], the box counts
+// nvalid[q] and, of the kept, nkept[q], and per-tile kept counts scanned in place (kept
+// total at tile_counts[tiles]); launch_len_compact then writes the kept boxes, in order, to
 // out.
 constexpr uint32_t kNoBin = 0xFFFFFFFFu;
 struct LenSel {
@@ -212,8 +212,8 @@ void launch_len_records(const Box *b, uint32_t n, LenSel ls, hipStream_t st);
 void launch_len_records_ranges(const Box *b, const uint32_t *ranges, uint32_t nr, LenSel ls,
                                hipStream_t st);
 void launch_len_prefilter(const uint32_t *binq, uint32_t n, int32_t nq, int32_t N, uint32_t *hist,
-                          uint32_t *thr, uint32_t *nvalid, uint32_t *tile_counts,
-                          uint32_t *partials, hipStream_t st);
+                          uint32_t *thr, uint32_t *nvalid, uint32_t *nkept,
+                          uint32_t *tile_counts, uint32_t *partials, hipStream_t st);
 void launch_len_compact(const Box *b, const uint32_t *binq, uint32_t n, const uint32_t *thr,
                         const uint32_t *tile_off, Box *out, hipStream_t st);
 // Both strands: dst holds each sequence's reverse complement at the sequence's own
@@ -451,6 +451,10 @@ void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, i
                              HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
                              uint32_t *nsel, hipStream_t st, WaveCtl *ctl = nullptr,
                              uint32_t *cursor = nullptr, uint32_t *classes = nullptr);
+// The selection order alone, of boxes that are merged (all of them kept).
+void launch_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
+                       HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
+                       uint32_t *nsel, hipStream_t st);
 void launch_merge_sweep(const Box *sorted, uint32_t n, Box *out, hipStream_t st);
 // The same sweep of ngroup whole groups, boxes [offs[g], offs[g + 1]) of sorted,
 // one block per group sweeping in parallel for at most `rounds` rounds per chunk

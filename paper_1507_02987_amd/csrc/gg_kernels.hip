@@ -4511,17 +4511,17 @@ __device__ uint32_t seg_rank(const Rec &r, bool live, uint32_t n, Pack pack, Les
                              Rec *__restrict__ s_r, uint64_t *__restrict__ s_key,
                              uint32_t *__restrict__ s_w)
 {
-    __shared__ uint32_t s_tie;
     const uint32_t i = threadIdx.x, n4 = (n + 3) & ~3u;
     const SegKey p = pack(r);
+    const bool whole = p.whole();  // by the widths alone
     const uint64_t key = live ? p.k : ~0ull;  // a live key's top bit is 0
     const uint32_t w = live ? p.x << kSegIx | i : i;
     __syncthreads();
-    if (i == 0) s_tie = 0;
     if (i < n4) {
         s_key[i] = i < n ? key : ~0ull;
         s_w[i] = i < n ? w : i;
     }
+    if (!whole && i < n) s_r[i] = r;
     __syncthreads();
     uint32_t rank = 0, same = 0;
     if ((i & ~63u) < n) {
@@ -4535,17 +4535,16 @@ __device__ uint32_t seg_rank(const Rec &r, bool live, uint32_t n, Pack pack, Les
                 same += eq && (x ^ w) >> kSegIx == 0u ? 1u : 0u;
             }
         }
+        if (i < n && live && same > 1 && !whole) {  // a few: compared whole among themselves
+            for (uint32_t j = 0; j < n; ++j) {
+                if (j == i || s_key[j] != key || (s_w[j] ^ w) >> kSegIx != 0u) continue;
+                const Rec o = s_r[j];
+                const bool before = less(o, r) || (j < i && !less(r, o));
+                rank += (before ? 1u : 0u) - (j < i ? 1u : 0u);  // counted by position above
+            }
+        }
     }
-    if (i < n && live && same > 1 && !p.whole()) s_tie = 1;
     __syncthreads();
-    if (s_tie) {
-        if (i < n) s_r[i] = r;
-        __syncthreads();
-        rank = 0;
-        for (uint32_t j = 0; j < n; ++j)
-            rank += less(s_r[j], r) || (j < i && !less(r, s_r[j])) ? 1u : 0u;
-        __syncthreads();
-    }
     return rank;
 }
 
@@ -4630,6 +4629,8 @@ struct BoxLess {
 // aligner's class counts.  A serial chain: 1,000 queries of up to 80 boxes took 46 us by
 // a network of record comparisons in LDS and one thread's sweep of each sequence's
 // boxes; 25 by counted places, 16 with the sweep in stretches.
+// MERGED: the boxes are merged already, and only put in selection order.
+template <bool MERGED>
 __global__ __launch_bounds__(kBlock) void k_merge_select_seg(
     const Box *__restrict__ in, Box *__restrict__ out, const uint32_t *__restrict__ seg_off,
     HitKeyLayout lay, int32_t N, uint32_t *__restrict__ qstart, uint32_t *__restrict__ qend,
@@ -4667,73 +4668,75 @@ __global__ __launch_bounds__(kBlock) void k_merge_select_seg(
     const int bl = lay.bp + 1;  // positions and lengths up to the longest query
     const bool small = n <= (uint32_t)kBlock;
     if (threadIdx.x == 0) s_live = 0;
-    // the boxes leave the extension unmerged, each on one diagonal: ds = qs + d, de = qe + d
-    auto merge_key = [&](const Box &b) {
-        SegKey k;
-        k.add((uint32_t)b.s, lay.bs);
-        k.add((uint32_t)b.qs, bl);
-        k.add((uint32_t)(b.ds - b.qs + lay.bias), lay.bd);
-        k.add((uint32_t)b.qe, bl);
-        return k;
-    };
-    if (small) {
-        Box b{};
-        if (threadIdx.x < n) b = in[a0 + threadIdx.x];
-        const uint32_t at = seg_rank(b, true, n, merge_key, BoxLess<false>(), s_r, s_key, s_w);
-        if (threadIdx.x < n) s_r[at] = b;
-    } else {
-        for (uint32_t i = threadIdx.x; i < n; i += kBlock) s_r[i] = in[a0 + i];
-        seg_order(
-            s_r, n, [](const Box &) { return true; }, merge_key, BoxLess<false>(), s_key, s_w);
-        Box tmp[4];
+    if constexpr (!MERGED) {
+        // the boxes leave the extension unmerged, each on one diagonal: ds = qs + d, de = qe + d
+        auto merge_key = [&](const Box &b) {
+            SegKey k;
+            k.add((uint32_t)b.s, lay.bs);
+            k.add((uint32_t)b.qs, bl);
+            k.add((uint32_t)(b.ds - b.qs + lay.bias), lay.bd);
+            k.add((uint32_t)b.qe, bl);
+            return k;
+        };
+        if (small) {
+            Box b{};
+            if (threadIdx.x < n) b = in[a0 + threadIdx.x];
+            const uint32_t at = seg_rank(b, true, n, merge_key, BoxLess<false>(), s_r, s_key, s_w);
+            if (threadIdx.x < n) s_r[at] = b;
+        } else {
+            for (uint32_t i = threadIdx.x; i < n; i += kBlock) s_r[i] = in[a0 + i];
+            seg_order(
+                s_r, n, [](const Box &) { return true; }, merge_key, BoxLess<false>(), s_key, s_w);
+            Box tmp[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (threadIdx.x + e * kBlock < n) tmp[e] = s_r[s_ix[threadIdx.x + e * kBlock]];
-        __syncthreads();
+            for (int e = 0; e < 4; ++e)
+                if (threadIdx.x + e * kBlock < n) tmp[e] = s_r[s_ix[threadIdx.x + e * kBlock]];
+            __syncthreads();
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (threadIdx.x + e * kBlock < n) s_r[threadIdx.x + e * kBlock] = tmp[e];
-    }
-    __syncthreads();
-    // A box that starts, in the query, at or past every end before it in its sequence joins
-    // none of those, and no later box joins across it: the sweep starts anew there.
-    // s rises along the order, so the largest (s, qe) before a box tells.
-    uint64_t most = 0;
-    for (uint32_t i0 = 0; i0 < n; i0 += kBlock) {
-        const uint32_t i = i0 + threadIdx.x;
-        const Box b = s_r[min(i, n - 1)];
-        uint64_t all;
-        const uint64_t before =
-            max(most, block_excl_max((uint64_t)(uint32_t)b.s << 32 | (uint32_t)b.qe, s_max, &all));
-        if (i < n) s_w[i] = (uint32_t)(before >> 32) != (uint32_t)b.s || (int32_t)before <= b.qs;
-        most = max(most, all);
-    }
-    __syncthreads();
-    // each stretch swept by the thread at its first box
-    uint32_t kept = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
-        if (i > 0 && !s_w[i]) continue;
-        Box cur = s_r[i];
-        uint32_t w = i, j = i + 1;
-        bool more = j < n && !s_w[min(j, n - 1)];
-        while (more) {
-            const Box h = s_r[j];
-            more = ++j < n && !s_w[min(j, n - 1)];
-            // by arithmetic, not by branches: one wait for the box, none for its tests
-            const bool join = (h.qs < cur.qe) & (h.ds < cur.de) & (cur.ds < h.de);
-            if (!join) s_r[w++] = cur;
-            cur.qs = join ? min(cur.qs, h.qs) : h.qs;
-            cur.qe = join ? max(cur.qe, h.qe) : h.qe;
-            cur.ds = join ? min(cur.ds, h.ds) : h.ds;
-            cur.de = join ? max(cur.de, h.de) : h.de;
-            cur.dmin = join ? min(cur.dmin, h.dmin) : h.dmin;
-            cur.dmax = join ? max(cur.dmax, h.dmax) : h.dmax;
+            for (int e = 0; e < 4; ++e)
+                if (threadIdx.x + e * kBlock < n) s_r[threadIdx.x + e * kBlock] = tmp[e];
         }
-        s_r[w++] = cur;
-        kept += w - i;
-        for (; w < j; ++w) s_r[w].q = -1;
+        __syncthreads();
+        // A box that starts, in the query, at or past every end before it in its sequence joins
+        // none of those, and no later box joins across it: the sweep starts anew there.
+        // s rises along the order, so the largest (s, qe) before a box tells.
+        uint64_t most = 0;
+        for (uint32_t i0 = 0; i0 < n; i0 += kBlock) {
+            const uint32_t i = i0 + threadIdx.x;
+            const Box b = s_r[min(i, n - 1)];
+            uint64_t all;
+            const uint64_t before =
+                max(most, block_excl_max((uint64_t)(uint32_t)b.s << 32 | (uint32_t)b.qe, s_max, &all));
+            if (i < n) s_w[i] = (uint32_t)(before >> 32) != (uint32_t)b.s || (int32_t)before <= b.qs;
+            most = max(most, all);
+        }
+        __syncthreads();
+        // each stretch swept by the thread at its first box
+        uint32_t kept = 0;
+        for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
+            if (i > 0 && !s_w[i]) continue;
+            Box cur = s_r[i];
+            uint32_t w = i, j = i + 1;
+            bool more = j < n && !s_w[min(j, n - 1)];
+            while (more) {
+                const Box h = s_r[j];
+                more = ++j < n && !s_w[min(j, n - 1)];
+                // by arithmetic, not by branches: one wait for the box, none for its tests
+                const bool join = (h.qs < cur.qe) & (h.ds < cur.de) & (cur.ds < h.de);
+                if (!join) s_r[w++] = cur;
+                cur.qs = join ? min(cur.qs, h.qs) : h.qs;
+                cur.qe = join ? max(cur.qe, h.qe) : h.qe;
+                cur.ds = join ? min(cur.ds, h.ds) : h.ds;
+                cur.de = join ? max(cur.de, h.de) : h.de;
+                cur.dmin = join ? min(cur.dmin, h.dmin) : h.dmin;
+                cur.dmax = join ? max(cur.dmax, h.dmax) : h.dmax;
+            }
+            s_r[w++] = cur;
+            kept += w - i;
+            for (; w < j; ++w) s_r[w].q = -1;
+        }
+        if (kept) atomicAdd(&s_live, kept);
     }
-    if (kept) atomicAdd(&s_live, kept);
     auto select_key = [&](const Box &b) {
         SegKey k;
         k.add((1u << bl) - 1u - (uint32_t)min(b.qe - b.qs, b.de - b.ds), bl);
@@ -4744,6 +4747,10 @@ __global__ __launch_bounds__(kBlock) void k_merge_select_seg(
         k.add((uint32_t)b.de, lay.bd);
         return k;
     };
+    if (MERGED) {
+        for (uint32_t i = threadIdx.x; i < n; i += kBlock) s_r[i] = in[a0 + i];
+        if (threadIdx.x == 0) s_live = n;
+    }
     __syncthreads();
     if (small) {
         const Box b = s_r[min(threadIdx.x, n - 1)];
@@ -4767,8 +4774,17 @@ void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, i
                              uint32_t *classes)
 {
     if (nq > 0)
-        k_merge_select_seg<<<nq, kBlock, 0, st>>>(in, out, seg_off, lay, N, qstart, qend, nsel, ctl,
-                                                  cursor, classes);
+        k_merge_select_seg<false><<<nq, kBlock, 0, st>>>(in, out, seg_off, lay, N, qstart, qend,
+                                                         nsel, ctl, cursor, classes);
+}
+
+void launch_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
+                       HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
+                       uint32_t *nsel, hipStream_t st)
+{
+    if (nq > 0)
+        k_merge_select_seg<true><<<nq, kBlock, 0, st>>>(in, out, seg_off, lay, N, qstart, qend, nsel,
+                                                        nullptr, nullptr, nullptr);
 }
 
 // Report order: alignments with score > 0 first, score descending, then seq,
@@ -5824,12 +5840,14 @@ __global__ __launch_bounds__(kBlock) void k_len_hist(const uint32_t *__restrict_
             if (h[i]) atomicAdd(&hist[(size_t)q0 * kLenBins + i], h[i]);
 }
 
-// One block per query: its box count (all bins) and the highest bin whose boxes
-// and the longer ones number at least N (bin 0 when the query has fewer).
+// One block per query: its box count (all bins), the highest bin whose boxes
+// and the longer ones number at least N (bin 0 when the query has fewer), and how many
+// those are.
 __global__ __launch_bounds__(kBlock) void k_len_threshold(const uint32_t *__restrict__ hist,
                                                           int32_t nq, int32_t N,
                                                           uint32_t *__restrict__ thr,
-                                                          uint32_t *__restrict__ nvalid)
+                                                          uint32_t *__restrict__ nvalid,
+                                                          uint32_t *__restrict__ nkept)
 {
     constexpr int kPer = kLenBins / kBlock;  // bins per thread, highest bins to thread 0
     for (int32_t q = blockIdx.x; q < nq; q += gridDim.x) {
@@ -5842,19 +5860,21 @@ __global__ __launch_bounds__(kBlock) void k_len_threshold(const uint32_t *__rest
         }
         uint32_t tot;
         uint32_t above = block_excl_scan<uint32_t>(sum, &tot);  // boxes in higher bins
-        uint32_t best = 0;  // a thread that crosses N names the bin; crossing is unique
+        uint64_t best = 0;  // a thread that crosses N names the bin; crossing is unique
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
             const uint32_t before = above;
             above += c[r];
             if (before < (uint32_t)N && above >= (uint32_t)N)
-                best = (uint32_t)(kLenBins - 1 - (threadIdx.x * kPer + r)) + 1;  // bin + 1
+                best = (uint64_t)above << 32 |
+                       (uint32_t)(kLenBins - (threadIdx.x * kPer + r));  // boxes kept, bin + 1
         }
-        uint32_t pick;
-        block_excl_scan<uint32_t>(best, &pick);  // sum: at most one thread is non-zero
+        uint64_t pick;
+        block_excl_scan<uint64_t>(best, &pick);  // sum: at most one thread is non-zero
         if (threadIdx.x == 0) {
-            thr[q] = pick ? pick - 1 : 0u;
+            thr[q] = pick ? (uint32_t)pick - 1u : 0u;
             nvalid[q] = tot;
+            nkept[q] = pick ? (uint32_t)(pick >> 32) : tot;
         }
     }
 }
@@ -5909,7 +5929,7 @@ void launch_len_records_ranges(const Box *b, const uint32_t *ranges, uint32_t nr
 }
 
 void launch_len_prefilter(const uint32_t *binq, uint32_t n, int32_t nq, int32_t N,
-                          uint32_t *hist, uint32_t *thr, uint32_t *nvalid,
+                          uint32_t *hist, uint32_t *thr, uint32_t *nvalid, uint32_t *nkept,
                           uint32_t *tile_counts, uint32_t *partials, hipStream_t st)
 {
     if (n == 0 || nq <= 0) return;
@@ -5917,7 +5937,7 @@ void launch_len_prefilter(const uint32_t *binq, uint32_t n, int32_t nq, int32_t 
     launch_fill_u32(hist, (size_t)nq * kLenBins, 0u, st);
     k_len_hist<<<(tiles + kLenHistTiles - 1) / kLenHistTiles, kBlock, 0, st>>>(binq, n, hist);
     k_len_threshold<<<std::min<uint32_t>((uint32_t)nq, kMaxGrid), kBlock, 0, st>>>(hist, nq, N, thr,
-                                                                                   nvalid);
+                                                                                   nvalid, nkept);
     k_len_keep<<<tiles, kBlock, 0, st>>>(nullptr, binq, n, thr, nullptr, tile_counts, nullptr);
     launch_scan_u32(tile_counts, tile_counts, tiles, partials, st);  // kept total at [tiles]
 }

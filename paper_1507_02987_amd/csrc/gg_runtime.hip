@@ -108,7 +108,7 @@ struct Workspace {
         btmp_b, bounds, blist, pcnt, cells_box, rbounds, rbelow, os_scratch, xqueue, gout,
         gctl, gplan, gcursor, gqflag, stiles, gtiles;
     DevBuf tb_in, tb_dir, tb_out;       // traceback: uploads, directions, results
-    DevBuf lhist, lthr, lvalid, ltile, lbinq;  // selection prefilter
+    DevBuf lhist, lthr, lvalid, lkoff, ltile, lbinq;  // selection prefilter
     DevBuf fkept, fkoff, fflag, ford;   // lone-diagonal filter (ford: largest query first)
     DevBuf tpos;                        // the position where each gather tile starts
     DevBuf mbig, mranges;               // merge groups that may outgrow an LDS window
@@ -145,7 +145,7 @@ struct Workspace {
                          &bound_q, &bound_off, &btmp_b, &bounds, &blist, &pcnt, &cells_box,
                          &rbounds, &rbelow, &os_scratch, &xqueue, &gout, &gctl, &gplan,
                          &gcursor, &gqflag, &stiles, &gtiles, &tb_in, &tb_dir, &tb_out, &lhist, &lthr,
-                         &lvalid, &ltile, &lbinq, &fkept, &fkoff, &fflag, &ford, &tpos, &selbox,
+                         &lvalid, &lkoff, &ltile, &lbinq, &fkept, &fkoff, &fflag, &ford, &tpos, &selbox,
                          &mbig, &mranges, &bsw_order, &qctx, &sbase, &scount};
         for (DevBuf *b : all)
             if (b->p) (void)hipFree(b->p);
@@ -1196,40 +1196,57 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     Box *merged = as<Box>(ws->boxes3);
     uint32_t nbox = nc;                // boxes in the selection order
     std::vector<uint32_t> nvalid_h;    // merged boxes per query, when prefiltered
+    bool seg_select = seg_path;        // put in selection order by query, in LDS
     if (!seg_path) {
         if (ls.binq) {
             // only boxes at least as long as a query's N-th longest can be selected
             const uint32_t tiles = (nc + kTile - 1) / kTile;
             TRY(ensure(ws->lhist, sizeof(uint32_t) * (size_t)nqw * kLenBins));
             TRY(ensure(ws->lthr, sizeof(uint32_t) * nqw));
-            TRY(ensure(ws->lvalid, sizeof(uint32_t) * nqw));
+            TRY(ensure(ws->lvalid, sizeof(uint32_t) * (2 * (size_t)nqw)));
+            TRY(ensure(ws->lkoff, sizeof(uint32_t) * ((size_t)nqw + 1)));
             TRY(ensure(ws->ltile, sizeof(uint32_t) * (tiles + 1)));
-            TRY(ensure(ws->partials, sizeof(uint64_t) * scan_partials_needed(tiles + 1)));
+            TRY(ensure(ws->partials,
+                       sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(tiles, nqw) + 1)));
+            uint32_t *nkept = as<uint32_t>(ws->lvalid) + nqw;
             launch_len_prefilter(ls.binq, nc, nqw, p->max_hits, as<uint32_t>(ws->lhist),
-                                 as<uint32_t>(ws->lthr),
-                                 as<uint32_t>(ws->lvalid), as<uint32_t>(ws->ltile),
-                                 as<uint32_t>(ws->partials), st);
+                                 as<uint32_t>(ws->lthr), as<uint32_t>(ws->lvalid), nkept,
+                                 as<uint32_t>(ws->ltile), as<uint32_t>(ws->partials), st);
             launch_len_compact(merged, ls.binq, nc, as<uint32_t>(ws->lthr),
                                as<uint32_t>(ws->ltile), as<Box>(ws->boxes), st);
-            nvalid_h.resize((size_t)nqw);
-            HIPCHK(hipMemcpyAsync(&nbox, as<uint32_t>(ws->ltile) + tiles, sizeof(uint32_t),
+            nvalid_h.resize(2 * (size_t)nqw);  // merged, then kept
+            HIPCHK(hipMemcpyAsync(nvalid_h.data(), ws->lvalid.p, sizeof(uint32_t) * 2 * nqw,
                                   hipMemcpyDeviceToHost, st));
-            HIPCHK(hipMemcpyAsync(nvalid_h.data(), ws->lvalid.p, sizeof(uint32_t) * nqw,
-                                  hipMemcpyDeviceToHost, st));
+            launch_scan_u32(nkept, as<uint32_t>(ws->lkoff), nqw, as<uint32_t>(ws->partials), st);
             SYNC(st);
             merged = as<Box>(ws->boxes);
+            nbox = 0;
+            uint32_t most = 0;
+            for (int32_t ql = 0; ql < nqw; ++ql) {
+                nbox += nvalid_h[(size_t)nqw + ql];
+                most = std::max(most, nvalid_h[(size_t)nqw + ql]);
+            }
+            seg_select = most <= (uint32_t)kSegCap;
         }
-        TRY(make_words({{F_Q, bq, 0}, {F_LEN_DESC, bl, (int32_t)maxL}, {F_S, bs, 0},
-                        {F_QS, bl, 0}, {F_DS, bsl, 0}, {F_QE, bl, 0}, {F_DE, bsl, 0}},
-                       words));
-        TRY(sort_records(ws, nbox, words,
-                         [&](const KeyWord &w, const uint32_t *pm, uint64_t *out) {
-                             launch_box_keys(merged, nbox, w, nqw, out, pm, st);
-                         },
-                         &perm));
-        launch_gather_boxes(merged, perm, nbox, as<Box>(ws->boxes2), st);
+        if (seg_select) {
+            // a block per query: the global sort of a few hundred boxes is some forty
+            // launches, 200 us
+            launch_select_seg(merged, as<Box>(ws->boxes2), as<uint32_t>(ws->lkoff), nqw, lay,
+                              p->max_hits, as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
+                              as<uint32_t>(ws->nsel), st);
+        } else {
+            TRY(make_words({{F_Q, bq, 0}, {F_LEN_DESC, bl, (int32_t)maxL}, {F_S, bs, 0},
+                            {F_QS, bl, 0}, {F_DS, bsl, 0}, {F_QE, bl, 0}, {F_DE, bsl, 0}},
+                           words));
+            TRY(sort_records(ws, nbox, words,
+                             [&](const KeyWord &w, const uint32_t *pm, uint64_t *out) {
+                                 launch_box_keys(merged, nbox, w, nqw, out, pm, st);
+                             },
+                             &perm));
+            launch_gather_boxes(merged, perm, nbox, as<Box>(ws->boxes2), st);
+        }
     }
-    if (!seg_path) {
+    if (!seg_select) {
         HIPCHK(hipMemsetAsync(ws->qstart.p, 0, sizeof(uint32_t) * nqw, st));
         HIPCHK(hipMemsetAsync(ws->qend.p, 0, sizeof(uint32_t) * nqw, st));
         launch_segments_box(as<Box>(ws->boxes2), nbox, nqw, as<uint32_t>(ws->qstart),

@@ -52,3 +52,25 @@ def test_records_about_the_sort_steps(ggo, counts):
         assert s["n_cands"] >= n
     check_stats(G, gix, qs, G.params(1024), want, wst)
     check_graph(G, gix, qs, G.params(1024), want, cap=1024)
+
+
+@pytest.mark.parametrize("n_long,N", [(1, 1), (40, 20), (300, 256), (300, 300), (1030, 1024)])
+def test_selection_of_a_prefiltered_query(ggo, n_long, N):
+    """Over kSegCap boxes: the global merge, and the longest of them put in selection
+    order by query where they fit (or by the global sort: the last case)."""
+    G = gpu()
+    db, qs = queries(7, (1100,))
+    rng = np.random.Generator(np.random.PCG64([12, n_long]))
+    # segments of 200 bases and up, each in a sequence of its own: a third share a length
+    longs = [rng.choice(list(b"ACGT"), 200 + (0 if s % 3 else 7 * (s % 50))).astype(np.uint8)
+             for s in range(n_long)]
+    seqs = np.concatenate([db.seqs] + longs)
+    off = np.concatenate([db.off, db.off[-1] + np.cumsum([len(x) for x in longs])])
+    db = synth.Database(seqs, off.astype(np.int64), "long segments")
+    buf = np.concatenate([qs.buf] + longs)
+    qs = synth.QuerySet(buf, np.array([0, len(buf)], np.int64), *[np.zeros(1)] * 4)
+    gix, oix = G.Index(db.seqs, db.off, 11), ggo.Index(db.seqs, db.off, 11)
+    want, wst = oracle_all(oix, qs, ggo.params(N))
+    assert wst[0]["n_cands"] > 1024 and wst[0]["n_selected"] == N
+    check_stats(G, gix, qs, G.params(N), want, wst)
+    check_graph(G, gix, qs, G.params(N), want, cap=1024)
