@@ -6161,37 +6161,21 @@ __device__ __forceinline__ CellOut sw_cell(int32_t hl, int32_t el, int32_t sl, i
     return c;
 }
 
-// Cell with every value offset by kBswBias (the rest of the sweep after the border
-// pairs, staged boxes): minus infinity is any value <= 0, so the zero that a DPP
-// lane shift brings into lane 0 and lane 63 is one, and the shift can feed the
-// subtraction or select that uses it.  The H floor is kBswBias; the score terms and
-// gap costs come in as VGPRs.  The same rules as sw_cell otherwise.
+// After the border pairs a staged box's values are offset by kBswBias: minus infinity is
+// then any value <= kBswBias, the H floor, since what a gap gives from below the floor stays
+// at or below it.  So E and F are kept at the floor (their maximum with it leaves H one
+// maximum), and the zero that a DPP lane shift brings into lane 0 or 63 needs no test.
 constexpr int32_t kBswBias = 1 << 29;
+constexpr int32_t kBswOut = 1 << 30;  // a gap or mismatch cost that leaves nothing
+// Bases past a box's end match none: a cell past the box is then no better than one in
+// the box that it comes from, and at a later place, so it is never the best one and needs
+// no test either.  A sweep reads up to kBswPad of them.
+constexpr int kBswPad = 80;
+constexpr uint32_t kBswQEnd = 4, kBswDEnd = 5;
 
-__device__ __forceinline__ CellOut sw_cell_b(int32_t hl, int32_t el, int32_t sl, int32_t sel,
-                                             int32_t hu, int32_t fu, int32_t su, int32_t sfu,
-                                             int32_t hd, int32_t sd, bool same, int32_t here,
-                                             int32_t vmatch, int32_t vmis, int32_t vo1,
-                                             int32_t vext)
-{
-    CellOut c;
-    const int32_t eo = hl - vo1, ee = el - vext;
-    const bool eop = eo >= ee;
-    c.E = eop ? eo : ee;
-    c.SE = eop ? sl : sel;
-    const int32_t fo = hu - vo1, fe = fu - vext;
-    const bool fop = fo >= fe;
-    c.F = fop ? fo : fe;
-    c.SF = fop ? su : sfu;
-    const int32_t g = hd + (same ? vmatch : vmis);
-    c.H = max(max(g, kBswBias), max(c.E, c.F));
-    const int32_t sg = hd > kBswBias ? sd : here;
-    c.S = (g == c.H) ? sg : ((c.E == c.H) ? c.SE : c.SF);
-    return c;
-}
-
-// A uniform value in a VGPR of its own (the compiler would otherwise rebuild it
-// from its SGPR inside the loop, where two SGPR operands cannot meet in one select).
+// A uniform value in a VGPR of its own: the compiler would otherwise rebuild it from its
+// SGPR inside the loop, where two SGPR operands cannot meet in one select, and know the
+// floor's sign, which costs it the three-way maxima and those with a lane shift.
 __device__ __forceinline__ int32_t in_vgpr(int32_t s)
 {
     int32_t v;
@@ -6206,7 +6190,7 @@ __device__ __forceinline__ int32_t in_vgpr(int32_t s)
 // Y's left neighbour is this lane's X, its upper the upper lane's X, its diagonal
 // this lane's previous Y.  Lanes past the band (u > W) follow lane W's cells, so
 // every base they read is in the box; no band cell reads their values.
-// Staged bank bases come in pairs: sd2[x] holds base x and base min(x + 1, C - 1).
+// Staged bank bases come in pairs: sd2[x] holds base x and base x + 1.
 template <bool STAGED>
 __device__ __forceinline__ void bsw_sweep(const uint8_t *__restrict__ sq,
                                           const uint16_t *__restrict__ sd2,
@@ -6322,72 +6306,73 @@ __device__ __forceinline__ void bsw_sweep(const uint8_t *__restrict__ sq,
     if constexpr (!STAGED) {
         for (; a <= a1; a += 2, ++i, ++j, hereX += 128) pair(std::false_type{});
     } else {
-        // In the box's interior every band lane's row and column are >= 1, so the
-        // bases need only the upper clamps, and X (resp. Y) lies in the box while a <
-        // limX (limY): i < R and j < C (j + 1 < C) with i = (a - d) / 2, j = (a + d) / 2.
-        const int32_t limX = laneX ? min(2 * R + dXl, 2 * C - dXl) : INT32_MIN;
-        const int32_t limY = laneY ? min(2 * R + dXl, 2 * C - dXl - 2) : INT32_MIN;
-        const int32_t vmatch = in_vgpr(match), vmis = in_vgpr(-mismatch), vo1 = in_vgpr(o1),
-                      vext = in_vgpr(ext);
+        // What a cell gives to the next ones is worked out in its own lane, one opened gap
+        // for both directions, and then shifted: X takes its E from the lower lane's Y and
+        // its F from this lane's, Y its E from this lane's X and its F from the upper lane's.
+        // Nothing leaves a slot past the band: its gaps cost kBswOut, and lane W's Y matches
+        // nothing, so that it stays at or below what its X has been.  Bound by the issue of
+        // one wave: 54 instructions a pair, 75 with tests of the box's end, masks of the
+        // band's and both sides' gaps worked out apart; the 2,477 boxes of 1,000 mid-size
+        // queries, as long as their longest one, in 117 us, 147 before.
+        const int32_t o1X = laneX ? o1 : kBswOut, extX = laneX ? ext : kBswOut;
+        const int32_t o1Y = laneY ? o1 : kBswOut, extY = laneY ? ext : kBswOut;
+        const int32_t matchY = laneY ? match : -kBswOut, misY = laneY ? -mismatch : -kBswOut;
+        const int32_t matchX = in_vgpr(match), misX = in_vgpr(-mismatch);
+        const int32_t low = in_vgpr(kBswBias);
         HX += kBswBias; EX += kBswBias; FX += kBswBias;
         HY += kBswBias; EY += kBswBias; FY += kBswBias;
-        int32_t bestb = best + kBswBias;
-        // Bases two pairs ahead, in two sets that the pairs use in turn (even pairs
-        // set 0, odd pairs set 1), so a read lands in the register its pair reads two
-        // pairs later, with no copy waiting for it in between.
-        // Bases two pairs ahead, in two sets that the pairs use in turn (even pairs
-        // set 0, odd pairs set 1), so a read lands in the register its pair reads two
-        // pairs later, with no copy waiting for it in between.
-        auto fast_pair = [&](int32_t &nq, uint32_t &nd) {
-            const int32_t qb = nq;
-            const uint32_t dd = nd;
-            nq = sq[min(i + 2, R - 1)];
-            nd = sd2[min(j + 2, C - 1)];
-            // keeps the reads here: without it the compiler moves them down to the pair
-            // that uses them (nothing in the loop writes LDS) and waits for them there
-            asm volatile("" ::: "memory");
+        int32_t bestb = laneX ? best + kBswBias : INT32_MAX;
+        const uint8_t *pq = sq + i;
+        const uint16_t *pd = sd2 + j;
+        // Bases two pairs ahead, in two sets that the pairs use in turn, so that a read has
+        // two pairs' time to land
+        auto fast_pair = [&](uint32_t &nq, uint32_t &nd, int ahead) {
+            const bool sx = nq == (nd & 0xffu), sy = nq == nd >> 8;
+            nq = pq[ahead];
+            nd = pd[ahead];
+            // keeps the reads before the pair's arithmetic: the compiler moves them down to
+            // the pair that uses them and waits for them there
+            asm volatile("" : "+v"(HX), "+v"(HY) : : "memory");
             {  // X
-                const CellOut c = sw_cell_b(from_lower_lane(HY), from_lower_lane(EY),
-                                            from_lower_lane(SY), from_lower_lane(SEY), HY, FY, SY,
-                                            SFY, HX, SX, qb == (int32_t)(dd & 0xffu), hereX,
-                                            vmatch, vmis, vo1, vext);
-                HX = c.H; EX = c.E; FX = c.F;
-                SX = c.S; SEX = c.SE; SFX = c.SF;
-                if (a < limX && c.H > bestb) {
-                    bestb = c.H;
-                    bcell = hereX;
-                    bstart = c.S;
-                }
+                const int32_t o = HY - o1Y, e = EY - extY, f = FY - extY;
+                const int32_t E = max(from_lower_lane(max(o, e)), low);
+                const int32_t SE = from_lower_lane(o < e ? SEY : SY);
+                const int32_t F = max(max(o, f), low), SF = o < f ? SFY : SY;
+                const int32_t g = HX + (sx ? matchX : misX), sg = HX > low ? SX : hereX;
+                HX = max(max(g, E), F);
+                SX = g == HX ? sg : (E == HX ? SE : SF);
+                EX = E; FX = F;
+                SEX = SE; SFX = SF;
+                const bool more = HX > bestb;
+                bestb = max(HX, bestb);
+                bcell = more ? hereX : bcell;
+                bstart = more ? SX : bstart;
             }
             {  // Y
-                const CellOut c = sw_cell_b(HX, EX, SX, SEX, from_upper_lane(HX),
-                                            from_upper_lane(FX), from_upper_lane(SX),
-                                            from_upper_lane(SFX), HY, SY,
-                                            qb == (int32_t)(dd >> 8), hereX + 1, vmatch, vmis,
-                                            vo1, vext);
-                HY = laneY ? c.H : 0;
-                EY = c.E;
-                FY = laneY ? c.F : 0;
-                SY = c.S; SEY = c.SE; SFY = c.SF;
-                if (a < limY && c.H > bestb) {
-                    bestb = c.H;
-                    bcell = hereX + 1;
-                    bstart = c.S;
-                }
+                const int32_t o = HX - o1X, e = EX - extX, f = FX - extX;
+                const int32_t E = max(max(o, e), low), SE = o < e ? SEX : SX;
+                const int32_t F = max(from_upper_lane(max(o, f)), low);
+                const int32_t SF = from_upper_lane(o < f ? SFX : SX);
+                const int32_t g = HY + (sy ? matchY : misY);
+                const int32_t sg = HY > low ? SY : hereX + 1;
+                HY = max(max(g, E), F);
+                SY = g == HY ? sg : (E == HY ? SE : SF);
+                EY = E; FY = F;
+                SEY = SE; SFY = SF;
+                const bool more = HY > bestb;
+                bestb = max(HY, bestb);
+                bcell = more ? hereX + 1 : bcell;
+                bstart = more ? SY : bstart;
             }
-            a += 2;
-            ++i;
-            ++j;
             hereX += 128;
         };
-        int32_t nq0 = sq[min(max(i, 0), R - 1)], nq1 = sq[min(max(i + 1, 0), R - 1)];
-        uint32_t nd0 = sd2[min(max(j, 0), C - 1)], nd1 = sd2[min(max(j + 1, 0), C - 1)];
-        // pairs in twos; an odd count ends with one pair past the box, whose cells
-        // are out of it (a >= limX, limY) and read no base outside the staged ones
-        while (a <= a1) {
-            fast_pair(nq0, nd0);
-            fast_pair(nq1, nd1);
+        uint32_t nq0 = pq[0], nq1 = pq[1], nd0 = pd[0], nd1 = pd[1];
+        // pairs in twos; an odd count ends with one pair past the box
+        for (; a <= a1; a += 4, pq += 2, pd += 2) {
+            fast_pair(nq0, nd0, 2);
+            fast_pair(nq1, nd1, 3);
         }
+        if (!laneX) bestb = kBswBias;
         best = bestb - kBswBias;
     }
 }
@@ -6504,8 +6489,8 @@ __global__ __launch_bounds__(64) void k_bsw(
     const uint32_t *__restrict__ sel_box, const uint32_t *__restrict__ order,
     const WaveCtl *__restrict__ ctl)
 {
-    __shared__ uint8_t s_q[kBswStage];
-    __shared__ uint16_t s_d2[kBswStage];  // bank bases x and min(x + 1, C - 1)
+    __shared__ uint8_t s_q[kBswStage + kBswPad];
+    __shared__ uint16_t s_d2[kBswStage + kBswPad];  // bank bases x and x + 1
     const int32_t lane = threadIdx.x;
     if (ctl) {
         nq = ctl->nqw;
@@ -6540,10 +6525,12 @@ __global__ __launch_bounds__(64) void k_bsw(
         else if (span > 512) __builtin_amdgcn_s_setprio(2);
         else if (span > 256) __builtin_amdgcn_s_setprio(1);
         if (R <= kBswStage && C <= kBswStage) {
-            for (int32_t x = lane; x < R; x += 64) s_q[x] = qp[x];
-            for (int32_t x = lane; x < C; x += 64)
-                s_d2[x] = (uint16_t)(db_base(dbw, dbase + x) |
-                                     (db_base(dbw, dbase + min(x + 1, C - 1)) << 8));
+            for (int32_t x = lane; x < R + kBswPad; x += 64) s_q[x] = x < R ? qp[x] : kBswQEnd;
+            for (int32_t x = lane; x < C + kBswPad; x += 64) {
+                const uint32_t b0 = x < C ? db_base(dbw, dbase + x) : kBswDEnd;
+                const uint32_t b1 = x + 1 < C ? db_base(dbw, dbase + x + 1) : kBswDEnd;
+                s_d2[x] = (uint16_t)(b0 | b1 << 8);
+            }
             __syncthreads();
             bsw_sweep<true>(s_q, s_d2, qp, dbw, dbase, R, C, c0, W, a0, a1, match, mismatch, o1,
                             ext, lane, best, bcell, bstart);
