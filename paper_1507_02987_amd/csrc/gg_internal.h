@@ -464,12 +464,13 @@ void launch_merge_groups(const Box *sorted, const uint32_t *offs, uint32_t ngrou
 // Merge (order and sweep) of boxes grouped by (query, sequence), fresh from the
 // extension, in windows of whole groups held in LDS; keys (group rank | qs |
 // d + bias | qe) take 12 + 2 bl + bd <= 64 bits.  Groups that may outgrow a
-// window are listed in big: big[0] = count, then (first, end) pairs, at most
-// big_cap of them; their positions in `out` are left for the global sort.  A
-// window's sweep runs in parallel over its boxes for at most `rounds` rounds of
-// segmented scans; a window that has not settled by then (every window when
-// rounds = 0) is swept group by group, one thread per group.  With ls.binq the
-// owned groups' slots get their length records.
+// window are listed in big: big[0] = count, and from big[2] (first, end) pairs, at most
+// big_cap of them; each of at most 8,192 boxes is then merged by a block of its own, the
+// longer ones listed the same way from big[2 + 2 big_cap], big[1] of them: their positions
+// in `out` are left for the global sort.  A window's or such a block's sweep runs in
+// parallel over its boxes for at most `rounds` rounds of segmented scans; one that has not
+// settled by then (every one when rounds = 0) is swept group by group, one thread per
+// group.  With ls.binq the merged groups' slots get their length records.
 constexpr int kMergeRounds = 12;
 void launch_merge_tiles(const Box *in, uint32_t n, int bl, int bd, int32_t bias, Box *out,
                         uint32_t *big, uint32_t big_cap, int rounds, LenSel ls, hipStream_t st);

@@ -59,11 +59,11 @@ __device__ __forceinline__ uint32_t db_code(const uint32_t *__restrict__ dbw, in
     return c;
 }
 
-// Exclusive scan over the 256 threads of a block; *total receives the block sum.
-template <typename T>
+// Exclusive scan over the threads of a block; *total receives the block sum.
+template <typename T, int THREADS = kBlock>
 __device__ __forceinline__ T block_excl_scan(T v, T *total)
 {
-    __shared__ T s_w[kBlock / 64];
+    __shared__ T s_w[THREADS / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     T x = v;
 #pragma unroll
@@ -75,7 +75,7 @@ __device__ __forceinline__ T block_excl_scan(T v, T *total)
     __syncthreads();
     T before = 0, tot = 0;
 #pragma unroll
-    for (int i = 0; i < kBlock / 64; ++i) {
+    for (int i = 0; i < THREADS / 64; ++i) {
         T t = s_w[i];
         if (i < w) before += t;
         tot += t;
@@ -4987,7 +4987,7 @@ __global__ void k_merge_sweep(const Box *__restrict__ s, uint32_t n, Box *__rest
 // their length records alone where there are any).  A group that may not fit (the last
 // one the block owns, when no other group starts before the block's reach) is recorded
 // in big[1 ..] as (first, end) and left to the global sort; big[0] counts them.
-// Bound by VALU instructions: 3.4 G runs in 107 ms, 39 of them in the sort (132 with
+// Bound by VALU instructions: 3.4 G runs in 93 ms, 39 of them in the sort (118 with
 // 512 keys to a wave, two waves of the four idle, and a 4-byte mark in every slot).
 // W is short of 1,024, so that a window's boxes (W more or less a group) seldom take
 // a fifth round of the block's threads.
@@ -4995,8 +4995,8 @@ constexpr uint32_t kMergeWin = 960;
 constexpr uint32_t kMergeSpan = 2048;
 static_assert(kMergeWin % 64 == 0 && kMergeSpan >= 2 * kMergeWin, "whole waves of positions");
 
-// Stable LSD radix sort of the m <= kMergeSpan keys in s_key (LDS), 8 bits per
-// pass, by a 256-thread block.  The keys are dealt to the four waves evenly (a window
+// Stable LSD radix sort of the m <= 8 THREADS keys in s_key (LDS), 8 bits per
+// pass, by a block of THREADS.  The keys are dealt to the waves evenly (a window
 // holds about half of what it may; with 512 keys to a wave two waves had none), in
 // registers, 64 per round; a key's rank among equal digits of its wave comes from
 // eight ballots (as the global passes rank a tile), the block scans the per-wave
@@ -5004,14 +5004,15 @@ static_assert(kMergeWin % 64 == 0 && kMergeSpan >= 2 * kMergeWin, "whole waves o
 // for the next pass.  Only passes whose digit varies across the keys run
 // (`varying`: OR of every key XOR the first), digits from bit `lo` up (keys equal
 // from bit lo up keep their order).
+template <int THREADS>
 __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_t varying, int lo)
 {
-    constexpr int kPerWave = kMergeSpan / (kBlock / 64);  // 512
-    constexpr int kRounds = kPerWave / 64;                 // 8
-    __shared__ uint16_t s_wc[kBlock / 64][kRadix];
+    constexpr int kWaves = THREADS / 64, kRounds = 8;
+    static_assert(THREADS >= kRadix, "a thread per digit");
+    __shared__ uint16_t s_wc[kWaves][kRadix];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
-    const int rounds = (int)((m + kBlock - 1) / kBlock);
+    const int rounds = (int)((m + THREADS - 1) / THREADS);
     const uint32_t first = (uint32_t)(w * rounds * 64 + lane);  // the lane's first key
     uint64_t k[kRounds];
 #pragma unroll
@@ -5022,8 +5023,9 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
     }
     for (int shift = lo; shift < 64; shift += kRadixBits) {
         if (((varying >> shift) & (kRadix - 1)) == 0) continue;  // same digit everywhere
+        if (THREADS == kRadix || threadIdx.x < kRadix)
 #pragma unroll
-        for (int i = 0; i < kBlock / 64; ++i) s_wc[i][threadIdx.x] = 0;
+            for (int i = 0; i < kWaves; ++i) s_wc[i][threadIdx.x] = 0;
         __syncthreads();
         uint32_t rank[kRounds];
 #pragma unroll
@@ -5049,16 +5051,19 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
         __syncthreads();
         {
             const uint32_t d = threadIdx.x;
-            uint32_t run = 0, wc[kBlock / 64];
+            const bool digit = THREADS == kRadix || d < kRadix;
+            uint32_t run = 0, wc[kWaves];
+            if (digit)
 #pragma unroll
-            for (int i = 0; i < kBlock / 64; ++i) {
-                wc[i] = run;
-                run += s_wc[i][d];
-            }
+                for (int i = 0; i < kWaves; ++i) {
+                    wc[i] = run;
+                    run += s_wc[i][d];
+                }
             uint32_t tot;
-            const uint32_t start = block_excl_scan<uint32_t>(run, &tot);
+            const uint32_t start = block_excl_scan<uint32_t, THREADS>(run, &tot);
+            if (digit)
 #pragma unroll
-            for (int i = 0; i < kBlock / 64; ++i) s_wc[i][d] = (uint16_t)(start + wc[i]);
+                for (int i = 0; i < kWaves; ++i) s_wc[i][d] = (uint16_t)(start + wc[i]);
         }
         __syncthreads();
 #pragma unroll
@@ -5089,13 +5094,14 @@ __device__ void lds_radix_sort(uint64_t *__restrict__ s_key, uint32_t m, uint64_
 // one round that swaps nothing is the usual cost.
 constexpr int kTieRounds = 8;
 
+template <int THREADS>
 __device__ bool lds_order_ties(uint64_t *__restrict__ s_key, uint32_t m, int lo, int rounds)
 {
     for (int round = 0; round < rounds; ++round) {
         bool swapped = false;
 #pragma unroll
         for (int phase = 0; phase < 2; ++phase) {
-            for (uint32_t i = 2 * threadIdx.x + phase; i + 1 < m; i += 2 * kBlock) {
+            for (uint32_t i = 2 * threadIdx.x + phase; i + 1 < m; i += 2 * THREADS) {
                 const uint64_t a = s_key[i], b = s_key[i + 1];
                 if ((a >> lo) == (b >> lo) && a > b) {
                     s_key[i] = b;
@@ -5202,11 +5208,11 @@ __device__ __forceinline__ MTest dpp_up(const MTest &a)
 // (f2, a2) -> (f1 | f2, f2 ? a2 : a1 + a2); within a wave by DPP (row shifts, then
 // the last lane of a row to the next one and of the first half to the second), so
 // no step goes through LDS.  Every thread of the block calls it.
-template <typename T>
+template <int THREADS, typename T>
 __device__ T seg_excl_union(bool f, const T &a, bool *start_before = nullptr)
 {
-    __shared__ int32_t s_wf[kBlock / 64];
-    __shared__ T s_wa[kBlock / 64];
+    __shared__ int32_t s_wf[THREADS / 64];
+    __shared__ T s_wa[THREADS / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int32_t fi = f ? 1 : 0;
     T x = a;
@@ -5250,6 +5256,7 @@ __device__ T seg_excl_union(bool f, const T &a, bool *start_before = nullptr)
 // round drops nothing every key's union is the sweep's and the starts are
 // exactly its.  Returns false (nothing written) when `rounds` rounds did not
 // settle; the caller then sweeps group by group.
+template <int THREADS>
 __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_t m,
                                      const uint16_t *__restrict__ s_start, uint32_t o,
                                      uint32_t nw, uint16_t *__restrict__ s_pg,
@@ -5257,8 +5264,8 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
                                      const Box *__restrict__ in, Box *__restrict__ out,
                                      uint32_t at, int rounds, LenSel ls)
 {
-    constexpr int kPer = kMergeSpan / kBlock;
-    const int per = (int)((m + kBlock - 1) / kBlock);
+    constexpr int kPer = 8;
+    const int per = (int)((m + THREADS - 1) / THREADS);
     const uint64_t mbl = (1ull << bl) - 1ull, mbd = (1ull << bd) - 1ull;
     const int gsh = 2 * bl + bd;
     const uint32_t j0 = threadIdx.x * (uint32_t)per;
@@ -5305,7 +5312,7 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
                 sa = magg_join(sa, b);
             }
         }
-        MTest run = seg_excl_union(sf, sa);
+        MTest run = seg_excl_union<THREADS>(sf, sa);
         bool changed = false;
 #pragma unroll
         for (int r = 0; r < kPer; ++r) {
@@ -5334,13 +5341,13 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
             carry = st ? b : magg_join(carry, b);
             sf = sf || st;
         }
-        carry = seg_excl_union(sf, carry);
+        carry = seg_excl_union<THREADS>(sf, carry);
     }
     // merged box k of group g goes to the group's k-th position: k is its rank
     // among the group's starts, P(j) - P(first key of g) with P(j) the starts in
     // [0, j]; the group's remaining positions are marked empty
     uint32_t tot;
-    const uint32_t before = block_excl_scan<uint32_t>((uint32_t)__popc(F), &tot);
+    const uint32_t before = block_excl_scan<uint32_t, THREADS>((uint32_t)__popc(F), &tot);
     s_f8[threadIdx.x] = (uint8_t)F;
 #pragma unroll
     for (int r = 0; r < kPer; ++r)
@@ -5375,6 +5382,57 @@ __device__ bool merge_sweep_parallel(const uint64_t *__restrict__ s_key, uint32_
         if (ls.binq) ls.binq[at + first + rank] = len_record(bx, ls.shift);
     }
     return true;
+}
+
+// The sweep of one group by one thread, keys [j0, j1) of s_key: merged boxes to the
+// group's first slots from `at` + j0, the rest marked empty.
+__device__ void merge_sweep_serial(const uint64_t *__restrict__ s_key, uint32_t j0, uint32_t j1,
+                                   int bl, int bd, int32_t bias, const Box *__restrict__ in,
+                                   Box *__restrict__ out, uint32_t at, LenSel ls)
+{
+    const uint64_t mbl = (1ull << bl) - 1ull, mbd = (1ull << bd) - 1ull;
+    const int2 qsid = *reinterpret_cast<const int2 *>(in + at + j0);
+    auto decode = [&](uint64_t key) {
+        const int32_t qe = (int32_t)(key & mbl);
+        const int32_t d = (int32_t)((key >> bl) & mbd) - bias;
+        const int32_t qs = (int32_t)((key >> (bl + bd)) & mbl);
+        return Box{qsid.x, qsid.y, qs, qe, qs + d, qe + d, d, d};
+    };
+    // a merged box to its slot, with its length record
+    auto emit = [&](uint32_t slot, const Box &bx) {
+        out[at + slot] = bx;
+        if (ls.binq) ls.binq[at + slot] = len_record(bx, ls.shift);
+    };
+    Box cur = decode(s_key[j0]);
+    uint32_t w = j0;
+    // keys read eight at a time ahead of the fold, which is serial in the group
+    constexpr uint32_t kAheadKeys = 8;
+    for (uint32_t j = j0 + 1; j < j1; j += kAheadKeys) {
+        uint64_t hk[kAheadKeys];
+#pragma unroll
+        for (uint32_t x = 0; x < kAheadKeys; ++x) hk[x] = s_key[min(j + x, j1 - 1)];
+#pragma unroll
+        for (uint32_t x = 0; x < kAheadKeys; ++x) {
+            if (j + x >= j1) break;
+            const Box h = decode(hk[x]);
+            if (h.qs < cur.qe && h.ds < cur.de && cur.ds < h.de) {
+                cur.qs = min(cur.qs, h.qs);
+                cur.qe = max(cur.qe, h.qe);
+                cur.ds = min(cur.ds, h.ds);
+                cur.de = max(cur.de, h.de);
+                cur.dmin = min(cur.dmin, h.dmin);
+                cur.dmax = max(cur.dmax, h.dmax);
+            } else {
+                emit(w++, cur);
+                cur = h;
+            }
+        }
+    }
+    emit(w++, cur);
+    for (; w < j1; ++w) {
+        if (ls.binq) ls.binq[at + w] = kNoBin;
+        else out[at + w].q = -1;
+    }
 }
 
 __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict__ in, uint32_t n,
@@ -5454,8 +5512,8 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
             if (lane == 0) {
                 const uint32_t slot = atomicAdd(big, 1u);
                 if (slot < big_cap) {
-                    big[1 + 2 * slot] = p0;
-                    big[2 + 2 * slot] = end;
+                    big[2 + 2 * slot] = p0;
+                    big[3 + 2 * slot] = end;
                 }
             }
         }
@@ -5488,59 +5546,88 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
     // sorted by (rank, qs, d) in passes over the bits above qe; keys equal there
     // (one start on one diagonal) are then put in qe order, or, when there are
     // too many of them, the keys are sorted again over every bit
-    lds_radix_sort(s_key, m, s_vary[0] & s_vary[1], bl);
-    if (!lds_order_ties(s_key, m, bl, kTieRounds)) lds_radix_sort(s_key, m, s_vary[0] & s_vary[1], 0);
+    lds_radix_sort<kBlock>(s_key, m, s_vary[0] & s_vary[1], bl);
+    if (!lds_order_ties<kBlock>(s_key, m, bl, kTieRounds))
+        lds_radix_sort<kBlock>(s_key, m, s_vary[0] & s_vary[1], 0);
     // the key-building ranks are no longer needed: their space holds the
     // parallel sweep's per-group counts
-    if (merge_sweep_parallel(s_key, m, s_start, o, nw, s_rank,
-                             reinterpret_cast<uint8_t *>(s_rank + kMergeWin), bl, bd, bias, in, out,
-                             base + o, rounds, ls))
+    if (merge_sweep_parallel<kBlock>(s_key, m, s_start, o, nw, s_rank,
+                                     reinterpret_cast<uint8_t *>(s_rank + kMergeWin), bl, bd, bias,
+                                     in, out, base + o, rounds, ls))
         return;
     // sweep each owned group from its keys
     for (uint32_t g = threadIdx.x; g < nw; g += kBlock) {
         const uint32_t j0 = s_start[g] - o, j1 = s_start[g + 1] - o;
-        const int2 qsid = *reinterpret_cast<const int2 *>(in + base + o + j0);
-        auto decode = [&](uint64_t key) {
-            const int32_t qe = (int32_t)(key & mbl);
-            const int32_t d = (int32_t)((key >> bl) & mbd) - bias;
-            const int32_t qs = (int32_t)((key >> (bl + bd)) & mbl);
-            return Box{qsid.x, qsid.y, qs, qe, qs + d, qe + d, d, d};
-        };
-        // a merged box to its slot, with its length record
-        auto emit = [&](uint32_t slot, const Box &bx) {
-            out[base + o + slot] = bx;
-            if (ls.binq) ls.binq[base + o + slot] = len_record(bx, ls.shift);
-        };
-        Box cur = decode(s_key[j0]);
-        uint32_t w = j0;
-        // keys read eight at a time ahead of the fold, which is serial in the group
-        constexpr uint32_t kAheadKeys = 8;
-        for (uint32_t j = j0 + 1; j < j1; j += kAheadKeys) {
-            uint64_t hk[kAheadKeys];
-#pragma unroll
-            for (uint32_t x = 0; x < kAheadKeys; ++x) hk[x] = s_key[min(j + x, j1 - 1)];
-#pragma unroll
-            for (uint32_t x = 0; x < kAheadKeys; ++x) {
-                if (j + x >= j1) break;
-                const Box h = decode(hk[x]);
-                if (h.qs < cur.qe && h.ds < cur.de && cur.ds < h.de) {
-                    cur.qs = min(cur.qs, h.qs);
-                    cur.qe = max(cur.qe, h.qe);
-                    cur.ds = min(cur.ds, h.ds);
-                    cur.de = max(cur.de, h.de);
-                    cur.dmin = min(cur.dmin, h.dmin);
-                    cur.dmax = max(cur.dmax, h.dmax);
-                } else {
-                    emit(w++, cur);
-                    cur = h;
-                }
+        merge_sweep_serial(s_key, j0, j1, bl, bd, bias, in, out, base + o, ls);
+    }
+}
+
+// The groups that k_merge_tiles left (big[0] of them from big[2] on, as first and end), a
+// block of kBigThreads each where they fit its LDS: ordered and swept there as a window
+// is.  Longer ones are listed after the first list, counted in big[1], for the global
+// sort.  That sort took a dozen passes of three launches each, and the groups' boxes were
+// packed and put back around it: the large workload's merge 107 ms, 95 without.
+constexpr int kBigThreads = 1024;
+constexpr uint32_t kBigSpan = 8 * kBigThreads;
+
+__global__ __launch_bounds__(kBigThreads) void k_merge_big(const Box *__restrict__ in, int bl,
+                                                           int bd, int32_t bias,
+                                                           Box *__restrict__ out,
+                                                           uint32_t *__restrict__ big,
+                                                           uint32_t big_cap, int rounds, LenSel ls)
+{
+    __shared__ uint64_t s_key[kBigSpan];
+    __shared__ uint16_t s_start[2], s_pg[1];
+    __shared__ uint8_t s_f8[kBigThreads];
+    __shared__ uint64_t s_vary[2];
+    const uint64_t mbl = (1ull << bl) - 1ull, mbd = (1ull << bd) - 1ull;
+    const uint32_t ng = min(big[0], big_cap);
+    for (uint32_t g = blockIdx.x; g < ng; g += gridDim.x) {
+        const uint32_t a = big[2 + 2 * g], e = big[3 + 2 * g], m = e - a;
+        if (m > kBigSpan) {
+            if (threadIdx.x == 0) {
+                uint32_t *huge = big + 2 + 2 * (size_t)big_cap;
+                const uint32_t slot = atomicAdd(big + 1, 1u);
+                huge[2 * slot] = a;
+                huge[2 * slot + 1] = e;
             }
+            continue;
         }
-        emit(w++, cur);
-        for (; w < j1; ++w) {
-            if (ls.binq) ls.binq[base + o + w] = kNoBin;
-            else out[base + o + w].q = -1;
+        __syncthreads();  // the last group's keys are read
+        if (threadIdx.x == 0) {
+            s_vary[0] = s_vary[1] = 0;
+            s_start[0] = 0;
+            s_start[1] = (uint16_t)m;
         }
+        __syncthreads();
+        uint64_t vary = 0, zeros = 0;
+        for (uint32_t j = threadIdx.x; j < m; j += kBigThreads) {
+            const Box b = in[a + j];
+            const uint64_t d = (uint64_t)(uint32_t)(b.ds - b.qs + bias);
+            const uint64_t key = ((uint64_t)(uint32_t)b.qs << (bl + bd)) | ((d & mbd) << bl) |
+                                 ((uint64_t)(uint32_t)b.qe & mbl);
+            s_key[j] = key;
+            vary |= key;
+            zeros |= ~key;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            vary |= __shfl_xor(vary, off, 64);
+            zeros |= __shfl_xor(zeros, off, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicOr(reinterpret_cast<unsigned long long *>(&s_vary[0]), (unsigned long long)vary);
+            atomicOr(reinterpret_cast<unsigned long long *>(&s_vary[1]), (unsigned long long)zeros);
+        }
+        __syncthreads();
+        const uint64_t varying = s_vary[0] & s_vary[1];
+        lds_radix_sort<kBigThreads>(s_key, m, varying, bl);
+        if (!lds_order_ties<kBigThreads>(s_key, m, bl, kTieRounds))
+            lds_radix_sort<kBigThreads>(s_key, m, varying, 0);
+        if (!merge_sweep_parallel<kBigThreads>(s_key, m, s_start, 0, 1, s_pg, s_f8, bl, bd, bias, in,
+                                               out, a, rounds, ls) &&
+            threadIdx.x == 0)
+            merge_sweep_serial(s_key, 0, m, bl, bd, bias, in, out, a, ls);
     }
 }
 
@@ -5620,7 +5707,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_groups(const Box *__restrict__
                     }
                 }
                 bool before = false;
-                carry = seg_excl_union(sf, sa, &before);
+                carry = seg_excl_union<kBlock>(sf, sa, &before);
                 if (!before) carry = magg_join(open, carry);
                 MAgg run = carry;
                 bool changed = false;
@@ -5723,9 +5810,12 @@ void launch_merge_tiles(const Box *in, uint32_t n, int bl, int bd, int32_t bias,
                         uint32_t *big, uint32_t big_cap, int rounds, LenSel ls, hipStream_t st)
 {
     if (n == 0) return;
-    launch_fill_u32(big, 1, 0u, st);
+    launch_fill_u32(big, 2, 0u, st);
     const uint32_t nb = (n + kMergeWin - 1) / kMergeWin;
     k_merge_tiles<<<nb, kBlock, 0, st>>>(in, n, bl, bd, bias, out, big, big_cap, rounds, ls);
+    // two blocks a CU; they end at once when there is no such group
+    const uint32_t blocks = std::min<uint32_t>(nb, 512);
+    k_merge_big<<<blocks, kBigThreads, 0, st>>>(in, bl, bd, bias, out, big, big_cap, rounds, ls);
 }
 
 void launch_copy_ranges(const Box *src, Box *dst, const uint32_t *ranges, const uint32_t *offs,

@@ -1140,21 +1140,21 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
                                 as<uint32_t>(ws->nsel), st);
         prof.end(nc);
     } else if (windows) {
-        // groups in LDS windows; the few that may outgrow a window by the global sort
+        // groups in LDS windows, those that may outgrow one a block each, the few longer still
+        // by the global sort
         constexpr uint32_t kBigCap = 1u << 16;
-        TRY(ensure(ws->mbig, sizeof(uint32_t) * (1 + 2 * (size_t)kBigCap)));
+        TRY(ensure(ws->mbig, sizeof(uint32_t) * (2 + 4 * (size_t)kBigCap)));
         launch_merge_tiles(boxes, nc, bl, bdm, (int32_t)maxL, as<Box>(ws->boxes3),
                            as<uint32_t>(ws->mbig), kBigCap, merge_sweep_rounds(), ls, st);
-        uint32_t nbig = 0;
-        HIPCHK(hipMemcpyAsync(h_nc, ws->mbig.p, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipMemcpyAsync(h_nc, ws->mbig.p, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         SYNC(st);
-        nbig = h_nc[0];
-        if (nbig > kBigCap) {
+        const uint32_t nleft = h_nc[0], nbig = h_nc[1];  // left by the windows, and by k_merge_big
+        if (nleft > kBigCap) {
             TRY(global_merge(boxes, nc, as<Box>(ws->boxes2), as<Box>(ws->boxes3)));
             if (ls.binq) launch_len_records(as<Box>(ws->boxes3), nc, ls, st);  // all anew
         } else if (nbig > 0) {
             std::vector<uint32_t> ranges(2 * (size_t)nbig), offs((size_t)nbig + 1, 0);
-            HIPCHK(hipMemcpyAsync(ranges.data(), as<uint32_t>(ws->mbig) + 1,
+            HIPCHK(hipMemcpyAsync(ranges.data(), as<uint32_t>(ws->mbig) + 2 + 2 * (size_t)kBigCap,
                                   sizeof(uint32_t) * 2 * nbig, hipMemcpyDeviceToHost, st));
             SYNC(st);
             // packed in position order, so the global sort keeps the groups' order

@@ -112,3 +112,39 @@ def test_merge_sweep_forms(ggo, bank, monkeypatch, merge, N):
         assert rc == 0
         assert int(st[i]["n_merged"]) == wst["n_merged"], (i, merge)
         assert as_rows(got[i]) == as_rows(h), f"query {i}, GG_MERGE={merge}"
+
+
+def one_group(L, T=1500):
+    """A sequence of one tract of L bases and a query of T of the same unit: a group of
+    a run for every way the tracts meet, (L + T) / 5 or so."""
+    rng = np.random.Generator(np.random.PCG64(np.random.SeedSequence([150702987, 92])))
+    acgt = np.frombuffer(b"ACGT", np.uint8)
+    unit = acgt[rng.integers(0, 4, 5)]
+    end = lambda: acgt[rng.integers(0, 4, 300)]
+    seq = np.concatenate([end(), np.resize(unit, L), end()])
+    q = np.concatenate([end(), np.resize(np.roll(unit, 2), T), end()])
+    other = end()
+    seqs = np.concatenate([seq, other])
+    return seqs, np.array([0, len(seq), len(seqs)], np.int64), q
+
+
+@pytest.mark.parametrize("merge", ["", "serial"])
+@pytest.mark.parametrize("L", [6_000, 39_510, 39_515, 39_520, 39_525, 60_000])
+def test_a_group_of_a_block(ggo, monkeypatch, merge, L):
+    """Groups over a window: up to 8,192 boxes by a block, more by the global sort."""
+    G = gpu()
+    if merge:
+        monkeypatch.setenv("GG_MERGE", merge)
+    for v in ("GG_GROUPING", "GG_GRAPH"):
+        monkeypatch.delenv(v, raising=False)
+    seqs, off, q = one_group(L)
+    gix, oix = G.Index(seqs, off, 11), ggo.Index(seqs, off, 11)
+    qoff = np.array([0, len(q)], np.int64)
+    for N in (20, 0):
+        rc, want, _, wst = oix.search(q, ggo.params(N), cap=100000)
+        assert rc == 0 and wst["n_cands"] > 1024
+        rc, got, n, st = gix.search_batch(q, qoff, G.params(N), cap=100000, stats=True)
+        assert rc == 0
+        for f in FIELDS:
+            assert int(st[0][f]) == wst[f], f
+        assert as_rows(got[0]) == as_rows(want)
