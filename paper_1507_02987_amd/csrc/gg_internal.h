@@ -446,11 +446,11 @@ void launch_gather_aligns(const Align *in, const uint32_t *perm, uint32_t n, Ali
 // out, per-query segments seg_off of at most kSegCap boxes), and the kept boxes' ranges
 // and the counts of the selected (the first N, all for N = 0).  A replayed wave: a query
 // over the LDS sort sets its ctl->qflag entry and selects none; the launch also moves
-// *cursor on and clears classes[0..64).
+// *cursor on.
 void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
                              HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
                              uint32_t *nsel, hipStream_t st, WaveCtl *ctl = nullptr,
-                             uint32_t *cursor = nullptr, uint32_t *classes = nullptr);
+                             uint32_t *cursor = nullptr);
 // The selection order alone, of boxes that are merged (all of them kept).
 void launch_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
                        HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
@@ -503,7 +503,8 @@ void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_o
                 int32_t gap_open, int32_t gap_extend, int32_t band, Align *out,
                 unsigned long long *cells_per_q, unsigned long long *cells_per_box,
                 hipStream_t st, const WaveCtl *ctl = nullptr, const uint32_t *sel_box = nullptr,
-                uint32_t *order_buf = nullptr);
+                uint32_t *order_buf = nullptr,
+                uint32_t sel_cap = 0);
 // dir_off[h] = 64 * (sum of q_end - q_start over hits before h), h in [0, n].
 void launch_dir_offsets(const int32_t *hits, int32_t n, int64_t *dir_off, hipStream_t st);
 // ops_len[h] = -1 where status[h] != 0.

@@ -4625,8 +4625,7 @@ struct BoxLess {
 // (merged boxes from a stretch's start, the rest marked empty), then written out in selection
 // order, with the range of the kept ones (qstart, qend) and how many of them are
 // selected (nsel; the first N, all for N = 0).  A replayed wave (ctl given) flags a
-// query of more boxes, and its block 0 moves the wave cursor on and clears the
-// aligner's class counts.  A serial chain: 1,000 queries of up to 80 boxes took 46 us by
+// query of more boxes, and its block 0 moves the wave cursor on.  A serial chain: 1,000 queries of up to 80 boxes took 46 us by
 // a network of record comparisons in LDS and one thread's sweep of each sequence's
 // boxes; 25 by counted places, 16 with the sweep in stretches.
 // MERGED: the boxes are merged already, and only put in selection order.
@@ -4634,8 +4633,7 @@ template <bool MERGED>
 __global__ __launch_bounds__(kBlock) void k_merge_select_seg(
     const Box *__restrict__ in, Box *__restrict__ out, const uint32_t *__restrict__ seg_off,
     HitKeyLayout lay, int32_t N, uint32_t *__restrict__ qstart, uint32_t *__restrict__ qend,
-    uint32_t *__restrict__ nsel, WaveCtl *__restrict__ ctl, uint32_t *__restrict__ cursor,
-    uint32_t *__restrict__ classes)
+    uint32_t *__restrict__ nsel, WaveCtl *__restrict__ ctl, uint32_t *__restrict__ cursor)
 {
     __shared__ Box s_r[kSegCap];
     __shared__ uint64_t s_key[kSegCap];
@@ -4645,10 +4643,7 @@ __global__ __launch_bounds__(kBlock) void k_merge_select_seg(
     const uint16_t *s_ix = reinterpret_cast<const uint16_t *>(s_key);  // seg_order's result
     const int32_t ql = blockIdx.x;
     if (ctl) {
-        if (ql == 0) {
-            if (threadIdx.x == 0) *cursor += 1;
-            if (threadIdx.x < 64) classes[threadIdx.x] = 0;
-        }
+        if (ql == 0 && threadIdx.x == 0) *cursor += 1;
         lay = ctl->lay;
     }
     uint32_t a0 = 0, n = 0;
@@ -4770,12 +4765,11 @@ __global__ __launch_bounds__(kBlock) void k_merge_select_seg(
 
 void launch_merge_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
                              HitKeyLayout lay, int32_t N, uint32_t *qstart, uint32_t *qend,
-                             uint32_t *nsel, hipStream_t st, WaveCtl *ctl, uint32_t *cursor,
-                             uint32_t *classes)
+                             uint32_t *nsel, hipStream_t st, WaveCtl *ctl, uint32_t *cursor)
 {
     if (nq > 0)
         k_merge_select_seg<false><<<nq, kBlock, 0, st>>>(in, out, seg_off, lay, N, qstart, qend,
-                                                         nsel, ctl, cursor, classes);
+                                                         nsel, ctl, cursor);
 }
 
 void launch_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t nq,
@@ -4784,7 +4778,7 @@ void launch_select_seg(const Box *in, Box *out, const uint32_t *seg_off, int32_t
 {
     if (nq > 0)
         k_merge_select_seg<true><<<nq, kBlock, 0, st>>>(in, out, seg_off, lay, N, qstart, qend, nsel,
-                                                        nullptr, nullptr, nullptr);
+                                                        nullptr, nullptr);
 }
 
 // Report order: alignments with score > 0 first, score descending, then seq,
@@ -6493,9 +6487,12 @@ __device__ __forceinline__ Box bsw_box(uint32_t b, const Box *__restrict__ sorte
 // chain of about R + C anti-diagonals, so the longest boxes bound the kernel's
 // time; listed first, they start at once and the short ones fill in around them.
 // Boxes are classed by floor(log2(R + C)) (order within a class is arbitrary: each
-// box writes its own output slot).  cnt[0..32) counts the classes, cnt[32..64)
-// hands out slots within them; both start at zero.
+// box writes its own output slot).  Block b orders every kOrderBlocks-th box from the b-th
+// on, and the blocks' lists are interleaved: longest first nearly enough, with no count
+// over all boxes and no launch for it.  Boxes that the chip holds at once (12 waves a CU,
+// by the LDS they stage in) all start together and are not ordered.
 constexpr int kOrderBlocks = 64;
+constexpr uint32_t kBswAtOnce = 256 * 12;
 
 __device__ __forceinline__ uint32_t bsw_class(const Box &bx)
 {
@@ -6503,67 +6500,35 @@ __device__ __forceinline__ uint32_t bsw_class(const Box &bx)
     return n ? 31u - (uint32_t)__clz(n) : 0u;
 }
 
-__global__ __launch_bounds__(kBlock) void k_bsw_classes(
-    const Box *__restrict__ sorted, const uint32_t *__restrict__ qstart,
-    const uint32_t *__restrict__ sel_off, int32_t nq, uint32_t total,
-    const uint32_t *__restrict__ sel_box, uint32_t *__restrict__ cnt,
-    const WaveCtl *__restrict__ ctl)
-{
-    __shared__ uint32_t s_c[32];
-    if (ctl) {
-        nq = ctl->nqw;
-        total = nq > 0 ? sel_off[nq] : 0;
-    }
-    if (threadIdx.x < 32) s_c[threadIdx.x] = 0;
-    __syncthreads();
-    for (uint32_t b = blockIdx.x * kBlock + threadIdx.x; b < total; b += gridDim.x * kBlock) {
-        int32_t q;
-        atomicAdd(&s_c[bsw_class(bsw_box(b, sorted, qstart, sel_off, nq, sel_box, q))], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x < 32 && s_c[threadIdx.x]) atomicAdd(&cnt[threadIdx.x], s_c[threadIdx.x]);
-}
-
 __global__ __launch_bounds__(kBlock) void k_bsw_order(
     const Box *__restrict__ sorted, const uint32_t *__restrict__ qstart,
     const uint32_t *__restrict__ sel_off, int32_t nq, uint32_t total,
-    const uint32_t *__restrict__ sel_box, uint32_t *__restrict__ cnt,
-    uint32_t *__restrict__ order, const WaveCtl *__restrict__ ctl)
+    const uint32_t *__restrict__ sel_box, uint32_t *__restrict__ order,
+    const WaveCtl *__restrict__ ctl)
 {
-    __shared__ uint32_t s_c[32], s_base[32];
+    __shared__ uint32_t s_c[32], s_at[32];
     if (ctl) {
         nq = ctl->nqw;
         total = nq > 0 ? sel_off[nq] : 0;
+        if (total <= kBswAtOnce) return;
     }
-    const uint32_t stride = gridDim.x * kBlock;
     if (threadIdx.x < 32) s_c[threadIdx.x] = 0;
     __syncthreads();
-    uint32_t cls[8], rank[8];  // a block's boxes: at most 8 per thread per sweep
-    for (uint32_t b0 = blockIdx.x * kBlock; b0 < total; b0 += 8 * stride) {
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const uint32_t b = b0 + r * stride + threadIdx.x;
-            cls[r] = 32;
-            if (b < total) {
-                int32_t q;
-                cls[r] = bsw_class(bsw_box(b, sorted, qstart, sel_off, nq, sel_box, q));
-                rank[r] = atomicAdd(&s_c[cls[r]], 1u);
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < 32) {  // the block's slots in each class, classes longest first
-            uint32_t above = 0;
-            for (uint32_t c = 31; c > threadIdx.x; --c) above += cnt[c];
-            const uint32_t n = s_c[threadIdx.x];
-            s_base[threadIdx.x] = n ? above + atomicAdd(&cnt[32 + threadIdx.x], n) : 0u;
-            s_c[threadIdx.x] = 0;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < 8; ++r)
-            if (cls[r] < 32) order[s_base[cls[r]] + rank[r]] = b0 + r * stride + threadIdx.x;
-        __syncthreads();
+    auto cls = [&](uint32_t b) {
+        int32_t q;
+        return bsw_class(bsw_box(b, sorted, qstart, sel_off, nq, sel_box, q));
+    };
+    for (uint32_t b = blockIdx.x + threadIdx.x * kOrderBlocks; b < total; b += kBlock * kOrderBlocks)
+        atomicAdd(&s_c[cls(b)], 1u);
+    __syncthreads();
+    if (threadIdx.x < 32) {
+        uint32_t above = 0;
+        for (uint32_t c = 31; c > threadIdx.x; --c) above += s_c[c];
+        s_at[threadIdx.x] = above;
     }
+    __syncthreads();
+    for (uint32_t b = blockIdx.x + threadIdx.x * kOrderBlocks; b < total; b += kBlock * kOrderBlocks)
+        order[atomicAdd(&s_at[cls(b)], 1u) * kOrderBlocks + blockIdx.x] = b;
 }
 
 // One wave (one block) per selected box; boxes whose bases fit kBswStage each
@@ -6586,6 +6551,7 @@ __global__ __launch_bounds__(64) void k_bsw(
         nq = ctl->nqw;
         qa = ctl->qa;
         total = nq > 0 ? sel_off[nq] : 0;
+        if (total <= kBswAtOnce) order = nullptr;
     }
     for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
     const uint32_t b = order ? order[i] : i;
@@ -6674,20 +6640,17 @@ void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_o
                 const uint32_t *dbw, const int64_t *seq_start, int32_t match, int32_t mismatch,
                 int32_t gap_open, int32_t gap_extend, int32_t band, Align *out,
                 unsigned long long *cells_per_q, unsigned long long *cells_per_box, hipStream_t st,
-                const WaveCtl *ctl, const uint32_t *sel_box, uint32_t *order_buf)
+                const WaveCtl *ctl, const uint32_t *sel_box, uint32_t *order_buf,
+                uint32_t sel_cap)
 {
     // graph form: the wave's selection count is read on the device
     const uint32_t grid = ctl ? 8 * kStrideGrid : std::min<uint32_t>(nsel_total, kMaxGrid);
     if (grid == 0) return;
     uint32_t *order = nullptr;
-    if (order_buf) {
-        uint32_t *cnt = order_buf;
-        order = order_buf + 64;
-        if (!ctl) launch_fill_u32(cnt, 64, 0u, st);  // a replayed wave's are cleared before
-        k_bsw_classes<<<kOrderBlocks, kBlock, 0, st>>>(sorted, qstart, sel_off, nq, nsel_total,
-                                                       sel_box, cnt, ctl);
+    if (order_buf && (ctl ? sel_cap : nsel_total) > kBswAtOnce) {
+        order = order_buf;
         k_bsw_order<<<kOrderBlocks, kBlock, 0, st>>>(sorted, qstart, sel_off, nq, nsel_total,
-                                                     sel_box, cnt, order, ctl);
+                                                     sel_box, order, ctl);
     }
     k_bsw<<<grid, 64, 0, st>>>(sorted, qstart, sel_off, nq, nsel_total, qcode, qoff, qa, dbw,
                                seq_start, match, mismatch, gap_open + gap_extend, gap_extend, band,

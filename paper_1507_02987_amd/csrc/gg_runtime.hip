@@ -113,7 +113,7 @@ struct Workspace {
     DevBuf tpos;                        // the position where each gather tile starts
     DevBuf mbig, mranges;               // merge groups that may outgrow an LDS window
     DevBuf selbox;                      // the box index of each selection (replayed waves)
-    DevBuf bsw_order;                   // the aligner's class counts and box order
+    DevBuf bsw_order;                   // the aligner's box order
     DevBuf qctx, sbase, scount;         // run starts from contexts: per position, per query
     // small pinned staging: [0] a wave's counts, [1] a batch's hit totals, query offsets
     // and small texts, [2] the replayed waves' plan, [3] their result counts and [4] their
@@ -1284,7 +1284,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     TRY(ensure(ws->cells_q, sizeof(unsigned long long) * nqw));
     HIPCHK(hipMemsetAsync(ws->cells_q.p, 0, sizeof(unsigned long long) * nqw, st));
     if (piece) TRY(ensure(ws->cells_box, sizeof(unsigned long long) * nsel));
-    TRY(ensure(ws->bsw_order, sizeof(uint32_t) * ((size_t)nsel + 64)));
+    TRY(ensure(ws->bsw_order, sizeof(uint32_t) * (size_t)nsel));
     prof.begin("align");
     launch_bsw(as<Box>(ws->boxes2), as<uint32_t>(ws->qstart), as<uint32_t>(ws->sel_off), nqw, nsel,
                as<uint8_t>(ws->qcode), as<int64_t>(ws->qoff), qa, ix->d_dbw, ix->d_seq_start,
@@ -1758,7 +1758,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     TRY(ensure(ws->aligns, sizeof(Align) * std::max<uint32_t>(sel_cap, 1)));
     TRY(ensure(ws->aligns2, sizeof(Align) * std::max<uint32_t>(sel_cap, 1)));
     TRY(ensure(ws->selbox, sizeof(uint32_t) * std::max<uint32_t>(sel_cap, 1)));
-    TRY(ensure(ws->bsw_order, sizeof(uint32_t) * ((size_t)sel_cap + 64)));
+    TRY(ensure(ws->bsw_order, sizeof(uint32_t) * (size_t)std::max<uint32_t>(sel_cap, 1)));
     TRY(ensure(ws->gctl, sizeof(WaveCtl)));
     TRY(ensure(ws->gplan, sizeof(WaveCtl) * nwave_cap));
     TRY(ensure(ws->gcursor, sizeof(uint32_t) * 4));
@@ -1882,8 +1882,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
         launch_merge_select_seg(as<Box>(ws->boxes), as<Box>(ws->boxes2),
                                 as<uint32_t>(ws->cand_off), nq_cap, HitKeyLayout{}, N,
                                 as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
-                                as<uint32_t>(ws->nsel), st, ctl, cursor,
-                                as<uint32_t>(ws->bsw_order));
+                                as<uint32_t>(ws->nsel), st, ctl, cursor);
         if (nq_cap <= 4096)  // scanned by one block, which lists the boxes too
             launch_select_scan(as<uint32_t>(ws->qstart), as<uint32_t>(ws->nsel), nq_cap,
                                as<uint32_t>(ws->sel_off), as<uint32_t>(ws->selbox), st);
@@ -1895,7 +1894,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
                    p->match, p->mismatch, p->gap_open, p->gap_extend, p->band,
                    as<Align>(ws->aligns), nullptr, nullptr, st, ctl,
                    nq_cap <= 4096 ? as<uint32_t>(ws->selbox) : nullptr,
-                   as<uint32_t>(ws->bsw_order));
+                   as<uint32_t>(ws->bsw_order), sel_cap);
         launch_report_seg(as<Align>(ws->aligns), as<Align>(ws->aligns2), as<uint32_t>(ws->sel_off),
                           nq_cap, HitKeyLayout{}, p->match, as<uint32_t>(ws->rstart),
                           as<uint32_t>(ws->rend), 0, cap, gout, gn, st, ctl, nout);
