@@ -4280,8 +4280,11 @@ void launch_extend(const Cand *c, uint32_t n, const uint8_t *qcode, const uint32
                  : (split ? k_extend<false, true> : k_extend<false, false>);
     k<<<nb, kBlock, 0, st>>>(c, n, qpack, qoff, qa, dbw, seq_start, match, mismatch, xdrop, out,
                              queue, qcap, qcount, steps, ctl);
+    // as many blocks as the chip holds, at most: how many walks are queued is known only
+    // there, and a grid for all that might be spends its time on blocks with none (65,536
+    // of them took 14 us)
     const uint64_t most = std::min<uint64_t>(2ull * nmax, qcap);  // queued walks at most
-    const uint32_t lb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((most + 3) / 4, 1u << 16));
+    const uint32_t lb = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((most + 3) / 4, kStrideGrid));
     k_extend_long<<<lb, kBlock, 0, st>>>(c, qcode, qoff, qa, dbw, seq_start, match, mismatch,
                                          xdrop, out, queue, qcap, qcount, ctl);
 }
@@ -6643,8 +6646,9 @@ void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_o
                 const WaveCtl *ctl, const uint32_t *sel_box, uint32_t *order_buf,
                 uint32_t sel_cap)
 {
-    // graph form: the wave's selection count is read on the device
-    const uint32_t grid = ctl ? 8 * kStrideGrid : std::min<uint32_t>(nsel_total, kMaxGrid);
+    // graph form: the wave's selection count, sel_cap at most, is read on the device
+    const uint32_t grid = ctl ? std::min(sel_cap, 8 * kStrideGrid)
+                              : std::min<uint32_t>(nsel_total, kMaxGrid);
     if (grid == 0) return;
     uint32_t *order = nullptr;
     if (order_buf && (ctl ? sel_cap : nsel_total) > kBswAtOnce) {
