@@ -6214,49 +6214,23 @@ __device__ __forceinline__ unsigned long long band_cells(int32_t R, int32_t C, i
     return n;
 }
 
-// One cell of the affine recurrence with start tracking (see the oracle's O9):
-// E/F open from the left/upper cell when the open term is >= the extend term;
-// H > 0 takes its start from G (its diagonal predecessor's start, or itself if
-// that H <= 0), else from E, else from F.  The start of a cell with H <= 0 is
-// left as that rule gives it: no cell with H > 0 inherits it (the diagonal
-// successor takes its own position, and a gap opened from H <= 0 is negative
-// and stays so, as the penalties are >= 0), and only cells with H > 0 are
-// reported.
-struct CellOut {
-    int32_t H, E, F, S, SE, SF;
-};
-
-__device__ __forceinline__ CellOut sw_cell(int32_t hl, int32_t el, int32_t sl, int32_t sel,
-                                           int32_t hu, int32_t fu, int32_t su, int32_t sfu,
-                                           int32_t hd, int32_t sd, bool same, int32_t here,
-                                           int32_t match, int32_t mismatch, int32_t o1,
-                                           int32_t ext)
-{
-    CellOut c;
-    const int32_t eo = hl - o1, ee = el - ext;
-    const bool eop = eo >= ee;
-    c.E = eop ? eo : ee;
-    c.SE = eop ? sl : sel;
-    const int32_t fo = hu - o1, fe = fu - ext;
-    const bool fop = fo >= fe;
-    c.F = fop ? fo : fe;
-    c.SF = fop ? su : sfu;
-    const int32_t g = hd + (same ? match : -mismatch);
-    c.H = max(max(g, 0), max(c.E, c.F));
-    const int32_t sg = hd > 0 ? sd : here;
-    c.S = (g == c.H) ? sg : ((c.E == c.H) ? c.SE : c.SF);
-    return c;
-}
-
-// After the border pairs a staged box's values are offset by kBswBias: minus infinity is
-// then any value <= kBswBias, the H floor, since what a gap gives from below the floor stays
-// at or below it.  So E and F are kept at the floor (their maximum with it leaves H one
-// maximum), and the zero that a DPP lane shift brings into lane 0 or 63 needs no test.
+// The affine recurrence with start tracking (see the oracle's O9): E and F open from the
+// left or upper cell when the open term is >= the extend term; H > 0 takes its start from
+// G (its diagonal predecessor's start, or itself if that H <= 0), else from E, else from
+// F.  The start of a cell with H <= 0 is left as that rule gives it: no cell with H > 0
+// inherits it (the diagonal successor takes its own position, and a gap opened from
+// H <= 0 stays there, as the penalties are >= 0), and only cells with H > 0 are reported.
+//
+// Values are offset by kBswBias: minus infinity is then any value <= kBswBias, the H floor,
+// since what a gap gives from below the floor stays at or below it.  So E and F are kept at
+// the floor (their maximum with it leaves H one maximum), and the zero that a DPP lane
+// shift brings into lane 0 or 63 needs no test.
 constexpr int32_t kBswBias = 1 << 29;
 constexpr int32_t kBswOut = 1 << 30;  // a gap or mismatch cost that leaves nothing
-// Bases past a box's end match none: a cell past the box is then no better than one in
-// the box that it comes from, and at a later place, so it is never the best one and needs
-// no test either.  A sweep reads up to kBswPad of them.
+// Bases before and past a box match none.  Cells before the box are then at the floor, as
+// its border is; a cell past it is no better than one in the box that it comes from, and
+// at a later place, so it is never the best one.  Neither needs a test.  A sweep reads up
+// to kBswPad such bases on each side.
 constexpr int kBswPad = 80;
 constexpr uint32_t kBswQEnd = 4, kBswDEnd = 5;
 
@@ -6275,15 +6249,12 @@ __device__ __forceinline__ int32_t in_vgpr(int32_t s)
 // column to the right.  X's left neighbour is the lower lane's previous Y, its
 // upper neighbour this lane's previous Y, its diagonal this lane's previous X;
 // Y's left neighbour is this lane's X, its upper the upper lane's X, its diagonal
-// this lane's previous Y.  Lanes past the band (u > W) follow lane W's cells, so
-// every base they read is in the box; no band cell reads their values.
-// Staged bank bases come in pairs: sd2[x] holds base x and base x + 1.
-template <bool STAGED>
-__device__ __forceinline__ void bsw_sweep(const uint8_t *__restrict__ sq,
-                                          const uint16_t *__restrict__ sd2,
-                                          const uint8_t *__restrict__ qp,
-                                          const uint32_t *__restrict__ dbw, int64_t dbase,
-                                          int32_t R, int32_t C, int32_t c0, int32_t W, int32_t a0,
+// this lane's previous Y.  Lanes past the band (u > W) follow lane W's cells, so that
+// their reads stay near the box; no band cell reads their values.
+// qat(i + kBswPad): the code of row i, kBswQEnd outside the box; dat(j + kBswPad): those of
+// columns j and j + 1 (in the low and the high byte), kBswDEnd outside.
+template <typename Q, typename D>
+__device__ __forceinline__ void bsw_sweep(Q qat, D dat, int32_t c0, int32_t W, int32_t a0,
                                           int32_t a1, int32_t match, int32_t mismatch, int32_t o1,
                                           int32_t ext, int32_t lane, int32_t &best,
                                           int32_t &bcell, int32_t &bstart)
@@ -6291,177 +6262,74 @@ __device__ __forceinline__ void bsw_sweep(const uint8_t *__restrict__ sq,
     const int32_t tX = 2 * lane, tY = tX + 1;
     const bool laneX = tX <= 2 * W, laneY = tY <= 2 * W;
     const int32_t dXl = min(tX, 2 * W) - W + c0;  // the lane's X diagonal j - i
-    int32_t i = (a0 - dXl) >> 1;
-    int32_t j = a0 - i;
+    const int32_t i = (a0 - dXl) >> 1;
     int32_t hereX = i * 128 + tX;
-    // the pair before the first, (i - 1, j - 1) and (i - 1, j), by the rule below: no
-    // in-box cell of the band lies on its anti-diagonals, so it is border or -inf
-    int32_t HX = (i < 1 || j < 1) ? 0 : kNegInf, EX = kNegInf, FX = kNegInf, SX = 0, SEX = 0,
-            SFX = 0;
-    int32_t HY = (i < 1 || j < 0) ? 0 : kNegInf, EY = kNegInf, FY = kNegInf, SY = 0, SEY = 0,
-            SFY = 0;
-    auto bases = [&](int32_t ii, int32_t jj, int32_t &qb, int32_t &dX, int32_t &dY) {
-        const int32_t ic = min(max(ii, 0), R - 1);
-        const int32_t jc = min(max(jj, 0), C - 1), jc1 = min(max(jj + 1, 0), C - 1);
-        if (STAGED) {
-            qb = sq[ic];
-            dX = sd2[jc] & 0xff;
-            dY = sd2[jc1] & 0xff;
-        } else {
-            qb = qp[ic];
-            dX = db_base(dbw, dbase + jc);
-            dY = db_base(dbw, dbase + jc1);
+    // What a cell gives to the next ones is worked out in its own lane, one opened gap
+    // for both directions, and then shifted: X takes its E from the lower lane's Y and
+    // its F from this lane's, Y its E from this lane's X and its F from the upper lane's.
+    // Nothing leaves a slot past the band: its gaps cost kBswOut, and lane W's Y matches
+    // nothing, so that it stays at or below what its X has been.  Bound by the issue of
+    // one wave: 54 instructions a pair, 75 with tests of the box's end, masks of the
+    // band's and both sides' gaps worked out apart; the 2,477 boxes of 1,000 mid-size
+    // queries, as long as their longest one, in 116 us, 147 before.
+    const int32_t o1X = laneX ? o1 : kBswOut, extX = laneX ? ext : kBswOut;
+    const int32_t o1Y = laneY ? o1 : kBswOut, extY = laneY ? ext : kBswOut;
+    const int32_t matchY = laneY ? match : -kBswOut, misY = laneY ? -mismatch : -kBswOut;
+    const int32_t matchX = in_vgpr(match), misX = in_vgpr(-mismatch);
+    const int32_t low = in_vgpr(kBswBias);
+    int32_t HX = low, EX = low, FX = low, SX = 0, SEX = 0, SFX = 0;
+    int32_t HY = low, EY = low, FY = low, SY = 0, SEY = 0, SFY = 0;
+    int32_t bestb = laneX ? kBswBias : INT32_MAX;
+    uint32_t ii = (uint32_t)(i + kBswPad), jj = (uint32_t)(a0 - i + kBswPad);
+    // Bases two pairs ahead, in two sets that the pairs use in turn, so that a read has
+    // two pairs' time to land
+    auto pair = [&](uint32_t &nq, uint32_t &nd, uint32_t ahead) {
+        const bool sx = nq == (nd & 0xffu), sy = nq == nd >> 8;
+        nq = qat(ii + ahead);
+        nd = dat(jj + ahead);
+        // keeps the reads before the pair's arithmetic: the compiler moves them down to
+        // the pair that uses them and waits for them there
+        asm volatile("" : "+v"(HX), "+v"(HY) : : "memory");
+        {  // X
+            const int32_t o = HY - o1Y, e = EY - extY, f = FY - extY;
+            const int32_t E = max(from_lower_lane(max(o, e)), low);
+            const int32_t SE = from_lower_lane(o < e ? SEY : SY);
+            const int32_t F = max(max(o, f), low), SF = o < f ? SFY : SY;
+            const int32_t g = HX + (sx ? matchX : misX), sg = HX > low ? SX : hereX;
+            HX = max(max(g, E), F);
+            SX = g == HX ? sg : (E == HX ? SE : SF);
+            EX = E; FX = F;
+            SEX = SE; SFX = SF;
+            const bool more = HX > bestb;
+            bestb = max(HX, bestb);
+            bcell = more ? hereX : bcell;
+            bstart = more ? SX : bstart;
         }
+        {  // Y
+            const int32_t o = HX - o1X, e = EX - extX, f = FX - extX;
+            const int32_t E = max(max(o, e), low), SE = o < e ? SEX : SX;
+            const int32_t F = max(from_upper_lane(max(o, f)), low);
+            const int32_t SF = from_upper_lane(o < f ? SFX : SX);
+            const int32_t g = HY + (sy ? matchY : misY);
+            const int32_t sg = HY > low ? SY : hereX + 1;
+            HY = max(max(g, E), F);
+            SY = g == HY ? sg : (E == HY ? SE : SF);
+            EY = E; FY = F;
+            SEY = SE; SFY = SF;
+            const bool more = HY > bestb;
+            bestb = max(HY, bestb);
+            bcell = more ? hereX + 1 : bcell;
+            bstart = more ? SY : bstart;
+        }
+        hereX += 128;
     };
-    int32_t nqb, ndX, ndY;  // bases of the next pair, read one pair ahead
-    bases(i, j, nqb, ndX, ndY);
-    // Every cell a lane computes follows one rule: a cell before the box (row or
-    // column < 0) is the border (H = 0, E = F = -inf), a slot outside the band is
-    // -inf, any other cell takes the recurrence.  In-box cells read only cells at or
-    // before them, so this gives them exactly the box's borders and band; cells past
-    // the box are never read and only kept out of the best cell.  The one neighbour
-    // no lane holds, left of slot 0, is the border in column 0 and -inf elsewhere.
-    // The first pairs hold cells before the box (row or column < 0); once every
-    // band lane has reached row and column 0 (after `edge` pairs) no cell is, and
-    // after one pair more slot 0's left neighbour is -inf for good: the rest of the
-    // sweep drops the border tests.  There only the one lane whose Y slot lies past
-    // the band (t = 2W + 1) is still forced to -inf, since its X reads it; other
-    // slots past the band are read by no in-band cell.
-    int32_t edge = (lane <= W) ? max(0, max(-i, -j)) : 0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) edge = max(edge, __shfl_xor(edge, off, 64));
-    edge = __builtin_amdgcn_readfirstlane(edge) + 1;
-    auto pair = [&](auto edge_tag) {
-        constexpr bool EDGE = decltype(edge_tag)::value;
-        const int32_t qb = nqb, dX = ndX, dY = ndY;
-        bases(i + 1, j + 1, nqb, ndX, ndY);
-        const bool before_row = EDGE && i < 0;
-        const bool rowin = (uint32_t)i < (uint32_t)R;
-        {  // X = (i, j): left = the lower lane's previous Y, up = this lane's previous Y
-            int32_t hl = from_lower_lane(HY), el = from_lower_lane(EY);
-            const int32_t sl = from_lower_lane(SY), sel = from_lower_lane(SEY);
-            if (lane == 0) {
-                hl = j == 0 ? 0 : kNegInf;
-                el = kNegInf;
-            }
-            const CellOut c = sw_cell(hl, el, sl, sel, HY, FY, SY, SFY, HX, SX, qb == dX, hereX,
-                                      match, mismatch, o1, ext);
-            if (EDGE) {
-                const bool border = before_row || j < 0;
-                HX = border ? 0 : (laneX ? c.H : kNegInf);
-                EX = (border || !laneX) ? kNegInf : c.E;
-                FX = (border || !laneX) ? kNegInf : c.F;
-            } else {
-                HX = c.H;
-                EX = c.E;
-                FX = c.F;
-            }
-            SX = c.S; SEX = c.SE; SFX = c.SF;
-            if (laneX && rowin && (uint32_t)j < (uint32_t)C && c.H > best) {
-                best = c.H;
-                bcell = hereX;
-                bstart = c.S;
-            }
-        }
-        {  // Y = (i, j + 1): left = this lane's X, up = the upper lane's X
-            const int32_t jy = j + 1;
-            const int32_t hu = from_upper_lane(HX), fu = from_upper_lane(FX);
-            const int32_t su = from_upper_lane(SX), sfu = from_upper_lane(SFX);
-            const CellOut c = sw_cell(HX, EX, SX, SEX, hu, fu, su, sfu, HY, SY, qb == dY, hereX + 1,
-                                      match, mismatch, o1, ext);
-            if (EDGE) {
-                const bool border = before_row || jy < 0;
-                HY = border ? 0 : (laneY ? c.H : kNegInf);
-                EY = (border || !laneY) ? kNegInf : c.E;
-                FY = (border || !laneY) ? kNegInf : c.F;
-            } else {
-                HY = laneY ? c.H : kNegInf;
-                EY = c.E;
-                FY = laneY ? c.F : kNegInf;
-            }
-            SY = c.S; SEY = c.SE; SFY = c.SF;
-            if (laneY && rowin && (uint32_t)jy < (uint32_t)C && c.H > best) {
-                best = c.H;
-                bcell = hereX + 1;
-                bstart = c.S;
-            }
-        }
-    };
-    int32_t a = a0;
-    for (const int32_t a_edge = a0 + 2 * edge; a <= a1 && a < a_edge; a += 2, ++i, ++j, hereX += 128)
-        pair(std::true_type{});
-    if constexpr (!STAGED) {
-        for (; a <= a1; a += 2, ++i, ++j, hereX += 128) pair(std::false_type{});
-    } else {
-        // What a cell gives to the next ones is worked out in its own lane, one opened gap
-        // for both directions, and then shifted: X takes its E from the lower lane's Y and
-        // its F from this lane's, Y its E from this lane's X and its F from the upper lane's.
-        // Nothing leaves a slot past the band: its gaps cost kBswOut, and lane W's Y matches
-        // nothing, so that it stays at or below what its X has been.  Bound by the issue of
-        // one wave: 54 instructions a pair, 75 with tests of the box's end, masks of the
-        // band's and both sides' gaps worked out apart; the 2,477 boxes of 1,000 mid-size
-        // queries, as long as their longest one, in 117 us, 147 before.
-        const int32_t o1X = laneX ? o1 : kBswOut, extX = laneX ? ext : kBswOut;
-        const int32_t o1Y = laneY ? o1 : kBswOut, extY = laneY ? ext : kBswOut;
-        const int32_t matchY = laneY ? match : -kBswOut, misY = laneY ? -mismatch : -kBswOut;
-        const int32_t matchX = in_vgpr(match), misX = in_vgpr(-mismatch);
-        const int32_t low = in_vgpr(kBswBias);
-        HX += kBswBias; EX += kBswBias; FX += kBswBias;
-        HY += kBswBias; EY += kBswBias; FY += kBswBias;
-        int32_t bestb = laneX ? best + kBswBias : INT32_MAX;
-        const uint8_t *pq = sq + i;
-        const uint16_t *pd = sd2 + j;
-        // Bases two pairs ahead, in two sets that the pairs use in turn, so that a read has
-        // two pairs' time to land
-        auto fast_pair = [&](uint32_t &nq, uint32_t &nd, int ahead) {
-            const bool sx = nq == (nd & 0xffu), sy = nq == nd >> 8;
-            nq = pq[ahead];
-            nd = pd[ahead];
-            // keeps the reads before the pair's arithmetic: the compiler moves them down to
-            // the pair that uses them and waits for them there
-            asm volatile("" : "+v"(HX), "+v"(HY) : : "memory");
-            {  // X
-                const int32_t o = HY - o1Y, e = EY - extY, f = FY - extY;
-                const int32_t E = max(from_lower_lane(max(o, e)), low);
-                const int32_t SE = from_lower_lane(o < e ? SEY : SY);
-                const int32_t F = max(max(o, f), low), SF = o < f ? SFY : SY;
-                const int32_t g = HX + (sx ? matchX : misX), sg = HX > low ? SX : hereX;
-                HX = max(max(g, E), F);
-                SX = g == HX ? sg : (E == HX ? SE : SF);
-                EX = E; FX = F;
-                SEX = SE; SFX = SF;
-                const bool more = HX > bestb;
-                bestb = max(HX, bestb);
-                bcell = more ? hereX : bcell;
-                bstart = more ? SX : bstart;
-            }
-            {  // Y
-                const int32_t o = HX - o1X, e = EX - extX, f = FX - extX;
-                const int32_t E = max(max(o, e), low), SE = o < e ? SEX : SX;
-                const int32_t F = max(from_upper_lane(max(o, f)), low);
-                const int32_t SF = from_upper_lane(o < f ? SFX : SX);
-                const int32_t g = HY + (sy ? matchY : misY);
-                const int32_t sg = HY > low ? SY : hereX + 1;
-                HY = max(max(g, E), F);
-                SY = g == HY ? sg : (E == HY ? SE : SF);
-                EY = E; FY = F;
-                SEY = SE; SFY = SF;
-                const bool more = HY > bestb;
-                bestb = max(HY, bestb);
-                bcell = more ? hereX + 1 : bcell;
-                bstart = more ? SY : bstart;
-            }
-            hereX += 128;
-        };
-        uint32_t nq0 = pq[0], nq1 = pq[1], nd0 = pd[0], nd1 = pd[1];
-        // pairs in twos; an odd count ends with one pair past the box
-        for (; a <= a1; a += 4, pq += 2, pd += 2) {
-            fast_pair(nq0, nd0, 2);
-            fast_pair(nq1, nd1, 3);
-        }
-        if (!laneX) bestb = kBswBias;
-        best = bestb - kBswBias;
+    uint32_t nq0 = qat(ii), nq1 = qat(ii + 1), nd0 = dat(jj), nd1 = dat(jj + 1);
+    // pairs in twos; an odd count ends with one pair past the box
+    for (int32_t a = a0; a <= a1; a += 4, ii += 2, jj += 2) {
+        pair(nq0, nd0, 2);
+        pair(nq1, nd1, 3);
     }
+    best = laneX ? bestb - kBswBias : 0;
 }
 
 // The b-th selected box and its wave query: named directly by sel_box, or the
@@ -6547,8 +6415,8 @@ __global__ __launch_bounds__(64) void k_bsw(
     const uint32_t *__restrict__ sel_box, const uint32_t *__restrict__ order,
     const WaveCtl *__restrict__ ctl)
 {
-    __shared__ uint8_t s_q[kBswStage + kBswPad];
-    __shared__ uint16_t s_d2[kBswStage + kBswPad];  // bank bases x and x + 1
+    __shared__ uint8_t s_q[kBswStage + 2 * kBswPad];    // from kBswPad rows before the box
+    __shared__ uint16_t s_d2[kBswStage + 2 * kBswPad];  // columns x and x + 1, likewise
     const int32_t lane = threadIdx.x;
     if (ctl) {
         nq = ctl->nqw;
@@ -6583,19 +6451,24 @@ __global__ __launch_bounds__(64) void k_bsw(
         if (span > 1024) __builtin_amdgcn_s_setprio(3);
         else if (span > 512) __builtin_amdgcn_s_setprio(2);
         else if (span > 256) __builtin_amdgcn_s_setprio(1);
+        auto qat = [&](uint32_t x) {
+            return x - kBswPad < (uint32_t)R ? (uint32_t)qp[x - kBswPad] : kBswQEnd;
+        };
+        auto dat = [&](uint32_t x) {
+            const uint32_t j = x - kBswPad;  // wraps round before the box
+            const uint32_t b0 = j < (uint32_t)C ? db_base(dbw, dbase + j) : kBswDEnd;
+            const uint32_t b1 = j + 1u < (uint32_t)C ? db_base(dbw, dbase + (j + 1u)) : kBswDEnd;
+            return b0 | b1 << 8;
+        };
         if (R <= kBswStage && C <= kBswStage) {
-            for (int32_t x = lane; x < R + kBswPad; x += 64) s_q[x] = x < R ? qp[x] : kBswQEnd;
-            for (int32_t x = lane; x < C + kBswPad; x += 64) {
-                const uint32_t b0 = x < C ? db_base(dbw, dbase + x) : kBswDEnd;
-                const uint32_t b1 = x + 1 < C ? db_base(dbw, dbase + x + 1) : kBswDEnd;
-                s_d2[x] = (uint16_t)(b0 | b1 << 8);
-            }
+            for (int32_t x = lane; x < R + 2 * kBswPad; x += 64) s_q[x] = (uint8_t)qat(x);
+            for (int32_t x = lane; x < C + 2 * kBswPad; x += 64) s_d2[x] = (uint16_t)dat(x);
             __syncthreads();
-            bsw_sweep<true>(s_q, s_d2, qp, dbw, dbase, R, C, c0, W, a0, a1, match, mismatch, o1,
-                            ext, lane, best, bcell, bstart);
+            bsw_sweep([&](uint32_t x) { return (uint32_t)s_q[x]; },
+                      [&](uint32_t x) { return (uint32_t)s_d2[x]; }, c0, W, a0, a1, match, mismatch,
+                      o1, ext, lane, best, bcell, bstart);
         } else {
-            bsw_sweep<false>(s_q, s_d2, qp, dbw, dbase, R, C, c0, W, a0, a1, match, mismatch, o1,
-                             ext, lane, best, bcell, bstart);
+            bsw_sweep(qat, dat, c0, W, a0, a1, match, mismatch, o1, ext, lane, best, bcell, bstart);
         }
     }
     __builtin_amdgcn_s_setprio(0);
@@ -6662,30 +6535,6 @@ void launch_bsw(const Box *sorted, const uint32_t *qstart, const uint32_t *sel_o
 }
 
 // ------------------------------------------------------------------ traceback
-// One cell of the recurrence (sw_cell) and its four direction bits: how H was reached
-// (0 diagonal, 1 gap in the query, 2 gap in the bank, 3 diagonal from a predecessor <= 0:
-// the path's first pair) and whether each gap was opened here (ties open).  The bits
-// of a cell with H <= 0 are never read: a path's cells in state 0 have H > 0, and a gap
-// with a value > 0 opens from such a cell.
-struct DirCell {
-    int32_t H, E, F;
-    uint32_t dir;
-};
-
-__device__ __forceinline__ DirCell dir_cell(int32_t hl, int32_t el, int32_t hu, int32_t fu,
-                                            int32_t hd, int32_t sub, int32_t o1, int32_t ext)
-{
-    DirCell c;
-    const int32_t eo = hl - o1, ee = el - ext, fo = hu - o1, fe = fu - ext;
-    c.E = max(eo, ee);
-    c.F = max(fo, fe);
-    const int32_t g = hd + sub;
-    c.H = max(max(g, 0), max(c.E, c.F));
-    c.dir = (g == c.H ? (hd > 0 ? 0u : 3u) : c.E == c.H ? 1u : 2u) | (eo >= ee ? 4u : 0u) |
-            (fo >= fe ? 8u : 0u);
-    return c;
-}
-
 // Where the directions of row i, lane u (its slots 2u and 2u + 1) lie in a hit's 64 R
 // bytes: the lanes of one step hold rows i, i - 1, ..., so rows skewed by the lane put
 // a step's bytes side by side.
@@ -6694,72 +6543,72 @@ __device__ __forceinline__ size_t dir_at(int32_t i, int32_t u, int32_t R)
     return (size_t)((uint32_t)(i + u) % (uint32_t)R) * 64 + (uint32_t)u;
 }
 
-// The directions of every band cell of an R x C rectangle, swept over anti-diagonals in
-// pairs exactly as bsw_sweep does (slots, borders and minus infinities are its rule);
-// qbase(i), dbase(j): the codes of a row and a column of the rectangle.  Returns H of the
-// rectangle's last cell (0 in lanes that do not hold it).
+// The directions of every band cell of an R x C rectangle: how H was reached (0 diagonal,
+// 1 gap in the query, 2 gap in the bank, 3 diagonal from a predecessor <= 0: the path's
+// first pair) and, 4 and 8, whether each gap was opened there (ties open).  The bits of a
+// cell with H <= 0 are never read: a path's cells in state 0 have H > 0, and a gap with a
+// value > 0 opens from such a cell.  Swept in pairs as bsw_sweep does, by its rules, with
+// the floor at 0.  Returns H of the rectangle's last cell (0 in lanes that do not hold it).
 template <typename Q, typename D>
-__device__ int32_t dir_sweep(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0, int32_t W,
-                             int32_t match, int32_t mismatch, int32_t o1, int32_t ext,
-                             int32_t lane, uint8_t *__restrict__ dirs)
+__device__ __forceinline__ int32_t dir_sweep(Q qat, D dat, int32_t R, int32_t C, int32_t c0,
+                                             int32_t W, int32_t match, int32_t mismatch,
+                                             int32_t o1, int32_t ext, int32_t lane,
+                                             uint8_t *__restrict__ dirs)
 {
     const int32_t clo = max(c0 - W, -(R - 1)), chi = min(c0 + W, C - 1);
-    const int32_t cs = min(max(C - R, clo), chi);
     const int64_t a_lo = clo <= 0 && chi >= 0 ? 0 : clo > 0 ? clo : -chi;
-    const int64_t a_hi = cs <= C - R ? 2 * (int64_t)(R - 1) + cs : 2 * (int64_t)(C - 1) - cs;
     const int64_t a0 = a_lo - ((a_lo - c0 + W) & 1);
-    const uint32_t pairs = (uint32_t)((a_hi - a0) / 2) + 1u;
-    const int32_t tX = 2 * lane;
+    // the last cell lies in the band, on the last anti-diagonal
+    const uint32_t pairs = (uint32_t)(((int64_t)R + C - 2 - a0) / 2) + 1u;
+    const int32_t tX = 2 * lane, tEnd = C - R - c0 + W;  // the last cell's slot
     const bool laneX = tX <= 2 * W, laneY = tX < 2 * W;
     const int32_t dX = min(tX, 2 * W) - W + c0;  // the lane's X diagonal j - i
-    int32_t i = (int32_t)((a0 - dX) >> 1), j = i + dX;
+    const int32_t i0 = (int32_t)((a0 - dX) >> 1);
+    const int32_t o1X = laneX ? o1 : kBswOut, extX = laneX ? ext : kBswOut;
+    const int32_t o1Y = laneY ? o1 : kBswOut, extY = laneY ? ext : kBswOut;
+    const int32_t matchY = laneY ? match : -kBswOut, misY = laneY ? -mismatch : -kBswOut;
+    const int32_t matchX = in_vgpr(match), misX = in_vgpr(-mismatch), low = in_vgpr(0);
+    int32_t HX = low, EX = low, FX = low, HY = low, EY = low, FY = low;
     uint32_t row = (uint32_t)((a0 + W - c0) >> 1) % (uint32_t)R;  // (i + lane) % R of band lanes
-    int32_t HX = i < 1 || j < 1 ? 0 : kNegInf, EX = kNegInf, FX = kNegInf;
-    int32_t HY = i < 1 || j < 0 ? 0 : kNegInf, EY = kNegInf, FY = kNegInf;
-    int32_t end = 0;
-    auto row_base = [&](int32_t x) { return qbase(min(max(x, 0), R - 1)); };
-    auto col_base = [&](int32_t x) { return dbase(min(max(x, 0), C - 1)); };
-    int32_t nq = row_base(i), nx = col_base(j), ny = col_base(j + 1);  // read one pair ahead
-    int32_t edge = laneX ? max(0, max(-i, -j)) : 0;  // pairs with cells before the rectangle
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) edge = max(edge, __shfl_xor(edge, off, 64));
-    auto pair = [&](auto edge_tag) {
-        constexpr bool EDGE = decltype(edge_tag)::value;
-        const int32_t qb = nq, bx = nx, by = ny;
-        nq = row_base(i + 1);
-        nx = by;  // the next pair's X column is this pair's Y column
-        ny = col_base(j + 2);
-        const bool rowin = (uint32_t)i < (uint32_t)R;
-        int32_t hl = from_lower_lane(HY), el = from_lower_lane(EY);
-        if (lane == 0) {
-            hl = j == 0 ? 0 : kNegInf;
-            el = kNegInf;
+    uint32_t ii = (uint32_t)(i0 + kBswPad), jj = (uint32_t)(i0 + dX + kBswPad);
+    const uint32_t in = laneX ? (uint32_t)R : 0u;  // rows whose directions the lane keeps
+    auto pair = [&](uint32_t &nq, uint32_t &nd, uint32_t ahead) {
+        const bool sx = nq == (nd & 0xffu), sy = nq == nd >> 8;
+        nq = qat(ii + ahead + 2);
+        nd = dat(jj + ahead + 2);
+        asm volatile("" : "+v"(HX), "+v"(HY) : : "memory");
+        uint32_t dir;
+        {  // X
+            const int32_t o = HY - o1Y, e = EY - extY, f = FY - extY;
+            const int32_t E = max(from_lower_lane(max(o, e)), low);
+            const int32_t eb = from_lower_lane(o >= e ? 4 : 0), fb = o >= f ? 8 : 0;
+            const int32_t F = max(max(o, f), low);
+            const int32_t g = HX + (sx ? matchX : misX), first = HX > low ? 0 : 3;
+            HX = max(max(g, E), F);
+            dir = (uint32_t)((g == HX ? first : E == HX ? 1 : 2) | eb | fb);
+            EX = E; FX = F;
         }
-        const DirCell x =
-            dir_cell(hl, el, HY, FY, HX, qb == bx ? match : -mismatch, o1, ext);
-        const bool bdx = EDGE && (i < 0 || j < 0);
-        HX = bdx ? 0 : x.H;
-        EX = bdx ? kNegInf : x.E;
-        FX = bdx ? kNegInf : x.F;
-        const DirCell y = dir_cell(HX, EX, from_upper_lane(HX), from_upper_lane(FX), HY,
-                                   qb == by ? match : -mismatch, o1, ext);
-        const bool bdy = EDGE && (i < 0 || j + 1 < 0);
-        HY = bdy ? 0 : laneY ? y.H : kNegInf;
-        EY = bdy ? kNegInf : y.E;
-        FY = bdy || !laneY ? kNegInf : y.F;
-        if (laneX && rowin) dirs[(size_t)row * 64 + (uint32_t)lane] = (uint8_t)(x.dir | y.dir << 4);
-        if (i == R - 1) {
-            if (laneX && j == C - 1) end = x.H;
-            if (laneY && j + 1 == C - 1) end = y.H;
+        {  // Y
+            const int32_t o = HX - o1X, e = EX - extX, f = FX - extX;
+            const int32_t E = max(max(o, e), low);
+            const int32_t F = max(from_upper_lane(max(o, f)), low);
+            const int32_t eb = o >= e ? 4 : 0, fb = from_upper_lane(o >= f ? 8 : 0);
+            const int32_t g = HY + (sy ? matchY : misY), first = HY > low ? 0 : 3;
+            HY = max(max(g, E), F);
+            dir |= (uint32_t)((g == HY ? first : E == HY ? 1 : 2) | eb | fb) << 4;
+            EY = E; FY = F;
         }
+        if (ii + ahead - kBswPad < in) dirs[(size_t)row * 64 + (uint32_t)lane] = (uint8_t)dir;
         row = row + 1u == (uint32_t)R ? 0u : row + 1u;
-        ++i;
-        ++j;
     };
+    uint32_t nq0 = qat(ii), nq1 = qat(ii + 1), nd0 = dat(jj), nd1 = dat(jj + 1);
     uint32_t p = 0;
-    for (const uint32_t pe = min(pairs, (uint32_t)edge + 1u); p < pe; ++p) pair(std::true_type{});
-    for (; p < pairs; ++p) pair(std::false_type{});
-    return end;
+    for (; p + 1 < pairs; p += 2, ii += 2, jj += 2) {
+        pair(nq0, nd0, 0);
+        pair(nq1, nd1, 1);
+    }
+    if (p < pairs) pair(nq0, nd0, 0);
+    return lane == tEnd >> 1 ? (tEnd & 1 ? HY : HX) : 0;
 }
 
 // The walk back from the rectangle's last cell, by the whole wave: the lanes look at
@@ -6768,7 +6617,7 @@ __device__ int32_t dir_sweep(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0,
 // right-aligned in [0, R + C) of ops.  Returns their number, or -1 when the walk does not
 // end on the rectangle's first cell with the hit's score.
 template <typename Q, typename D>
-__device__ int32_t dir_walk(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0, int32_t W,
+__device__ int32_t dir_walk(Q qat, D dat, int32_t R, int32_t C, int32_t c0, int32_t W,
                             int32_t match, int32_t mismatch, int32_t o1, int32_t ext,
                             int32_t score, int32_t lane, const uint8_t *dirs, char *ops)
 {
@@ -6796,7 +6645,7 @@ __device__ int32_t dir_walk(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0, 
             // lane f's own pair belongs to the path only where the path starts with it
             const int32_t n = f + (f < 64 && (fd & 3u) == 3u ? 1 : 0);
             const bool in = lane < n;
-            const bool eq = in && qbase(max(ci, 0)) == dbase(max(cj, 0));
+            const bool eq = in && qat((uint32_t)ci + kBswPad) == (dat((uint32_t)cj + kBswPad) & 0xffu);
             if (in) last[-(k + lane)] = eq ? '=' : 'X';
             const int32_t same = (int32_t)__popcll(__ballot(eq));
             sum += same * match - (n - same) * mismatch;
@@ -6826,7 +6675,8 @@ __device__ int32_t dir_walk(Q qbase, D dbase, int32_t R, int32_t C, int32_t c0, 
 // takes a pair of anti-diagonals a step, its lanes' values handed over by DPP, where a row
 // a step needed a 6-step prefix maximum through LDS; and the walk takes a stretch of up to
 // 64 cells a step, where a cell a step waited for its own load.  The hits of a query of
-// 3,000 bases: 64 us, 389 a row and a cell a step.
+// 3,000 bases: 43 us, 389 a row and a cell a step (64 with the sweep's cells before the
+// rectangle and its last cell tested in every pair).
 __global__ __launch_bounds__(64) void k_traceback(
     const int32_t *__restrict__ hits, int32_t n, const uint8_t *__restrict__ qascii, int64_t qlen,
     const uint32_t *__restrict__ dbw, const int64_t *__restrict__ seq_start, int32_t n_seqs,
@@ -6835,7 +6685,8 @@ __global__ __launch_bounds__(64) void k_traceback(
     const int64_t *__restrict__ ops_off, char *__restrict__ ops, int32_t *__restrict__ ops_len,
     int32_t *__restrict__ status)
 {
-    __shared__ uint8_t s_q[kBswStage], s_d[kBswStage];
+    __shared__ uint8_t s_q[kBswStage + 2 * kBswPad];
+    __shared__ uint16_t s_d2[kBswStage + 2 * kBswPad];
     const int32_t lane = threadIdx.x;
     for (int32_t h = blockIdx.x; h < n; h += gridDim.x) {
         const int32_t *hr = hits + (size_t)h * kHitInts;
@@ -6853,32 +6704,41 @@ __global__ __launch_bounds__(64) void k_traceback(
             const uint8_t *qp = qascii + qs;
             const int64_t db0 = seq_start[s] + ds;
             uint8_t *dh = dirs + dir_off[h];
+            auto qat = [&](uint32_t x) {
+                const uint32_t i = x - kBswPad;  // wraps round before the rectangle
+                if (i >= (uint32_t)R) return kBswQEnd;
+                const uint32_t l = (qp[i] >> 1) & 3u;  // of a letter that is known to be a base
+                return l ^ (l >> 1);
+            };
+            auto dat = [&](uint32_t x) {
+                const uint32_t j = x - kBswPad;
+                const uint32_t b0 = j < (uint32_t)C ? db_base(dbw, db0 + j) : kBswDEnd;
+                const uint32_t b1 = j + 1u < (uint32_t)C ? db_base(dbw, db0 + (j + 1u)) : kBswDEnd;
+                return b0 | b1 << 8;
+            };
             const bool staged = R <= kBswStage && C <= kBswStage;
             bool bad = false;
-            for (int32_t x = lane; x < R; x += 64) {
-                const int32_t c = base_code(qp[x]);
-                bad |= c < 0;
-                if (staged) s_q[x] = (uint8_t)c;
+            for (int32_t x = lane; x < R; x += 64) bad |= base_code(qp[x]) < 0;
+            if (staged) {
+                for (int32_t x = lane; x < R + 2 * kBswPad; x += 64) s_q[x] = (uint8_t)qat(x);
+                for (int32_t x = lane; x < C + 2 * kBswPad; x += 64) s_d2[x] = (uint16_t)dat(x);
             }
-            if (staged)
-                for (int32_t x = lane; x < C; x += 64) s_d[x] = (uint8_t)db_base(dbw, db0 + x);
             __syncthreads();
-            auto trace = [&](auto qbase, auto dbase) {
-                const int32_t end = dir_sweep(qbase, dbase, R, C, cc, W, match, mismatch, o1, ext,
-                                              lane, dh);
+            auto trace = [&](auto q, auto d) {
+                const int32_t end =
+                    dir_sweep(q, d, R, C, cc, W, match, mismatch, o1, ext, lane, dh);
                 __threadfence_block();
                 __syncthreads();
                 if (__ballot(end == score) == 0ull) return -1;
-                return dir_walk(qbase, dbase, R, C, cc, W, match, mismatch, o1, ext, score, lane,
-                                dh, ops + ops_off[h]);
+                return dir_walk(q, d, R, C, cc, W, match, mismatch, o1, ext, score, lane, dh,
+                                ops + ops_off[h]);
             };
             if (__ballot(bad) == 0ull) {
                 if (staged)
-                    len = trace([&](int32_t x) { return (int32_t)s_q[x]; },
-                                [&](int32_t x) { return (int32_t)s_d[x]; });
+                    len = trace([&](uint32_t x) { return (uint32_t)s_q[x]; },
+                                [&](uint32_t x) { return (uint32_t)s_d2[x]; });
                 else
-                    len = trace([&](int32_t x) { return base_code(qp[x]); },
-                                [&](int32_t x) { return (int32_t)db_base(dbw, db0 + x); });
+                    len = trace(qat, dat);
             }
         }
         if (lane == 0) {
