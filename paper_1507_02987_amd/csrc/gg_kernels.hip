@@ -3487,7 +3487,8 @@ void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *ca
 // Whole waves take contiguous ranges of runs, and a lane whose run ends takes the
 // next one of its wave's range, a chunk of every lane's run per round: a run has five
 // hits on average, but one in a wave of 64 often has the 27 of a 300 bp repeat (72 ms
-// for 3.4 G runs when a wave waited for its longest run, window by window; 54 now).
+// for 3.4 G runs when a wave waited for its longest run, window by window; 54 so, 50 with
+// a run's key and sequence read ahead).
 __global__ __launch_bounds__(kBlock) void k_run_ends(RunStarts a, const uint64_t *__restrict__ keys,
                                                      uint32_t n, const uint32_t *__restrict__ off,
                                                      int32_t nqw, Cand *__restrict__ cands)
@@ -3511,29 +3512,51 @@ __global__ __launch_bounds__(kBlock) void k_run_ends(RunStarts a, const uint64_t
     uint32_t qend = off[ql + 1], i = 0;
     int64_t q0 = a.qoff[a.qa + ql];
     int32_t L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
+    // The range's runs in blocks of 64, a run per lane, three blocks under way: one handed
+    // out by lane exchange, one whose sequences are being read, one whose keys are.
+    uint64_t at = next;  // first run of the block handed out; `next` is the next run in it
+    auto key_at = [&](uint64_t x) { return keys[min(x + (uint64_t)lane, stop - 1)]; };
+    auto seq_of = [&](uint64_t key) { return (int32_t)shr64(key, a.lay.bp + a.lay.bd); };
+    uint64_t k0 = key_at(at), k1 = key_at(at + 64), k2 = key_at(at + 128);
+    int64_t s0 = a.seq_start[seq_of(k0)], s1 = a.seq_start[seq_of(k1)];
+    int64_t e0 = a.seq_start[seq_of(k0) + 1], e1 = a.seq_start[seq_of(k1) + 1];
     bool have = false;
     Cand c{0, 0, 0, 0, 0};
     RunWalk w{};
     for (;;) {
         const uint64_t need = __ballot(!have);
         if (need && next < stop) {
-            if (!have) {
-                const uint64_t x = next + (uint64_t)__popcll(need & below);
-                if (x < stop) {
-                    have = true;
-                    i = (uint32_t)x;
-                    if (i >= qend) {
-                        while (i >= off[ql + 1]) ++ql;
-                        qend = off[ql + 1];
-                        q0 = a.qoff[a.qa + ql];
-                        L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
-                    }
-                    w = run_open(a, a.lay, keys[i], q0, L, &c);
+            const uint32_t x = (uint32_t)(next - at) + (uint32_t)__popcll(need & below);
+            const uint64_t key = __shfl((unsigned long long)k0, x & 63, 64);
+            const int64_t ss = __shfl((long long)s0, x & 63, 64);
+            const int32_t ns = __shfl((int32_t)(e0 - s0), x & 63, 64);
+            if (!have && x < 64 && at + x < stop) {
+                have = true;
+                i = (uint32_t)(at + x);
+                if (i >= qend) {
+                    while (i >= off[ql + 1]) ++ql;
+                    qend = off[ql + 1];
+                    q0 = a.qoff[a.qa + ql];
+                    L = (int32_t)(a.qoff[a.qa + ql + 1] - q0);
                 }
+                c.qs = (int32_t)(key & low_mask(a.lay.bp));
+                c.d = (int32_t)((key >> a.lay.bp) & low_mask(a.lay.bd)) - a.lay.bias;
+                c.s = seq_of(key);
+                w = run_walk(q0, L, ss, ns, c.d, c.qs, a.span);
             }
-            next += (uint64_t)__popcll(need);
+            next = min(next + (uint64_t)__popcll(need), at + 64);
+            if (next == at + 64) {
+                at = next;
+                k0 = k1;
+                s0 = s1;
+                e0 = e1;
+                k1 = k2;
+                s1 = a.seq_start[seq_of(k1)];
+                e1 = a.seq_start[seq_of(k1) + 1];
+                k2 = key_at(at + 128);
+            }
         }
-        if (__ballot(have) == 0) break;
+        if (__ballot(have) == 0 && next >= stop) break;
         if (have && run_chunk(a, wm, nw, w)) {
             cands[i] = Cand{ql, c.s, c.d, c.qs, c.qs + w.hit + a.span};
             have = false;
