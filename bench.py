@@ -224,7 +224,7 @@ def rooflines(stages: dict, cells: int, nprof: int, workload: str):
 STAGES = ("encode", "scan", "gather_prep", "probe", "run_ends", "gather_count", "gather", "group",
           "gather_filter", "filter",
           "filter_compact", "sort_hist", "sort_scan", "sort_scatter", "chain", "chain_write",
-          "extend", "merge", "merge_sweep", "select", "align", "report", "graph")
+          "extend", "merge", "select", "align", "report", "graph")
 
 
 def profile_steps(gix, run, nprof: int):

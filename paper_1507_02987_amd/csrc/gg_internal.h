@@ -67,7 +67,7 @@ struct HitKeyLayout {
 };
 
 // One wave of a graph-replayed batch, in device memory.  The host plans the waves
-// (qa .. bq, and the hit-key layout); k_wave_begin copies the next plan entry
+// (qa .. bq, and the hit-key layout); k_wave_prep copies the next plan entry
 // here, and the kernels that produce the run and selection counts store them.
 // Kernels given a WaveCtl read their sizes from it instead of their arguments,
 // so one captured graph serves every wave.

@@ -1556,7 +1556,7 @@ gg_status run_ranges(const gg_index *ix, Workspace *ws, Prof &prof, const gg_par
 
 // ---- graph-replayed batches
 // Waves of a batch are replayed from one captured HIP graph: every kernel reads
-// the wave's sizes from a device WaveCtl (see k_wave_begin), so after the single
+// the wave's sizes from a device WaveCtl (see k_wave_prep), so after the single
 // synchronisation that gives the per-query hit counts, all waves run without
 // further host round trips, and the graph is reused by later calls of the same
 // shape.  It covers the radix-sort grouping with per-query LDS sorts: a wave in
