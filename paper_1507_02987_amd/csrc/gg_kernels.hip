@@ -6252,10 +6252,13 @@ constexpr int32_t kBswBias = 1 << 29;
 constexpr int32_t kBswOut = 1 << 30;  // a gap or mismatch cost that leaves nothing
 // Bases before and past a box match none.  Cells before the box are then at the floor, as
 // its border is; a cell past it is no better than one in the box that it comes from, and
-// at a later place, so it is never the best one.  Neither needs a test.  A sweep reads up
-// to kBswPad such bases on each side.
-constexpr int kBswPad = 80;
+// at a later place, so it is never the best one.  Neither needs a test.
 constexpr uint32_t kBswQEnd = 4, kBswDEnd = 5;
+constexpr int kBswPad = 80;  // such bases on each side that a sweep may read, at most
+// Pairs whose bases are staged in LDS at a time: with the lanes' spread and the reads
+// ahead, kBswStage rows and columns.
+constexpr int kBswPart = kBswStage - kBswPad;
+static_assert(kBswPart % 2 == 0, "pairs are taken in twos");
 
 // A uniform value in a VGPR of its own: the compiler would otherwise rebuild it from its
 // SGPR inside the loop, where two SGPR operands cannot meet in one select, and know the
@@ -6274,10 +6277,12 @@ __device__ __forceinline__ int32_t in_vgpr(int32_t s)
 // Y's left neighbour is this lane's X, its upper the upper lane's X, its diagonal
 // this lane's previous Y.  Lanes past the band (u > W) follow lane W's cells, so that
 // their reads stay near the box; no band cell reads their values.
-// qat(i + kBswPad): the code of row i, kBswQEnd outside the box; dat(j + kBswPad): those of
-// columns j and j + 1 (in the low and the high byte), kBswDEnd outside.
-template <typename Q, typename D>
-__device__ __forceinline__ void bsw_sweep(Q qat, D dat, int32_t c0, int32_t W, int32_t a0,
+// stage(i, j, n) puts rows i .. i + n - 1 in sq (their codes, kBswQEnd outside the box) and
+// columns from j on in sd2 (the codes of columns j and j + 1 in the low and the high byte,
+// kBswDEnd outside); it is called for every kBswPart pairs.
+template <typename Stage>
+__device__ __forceinline__ void bsw_sweep(const uint8_t *sq, const uint16_t *sd2, Stage stage,
+                                          int32_t c0, int32_t W, int32_t a0,
                                           int32_t a1, int32_t match, int32_t mismatch, int32_t o1,
                                           int32_t ext, int32_t lane, int32_t &best,
                                           int32_t &bcell, int32_t &bstart)
@@ -6303,13 +6308,16 @@ __device__ __forceinline__ void bsw_sweep(Q qat, D dat, int32_t c0, int32_t W, i
     int32_t HX = low, EX = low, FX = low, SX = 0, SEX = 0, SFX = 0;
     int32_t HY = low, EY = low, FY = low, SY = 0, SEY = 0, SFY = 0;
     int32_t bestb = laneX ? kBswBias : INT32_MAX;
-    uint32_t ii = (uint32_t)(i + kBswPad), jj = (uint32_t)(a0 - i + kBswPad);
+    // the first pair's lowest row (lane W's) and column (lane 0's); the lane's from there
+    const int32_t iLo = (a0 - c0 - W) >> 1, jLo = a0 - ((a0 - c0 + W) >> 1);
+    const uint8_t *pq = sq;
+    const uint16_t *pd = sd2;
     // Bases two pairs ahead, in two sets that the pairs use in turn, so that a read has
     // two pairs' time to land
     auto pair = [&](uint32_t &nq, uint32_t &nd, uint32_t ahead) {
         const bool sx = nq == (nd & 0xffu), sy = nq == nd >> 8;
-        nq = qat(ii + ahead);
-        nd = dat(jj + ahead);
+        nq = pq[ahead];
+        nd = pd[ahead];
         // keeps the reads before the pair's arithmetic: the compiler moves them down to
         // the pair that uses them and waits for them there
         asm volatile("" : "+v"(HX), "+v"(HY) : : "memory");
@@ -6346,11 +6354,18 @@ __device__ __forceinline__ void bsw_sweep(Q qat, D dat, int32_t c0, int32_t W, i
         }
         hereX += 128;
     };
-    uint32_t nq0 = qat(ii), nq1 = qat(ii + 1), nd0 = dat(jj), nd1 = dat(jj + 1);
-    // pairs in twos; an odd count ends with one pair past the box
-    for (int32_t a = a0; a <= a1; a += 4, ii += 2, jj += 2) {
-        pair(nq0, nd0, 2);
-        pair(nq1, nd1, 3);
+    const int32_t pairs = (a1 - a0 + 1) / 2;
+    for (int32_t p = 0; p < pairs; p += kBswPart) {
+        const int32_t n = min(kBswPart, pairs - p);
+        stage(iLo + p, jLo + p, n + kBswPad);
+        pq = sq + (i - iLo);
+        pd = sd2 + (a0 - i - jLo);
+        uint32_t nq0 = pq[0], nq1 = pq[1], nd0 = pd[0], nd1 = pd[1];
+        // pairs in twos; an odd count ends with one pair past the box
+        for (int32_t k = 0; k < n; k += 2, pq += 2, pd += 2) {
+            pair(nq0, nd0, 2);
+            pair(nq1, nd1, 3);
+        }
     }
     best = laneX ? bestb - kBswBias : 0;
 }
@@ -6425,9 +6440,9 @@ __global__ __launch_bounds__(kBlock) void k_bsw_order(
         order[atomicAdd(&s_at[cls(b)], 1u) * kOrderBlocks + blockIdx.x] = b;
 }
 
-// One wave (one block) per selected box; boxes whose bases fit kBswStage each
-// for query and data bank are first staged in LDS.  Block i takes the order[i]-th
-// box (the i-th without an order), then every gridDim.x-th after it.
+// One wave (one block) per selected box, its bases staged in LDS, a long one's in parts (a
+// 6,000 x 6,000 box that read them from memory took 1,312 us; 684 so).  Block i takes the
+// order[i]-th box (the i-th without an order), then every gridDim.x-th after it.
 __global__ __launch_bounds__(64) void k_bsw(
     const Box *__restrict__ sorted, const uint32_t *__restrict__ qstart,
     const uint32_t *__restrict__ sel_off, int32_t nq, uint32_t total,
@@ -6438,8 +6453,8 @@ __global__ __launch_bounds__(64) void k_bsw(
     const uint32_t *__restrict__ sel_box, const uint32_t *__restrict__ order,
     const WaveCtl *__restrict__ ctl)
 {
-    __shared__ uint8_t s_q[kBswStage + 2 * kBswPad];    // from kBswPad rows before the box
-    __shared__ uint16_t s_d2[kBswStage + 2 * kBswPad];  // columns x and x + 1, likewise
+    __shared__ uint8_t s_q[kBswStage];
+    __shared__ uint16_t s_d2[kBswStage];  // columns x and x + 1
     const int32_t lane = threadIdx.x;
     if (ctl) {
         nq = ctl->nqw;
@@ -6474,25 +6489,19 @@ __global__ __launch_bounds__(64) void k_bsw(
         if (span > 1024) __builtin_amdgcn_s_setprio(3);
         else if (span > 512) __builtin_amdgcn_s_setprio(2);
         else if (span > 256) __builtin_amdgcn_s_setprio(1);
-        auto qat = [&](uint32_t x) {
-            return x - kBswPad < (uint32_t)R ? (uint32_t)qp[x - kBswPad] : kBswQEnd;
-        };
-        auto dat = [&](uint32_t x) {
-            const uint32_t j = x - kBswPad;  // wraps round before the box
-            const uint32_t b0 = j < (uint32_t)C ? db_base(dbw, dbase + j) : kBswDEnd;
-            const uint32_t b1 = j + 1u < (uint32_t)C ? db_base(dbw, dbase + (j + 1u)) : kBswDEnd;
-            return b0 | b1 << 8;
-        };
-        if (R <= kBswStage && C <= kBswStage) {
-            for (int32_t x = lane; x < R + 2 * kBswPad; x += 64) s_q[x] = (uint8_t)qat(x);
-            for (int32_t x = lane; x < C + 2 * kBswPad; x += 64) s_d2[x] = (uint16_t)dat(x);
+        auto stage = [&](int32_t i0, int32_t j0, int32_t n) {
+            __syncthreads();  // the last ones are read
+            for (int32_t x = lane; x < n; x += 64) {
+                const uint32_t i = (uint32_t)(i0 + x), j = (uint32_t)(j0 + x);  // wrap round
+                s_q[x] = i < (uint32_t)R ? qp[i] : (uint8_t)kBswQEnd;
+                const uint32_t b0 = j < (uint32_t)C ? db_base(dbw, dbase + j) : kBswDEnd;
+                const uint32_t b1 = j + 1u < (uint32_t)C ? db_base(dbw, dbase + (j + 1u)) : kBswDEnd;
+                s_d2[x] = (uint16_t)(b0 | b1 << 8);
+            }
             __syncthreads();
-            bsw_sweep([&](uint32_t x) { return (uint32_t)s_q[x]; },
-                      [&](uint32_t x) { return (uint32_t)s_d2[x]; }, c0, W, a0, a1, match, mismatch,
-                      o1, ext, lane, best, bcell, bstart);
-        } else {
-            bsw_sweep(qat, dat, c0, W, a0, a1, match, mismatch, o1, ext, lane, best, bcell, bstart);
-        }
+        };
+        bsw_sweep(s_q, s_d2, stage, c0, W, a0, a1, match, mismatch, o1, ext, lane, best, bcell,
+                  bstart);
     }
     __builtin_amdgcn_s_setprio(0);
 #pragma unroll
@@ -6530,7 +6539,6 @@ __global__ __launch_bounds__(64) void k_bsw(
         if (cells_q) atomicAdd(&cells_q[q], cells);
         if (cells_box) cells_box[b] = cells;
     }
-    __syncthreads();  // the next box restages s_q and s_d2
     }
 }
 
@@ -6572,8 +6580,9 @@ __device__ __forceinline__ size_t dir_at(int32_t i, int32_t u, int32_t R)
 // cell with H <= 0 are never read: a path's cells in state 0 have H > 0, and a gap with a
 // value > 0 opens from such a cell.  Swept in pairs as bsw_sweep does, by its rules, with
 // the floor at 0.  Returns H of the rectangle's last cell (0 in lanes that do not hold it).
-template <typename Q, typename D>
-__device__ __forceinline__ int32_t dir_sweep(Q qat, D dat, int32_t R, int32_t C, int32_t c0,
+template <typename Stage>
+__device__ __forceinline__ int32_t dir_sweep(const uint8_t *sq, const uint16_t *sd2, Stage stage,
+                                             int32_t R, int32_t C, int32_t c0,
                                              int32_t W, int32_t match, int32_t mismatch,
                                              int32_t o1, int32_t ext, int32_t lane,
                                              uint8_t *__restrict__ dirs)
@@ -6593,12 +6602,15 @@ __device__ __forceinline__ int32_t dir_sweep(Q qat, D dat, int32_t R, int32_t C,
     const int32_t matchX = in_vgpr(match), misX = in_vgpr(-mismatch), low = in_vgpr(0);
     int32_t HX = low, EX = low, FX = low, HY = low, EY = low, FY = low;
     uint32_t row = (uint32_t)((a0 + W - c0) >> 1) % (uint32_t)R;  // (i + lane) % R of band lanes
-    uint32_t ii = (uint32_t)(i0 + kBswPad), jj = (uint32_t)(i0 + dX + kBswPad);
+    const int32_t iLo = (int32_t)((a0 - c0 - W) >> 1), jLo = (int32_t)(a0 - ((a0 - c0 + W) >> 1));
+    const uint8_t *pq = sq;
+    const uint16_t *pd = sd2;
+    uint32_t i = (uint32_t)i0;
     const uint32_t in = laneX ? (uint32_t)R : 0u;  // rows whose directions the lane keeps
     auto pair = [&](uint32_t &nq, uint32_t &nd, uint32_t ahead) {
         const bool sx = nq == (nd & 0xffu), sy = nq == nd >> 8;
-        nq = qat(ii + ahead + 2);
-        nd = dat(jj + ahead + 2);
+        nq = pq[ahead + 2];
+        nd = pd[ahead + 2];
         asm volatile("" : "+v"(HX), "+v"(HY) : : "memory");
         uint32_t dir;
         {  // X
@@ -6621,16 +6633,21 @@ __device__ __forceinline__ int32_t dir_sweep(Q qat, D dat, int32_t R, int32_t C,
             dir |= (uint32_t)((g == HY ? first : E == HY ? 1 : 2) | eb | fb) << 4;
             EY = E; FY = F;
         }
-        if (ii + ahead - kBswPad < in) dirs[(size_t)row * 64 + (uint32_t)lane] = (uint8_t)dir;
+        if (i + ahead < in) dirs[(size_t)row * 64 + (uint32_t)lane] = (uint8_t)dir;
         row = row + 1u == (uint32_t)R ? 0u : row + 1u;
     };
-    uint32_t nq0 = qat(ii), nq1 = qat(ii + 1), nd0 = dat(jj), nd1 = dat(jj + 1);
-    uint32_t p = 0;
-    for (; p + 1 < pairs; p += 2, ii += 2, jj += 2) {
-        pair(nq0, nd0, 0);
-        pair(nq1, nd1, 1);
+    for (uint32_t p = 0; p < pairs; p += kBswPart) {
+        const uint32_t n = min((uint32_t)kBswPart, pairs - p);
+        stage(iLo + (int32_t)p, jLo + (int32_t)p, (int32_t)n + kBswPad);
+        pq = sq + (i0 - iLo);
+        pd = sd2 + (i0 + dX - jLo);
+        uint32_t nq0 = pq[0], nq1 = pq[1], nd0 = pd[0], nd1 = pd[1], r = 0;
+        for (; r + 1 < n; r += 2, pq += 2, pd += 2, i += 2) {
+            pair(nq0, nd0, 0);
+            pair(nq1, nd1, 1);
+        }
+        if (r < n) pair(nq0, nd0, 0);
     }
-    if (p < pairs) pair(nq0, nd0, 0);
     return lane == tEnd >> 1 ? (tEnd & 1 ? HY : HX) : 0;
 }
 
@@ -6668,7 +6685,7 @@ __device__ int32_t dir_walk(Q qat, D dat, int32_t R, int32_t C, int32_t c0, int3
             // lane f's own pair belongs to the path only where the path starts with it
             const int32_t n = f + (f < 64 && (fd & 3u) == 3u ? 1 : 0);
             const bool in = lane < n;
-            const bool eq = in && qat((uint32_t)ci + kBswPad) == (dat((uint32_t)cj + kBswPad) & 0xffu);
+            const bool eq = in && qat(ci) == dat(cj);
             if (in) last[-(k + lane)] = eq ? '=' : 'X';
             const int32_t same = (int32_t)__popcll(__ballot(eq));
             sum += same * match - (n - same) * mismatch;
@@ -6708,8 +6725,8 @@ __global__ __launch_bounds__(64) void k_traceback(
     const int64_t *__restrict__ ops_off, char *__restrict__ ops, int32_t *__restrict__ ops_len,
     int32_t *__restrict__ status)
 {
-    __shared__ uint8_t s_q[kBswStage + 2 * kBswPad];
-    __shared__ uint16_t s_d2[kBswStage + 2 * kBswPad];
+    __shared__ uint8_t s_q[kBswStage];
+    __shared__ uint16_t s_d2[kBswStage];
     const int32_t lane = threadIdx.x;
     for (int32_t h = blockIdx.x; h < n; h += gridDim.x) {
         const int32_t *hr = hits + (size_t)h * kHitInts;
@@ -6727,41 +6744,31 @@ __global__ __launch_bounds__(64) void k_traceback(
             const uint8_t *qp = qascii + qs;
             const int64_t db0 = seq_start[s] + ds;
             uint8_t *dh = dirs + dir_off[h];
-            auto qat = [&](uint32_t x) {
-                const uint32_t i = x - kBswPad;  // wraps round before the rectangle
-                if (i >= (uint32_t)R) return kBswQEnd;
-                const uint32_t l = (qp[i] >> 1) & 3u;  // of a letter that is known to be a base
-                return l ^ (l >> 1);
+            // a letter that is known to be a base
+            auto code = [](uint32_t c) { const uint32_t l = (c >> 1) & 3u; return l ^ (l >> 1); };
+            auto stage = [&](int32_t i0, int32_t j0, int32_t m) {
+                __syncthreads();  // the last ones are read
+                for (int32_t x = lane; x < m; x += 64) {
+                    const uint32_t i = (uint32_t)(i0 + x), j = (uint32_t)(j0 + x);  // wrap round
+                    s_q[x] = (uint8_t)(i < (uint32_t)R ? code(qp[i]) : kBswQEnd);
+                    const uint32_t b0 = j < (uint32_t)C ? db_base(dbw, db0 + j) : kBswDEnd;
+                    const uint32_t b1 = j + 1u < (uint32_t)C ? db_base(dbw, db0 + (j + 1u)) : kBswDEnd;
+                    s_d2[x] = (uint16_t)(b0 | b1 << 8);
+                }
+                __syncthreads();
             };
-            auto dat = [&](uint32_t x) {
-                const uint32_t j = x - kBswPad;
-                const uint32_t b0 = j < (uint32_t)C ? db_base(dbw, db0 + j) : kBswDEnd;
-                const uint32_t b1 = j + 1u < (uint32_t)C ? db_base(dbw, db0 + (j + 1u)) : kBswDEnd;
-                return b0 | b1 << 8;
-            };
-            const bool staged = R <= kBswStage && C <= kBswStage;
             bool bad = false;
             for (int32_t x = lane; x < R; x += 64) bad |= base_code(qp[x]) < 0;
-            if (staged) {
-                for (int32_t x = lane; x < R + 2 * kBswPad; x += 64) s_q[x] = (uint8_t)qat(x);
-                for (int32_t x = lane; x < C + 2 * kBswPad; x += 64) s_d2[x] = (uint16_t)dat(x);
-            }
-            __syncthreads();
-            auto trace = [&](auto q, auto d) {
-                const int32_t end =
-                    dir_sweep(q, d, R, C, cc, W, match, mismatch, o1, ext, lane, dh);
+            if (__ballot(bad) == 0ull) {
+                const int32_t end = dir_sweep(s_q, s_d2, stage, R, C, cc, W, match, mismatch, o1, ext,
+                                              lane, dh);
                 __threadfence_block();
                 __syncthreads();
-                if (__ballot(end == score) == 0ull) return -1;
-                return dir_walk(q, d, R, C, cc, W, match, mismatch, o1, ext, score, lane, dh,
-                                ops + ops_off[h]);
-            };
-            if (__ballot(bad) == 0ull) {
-                if (staged)
-                    len = trace([&](uint32_t x) { return (uint32_t)s_q[x]; },
-                                [&](uint32_t x) { return (uint32_t)s_d2[x]; });
-                else
-                    len = trace(qat, dat);
+                if (__ballot(end == score) != 0ull)
+                    len = dir_walk([&](int32_t i) { return code(qp[i]); },
+                                   [&](int32_t j) { return (uint32_t)db_base(dbw, db0 + j); }, R, C,
+                                   cc, W, match, mismatch, o1, ext, score, lane, dh,
+                                   ops + ops_off[h]);
             }
         }
         if (lane == 0) {

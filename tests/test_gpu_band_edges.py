@@ -33,3 +33,25 @@ def test_ends_of_box_and_band(ggo, band, score):
     assert sum(s["n_out"] for s in wst) >= 8
     check_stats(G, gix, qs, G.params(20, **kw), want, wst)
     check_graph(G, gix, qs, G.params(20, **kw), want)
+
+
+@pytest.mark.parametrize("n", [4_015, 4_016, 4_017, 8_031, 8_033, 9_500])
+def test_long_boxes_in_parts(ggo, n):
+    """Boxes of more pairs than are staged at a time, and their paths."""
+    G = gpu()
+    rng = np.random.Generator(np.random.PCG64([32, n]))
+    bank = rng.choice(list(b"ACGT"), 12_000).astype(np.uint8)
+    db = synth.Database(bank, np.array([0, len(bank)], np.int64), "one sequence")
+    q = bank[1_000:1_000 + n].copy()
+    q[rng.random(n) < 0.03] = ord("A")
+    qs = synth.QuerySet(q, np.array([0, n], np.int64), *[np.zeros(1)] * 4)
+    gix, oix = G.Index(db.seqs, db.off, 11), ggo.Index(db.seqs, db.off, 11)
+    want, wst = oracle_all(oix, qs, ggo.params(3))
+    check_stats(G, gix, qs, G.params(3), want, wst)
+    check_graph(G, gix, qs, G.params(3), want)
+    rc, hits, k = gix.search(q, G.params(3), cap=3)
+    assert rc == 0 and int(hits[0]["q_end"] - hits[0]["q_start"]) > n - 100
+    rc, ops = gix.traceback(q, G.params(3), hits)
+    assert rc == 0
+    for h, got in zip(hits, ops):
+        assert got == oix.traceback(q.tobytes(), ggo.params(3), tuple(int(x) for x in h.tolist()))
