@@ -3193,8 +3193,7 @@ __global__ __launch_bounds__(kBlock, 5) void k_run_starts(RunStarts a,
 // (75 by blocks): what is left is the lists themselves, a 128-byte line or two of the
 // postings for six hits; more rows under way or more waves change nothing.
 __global__ __launch_bounds__(kBlock, 6) void k_run_starts_short(RunStarts a,
-                                                                const WaveCtl *__restrict__ ctl,
-                                                                int32_t tiles)
+                                                                const WaveCtl *__restrict__ ctl)
 {
     if (ctl) {
         a.np = ctl->np;
@@ -3206,14 +3205,15 @@ __global__ __launch_bounds__(kBlock, 6) void k_run_starts_short(RunStarts a,
     constexpr int kWaves = kBlock / 64, kRows = 4;  // rows with loads under way
     __shared__ int32_t s_p[kTile];   // 1 + position (from the wave's first) at its first hit
     __shared__ uint32_t s_hit[kTile], s_pos[kTile];  // the starts: hit | unsure, position
-    __shared__ uint32_t s_n[2], s_at, s_m;  // starts of the tile (even and odd ones in turn)
+    __shared__ uint32_t s_n, s_at, s_m;  // starts of the tile, those kept
     __shared__ int32_t s_q[2];              // first and last query of those kept
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
     const bool lengths = a.min_len > 2 * a.span;  // two hits may be too short
     int32_t *mark = s_p + wv * kSubTile;
-    const uint32_t b0 = blockIdx.x * (uint32_t)(tiles * kTile);  // the block's first hit
-    if (threadIdx.x < 2) s_n[threadIdx.x] = 0;
+    const uint32_t b0 = blockIdx.x * (uint32_t)kTile;  // the block's first hit
+    if (b0 >= a.nhits) return;  // a graph's grid covers the largest wave
+    if (threadIdx.x == 0) s_n = 0;
     __syncthreads();
     // Settles the unsure ones of the tile's n starts, then writes the keys of those kept:
     // with one add to the query's count where they all are of one query.
@@ -3282,88 +3282,79 @@ __global__ __launch_bounds__(kBlock, 6) void k_run_starts_short(RunStarts a,
         }
         __syncthreads();
     };
-    for (int32_t ti = 0; ti < tiles; ++ti) {
-        const uint32_t tile = blockIdx.x * (uint32_t)tiles + (uint32_t)ti;
-        if (tile * (uint32_t)kTile >= a.nhits) break;  // a graph's grid covers the largest wave
-        uint32_t *count = &s_n[ti & 1];
-        const uint32_t sub = tile * kWaves + (uint32_t)wv, h0 = sub * kSubTile;
-        if (h0 < a.nhits) {
-            const uint32_t cnt = min((uint32_t)kSubTile, a.nhits - h0);
-            uint32_t lo, hi;  // positions of the wave's first hit and of the first after it
-            if (a.tile_pos) {
-                lo = a.tile_pos[sub];
-                hi = h0 + cnt < a.nhits ? a.tile_pos[sub + 1] : (uint32_t)(a.np - 1);
-            } else {  // the last position with hrel <= the first or last hit
-                const uint32_t j = lane & 1 ? h0 + cnt - 1 : h0;
-                uint32_t x = 0, y = (uint32_t)(a.np - 1);
-                while (x < y) {
-                    const uint32_t m = x + ((y - x + 1) >> 1);
-                    if (a.hrel[m] <= j) x = m;
-                    else y = m - 1;
-                }
-                lo = __shfl(x, 0, 64);
-                hi = __shfl(x, 1, 64);
+    const uint32_t sub = blockIdx.x * kWaves + (uint32_t)wv, h0 = sub * kSubTile;
+    if (h0 < a.nhits) {
+        const uint32_t cnt = min((uint32_t)kSubTile, a.nhits - h0);
+        uint32_t lo, hi;  // positions of the wave's first hit and of the first after it
+        if (a.tile_pos) {
+            lo = a.tile_pos[sub];
+            hi = h0 + cnt < a.nhits ? a.tile_pos[sub + 1] : (uint32_t)(a.np - 1);
+        } else {  // the last position with hrel <= the first or last hit
+            const uint32_t j = lane & 1 ? h0 + cnt - 1 : h0;
+            uint32_t x = 0, y = (uint32_t)(a.np - 1);
+            while (x < y) {
+                const uint32_t m = x + ((y - x + 1) >> 1);
+                if (a.hrel[m] <= j) x = m;
+                else y = m - 1;
             }
-            lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)lo);
-            hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)hi);
-#pragma unroll
-            for (int r = 0; r < kItems; ++r) mark[r * 64 + lane] = 0;
-            __builtin_amdgcn_wave_barrier();
-            for (uint32_t p = lo + lane; p <= hi; p += 64) {
-                const uint32_t r0 = a.hrel[p], r1 = a.hrel[p + 1];
-                if (r1 > r0 && r1 > h0 && r0 < h0 + cnt)
-                    mark[max(r0, h0) - h0] = (int32_t)(p - lo) + 1;
-            }
-            __builtin_amdgcn_wave_barrier();
-            int32_t run = 0;
-#pragma unroll
-            for (int h = 0; h < kItems; h += kRows) {
-                uint32_t pos[kRows];
-                uint4 q[kRows];  // vm, n0, n1, head
-                uint2 cn[kRows];
-#pragma unroll
-                for (int r = 0; r < kRows; ++r) {
-                    const int32_t pr = max(wave_run_max(mark[(h + r) * 64 + lane]), run);
-                    run = __builtin_amdgcn_readlane(pr, 63);
-                    pos[r] = lo + (uint32_t)pr - 1u;  // lanes past the last hit: its position
-                    q[r] = *reinterpret_cast<const uint4 *>(a.qctx + pos[r]);
-                }
-#pragma unroll
-                for (int r = 0; r < kRows; ++r)
-                    cn[r] = a.next[q[r].w + h0 + min((uint32_t)((h + r) * 64 + lane), cnt - 1)];
-#pragma unroll
-                for (int r = 0; r < kRows; ++r) {
-                    const uint32_t l = (uint32_t)((h + r) * 64 + lane);
-                    const uint32_t nm = ctx_match(cn[r], q[r].y, q[r].z, q[r].x, a.shape);
-                    bool st = l < cnt && nm != 0, un = false;
-                    if (__ballot(st) == 0ull) continue;
-                    if (st) {
-                        const QCtx &c = a.qctx[pos[r]];
-                        const uint32_t pm = ctx_match(a.prev[q[r].w + h0 + l], c.p0, c.p1,
-                                                      q[r].x >> kCtx, a.shape);
-                        st = (pm & a.shape.exact) == 0;
-                        un = lengths || (nm & a.shape.exact) == 0 || pm != 0;
-                    }
-                    const uint64_t m = __ballot(st);
-                    if (m == 0) continue;
-                    uint32_t at = 0;
-                    if (lane == 0) at = atomicAdd(count, (uint32_t)__popcll(m));
-                    at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
-                    if (st) {
-                        at += (uint32_t)__popcll(m & below);
-                        s_hit[at] = (h0 - b0 + l) | (un ? kStartUnsure : 0u);
-                        s_pos[at] = pos[r];
-                    }
-                }
-            }
+            lo = __shfl(x, 0, 64);
+            hi = __shfl(x, 1, 64);
         }
-        __syncthreads();
-        const uint32_t n = *count;  // the next tile adds to the other one
-        if (n) {
-            flush(n);
-            if (threadIdx.x == 0) *count = 0;  // added to again after the next barrier
+        lo = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)lo);
+        hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)hi);
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) mark[r * 64 + lane] = 0;
+        __builtin_amdgcn_wave_barrier();
+        for (uint32_t p = lo + lane; p <= hi; p += 64) {
+            const uint32_t r0 = a.hrel[p], r1 = a.hrel[p + 1];
+            if (r1 > r0 && r1 > h0 && r0 < h0 + cnt)
+                mark[max(r0, h0) - h0] = (int32_t)(p - lo) + 1;
+        }
+        __builtin_amdgcn_wave_barrier();
+        int32_t run = 0;
+#pragma unroll
+        for (int h = 0; h < kItems; h += kRows) {
+            uint32_t pos[kRows];
+            uint4 q[kRows];  // vm, n0, n1, head
+            uint2 cn[kRows];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int32_t pr = max(wave_run_max(mark[(h + r) * 64 + lane]), run);
+                run = __builtin_amdgcn_readlane(pr, 63);
+                pos[r] = lo + (uint32_t)pr - 1u;  // lanes past the last hit: its position
+                q[r] = *reinterpret_cast<const uint4 *>(a.qctx + pos[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < kRows; ++r)
+                cn[r] = a.next[q[r].w + h0 + min((uint32_t)((h + r) * 64 + lane), cnt - 1)];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const uint32_t l = (uint32_t)((h + r) * 64 + lane);
+                const uint32_t nm = ctx_match(cn[r], q[r].y, q[r].z, q[r].x, a.shape);
+                bool st = l < cnt && nm != 0, un = false;
+                if (__ballot(st) == 0ull) continue;
+                if (st) {
+                    const QCtx &c = a.qctx[pos[r]];
+                    const uint32_t pm = ctx_match(a.prev[q[r].w + h0 + l], c.p0, c.p1,
+                                                  q[r].x >> kCtx, a.shape);
+                    st = (pm & a.shape.exact) == 0;
+                    un = lengths || (nm & a.shape.exact) == 0 || pm != 0;
+                }
+                const uint64_t m = __ballot(st);
+                if (m == 0) continue;
+                uint32_t at = 0;
+                if (lane == 0) at = atomicAdd(&s_n, (uint32_t)__popcll(m));
+                at = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)at);
+                if (st) {
+                    at += (uint32_t)__popcll(m & below);
+                    s_hit[at] = (h0 - b0 + l) | (un ? kStartUnsure : 0u);
+                    s_pos[at] = pos[r];
+                }
+            }
         }
     }
+    __syncthreads();
+    if (s_n) flush(s_n);
 }
 
 void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const WaveCtl *ctl,
@@ -3371,13 +3362,16 @@ void launch_run_starts(const RunStarts &a, bool both, hipStream_t st, const Wave
 {
     const uint32_t h = ctl ? hits_cap : a.nhits;
     if (h == 0) return;
+    const uint32_t nt = (h + kTile - 1) / kTile;
+    if (!both) {  // a tile per block: with eight, 2,500 mid-size queries took 702 us for 662
+        k_run_starts_short<<<nt, kBlock, 0, st>>>(a, ctl);
+        return;
+    }
     // eight tiles per block once every CU gets several such blocks: fewer, larger
     // writes and counter adds
-    const uint32_t nt = (h + kTile - 1) / kTile;
     const int32_t tiles = nt >= kStartTiles * 256u * 8u ? kStartTiles : 1;
     const uint32_t nb = (nt + tiles - 1) / tiles;
-    if (both) k_run_starts<<<nb, kBlock, 0, st>>>(a, ctl, tiles);
-    else k_run_starts_short<<<nb, kBlock, 0, st>>>(a, ctl, tiles);
+    k_run_starts<<<nb, kBlock, 0, st>>>(a, ctl, tiles);
 }
 
 // QCtx::head of a piece's positions, once their hits are scanned.
