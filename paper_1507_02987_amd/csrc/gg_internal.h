@@ -25,6 +25,7 @@ constexpr uint32_t kBucketCapMax = 512;  // most keys of one bucket (one wave so
 constexpr uint32_t kBucketBig = 16384;   // most keys of one bucket sorted by a block (128 KiB)
 constexpr int kPackSlack = 8;            // words that may be read past packed bases
 constexpr int kPackFront = 64;           // and before them (a left walk reads 32 bases back)
+constexpr int kPackWords = kBlock / 16;  // words of a block's packed bases
 constexpr int kMaxProbe = 4;             // neighbour windows probed per side (G / k + 1)
 constexpr int kBoundCap = 2048;          // run bounds of one query paired in LDS
 constexpr int kLenBins = 1024;           // box-length bins of the selection prefilter
@@ -32,6 +33,17 @@ constexpr int kLenBins = 1024;           // box-length bins of the selection pre
 // kernels with a wave or block per record loop over records beyond this grid.
 constexpr uint32_t kMaxGrid = 1u << 20;
 constexpr uint32_t kStrideGrid = 2048;  // blocks of a graph's grid-stride kernels
+
+// Words of T packed bases with those that may be read past them, and the word that thread t
+// of block b, one of ceil(T / kBlock), writes (-1: none): the words of its own bases and, in
+// the last block, what is left after them.
+__host__ __device__ inline int64_t packed_words(int64_t T) { return (T + 15) / 16 + kPackSlack; }
+__host__ __device__ inline int64_t packed_word(int64_t b, int32_t t, int64_t T)
+{
+    const bool last = (b + 1) * kBlock >= T;
+    const int64_t w = b * kPackWords + t;
+    return t < kPackWords + (last ? kPackSlack : 0) && w < packed_words(T) ? w : -1;
+}
 
 // First or last hit of a run of several hits: query (local), sequence, diagonal, qpos.
 struct Bound {
@@ -142,7 +154,7 @@ struct KeyWord {
 
 // bq[b]: the query of base b * kBlock; *err (host memory) is set at a byte outside the
 // alphabet; qpack, when given: the codes packed 16 bases to a word like the data bank,
-// (T + 15) / 16 + kPackSlack words.
+// packed_words(T) words.
 void launch_encode_kmers(const uint8_t *ascii, const int64_t *qoff, int32_t nq, int64_t T,
                          int32_t span, uint32_t mask, const uint32_t *list_off, uint8_t *qcode,
                          uint32_t *kcode, uint32_t *cnt, uint32_t *lhead, int32_t *qid,

@@ -408,14 +408,14 @@ __global__ __launch_bounds__(kBlock) void k_encode_kmers(
         s_c[x] = (uint8_t)c;
     }
     __syncthreads();
-    constexpr int kWords = kBlock / 16;
-    if (qpack && threadIdx.x < kWords + kPackSlack) {  // packed, zeros after the last
-        const int64_t w = (int64_t)blockIdx.x * kWords + threadIdx.x;
+    // packed, zeros after the last
+    const int64_t w = qpack ? packed_word(blockIdx.x, (int32_t)threadIdx.x, T) : -1;
+    if (w >= 0) {
         uint32_t v = 0;
-        if (threadIdx.x < kWords)
+        if (threadIdx.x < kPackWords)
 #pragma unroll
             for (int t = 0; t < 16; ++t) v |= (uint32_t)s_c[16 * threadIdx.x + t] << (30 - 2 * t);
-        if (threadIdx.x < kWords || (last && w < (T + 15) / 16 + kPackSlack)) qpack[w] = v;
+        qpack[w] = v;
     }
     const int64_t g = g0 + threadIdx.x;
     if (g >= T) return;

@@ -2002,7 +2002,7 @@ gg_status encode_batch(const gg_index *ix, Workspace *ws, Prof *prof, const char
     TRY(ensure(ws->hoff, sizeof(uint64_t) * (T + 1)));
     TRY(ensure(ws->partials, sizeof(uint64_t) * scan_partials_needed(std::max<int64_t>(T, nq + 1))));
     if (pack)
-        TRY(ensure(ws->qpack, sizeof(uint32_t) * (kPackFront + (size_t)(T + 15) / 16 + kPackSlack)));
+        TRY(ensure(ws->qpack, sizeof(uint32_t) * (kPackFront + (size_t)packed_words(T))));
     void *pin;
     TRY(pinned(ws, o_up + up, &pin, 1));
     uint64_t *h_qtot = static_cast<uint64_t *>(pin);
