@@ -3304,13 +3304,13 @@ __global__ __launch_bounds__(kBlock, 6) void k_run_starts_short(RunStarts a,
         hi = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)hi);
 #pragma unroll
         for (int r = 0; r < kItems; ++r) mark[r * 64 + lane] = 0;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();  // marks are set and read by other lanes than cleared them
         for (uint32_t p = lo + lane; p <= hi; p += 64) {
             const uint32_t r0 = a.hrel[p], r1 = a.hrel[p + 1];
             if (r1 > r0 && r1 > h0 && r0 < h0 + cnt)
                 mark[max(r0, h0) - h0] = (int32_t)(p - lo) + 1;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         int32_t run = 0;
 #pragma unroll
         for (int h = 0; h < kItems; h += kRows) {
