@@ -2857,13 +2857,14 @@ __device__ int32_t run_rest(const RunStarts &a, uint64_t wm, int32_t nw, RunWalk
 {
     for (;; w.o += 64 * nw * a.span) {
         const int32_t o = w.o + lane * nw * a.span;
-        uint32_t bits = 0;
+        uint64_t bits = 0;  // a chunk holds up to 64 windows (span 1)
         if (o <= w.last)
-            chunk_windows(a, wm, nw, w, o,
-                          [&](int32_t j, int32_t, bool hit) { bits |= (hit ? 1u : 0u) << j; });
+            chunk_windows(a, wm, nw, w, o, [&](int32_t j, int32_t, bool hit) {
+                bits |= (uint64_t)(hit ? 1u : 0u) << j;
+            });
         // windows without a hit just before the lane's: mmax - 1 <= 2 matter, and a
         // chunk holds two at least
-        const uint32_t pb = __shfl_up(bits, 1, 64);
+        const uint64_t pb = __shfl_up((unsigned long long)bits, 1, 64);
         int32_t miss = (pb >> (nw - 1)) & 1u ? 0 : (pb >> (nw - 2)) & 1u ? 1 : 2;
         if (lane == 0) miss = w.miss;
         int32_t hit = -1;
