@@ -432,7 +432,7 @@ __global__ __launch_bounds__(kBlock) void k_encode_kmers(
         for (int32_t t = 0; t < span; ++t)
             if ((mask >> t) & 1u) code = code * 4u + s_c[threadIdx.x + t];  // kept bases only
         head = list_off[code];
-        n = list_off[code + 1] - head;
+        n = list_off[(size_t)code + 1] - head;
     }
     kcode[g] = code;
     cnt[g] = n;
