@@ -298,7 +298,8 @@ void launch_ctx_heads(const uint32_t *pbase, const uint32_t *hrel, int64_t np, Q
 // launch_run_compact takes the starts from their queries' places (a.out) and
 // writes the runs in query order (offsets: off given, or, in a replayed wave of few
 // queries, summed here; then also off[0 .. nq_cap] and ctl->nc are written and *clear
-// zeroed); launch_run_ends takes n starts packed in query order, off[ql] their
+// zeroed); a replayed wave's query of more than kSegCap starts is flagged, and none of its
+// runs are written; launch_run_ends takes n starts packed in query order, off[ql] their
 // offsets.
 void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *cands,
                         hipStream_t st, WaveCtl *ctl = nullptr, int32_t nq_cap = 0,

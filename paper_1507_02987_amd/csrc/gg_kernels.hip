@@ -3402,6 +3402,21 @@ __device__ __forceinline__ RunWalk run_open(const RunStarts &a, const HitKeyLayo
     return run_walk(q0, L, s0, (int32_t)(a.seq_start[c->s + 1] - s0), c->d, c->qs, a.span);
 }
 
+// A replayed wave's query with more runs than the per-query LDS sorts hold is run again by
+// the host: it is flagged here, and none of its runs are taken.  (Taken by its one block and
+// extended, only to be dropped by the merge, they cost 500 reads with 25 tandem repeats among
+// them 237 ms on a 400 Mbp bank, 5.1 dropped here, 23 from stored hits.)
+__device__ __forceinline__ uint32_t seg_starts(uint32_t n) { return n > (uint32_t)kSegCap ? 0u : n; }
+
+__global__ void k_run_limit(uint32_t *__restrict__ scount, int32_t nq_cap,
+                            WaveCtl *__restrict__ ctl)
+{
+    const int32_t ql = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (ql >= nq_cap || seg_starts(scount[ql]) == scount[ql]) return;
+    scount[ql] = 0;
+    ctl->qflag[ctl->qa + ql] = 1u;
+}
+
 // Block ql: the runs of the wave's query ql, from its place in a.out to off[ql].  A
 // lane takes a run for kRunLane chunks; what is left of a long one is finished by its
 // whole wave (a 10 kb copy alone took 30 us a lane at a time).
@@ -3422,14 +3437,26 @@ __global__ __launch_bounds__(kBlock) void k_run_compact(RunStarts a, int32_t nqw
         lay = ctl->lay;
     }
     // counts past the wave's queries are zero, so offsets there are the total
-    const uint32_t at = sum ? block_sum(a.scount, (uint32_t)ql) : off[ql];
-    const uint32_t n = a.scount[ql];
-    if (ctl && threadIdx.x == 0) {
-        if (sum) off[ql] = at;
-        if (ql == (int32_t)gridDim.x - 1) {
-            if (sum) off[ql + 1] = at + n;
-            ctl->nc = at + n;
-            *clear = 0u;
+    uint32_t at, n = a.scount[ql];
+    if (sum) {
+        uint32_t before = 0;
+        for (uint32_t i = threadIdx.x; i < (uint32_t)ql; i += kBlock)
+            before += seg_starts(a.scount[i]);
+        block_excl_scan<uint32_t>(before, &at);
+    } else {
+        at = off[ql];
+    }
+    if (ctl) {  // (without sum, k_run_limit has been over the counts)
+        const bool over = seg_starts(n) != n;
+        n = seg_starts(n);
+        if (threadIdx.x == 0) {
+            if (over) ctl->qflag[qa + ql] = 1u;
+            if (sum) off[ql] = at;
+            if (ql == (int32_t)gridDim.x - 1) {
+                if (sum) off[ql + 1] = at + n;
+                ctl->nc = at + n;
+                *clear = 0u;
+            }
         }
     }
     if (ql >= nqw || n == 0) return;
@@ -3475,7 +3502,10 @@ void launch_run_compact(const RunStarts &a, int32_t nqw, uint32_t *off, Cand *ca
     // a replayed wave of a few thousand queries skips the scan: blocks add up the
     // counts before them
     const bool sum = ctl && nq_cap <= 4096;
-    if (ctl && !sum) launch_scan_u32(a.scount, off, nq_cap, partials, st);
+    if (ctl && !sum) {
+        k_run_limit<<<(nq_cap + kBlock - 1) / kBlock, kBlock, 0, st>>>(a.scount, nq_cap, ctl);
+        launch_scan_u32(a.scount, off, nq_cap, partials, st);
+    }
     k_run_compact<<<nb, kBlock, 0, st>>>(a, nqw, off, cands, ctl, sum, clear);
 }
 
