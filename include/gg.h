@@ -241,6 +241,15 @@ gg_status gg_index_info(const gg_index *index, int64_t *n_postings, int64_t *n_b
                         int64_t *n_seqs, int32_t *k);
 
 /*
+ * Device bytes of the index's contexts: 16 per posting, the codes of the windows around each
+ * posting's own, from which grouping 2 (below) takes its runs.  A built index has them in
+ * the memory that its build sorted the windows in.  0 for a loaded index that the device
+ * had no more room for, or whose lists do not hold every window of their codes: grouping 2
+ * then sorts every hit.
+ */
+gg_status gg_index_contexts(const gg_index *index, uint64_t *bytes);
+
+/*
  * Device bytes the batched search may use for index hits at once (two 8-byte
  * keys per hit).  Queries are processed in waves that fit it.  A query whose
  * hits exceed it alone is searched in pieces over ranges of data-bank sequence
@@ -258,7 +267,8 @@ gg_status gg_index_set_hit_budget(gg_index *index, uint64_t bytes);
  *              2 (the default) take run starts from the neighbour windows' codes kept
  *              beside each posting, and sort those; radix-sort all hits of a wave where
  *              one hit is a run long enough to keep (min_hsp_len at most the window
- *              span) or max_gap reaches past three windows.
+ *              span), max_gap reaches past three windows, or the index has no contexts
+ *              (gg_index_contexts).
  * lane_steps : X-drop steps (Section 2.2 phase 3) one lane takes before a whole
  *              wave resumes the walk; 0..4096 (0: every walk by a wave), default 256.
  * ms         : gg_index_autotune only: wall time of the sample batch with this

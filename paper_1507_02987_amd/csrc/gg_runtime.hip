@@ -175,8 +175,7 @@ struct gg_index {
     uint32_t *d_dbw = nullptr;
     int64_t *d_seq_start = nullptr;
     // contexts of the postings (16 bytes each beside their 8; one allocation, d_next),
-    // absent when the device has no room for them or a loaded file's lists are not
-    // the bank's
+    // absent when a loaded file's lists are not the bank's or there was no room for them
     uint2 *d_next = nullptr, *d_prev = nullptr;
     bool cut = false;  // some windows' lists were dropped
     uint64_t hit_budget = 0;
@@ -2205,21 +2204,16 @@ gg_status index_finish(gg_index *ix)
     return GG_OK;
 }
 
-// The postings' contexts, on the given stream (waited for by the caller's next
-// synchronisation; the null stream is waited for here).  Without room for them the
-// index goes on without.
+// Device bytes of n postings' contexts.
+size_t contexts_bytes(uint64_t n) { return 2 * sizeof(uint2) * std::max<uint64_t>(n, 1); }
+
+// The postings' contexts, in the index's block for them, on the given stream (waited for).
 gg_status index_contexts(gg_index *ix, hipStream_t st)
 {
-    if (hipMalloc((void **)&ix->d_next, 2 * sizeof(uint2) * std::max<uint64_t>(ix->n_post, 1)) !=
-        hipSuccess) {
-        (void)hipGetLastError();
-        ix->d_next = nullptr;
-        return GG_OK;
-    }
     ix->d_prev = ix->d_next + ix->n_post;
     launch_contexts(ix->d_post, (uint32_t)ix->n_post, ix->d_dbw, ix->d_seq_start, ix->span,
                     ix->mask, ctx_shape(ix->k), ix->d_next, ix->d_prev, st);
-    if (!st) SYNC(st);
+    SYNC(st);
     return GG_OK;
 }
 
@@ -2324,12 +2318,19 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     if ((s = alloc((void **)&ix->d_list_off, sizeof(uint32_t) * (ncode + 1))) != GG_OK ||
         (!cut && (s = alloc((void **)&ix->d_post, sizeof(int2) * n_post)) != GG_OK) ||
         (s = alloc_bank(ix, nwords)) != GG_OK ||
+        (s = alloc((void **)&ix->d_next, contexts_bytes(n_post))) != GG_OK ||
         (s = alloc((void **)&ix->d_seq_start, sizeof(int64_t) * (n_seqs + 1))) != GG_OK)
         return fail(s);
 
     // Sections 2, 2.1 on the GPU: pack the bases, code every window, sort the
     // windows stably by code (they start in (seq, pos) order, so every list stays
     // in that order), list heads = exclusive scan of the per-code counts.
+    hipStream_t bst = nullptr;
+    if (hipStreamCreateWithFlags(&bst, hipStreamNonBlocking) != hipSuccess) return fail(GG_EDEVICE);
+    struct StreamGuard {
+        hipStream_t s;
+        ~StreamGuard() { (void)hipStreamDestroy(s); }
+    } sg{bst};
     {
         // the build's temporaries in one allocation (a large one costs its 0.1 - 0.6 ms
         // of mapping and unmapping once)
@@ -2347,19 +2348,12 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
                 return at;
             }
         } tmp;
-        hipStream_t bst = nullptr;
-        if (hipStreamCreateWithFlags(&bst, hipStreamNonBlocking) != hipSuccess) return fail(GG_EDEVICE);
-        struct StreamGuard {
-            hipStream_t s;
-            ~StreamGuard() { (void)hipStreamDestroy(s); }
-        } sg{bst};
         const uint32_t nw = (uint32_t)n_post;
         const size_t parts = std::max<size_t>(scan_partials_needed(radix_hist_needed(nw)),
                                               scan_partials_needed((int64_t)ncode + 1));
         const size_t o_ascii = tmp.take((size_t)total);
         const size_t o_woff = tmp.take(sizeof(uint32_t) * (n_seqs + 1));
         const size_t o_err = tmp.take(sizeof(int32_t) * 4);
-        const size_t o_keys = tmp.take(sizeof(uint64_t) * nw), o_keys2 = tmp.take(sizeof(uint64_t) * nw);
         const size_t o_wseq = tmp.take(sizeof(uint32_t) * nw);
         const size_t o_hist = tmp.take(sizeof(uint32_t) * radix_hist_needed(nw));
         const size_t o_parts = tmp.take(sizeof(uint32_t) * parts);
@@ -2372,8 +2366,9 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
         auto *d_ascii = reinterpret_cast<uint8_t *>(tmp.p + o_ascii);
         auto *d_woff = reinterpret_cast<uint32_t *>(tmp.p + o_woff);
         auto *d_err = reinterpret_cast<int32_t *>(tmp.p + o_err);
-        auto *d_keys = reinterpret_cast<uint64_t *>(tmp.p + o_keys);
-        auto *d_keys2 = reinterpret_cast<uint64_t *>(tmp.p + o_keys2);
+        // the windows' keys lie where the postings' contexts will: they take as much, so a
+        // build that fits the device keeps its contexts
+        auto *d_keys = reinterpret_cast<uint64_t *>(ix->d_next), *d_keys2 = d_keys + nw;
         auto *d_wseq = reinterpret_cast<uint32_t *>(tmp.p + o_wseq);
         auto *d_hist = reinterpret_cast<uint32_t *>(tmp.p + o_hist);
         auto *d_parts = reinterpret_cast<uint32_t *>(tmp.p + o_parts);
@@ -2418,13 +2413,21 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
                 return fail(GG_EDEVICE);
             ix->cut = kept != nw;
         }
-        if ((s = index_contexts(ix, bst)) != GG_OK) return fail(s);
         if (hipMemcpyAsync(&err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, bst) != hipSuccess ||
             hipStreamSynchronize(bst) != hipSuccess || hipGetLastError() != hipSuccess)
             return fail(GG_EDEVICE);
         if (err) return fail(GG_EINVAL);
     }
 
+    static_assert(2 * sizeof(uint2) == 2 * sizeof(uint64_t), "two keys a window, two contexts");
+    if (ix->cut) {  // the kept postings' contexts take less, if that much is to be had
+        uint2 *less = nullptr;
+        if (alloc((void **)&less, contexts_bytes(ix->n_post)) == GG_OK) {
+            (void)hipFree(ix->d_next);
+            ix->d_next = less;
+        }
+    }
+    if ((s = index_contexts(ix, bst)) != GG_OK) return fail(s);
     if ((s = index_finish(ix)) != GG_OK) return fail(s);
     *out = ix;
     return GG_OK;
@@ -2484,6 +2487,13 @@ gg_status gg_index_info(const gg_index *ix, int64_t *n_postings, int64_t *n_base
     if (n_bases) *n_bases = ix->n_bases;
     if (n_seqs) *n_seqs = ix->n_seqs;
     if (k) *k = ix->k;
+    return GG_OK;
+}
+
+gg_status gg_index_contexts(const gg_index *ix, uint64_t *bytes)
+{
+    if (!ix || !bytes) return GG_EINVAL;
+    *bytes = ix->d_next ? 2 * sizeof(uint2) * ix->n_post : 0;
     return GG_OK;
 }
 
@@ -2731,7 +2741,14 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
     bool complete = false;
     if ((st = lists_complete(ix, &complete)) != GG_OK) return fail(st);
     ix->cut = nwin != ix->n_post;
-    if (complete && (st = index_contexts(ix, nullptr)) != GG_OK) return fail(st);
+    if (complete) {
+        if (hipMalloc((void **)&ix->d_next, contexts_bytes(ix->n_post)) == hipSuccess) {
+            if ((st = index_contexts(ix, nullptr)) != GG_OK) return fail(st);
+        } else {  // no room: the index goes on without (gg_index_contexts tells)
+            (void)hipGetLastError();
+            ix->d_next = nullptr;
+        }
+    }
     if ((st = index_finish(ix)) != GG_OK) return fail(st);
     *out = ix;
     return GG_OK;

@@ -29,7 +29,7 @@ STAT_DTYPE = np.dtype([(f, np.int64) for f in STAT_FIELDS])
 
 # Exported symbols of include/gg.h, in declaration order.
 SYMBOLS = ("gg_index_build", "gg_index_build_masked", "gg_index_build_ex", "gg_index_free",
-           "gg_index_info", "gg_index_export", "gg_index_save", "gg_index_load",
+           "gg_index_info", "gg_index_contexts", "gg_index_export", "gg_index_save", "gg_index_load",
            "gg_karlin_altschul", "gg_traceback_noalloc", "gg_hit_significance", "gg_traceback",
            "gg_index_set_hit_budget",
            "gg_index_get_tuning", "gg_index_set_tuning", "gg_index_autotune",
@@ -128,6 +128,7 @@ def lib():
         L.gg_index_free.argtypes = [vp]
         L.gg_index_free.restype = None
         L.gg_index_info.argtypes = [vp, vp, vp, vp, vp]
+        L.gg_index_contexts.argtypes = [vp, C.POINTER(u64)]
         L.gg_index_set_hit_budget.argtypes = [vp, u64]
         L.gg_index_get_tuning.argtypes = [vp, C.POINTER(Tuning)]
         L.gg_index_set_tuning.argtypes = [vp, C.POINTER(Tuning)]
@@ -237,6 +238,14 @@ class Index:
         if rc != GG_OK:
             raise GGError(rc, "gg_index_info")
         return {"n_postings": a.value, "n_bases": b.value, "n_seqs": c.value, "k": k.value}
+
+    def contexts(self) -> int:
+        """gg_index_contexts: device bytes of the postings' contexts, 0 without them."""
+        n = C.c_uint64()
+        rc = lib().gg_index_contexts(self._h, C.byref(n))
+        if rc != GG_OK:
+            raise GGError(rc, "gg_index_contexts")
+        return n.value
 
     def save(self, path: str):
         """gg_index_save: the index and its 2-bit bank to a file."""
