@@ -241,11 +241,13 @@ gg_status gg_index_info(const gg_index *index, int64_t *n_postings, int64_t *n_b
                         int64_t *n_seqs, int32_t *k);
 
 /*
- * Device bytes of the index's contexts: 16 per posting, the codes of the windows around each
- * posting's own, from which grouping 2 (below) takes its runs.  A built index has them in
- * the memory that its build sorted the windows in.  0 for a loaded index that the device
- * had no more room for, or whose lists do not hold every window of their codes: grouping 2
- * then sorts every hit.
+ * Device bytes of the index's contexts: 16 per posting beside its own 8, the codes of the
+ * windows around each posting's, from which grouping 2 (below) takes its runs.  0 without
+ * them, where grouping 2 sorts every hit: they are kept only where they take no more than
+ * half of what the index leaves free (a build sorts its windows in the same memory), and not
+ * for a loaded index whose lists lack windows of their codes; and a search that finds no
+ * device memory frees them for good, once the searches that read them are through, and goes
+ * on without.
  */
 gg_status gg_index_contexts(const gg_index *index, uint64_t *bytes);
 
@@ -255,7 +257,8 @@ gg_status gg_index_contexts(const gg_index *index, uint64_t *bytes);
  * hits exceed it alone is searched in pieces over ranges of data-bank sequence
  * ids (every phase up to the alignment is per sequence, so the result is the
  * same); it fails with GG_EBUDGET only if one sequence's hits exceed the budget.
- * 0 restores the default, min(16 GiB, a quarter of free device memory).
+ * 0 restores the default, min(16 GiB, a quarter of the device memory that was free after
+ * the index was made, its contexts not counted).
  */
 gg_status gg_index_set_hit_budget(gg_index *index, uint64_t bytes);
 

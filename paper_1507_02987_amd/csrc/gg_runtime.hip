@@ -16,6 +16,7 @@
 #include <mutex>
 #include <tuple>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -115,6 +116,7 @@ struct Workspace {
     DevBuf selbox;                      // the box index of each selection (replayed waves)
     DevBuf bsw_order;                   // the aligner's box order
     DevBuf qctx, sbase, scount;         // run starts from contexts: per position, per query
+    bool ctxs = false;                  // the search under way reads the index's contexts
     // small pinned staging: [0] a wave's counts, [1] a batch's hit totals, query offsets
     // and small texts, [2] the replayed waves' plan, [3] their result counts and [4] their
     // results (where a captured graph writes: nothing else lies in those two)
@@ -175,8 +177,12 @@ struct gg_index {
     uint32_t *d_dbw = nullptr;
     int64_t *d_seq_start = nullptr;
     // contexts of the postings (16 bytes each beside their 8; one allocation, d_next),
-    // absent when a loaded file's lists are not the bank's or there was no room for them
-    uint2 *d_next = nullptr, *d_prev = nullptr;
+    // absent where they do not fit or a loaded file's lists are not the bank's; freed for
+    // good when a call finds no memory (ContextsHold, drop_contexts)
+    mutable uint2 *d_next = nullptr, *d_prev = nullptr;
+    mutable int ctx_users = 0;      // searches that read them, under ws_mu like the rest
+    mutable bool ctx_going = false;  // no further search takes them
+    mutable std::condition_variable ctx_cv;
     bool cut = false;  // some windows' lists were dropped
     uint64_t hit_budget = 0;
     uint64_t default_budget = 0;
@@ -222,6 +228,75 @@ void put_ws(const gg_index *ix, Workspace *ws)
 {
     std::lock_guard<std::mutex> g(ix->ws_mu);
     ix->ws_free.push_back(ws);
+}
+
+// Device bytes of n postings' contexts.
+size_t contexts_bytes(uint64_t n) { return 2 * sizeof(uint2) * std::max<uint64_t>(n, 1); }
+
+// A search's hold on the index's contexts: they are not freed while it reads them.
+struct ContextsHold {
+    const gg_index *ix;
+    bool has = false;
+    explicit ContextsHold(const gg_index *i) : ix(i)
+    {
+        std::lock_guard<std::mutex> g(ix->ws_mu);
+        has = ix->d_next && !ix->ctx_going;
+        if (has) ++ix->ctx_users;
+    }
+    ~ContextsHold()
+    {
+        if (!has) return;
+        std::lock_guard<std::mutex> g(ix->ws_mu);
+        if (--ix->ctx_users == 0) ix->ctx_cv.notify_all();
+    }
+    ContextsHold(const ContextsHold &) = delete;
+};
+
+bool has_contexts(const gg_index *ix)
+{
+    std::lock_guard<std::mutex> g(ix->ws_mu);
+    return ix->d_next;
+}
+
+// For a call that found no device memory and reads no contexts itself (any more): frees them
+// once the searches that do are through, if another call has not.
+void drop_contexts(const gg_index *ix)
+{
+    std::unique_lock<std::mutex> g(ix->ws_mu);
+    if (!ix->d_next) return;
+    if (ix->ctx_going) {  // another call is about to
+        ix->ctx_cv.wait(g, [&] { return !ix->d_next; });
+        return;
+    }
+    ix->ctx_going = true;
+    ix->ctx_cv.wait(g, [&] { return ix->ctx_users == 0; });
+    g.unlock();
+    // the driver gives freed memory back some milliseconds later
+    size_t before = 0, now = 0, total = 0;
+    const bool known = hipMemGetInfo(&before, &total) == hipSuccess;
+    (void)hipFree(ix->d_next);
+    for (int i = 0; known && i < 100; ++i) {
+        if (hipMemGetInfo(&now, &total) != hipSuccess ||
+            now >= before + contexts_bytes(ix->n_post) / 2)
+            break;
+        std::this_thread::sleep_for(std::chrono::milliseconds(2));
+    }
+    (void)hipGetLastError();
+    g.lock();
+    ix->d_next = ix->d_prev = nullptr;
+    ix->ctx_cv.notify_all();
+}
+
+// A call that finds no device memory is run once more without the index's contexts: what
+// fitted beside the index alone does not fail for them.
+template <typename F>
+gg_status with_room(const gg_index *ix, F run)
+{
+    const bool had = has_contexts(ix);
+    const gg_status s = run();
+    if (s != GG_ENOMEM || !had) return s;
+    drop_contexts(ix);
+    return run();
 }
 
 gg_status pinned(Workspace *ws, size_t bytes, void **p, int slot = 0)
@@ -493,11 +568,19 @@ bool filter_for(const gg_index *ix, const gg_params *p, uint64_t hits, int64_t n
 // every kept run has two hits at least (M > span) and the gap limit stays within the
 // windows a context holds; else, and when GG_GROUPING=sort pins it, every hit is
 // stored and sorted.
-bool contexts_for(const gg_index *ix, const gg_params *p)
+bool contexts_for(const gg_index *ix, const Workspace *ws, const gg_params *p)
 {
     const char *g = getenv("GG_GROUPING");
     if (g && !strcmp(g, "sort")) return false;
-    return ix->d_next && p->min_hsp_len > ix->span && p->max_gap / ix->span + 1 <= kCtx;
+    return ws->ctxs && p->min_hsp_len > ix->span && p->max_gap / ix->span + 1 <= kCtx;
+}
+
+// GG_ROOM=none: a search by contexts finds no memory for its buffers (for tests of what it
+// then does).
+bool no_room()
+{
+    const char *e = getenv("GG_ROOM");
+    return e && !strcmp(e, "none");
 }
 
 CtxPrep ctx_prep(const gg_index *ix, Workspace *ws, const gg_params *p)
@@ -601,12 +684,13 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
     // ---- S3 gather
     const int64_t np = g1 - g0;
     const bool lookback = sort_kind_from_env() == kOneSweep;
-    const bool ctxs = grouping == kSort && !lookback && contexts_for(ix, p);
+    const bool ctxs = grouping == kSort && !lookback && contexts_for(ix, ws, p);
     const bool both = H64 >= kCtxBothMean * (uint64_t)np;  // long lists
     CtxPrep cp;
     TRY(ensure(ws->hrel, sizeof(uint32_t) * (np + 1)));
     TRY(ensure(ws->pbase, sizeof(uint32_t) * (np + 1)));
     if (ctxs) {
+        if (no_room()) return GG_ENOMEM;
         TRY(ensure(ws->qctx, sizeof(QCtx) * np));
         TRY(ensure(ws->sbase, sizeof(uint32_t) * nqw));
         TRY(ensure(ws->scount, sizeof(uint32_t) * nqw));
@@ -1692,7 +1776,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     if ((uint64_t)maxL * (uint64_t)p->match >= (1ull << 30)) return GG_EINVAL;
     uint64_t hsum = 0;
     for (const WaveCtl &w : plan) hsum += w.H;
-    const bool ctxs = contexts_for(ix, p);
+    const bool ctxs = contexts_for(ix, ws, p);
     const bool filt = !ctxs && filter_for(ix, p, hsum, nq);
     const bool fused = fused_filter_enabled();
     // radix tiles within query segments, all waves in one table (none when the
@@ -1731,6 +1815,7 @@ gg_status run_graph_waves(const gg_index *ix, Workspace *ws, Prof &prof, const g
     const uint32_t runs_cap = ctxs ? hits_cap / 2 + (uint32_t)nq_cap + 1 : hits_cap;
     TRY(ensure(ws->keys, sizeof(uint64_t) * runs_cap));
     if (ctxs) {
+        if (no_room()) return GG_ENOMEM;
         TRY(ensure(ws->qctx, sizeof(QCtx) * np_cap));
         TRY(ensure(ws->sbase, sizeof(uint32_t) * nq_cap));
         TRY(ensure(ws->scount, sizeof(uint32_t) * nq_cap));
@@ -2109,11 +2194,14 @@ gg_status count_hits(const gg_index *ix, const char *qbuf, const int64_t *qoff, 
         std::copy(h_qtot, h_qtot + n_q, hits);
         return GG_OK;
     };
-    gg_status s = run();
-    if (s != GG_OK) {
-        (void)hipStreamSynchronize(ws->st);
-        (void)hipGetLastError();
-    }
+    gg_status s = with_room(ix, [&] {
+        const gg_status r = run();
+        if (r != GG_OK) {
+            (void)hipStreamSynchronize(ws->st);
+            (void)hipGetLastError();
+        }
+        return r;
+    });
     put_ws(ix, ws);
     return s;
 }
@@ -2132,11 +2220,17 @@ gg_status search_batch_budget(const gg_index *ix, const char *qbuf, const int64_
     TRY(get_ws(ix, &ws));
     BatchOut bo{out, cap, n_out, stats};
     bo.device = device;
-    gg_status s = run_batch(ix, ws, qbuf, qoff, n_q, params, bo, budget);
-    if (s != GG_OK) {
-        (void)hipStreamSynchronize(ws->st);
-        (void)hipGetLastError();
-    }
+    gg_status s = with_room(ix, [&] {
+        const ContextsHold hold(ix);
+        ws->ctxs = hold.has;
+        bo.truncated = false;
+        const gg_status r = run_batch(ix, ws, qbuf, qoff, n_q, params, bo, budget);
+        if (r != GG_OK) {
+            (void)hipStreamSynchronize(ws->st);
+            (void)hipGetLastError();
+        }
+        return r;
+    });
     put_ws(ix, ws);
     if (s == GG_OK && bo.truncated) s = GG_ETRUNC;
     return s;
@@ -2190,6 +2284,8 @@ gg_status index_finish(gg_index *ix)
 {
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return GG_EDEVICE;
+    // of what the index alone leaves free: its contexts make no wave smaller
+    if (ix->d_next) free_b += contexts_bytes(ix->n_post);
     ix->default_budget = std::min<uint64_t>((uint64_t)16 << 30, free_b / 4);
     int lds = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ix->device) !=
@@ -2204,8 +2300,12 @@ gg_status index_finish(gg_index *ix)
     return GG_OK;
 }
 
-// Device bytes of n postings' contexts.
-size_t contexts_bytes(uint64_t n) { return 2 * sizeof(uint2) * std::max<uint64_t>(n, 1); }
+// Contexts are kept where they leave as much device memory as they take, of what the index
+// itself left (free_b), for searches and for others on the GPU.
+bool contexts_fit(const gg_index *ix, size_t free_b)
+{
+    return contexts_bytes(ix->n_post) <= free_b / 2;
+}
 
 // The postings' contexts, in the index's block for them, on the given stream (waited for).
 gg_status index_contexts(gg_index *ix, hipStream_t st)
@@ -2304,6 +2404,8 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
         return s;
     };
     if (hipSetDevice(device) != hipSuccess) return fail(GG_EDEVICE);
+    size_t free0 = 0, total0 = 0;
+    if (hipMemGetInfo(&free0, &total0) != hipSuccess) return fail(GG_EDEVICE);
     auto alloc = [](void **dst, size_t bytes) -> gg_status {
         if (hipMalloc(dst, std::max<size_t>(bytes, 16)) != hipSuccess) {
             (void)hipGetLastError();
@@ -2427,7 +2529,14 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
             ix->d_next = less;
         }
     }
-    if ((s = index_contexts(ix, bst)) != GG_OK) return fail(s);
+    const size_t own = sizeof(uint32_t) * (ncode + 1) + sizeof(int2) * ix->n_post +
+                       sizeof(uint32_t) * (size_t)nwords + sizeof(int64_t) * (n_seqs + 1);
+    if (contexts_fit(ix, free0 > own ? free0 - own : 0)) {
+        if ((s = index_contexts(ix, bst)) != GG_OK) return fail(s);
+    } else {
+        (void)hipFree(ix->d_next);
+        ix->d_next = nullptr;
+    }
     if ((s = index_finish(ix)) != GG_OK) return fail(s);
     *out = ix;
     return GG_OK;
@@ -2493,7 +2602,8 @@ gg_status gg_index_info(const gg_index *ix, int64_t *n_postings, int64_t *n_base
 gg_status gg_index_contexts(const gg_index *ix, uint64_t *bytes)
 {
     if (!ix || !bytes) return GG_EINVAL;
-    *bytes = ix->d_next ? 2 * sizeof(uint2) * ix->n_post : 0;
+    std::lock_guard<std::mutex> g(ix->ws_mu);
+    *bytes = ix->d_next && !ix->ctx_going ? 2 * sizeof(uint2) * ix->n_post : 0;
     return GG_OK;
 }
 
@@ -2741,12 +2851,14 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
     bool complete = false;
     if ((st = lists_complete(ix, &complete)) != GG_OK) return fail(st);
     ix->cut = nwin != ix->n_post;
-    if (complete) {
-        if (hipMalloc((void **)&ix->d_next, contexts_bytes(ix->n_post)) == hipSuccess) {
-            if ((st = index_contexts(ix, nullptr)) != GG_OK) return fail(st);
-        } else {  // no room: the index goes on without (gg_index_contexts tells)
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return fail(GG_EDEVICE);
+    if (complete && contexts_fit(ix, free_b)) {
+        if (hipMalloc((void **)&ix->d_next, contexts_bytes(ix->n_post)) != hipSuccess) {
             (void)hipGetLastError();
             ix->d_next = nullptr;
+        } else if ((st = index_contexts(ix, nullptr)) != GG_OK) {
+            return fail(st);
         }
     }
     if ((st = index_finish(ix)) != GG_OK) return fail(st);

@@ -1,10 +1,13 @@
 """Indexes and searches on a GPU whose memory is nearly taken.
 
-The rest of the memory is held by buffers that are given back at the end.  An index keeps
-its postings' contexts whenever they fit once the build's temporaries are gone.
+The rest of the memory is held by buffers that are given back at the end.  A build that
+fits has its postings' contexts; a loaded index has them where they leave as much memory as
+they take; and a search that finds no memory goes on without them.
 """
 import contextlib
 import ctypes
+import functools
+import time
 
 import numpy as np
 import pytest
@@ -27,11 +30,14 @@ def free_bytes(G):
 
 @contextlib.contextmanager
 def leave(G, target):
-    """Holds all but about `target` bytes of the free memory."""
+    """Holds all but about `target` bytes of the free memory, what the driver gives back
+    late (some milliseconds after a free) included; gives a call that does so again, for
+    another target if it is given one (the memory itself takes seconds)."""
     held = []
-    size = 32 << 30
-    try:
-        while size >= 4 * MB:
+
+    def fill(target):
+        size = 32 << 30
+        while size >= 2 * MB:
             if free_bytes(G) - size < target:
                 size //= 2
                 continue
@@ -39,16 +45,32 @@ def leave(G, target):
                 held.append(G.DeviceBuffer(size))
             except G.GGError:
                 size //= 2
-        yield
+
+    def settle(target=target):
+        quiet = 0
+        while quiet < 3:
+            n = len(held)
+            fill(target)
+            quiet = quiet + 1 if len(held) == n else 0
+            time.sleep(0.1)
+
+    try:
+        settle()
+        yield settle
     finally:
         for b in held:
             b.close()
 
 
+@functools.lru_cache(maxsize=1)
 def bank(bases, seed=61, n=2000):
     rng = np.random.Generator(np.random.PCG64([seed, bases]))
     seqs = np.frombuffer(b"ACGT", np.uint8)[rng.integers(0, 4, bases, dtype=np.uint8)]
     return seqs, np.linspace(0, bases, n + 1).astype(np.int64)
+
+
+def small_bank():
+    return bank.__wrapped__(100_000)
 
 
 def test_contexts_of_a_tight_build():
@@ -56,13 +78,13 @@ def test_contexts_of_a_tight_build():
     temporaries, 291 of them the windows' keys.  900 MB hold what the build needs, not that
     and the contexts; 600 MB do not hold the build."""
     G = gpu()
-    G.Index(*bank(100_000), SPAN).close()  # kernels loaded, first buffers allocated
+    G.Index(*small_bank(), SPAN).close()  # kernels loaded, first buffers allocated
     seqs, off = bank(200_000_000)
-    with leave(G, 900 * MB):
+    with leave(G, 900 * MB) as settle:
         ix = G.Index(seqs, off, SPAN)
         assert ix.contexts() == 16 * ix.info()["n_postings"]
         ix.close()
-    with leave(G, 600 * MB):
+        settle(600 * MB)
         with pytest.raises(G.GGError) as e:
             G.Index(seqs, off, SPAN)
         assert e.value.status == G.GG_ENOMEM
@@ -72,7 +94,7 @@ def test_contexts_of_an_index_with_a_cutoff():
     """16 bytes for each posting that is kept."""
     G = gpu()
     rng = np.random.Generator(np.random.PCG64(62))
-    seqs, off = bank(300_000, n=100)
+    seqs, off = bank.__wrapped__(300_000, n=100)
     seqs[100_000:200_000] = np.resize(np.frombuffer(b"ACC", np.uint8), 100_000)
     ix = G.Index(seqs, off, SPAN, max_posting=20)
     n = ix.info()["n_postings"]
@@ -80,3 +102,85 @@ def test_contexts_of_an_index_with_a_cutoff():
     q = seqs[int(rng.integers(0, 50_000)):][:2000].copy()
     rc, hits, _ = ix.search(q, G.params(5), cap=5)
     assert rc == 0 and len(hits) > 0 and as_rows(hits)[0][3] - as_rows(hits)[0][2] > 1000
+
+
+def queries(seqs, n, length, seed=63):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    at = rng.integers(0, len(seqs) - length, n)
+    return (np.concatenate([seqs[a:a + length] for a in at]),
+            np.arange(n + 1, dtype=np.int64) * length)
+
+
+def budget_of(G, ix):
+    srv = G.Server(ix, G.params(5), 0, 4)
+    b = srv.info()["budget_bytes"]
+    srv.close()
+    return b
+
+
+def test_loaded_index_leaves_memory_for_others(tmp_path):
+    """212 MB of index and 291 MB of contexts: in 650 MB they would leave less than they take."""
+    G = gpu()
+    seqs, off = bank(200_000_000)
+    ix = G.Index(seqs, off, SPAN)
+    path, want = str(tmp_path / "a.gg"), budget_of(G, ix)
+    ix.save(path)
+    ix.close()
+    got = []
+    with leave(G, 900 * MB) as settle:
+        for room in (900, 650):
+            settle(room * MB)
+            ix = G.Index.load(path)
+            got.append((ix.contexts() > 0, abs(budget_of(G, ix) - (room - 212) * MB // 4) < 8 * MB))
+            ix.close()
+    assert got == [(True, True), (False, True)]
+    assert want == 16 << 30
+
+
+def test_a_search_without_memory_goes_on_without_contexts(monkeypatch):
+    """The search is told that its buffers by contexts do not fit: batches replayed, with
+    statistics and in ranges of sequences, requests to the search service, and batches of
+    four threads, each on an index of its own.  Afterwards, with memory, the same results."""
+    from concurrent.futures import ThreadPoolExecutor
+
+    G = gpu()
+    seqs, off = bank.__wrapped__(3_000_000, n=300)
+    prm = G.params(5)
+    q, qoff = queries(seqs, 200, 300)
+
+    def batch(ix, stats=False):
+        rc, hits, n, st = ix.search_batch(q, qoff, prm, cap=5, stats=stats)
+        return rc, [as_rows(h) for h in hits], n.tolist(), st.tolist() if stats else None
+
+    def pieces(ix):
+        ix.set_hit_budget(16 * 4096)
+        return batch(ix, True)
+
+    def serve(ix):
+        srv = G.Server(ix, prm, 0, 16)
+        tickets = [srv.submit(q[a:b]) for a, b in zip(qoff[:-1], qoff[1:])]
+        got = [srv.poll(t, cap=5, timeout_us=-1) for t in tickets]
+        srv.close()
+        return max(g[0] for g in got), [(as_rows(g[1]), g[2]) for g in got]
+
+    def threads(ix):
+        with ThreadPoolExecutor(4) as ex:
+            got = list(ex.map(lambda i: batch(ix, i % 2 == 0), range(16)))
+        return max(g[0] for g in got), all(g[:3] == got[0][:3] for g in got), got[0]
+
+    for call in (batch, lambda ix: batch(ix, True), pieces, serve, threads):
+        monkeypatch.delenv("GG_ROOM", raising=False)
+        ix = G.Index(seqs, off, SPAN)
+        ix.profile(True)
+        want = call(ix)
+        assert want[0] == 0 and ix.contexts() > 0
+        ix.close()
+        monkeypatch.setenv("GG_ROOM", "none")
+        ix = G.Index(seqs, off, SPAN)
+        assert ix.contexts() > 0
+        got = call(ix)
+        assert got[0] == 0 and ix.contexts() == 0
+        monkeypatch.delenv("GG_ROOM")
+        same = [got == want, call(ix) == want]
+        assert all(same)
+        ix.close()
