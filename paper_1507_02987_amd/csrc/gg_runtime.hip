@@ -2278,14 +2278,11 @@ void gg_index_free(gg_index *ix)
 // the windows by code, so each list keeps (sequence, position) order.
 namespace {
 
-// Device-dependent settings of a built or loaded index: the default hit budget
-// and the LDS bucket sizes.
-gg_status index_finish(gg_index *ix)
+// Device-dependent settings of a built or loaded index: the default hit budget, from the
+// memory that the index alone leaves free (its contexts make no wave smaller), and the LDS
+// bucket sizes.
+gg_status index_finish(gg_index *ix, size_t free_b)
 {
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return GG_EDEVICE;
-    // of what the index alone leaves free: its contexts make no wave smaller
-    if (ix->d_next) free_b += contexts_bytes(ix->n_post);
     ix->default_budget = std::min<uint64_t>((uint64_t)16 << 30, free_b / 4);
     int lds = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ix->device) !=
@@ -2307,14 +2304,12 @@ bool contexts_fit(const gg_index *ix, size_t free_b)
     return contexts_bytes(ix->n_post) <= free_b / 2;
 }
 
-// The postings' contexts, in the index's block for them, on the given stream (waited for).
-gg_status index_contexts(gg_index *ix, hipStream_t st)
+// The postings' contexts, in the index's block for them, on the given stream.
+void index_contexts(gg_index *ix, hipStream_t st)
 {
     ix->d_prev = ix->d_next + ix->n_post;
     launch_contexts(ix->d_post, (uint32_t)ix->n_post, ix->d_dbw, ix->d_seq_start, ix->span,
                     ix->mask, ctx_shape(ix->k), ix->d_next, ix->d_prev, st);
-    SYNC(st);
-    return GG_OK;
 }
 
 // The packed bank's words, with those that may be read before and past them.
@@ -2330,20 +2325,29 @@ gg_status alloc_bank(gg_index *ix, int64_t nwords)
     return GG_OK;
 }
 
-// Whether every list of a loaded index holds exactly the bank's windows of its code,
-// in order, or none of them (a repeat cutoff).
-gg_status lists_complete(const gg_index *ix, bool *complete)
+// A loaded index's contexts.  They stand for the lists only where every list holds exactly the
+// bank's windows of its code, in order, or none of them (a repeat cutoff): built and checked
+// in one go, and given back where that is not so, or where they do not fit.
+gg_status load_contexts(gg_index *ix, size_t free_b)
 {
-    unsigned long long *d = nullptr, h[2] = {0, 0};
-    HIPCHK(hipMalloc((void **)&d, sizeof(h)));
-    hipError_t e = hipMemcpy(d, h, sizeof(h), hipMemcpyHostToDevice);
+    unsigned long long h[2] = {0, 0};
+    const size_t bytes = contexts_bytes(ix->n_post);  // and after them the check's two counts
+    if (!contexts_fit(ix, free_b) || hipMalloc((void **)&ix->d_next, bytes + sizeof(h)) != hipSuccess) {
+        (void)hipGetLastError();
+        ix->d_next = nullptr;
+        return GG_OK;
+    }
+    auto *d = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(ix->d_next) + bytes);
+    launch_fill_u32(reinterpret_cast<uint32_t *>(d), sizeof(h) / sizeof(uint32_t), 0u, nullptr);
     launch_check_lists(ix->d_list_off, ix->d_post, (uint32_t)ix->n_post, ix->d_dbw,
                        ix->d_seq_start, (int32_t)ix->n_seqs, ix->span, ix->mask, d, d + 1, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(h, d, sizeof(h), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipGetLastError();
-    (void)hipFree(d);
-    HIPCHK(e);
-    *complete = h[0] == 0 && h[1] == ix->n_post;
+    index_contexts(ix, nullptr);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpy(h, d, sizeof(h), hipMemcpyDeviceToHost));  // waits for all of them
+    if (h[0] != 0 || h[1] != ix->n_post) {
+        (void)hipFree(ix->d_next);
+        ix->d_next = ix->d_prev = nullptr;
+    }
     return GG_OK;
 }
 
@@ -2531,13 +2535,16 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     }
     const size_t own = sizeof(uint32_t) * (ncode + 1) + sizeof(int2) * ix->n_post +
                        sizeof(uint32_t) * (size_t)nwords + sizeof(int64_t) * (n_seqs + 1);
-    if (contexts_fit(ix, free0 > own ? free0 - own : 0)) {
-        if ((s = index_contexts(ix, bst)) != GG_OK) return fail(s);
+    const size_t free_b = free0 > own ? free0 - own : 0;
+    if (contexts_fit(ix, free_b)) {
+        index_contexts(ix, bst);
+        if (hipStreamSynchronize(bst) != hipSuccess || hipGetLastError() != hipSuccess)
+            return fail(GG_EDEVICE);
     } else {
         (void)hipFree(ix->d_next);
         ix->d_next = nullptr;
     }
-    if ((s = index_finish(ix)) != GG_OK) return fail(s);
+    if ((s = index_finish(ix, free_b)) != GG_OK) return fail(s);
     *out = ix;
     return GG_OK;
 }
@@ -2801,8 +2808,12 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
         return GG_EINVAL;
     for (uint64_t c = 0; c + 1 < nheads; ++c)
         if (heads[c + 1] < heads[c]) return GG_EINVAL;
+    // y is a multiple of the span where y * mul, mod 2^64, is below mul (Lemire, Kaser and Kurz,
+    // "Faster remainder by direct computation", 2019); mul is 0 for a span of 1
+    const uint64_t mul = ~0ull / (uint64_t)hd.span + 1ull;
     for (const int2 &e : post) {
-        if (e.x < 0 || e.x >= hd.n_seqs || e.y < 0 || e.y % hd.span != 0) return GG_EINVAL;
+        if (e.x < 0 || e.x >= hd.n_seqs || e.y < 0 || (uint64_t)e.y * mul > mul - 1ull)
+            return GG_EINVAL;
         if ((int64_t)e.y + hd.span > seq_start[(size_t)e.x + 1] - seq_start[(size_t)e.x])
             return GG_EINVAL;
     }
@@ -2844,24 +2855,14 @@ gg_status gg_index_load(const char *path, int32_t device, gg_index **out)
     if (hipMemcpy(ix->d_dbw, bank.data(), sizeof(uint32_t) * bank.size(), hipMemcpyHostToDevice) !=
         hipSuccess)
         return fail(GG_EDEVICE);
-    // contexts stand for the lists only where each list holds every window of its code
     uint64_t nwin = 0;
     for (int64_t s = 0; s < hd.n_seqs; ++s)
         nwin += (uint64_t)((seq_start[(size_t)s + 1] - seq_start[(size_t)s]) / hd.span);
-    bool complete = false;
-    if ((st = lists_complete(ix, &complete)) != GG_OK) return fail(st);
     ix->cut = nwin != ix->n_post;
     size_t free_b = 0, total_b = 0;
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return fail(GG_EDEVICE);
-    if (complete && contexts_fit(ix, free_b)) {
-        if (hipMalloc((void **)&ix->d_next, contexts_bytes(ix->n_post)) != hipSuccess) {
-            (void)hipGetLastError();
-            ix->d_next = nullptr;
-        } else if ((st = index_contexts(ix, nullptr)) != GG_OK) {
-            return fail(st);
-        }
-    }
-    if ((st = index_finish(ix)) != GG_OK) return fail(st);
+    if ((st = load_contexts(ix, free_b)) != GG_OK) return fail(st);
+    if ((st = index_finish(ix, free_b)) != GG_OK) return fail(st);
     *out = ix;
     return GG_OK;
 }
