@@ -378,7 +378,8 @@ gg_status gg_device_read(const void *src, uint64_t bytes, uint64_t *sum);
  * rest of each query), "filter_compact" (the kept hits' move into one array),
  * "sort_hist", "sort_scan", "sort_scatter" (one mark per radix pass of the hit
  * or run sort, when it runs), "chain" (run counts),
- * "chain_write", "extend", "merge" (ordering and sweep),
+ * "chain_write", "extend", "merge" (ordering and sweep), "merge_sweep" (those of "merge"
+ * where every query is ordered and swept by one block, counted in both),
  * "select", "align" (the banded Smith-Waterman kernel alone), "report", and
  * "graph" (all replays of a batch's captured wave graph, whose kernels are not
  * timed one by one: units = waves).  ms is the summed GPU time between the marks,

@@ -351,6 +351,13 @@ struct Prof {
         ws->marks.push_back({name, open, e1, units});
         open = -1;
     }
+    void also(const char *n)  // the last mark under a second name
+    {
+        if (!on || ws->marks.empty()) return;
+        auto m = ws->marks.back();
+        m.name = n;
+        ws->marks.push_back(m);
+    }
     void collect()  // after the stream has been synchronised
     {
         if (!on || ws->marks.empty()) return;
@@ -1222,6 +1229,7 @@ gg_status run_wave(const gg_index *ix, Workspace *ws, Prof &prof, const gg_param
                                 p->max_hits, as<uint32_t>(ws->qstart), as<uint32_t>(ws->qend),
                                 as<uint32_t>(ws->nsel), st);
         prof.end(nc);
+        prof.also("merge_sweep");
     } else if (windows) {
         // groups in LDS windows, those that may outgrow one a block each, the few longer still
         // by the global sort
