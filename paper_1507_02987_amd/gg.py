@@ -24,6 +24,7 @@ HIT_FIELDS = ("seq_id", "score", "q_start", "q_end", "d_start", "d_end",
               "box_q_start", "box_q_end", "box_d_start", "box_d_end", "box_len",
               "band_d0")
 HIT_DTYPE = np.dtype([(f, np.int32) for f in HIT_FIELDS])
+_ROW = np.dtype((np.void, HIT_DTYPE.itemsize))
 STAT_FIELDS = ("n_kmers", "n_hits", "n_cands", "n_merged", "n_selected", "n_cells", "n_out")
 STAT_DTYPE = np.dtype([(f, np.int64) for f in STAT_FIELDS])
 
@@ -170,13 +171,14 @@ def _u8(x) -> np.ndarray:
     return np.frombuffer(bytes(x), dtype=np.uint8)
 
 
-def _rows(raw: memoryview, first: int, n: int) -> np.ndarray:
-    """A copy of n hit records from record `first` of raw's bytes.  By bytes: numpy copies
-    structured arrays field by field (80 queries' hits in 580 us, 76 by bytes)."""
-    if n == 0:
-        return np.zeros(0, HIT_DTYPE)
-    size = HIT_DTYPE.itemsize
-    return np.frombuffer(bytearray(raw[first * size:(first + n) * size]), HIT_DTYPE)
+def _rows(out: np.ndarray, starts, counts) -> list[np.ndarray]:
+    """Copies of the hit records out[a:a + n], arrays of their own.  As opaque records: numpy
+    copies structured arrays field by field (80 queries' 50 hits in 747 us, 93 so)."""
+    flat = out.view(_ROW)
+    res = [flat[a:a + n].copy() for a, n in zip(starts, counts)]
+    for r in res:
+        r.dtype = HIT_DTYPE
+    return res
 
 
 class Index:
@@ -337,7 +339,7 @@ class Index:
                              cap, C.byref(n))
         if rc not in (GG_OK, GG_ETRUNC):
             return rc, np.zeros(0, HIT_DTYPE), 0
-        return rc, _rows(memoryview(out.view(np.uint8)), 0, min(n.value, cap)), n.value
+        return rc, _rows(out, (0,), (min(n.value, cap),))[0], n.value
 
     def search_batch(self, qbuf, qoff, prm: Params, cap: int = 1024, stats: bool = False):
         """gg_search_batch: returns (status, list of hit arrays, counts, stats or None)."""
@@ -352,8 +354,8 @@ class Index:
                                    _ptr(st) if stats else None)
         if rc not in (GG_OK, GG_ETRUNC):
             return rc, [], nout[:nq], None
-        raw = memoryview(out.view(np.uint8))
-        res = [_rows(raw, i * cap, min(m, cap)) for i, m in enumerate(nout[:nq].tolist())]
+        res = _rows(out, range(0, nq * cap, cap) if cap else [0] * nq,
+                    np.minimum(nout[:nq], cap).tolist())
         return rc, res, nout[:nq].copy(), (st[:nq] if stats else None)
 
     def search_batch_into(self, qbuf: np.ndarray, qoff: np.ndarray, prm: Params, out: np.ndarray,
@@ -465,7 +467,7 @@ class Server:
         n = C.c_int32()
         rc = lib().gg_serve_poll(self._h, ticket, _ptr(out), cap, C.byref(n), timeout_us)
         if rc in (GG_OK, GG_ETRUNC):
-            return rc, _rows(memoryview(out.view(np.uint8)), 0, min(n.value, cap)), n.value
+            return rc, _rows(out, (0,), (min(n.value, cap),))[0], n.value
         return rc, np.zeros(0, HIT_DTYPE), 0
 
     def info(self) -> dict:
