@@ -178,20 +178,23 @@ def cpu_baseline(db, qs, max_hits: int, cap: int, hits_per_query: np.ndarray):
 
 
 # Algorithmic work per launch of each modelled kernel:
-#  probe   - HBM: 8 B of the following windows' codes per hit
+#  probe   - HBM: 8 B of the following windows' codes per hit; in lists of 64 postings and
+#            more on average, 16 B (the windows' before it too), by k_run_starts
 #  gather  - HBM: 8 B posting read + 8 B key write per hit
 #  filter  - HBM: 8 B key read per hit (the kept few are written back)
 #  sort_*  - HBM: 16 B per key per scatter pass, 8 B per histogram pass
 #  align   - integer ALU: ALIGN_OPS_PER_CELL int32 operations per in-band cell
-KERNEL = {"probe": "k_run_starts", "gather": "k_gather", "filter": "k_hit_filter",
+KERNEL = {"probe": "k_run_starts_short", "gather": "k_gather", "filter": "k_hit_filter",
           "gather_filter": "k_gather_filter",
           "sort_scatter": "k_rs_scatter_seg",
           "sort_hist": "k_rs_hist_seg", "align": "k_bsw"}
 
 
 def rooflines(stages: dict, cells: int, nprof: int, workload: str):
+    probe, prep = (stages.get(s, {}).get("units", 0) for s in ("probe", "gather_prep"))
+    both_sides = probe >= 64 * max(prep, 1)
     model = {
-        "probe": ("hbm", lambda st: 8 * st["units"]),
+        "probe": ("hbm", lambda st: (16 if both_sides else 8) * st["units"]),
         "gather": ("hbm", lambda st: 16 * st["units"]),
         "filter": ("hbm", lambda st: 8 * st["units"]),
         # one posting entry read per hit; the kept keys it writes are a few per mille
@@ -211,7 +214,8 @@ def rooflines(stages: dict, cells: int, nprof: int, workload: str):
             achieved, peak, unit = per_launch / avg_s / 1e9, HBM_PEAK_GBS, "GB/s"
         else:
             achieved, peak, unit = per_launch / avg_s / 1e12, VALU_PEAK_TOPS, "TOP/s"
-        return {"bound": bound, "kernel": KERNEL[stage], "achieved": round(achieved, 2),
+        kernel = "k_run_starts" if stage == "probe" and both_sides else KERNEL[stage]
+        return {"bound": bound, "kernel": kernel, "achieved": round(achieved, 2),
                 "peak": peak, "unit": unit, "frac": round(achieved / peak, 4),
                 "traffic": traffic_for(stage, workload), "avg_launch_us": round(avg_s * 1e6, 2),
                 "launches": st["launches"] // nprof,

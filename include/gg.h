@@ -373,20 +373,20 @@ gg_status gg_device_read(const void *src, uint64_t bytes, uint64_t *sum);
  * Enabling (on or off) clears the totals; when on, HIP events are recorded around
  * each stage on the stream it runs on.  Names: "encode", "scan", "gather_prep",
  * "probe" (run starts, from the postings' contexts or by probing the bank), "run_ends"
- * (the starts' runs), "gather" (the posting-gather kernel alone), "filter" (the kernel dropping hits
- * alone on their (sequence, diagonal) when M exceeds the seed span and sorting the
- * rest of each query), "filter_compact" (the kept hits' move into one array),
- * "sort_hist", "sort_scan", "sort_scatter" (one mark per radix pass of the hit
- * or run sort, when it runs), "chain" (run counts),
- * "chain_write", "extend", "merge" (ordering and sweep), "merge_sweep" (those of "merge"
- * where every query is ordered and swept by one block, counted in both),
- * "select", "align" (the banded Smith-Waterman kernel alone), "report", and
- * "graph" (all replays of a batch's captured wave graph, whose kernels are not
- * timed one by one: units = waves).  ms is the summed GPU time between the marks,
- * launches the number of marks, units the work they covered (query bases for
- * encode and scan, positions for gather_prep, hits for probe, gather, filter and the
- * sort marks (runs there when run starts are sorted), runs for run_ends, hits left after the filter for the chain marks, runs for
- * extend/merge/select, boxes for align/report).
+ * (the starts' runs), "gather" (the posting-gather kernel alone), "filter" (the kernel
+ * dropping hits alone on their (sequence, diagonal) when M exceeds the seed span and
+ * sorting the rest of each query), "filter_compact" (the kept hits' move into one array),
+ * "sort_hist", "sort_scan", "sort_scatter" (one mark per radix pass of the hit or run
+ * sort, when it runs), "chain" (run counts), "chain_write", "extend", "merge" (ordering
+ * and sweep), "merge_sweep" (those of "merge" where every query is ordered and swept by
+ * one block, counted in both), "select", "align" (the banded Smith-Waterman kernel alone),
+ * "report", and "graph" (all replays of a batch's captured wave graph, whose kernels are
+ * not timed one by one: units = waves).  A stage that a search does not take reads zeros:
+ * one by contexts has no gather, filter or chain.  ms is the summed GPU time between the
+ * marks, launches the number of marks, units the work they covered (query bases for encode
+ * and scan, positions for gather_prep, hits for probe, gather, filter and the sort marks
+ * (runs there when run starts are sorted), runs for run_ends, hits left after the filter
+ * for the chain marks, runs for extend/merge/select, boxes for align/report).
  *
  * Batched calls without statistics, with the radix-sort grouping and 1 <= max_hits
  * <= 1024, run each wave as a replay of one captured HIP graph (all waves after a

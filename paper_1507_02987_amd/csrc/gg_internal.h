@@ -495,17 +495,14 @@ void launch_segments_box(const Box *sorted, uint32_t n, int32_t nq, uint32_t *qs
                          uint32_t *qend, hipStream_t st);
 void launch_segments_align(const Align *sorted, uint32_t n, int32_t nq, uint32_t *qstart,
                            uint32_t *qend, hipStream_t st);
-// A replayed wave's per-query run ranges, counts and offsets (off[0..nq_cap]: runs
-// are in query order, so offsets are the ranges' starts), and its per-query
-// selected-box ranges and counts capped at N (each query's boxes in its own
-// segment, selected ones first); grids of nq_cap threads (the first also zeroes
-// *clear, the extension's queue count, when given).  The _scan form also
-// writes the counts' exclusive scan (sel_off[0..nq_cap]) and, for the aligner,
-// the box index of every selection (sel_box[sel_off[q] + r] = qstart[q] + r),
-// from one block.
+// A replayed wave's per-query run ranges, counts and offsets (off[0..nq_cap]: runs are in
+// query order, so offsets are the ranges' starts); also zeroes *clear, the extension's queue
+// count, when given.
 void launch_cand_ranges_ctl(const Cand *c, int32_t nq_cap, uint32_t *qstart, uint32_t *qend,
                             uint32_t *counts, uint32_t *off, uint32_t *clear, const WaveCtl *ctl,
                             hipStream_t st);
+// The exclusive scan of a replayed wave's selection counts (sel_off[0..nq_cap]) and the box of
+// each selection (sel_box[sel_off[q] + r] = qstart[q] + r), from one block.
 void launch_select_scan(const uint32_t *qstart, const uint32_t *nsel, int32_t nq_cap,
                         uint32_t *sel_off, uint32_t *sel_box, hipStream_t st);
 void launch_select_counts(const uint32_t *qstart, const uint32_t *qend, int32_t nq,

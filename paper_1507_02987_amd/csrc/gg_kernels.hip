@@ -1851,8 +1851,6 @@ __global__ __launch_bounds__(kBlock) void k_os_scan(uint32_t *__restrict__ hist,
     }
 }
 
-// Last node of a replayed wave graph: move the cursor to the next planned wave
-// (the first node, the wave preparation, takes the plan entry at the cursor).
 __global__ void k_fill_u32(uint32_t *__restrict__ p, size_t n, uint32_t v)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -5031,7 +5029,7 @@ __global__ void k_merge_sweep(const Box *__restrict__ s, uint32_t n, Box *__rest
 // group: merged boxes from the group's first position, the rest marked empty (by
 // their length records alone where there are any).  A group that may not fit (the last
 // one the block owns, when no other group starts before the block's reach) is recorded
-// in big[1 ..] as (first, end) and left to the global sort; big[0] counts them.
+// from big[2] on as (first, end) and left to k_merge_big; big[0] counts them.
 // Bound by VALU instructions: 3.4 G runs in 93 ms, 39 of them in the sort (118 with
 // 512 keys to a wave, two waves of the four idle, and a 4-byte mark in every slot).
 // W is short of 1,024, so that a window's boxes (W more or less a group) seldom take
@@ -5536,7 +5534,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_merge_tiles(const Box *__restrict
     if (nw == 0) return;
     if (nw == ns && lim < n) {
         // the last owned group reaches past the range: find its end, leave it to
-        // the global sort
+        // k_merge_big
         const uint32_t p0 = base + s_start[nw - 1];
         if (wv == 0) {
             const int2 g = *reinterpret_cast<const int2 *>(in + p0);
@@ -6120,13 +6118,10 @@ __global__ void k_select_counts(const uint32_t *__restrict__ qstart,
     nsel[q] = (N > 0 && c > (uint32_t)N) ? (uint32_t)N : c;
 }
 
-// A replayed wave's per-query ranges and counts in one launch (no zero-fill, no
-// per-record pass), thread ql for query ql of the nq_cap grid.  Runs are in query
-// order, so a binary search finds each query's range; a query's selected boxes
-// lead its own segment [seg_off[ql], seg_off[ql + 1]) (valid boxes sort first), so
-// a binary search in the segment finds where they end.  counts[ql] is the range's
-// length, capped at N when N > 0; queries past the wave, and flagged queries (their
-// runs outgrew the LDS sort: the host runs them again), get empty ranges.
+// A replayed wave's per-query run ranges, counts and offsets in one launch (no zero-fill,
+// no per-record pass), thread q for query q of the nq_cap grid.  Runs are in query order,
+// so two binary searches find each query's; queries past the wave get empty ranges at the
+// end.
 __global__ void k_cand_ranges(const Cand *__restrict__ c, int32_t nq_cap,
                               uint32_t *__restrict__ qstart, uint32_t *__restrict__ qend,
                               uint32_t *__restrict__ counts, uint32_t *__restrict__ off,
