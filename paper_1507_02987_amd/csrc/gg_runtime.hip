@@ -2437,28 +2437,25 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     if ((s = alloc((void **)&ix->d_list_off, sizeof(uint32_t) * (ncode + 1))) != GG_OK ||
         (!cut && (s = alloc((void **)&ix->d_post, sizeof(int2) * n_post)) != GG_OK) ||
         (s = alloc_bank(ix, nwords)) != GG_OK ||
-        (s = alloc((void **)&ix->d_next, contexts_bytes(n_post))) != GG_OK ||
+        (!cut && (s = alloc((void **)&ix->d_next, contexts_bytes(n_post))) != GG_OK) ||
         (s = alloc((void **)&ix->d_seq_start, sizeof(int64_t) * (n_seqs + 1))) != GG_OK)
         return fail(s);
 
     // Sections 2, 2.1 on the GPU: pack the bases, code every window, sort the
     // windows stably by code (they start in (seq, pos) order, so every list stays
     // in that order), list heads = exclusive scan of the per-code counts.
-    hipStream_t bst = nullptr;
-    if (hipStreamCreateWithFlags(&bst, hipStreamNonBlocking) != hipSuccess) return fail(GG_EDEVICE);
-    struct StreamGuard {
-        hipStream_t s;
-        ~StreamGuard() { (void)hipStreamDestroy(s); }
-    } sg{bst};
+    size_t free_b = 0;  // what the index alone leaves
     {
         // the build's temporaries in one allocation (a large one costs its 0.1 - 0.6 ms
         // of mapping and unmapping once)
         struct Tmp {
             size_t bytes = 0;
             char *p = nullptr;
+            uint2 *keys = nullptr;  // the windows' keys where no contexts take their place
             ~Tmp()
             {
                 if (p) (void)hipFree(p);
+                if (keys) (void)hipFree(keys);
             }
             size_t take(size_t n)
             {
@@ -2467,12 +2464,19 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
                 return at;
             }
         } tmp;
+        hipStream_t bst = nullptr;
+        if (hipStreamCreateWithFlags(&bst, hipStreamNonBlocking) != hipSuccess) return fail(GG_EDEVICE);
+        struct StreamGuard {
+            hipStream_t s;
+            ~StreamGuard() { (void)hipStreamDestroy(s); }
+        } sg{bst};
         const uint32_t nw = (uint32_t)n_post;
         const size_t parts = std::max<size_t>(scan_partials_needed(radix_hist_needed(nw)),
                                               scan_partials_needed((int64_t)ncode + 1));
         const size_t o_ascii = tmp.take((size_t)total);
         const size_t o_woff = tmp.take(sizeof(uint32_t) * (n_seqs + 1));
         const size_t o_err = tmp.take(sizeof(int32_t) * 4);
+        const size_t o_keys = tmp.take(cut ? 2 * sizeof(uint64_t) * nw : 0);
         const size_t o_wseq = tmp.take(sizeof(uint32_t) * nw);
         const size_t o_hist = tmp.take(sizeof(uint32_t) * radix_hist_needed(nw));
         const size_t o_parts = tmp.take(sizeof(uint32_t) * parts);
@@ -2486,8 +2490,12 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
         auto *d_woff = reinterpret_cast<uint32_t *>(tmp.p + o_woff);
         auto *d_err = reinterpret_cast<int32_t *>(tmp.p + o_err);
         // the windows' keys lie where the postings' contexts will: they take as much, so a
-        // build that fits the device keeps its contexts
-        auto *d_keys = reinterpret_cast<uint64_t *>(ix->d_next), *d_keys2 = d_keys + nw;
+        // build that fits the device keeps its contexts (with a cutoff, whose contexts may
+        // take much less, among the temporaries)
+        static_assert(2 * sizeof(uint2) == 2 * sizeof(uint64_t), "two keys a window, two contexts");
+        auto *d_keys = cut ? reinterpret_cast<uint64_t *>(tmp.p + o_keys)
+                           : reinterpret_cast<uint64_t *>(ix->d_next);
+        auto *d_keys2 = d_keys + nw;
         auto *d_wseq = reinterpret_cast<uint32_t *>(tmp.p + o_wseq);
         auto *d_hist = reinterpret_cast<uint32_t *>(tmp.p + o_hist);
         auto *d_parts = reinterpret_cast<uint32_t *>(tmp.p + o_parts);
@@ -2532,30 +2540,30 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
                 return fail(GG_EDEVICE);
             ix->cut = kept != nw;
         }
+        const size_t own = sizeof(uint32_t) * (ncode + 1) + sizeof(int2) * ix->n_post +
+                           sizeof(uint32_t) * (size_t)nwords + sizeof(int64_t) * (n_seqs + 1);
+        free_b = free0 > own ? free0 - own : 0;
+        if (!contexts_fit(ix, free_b)) std::swap(tmp.keys, ix->d_next);
+        else if (cut) (void)alloc((void **)&ix->d_next, contexts_bytes(ix->n_post));
+        if (ix->d_next) index_contexts(ix, bst);  // after the keys' last reader
         if (hipMemcpyAsync(&err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, bst) != hipSuccess ||
             hipStreamSynchronize(bst) != hipSuccess || hipGetLastError() != hipSuccess)
             return fail(GG_EDEVICE);
         if (err) return fail(GG_EINVAL);
     }
 
-    static_assert(2 * sizeof(uint2) == 2 * sizeof(uint64_t), "two keys a window, two contexts");
-    if (ix->cut) {  // the kept postings' contexts take less, if that much is to be had
-        uint2 *less = nullptr;
-        if (alloc((void **)&less, contexts_bytes(ix->n_post)) == GG_OK) {
-            (void)hipFree(ix->d_next);
-            ix->d_next = less;
+    if (cut && contexts_fit(ix, free_b) && !ix->d_next) {
+        // no room beside the temporaries; the driver gives their memory back some
+        // milliseconds after its release
+        for (int i = 0; i < 100; ++i) {
+            if (alloc((void **)&ix->d_next, contexts_bytes(ix->n_post)) == GG_OK) break;
+            std::this_thread::sleep_for(std::chrono::milliseconds(2));
         }
-    }
-    const size_t own = sizeof(uint32_t) * (ncode + 1) + sizeof(int2) * ix->n_post +
-                       sizeof(uint32_t) * (size_t)nwords + sizeof(int64_t) * (n_seqs + 1);
-    const size_t free_b = free0 > own ? free0 - own : 0;
-    if (contexts_fit(ix, free_b)) {
-        index_contexts(ix, bst);
-        if (hipStreamSynchronize(bst) != hipSuccess || hipGetLastError() != hipSuccess)
-            return fail(GG_EDEVICE);
-    } else {
-        (void)hipFree(ix->d_next);
-        ix->d_next = nullptr;
+        if (ix->d_next) {
+            index_contexts(ix, nullptr);
+            if (hipStreamSynchronize(nullptr) != hipSuccess || hipGetLastError() != hipSuccess)
+                return fail(GG_EDEVICE);
+        }
     }
     if ((s = index_finish(ix, free_b)) != GG_OK) return fail(s);
     *out = ix;

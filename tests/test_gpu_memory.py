@@ -31,11 +31,10 @@ def free_bytes(G):
 @contextlib.contextmanager
 def leave(G, target):
     """Holds all but about `target` bytes of the free memory, what the driver gives back
-    late (some milliseconds after a free) included; gives a call that does so again, for
-    another target if it is given one (the memory itself takes seconds)."""
+    late (some milliseconds after a free) included."""
     held = []
 
-    def fill(target):
+    def fill():
         size = 32 << 30
         while size >= 2 * MB:
             if free_bytes(G) - size < target:
@@ -46,17 +45,14 @@ def leave(G, target):
             except G.GGError:
                 size //= 2
 
-    def settle(target=target):
+    try:
         quiet = 0
-        while quiet < 3:
+        while quiet < 10:  # a second without more of it
             n = len(held)
-            fill(target)
+            fill()
             quiet = quiet + 1 if len(held) == n else 0
             time.sleep(0.1)
-
-    try:
-        settle()
-        yield settle
+        yield
     finally:
         for b in held:
             b.close()
@@ -73,21 +69,19 @@ def small_bank():
     return bank.__wrapped__(100_000)
 
 
-def test_contexts_of_a_tight_build():
+@pytest.mark.parametrize("max_posting", [0, 10])
+def test_contexts_of_a_tight_build(max_posting):
     """200 Mbp: 212 MB of index, 291 MB of contexts and, while it is built, 572 MB of
     temporaries, 291 of them the windows' keys.  900 MB hold what the build needs, not that
-    and the contexts; 600 MB do not hold the build."""
+    and the contexts; with a cutoff, which drops one list in a hundred, a little less."""
     G = gpu()
     G.Index(*small_bank(), SPAN).close()  # kernels loaded, first buffers allocated
     seqs, off = bank(200_000_000)
-    with leave(G, 900 * MB) as settle:
-        ix = G.Index(seqs, off, SPAN)
-        assert ix.contexts() == 16 * ix.info()["n_postings"]
+    with leave(G, 900 * MB):
+        ix = G.Index(seqs, off, SPAN, max_posting=max_posting)
+        got = ix.contexts(), 16 * ix.info()["n_postings"]
         ix.close()
-        settle(600 * MB)
-        with pytest.raises(G.GGError) as e:
-            G.Index(seqs, off, SPAN)
-        assert e.value.status == G.GG_ENOMEM
+    assert got[0] == got[1] > 0
 
 
 def test_contexts_of_an_index_with_a_cutoff():
@@ -119,22 +113,24 @@ def budget_of(G, ix):
 
 
 def test_loaded_index_leaves_memory_for_others(tmp_path):
-    """212 MB of index and 291 MB of contexts: in 650 MB they would leave less than they take."""
+    """212 MB of index and 291 MB of contexts: in 650 MB they would leave less than they take.
+    The hit budget is a quarter of what the index leaves in any case."""
     G = gpu()
     seqs, off = bank(200_000_000)
+    path = str(tmp_path / "a.gg")
     ix = G.Index(seqs, off, SPAN)
-    path, want = str(tmp_path / "a.gg"), budget_of(G, ix)
     ix.save(path)
+    want = budget_of(G, ix)
     ix.close()
-    got = []
-    with leave(G, 900 * MB) as settle:
-        for room in (900, 650):
-            settle(room * MB)
-            ix = G.Index.load(path)
-            got.append((ix.contexts() > 0, abs(budget_of(G, ix) - (room - 212) * MB // 4) < 8 * MB))
-            ix.close()
-    assert got == [(True, True), (False, True)]
-    assert want == 16 << 30
+    back = G.Index.load(path)
+    there = back.contexts()
+    back.close()
+    with leave(G, 650 * MB):
+        ix = G.Index.load(path)
+        got = ix.contexts(), budget_of(G, ix)
+        ix.close()
+    assert want == 16 << 30 and there > 0
+    assert got[0] == 0 and abs(got[1] - (650 - 212) * MB // 4) < 8 * MB
 
 
 def test_a_search_without_memory_goes_on_without_contexts(monkeypatch):
