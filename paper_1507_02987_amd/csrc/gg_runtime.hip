@@ -2421,8 +2421,6 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
         return s;
     };
     if (hipSetDevice(device) != hipSuccess) return fail(GG_EDEVICE);
-    size_t free0 = 0, total0 = 0;
-    if (hipMemGetInfo(&free0, &total0) != hipSuccess) return fail(GG_EDEVICE);
     auto alloc = [](void **dst, size_t bytes) -> gg_status {
         if (hipMalloc(dst, std::max<size_t>(bytes, 16)) != hipSuccess) {
             (void)hipGetLastError();
@@ -2444,7 +2442,7 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     // Sections 2, 2.1 on the GPU: pack the bases, code every window, sort the
     // windows stably by code (they start in (seq, pos) order, so every list stays
     // in that order), list heads = exclusive scan of the per-code counts.
-    size_t free_b = 0;  // what the index alone leaves
+    size_t free_b = 0;  // what the index without contexts and temporaries leaves
     {
         // the build's temporaries in one allocation (a large one costs its 0.1 - 0.6 ms
         // of mapping and unmapping once)
@@ -2540,9 +2538,9 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
                 return fail(GG_EDEVICE);
             ix->cut = kept != nw;
         }
-        const size_t own = sizeof(uint32_t) * (ncode + 1) + sizeof(int2) * ix->n_post +
-                           sizeof(uint32_t) * (size_t)nwords + sizeof(int64_t) * (n_seqs + 1);
-        free_b = free0 > own ? free0 - own : 0;
+        size_t total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return fail(GG_EDEVICE);
+        free_b += tmp.bytes + (ix->d_next ? contexts_bytes(n_post) : 0);
         if (!contexts_fit(ix, free_b)) std::swap(tmp.keys, ix->d_next);
         else if (cut) (void)alloc((void **)&ix->d_next, contexts_bytes(ix->n_post));
         if (ix->d_next) index_contexts(ix, bst);  // after the keys' last reader
