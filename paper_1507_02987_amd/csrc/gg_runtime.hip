@@ -271,7 +271,7 @@ void drop_contexts(const gg_index *ix)
     ix->ctx_going = true;
     ix->ctx_cv.wait(g, [&] { return ix->ctx_users == 0; });
     g.unlock();
-    // the driver gives freed memory back some milliseconds later
+    // freed memory comes back some milliseconds later
     size_t before = 0, now = 0, total = 0;
     const bool known = hipMemGetInfo(&before, &total) == hipSuccess;
     (void)hipFree(ix->d_next);
@@ -2551,8 +2551,8 @@ gg_status index_build(const char *seqs, const int64_t *seq_off, int64_t n_in, in
     }
 
     if (cut && contexts_fit(ix, free_b) && !ix->d_next) {
-        // no room beside the temporaries; the driver gives their memory back some
-        // milliseconds after its release
+        // no room beside the temporaries, whose memory comes back some milliseconds after
+        // its release
         for (int i = 0; i < 100; ++i) {
             if (alloc((void **)&ix->d_next, contexts_bytes(ix->n_post)) == GG_OK) break;
             std::this_thread::sleep_for(std::chrono::milliseconds(2));

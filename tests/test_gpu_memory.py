@@ -30,8 +30,8 @@ def free_bytes(G):
 
 @contextlib.contextmanager
 def leave(G, target):
-    """Holds all but about `target` bytes of the free memory, what the driver gives back
-    late (some milliseconds after a free) included."""
+    """Holds all but about `target` bytes of the free memory, what comes back late (some
+    milliseconds after a free) included."""
     held = []
 
     def fill():
